@@ -498,20 +498,45 @@ layernorm_backward_dequant_kernel(const uint8_t *__restrict__ codes, const float
 
 // ---- parameter gradients of an active LayerNorm: column sums over all rows --------------
 // gamma^_j = sum_r x~_rj * y^_rj,  beta^_j = sum_r y^_rj.  A workgroup owns a slab of
-// kSlabRows consecutive rows and a group of 256 columns: lane l of every wave holds the
+// consecutive rows and a group of 256 columns: lane l of every wave holds the
 // 16-byte column vector l of the group (a wave reads 1 KiB of a row at a time), the four
 // waves take every fourth row of the slab, accumulate in fp32 and are added in wave order
 // through LDS; one partial per slab and column goes to the workspace.  The second kernel adds
 // the slabs' partials in fp64 in a fixed order.  No atomics: the result does not depend on
-// scheduling.  (Smaller slabs fill the chip better but leave more partials to the second
-// kernel, which then dominates: 64-row slabs of whole rows took 0.093 ms, 16-row ones 0.185.)
-constexpr int kSlabRows = 256;
+// scheduling.
+//
+// Slabs: the second kernel reads one partial per slab and column, so there are as few as fill the chip --
+// about 1024 workgroups (4 a compute unit; one covers 256 fp32 or 512 bf16 columns), no slab under 16 rows
+// (the four waves' four rows in flight) or over 256.  The time of a small call is the chip left idle: with
+// 256-row slabs throughout, 4096 x 768 fp32 has 48 workgroups and took 21.7 us (bf16 52.5) against 9.8 now,
+// which is the host's two launches (24 us of kernels to 6); 25216 x 768 34.2 -> 29.0; 49152 x 1024
+// 69.9 -> 65.2 (6.2 TB/s), bf16 68.4 -> 39.2.  Half as many workgroups: bf16 62.6; twice: fp32 30.6 and 66.3.
+constexpr int kMaxSlabRows = 256, kMinSlabRows = 16;
+constexpr int64_t kSlabWorkgroups = 1024;
 constexpr int kGroupVecs = kWave;           // column vectors per workgroup: 256 columns (fp32), 512 (bf16)
+int slab_rows_for(int64_t rows, int64_t H, int epv, int64_t room)      // room >= least: slabs the workspace holds
+{
+    const int64_t most = (rows + kMinSlabRows - 1) / kMinSlabRows, least = (rows + kMaxSlabRows - 1) / kMaxSlabRows;
+    const int64_t fill = (kSlabWorkgroups * kGroupVecs * epv + H - 1) / H;
+    int64_t slabs = fill < least ? least : (fill < most ? fill : most);
+    if (slabs > room) slabs = room;
+    const int64_t per = slabs > 0 ? (rows + slabs - 1) / slabs : kMinSlabRows;
+    return (int)((per + kMinSlabRows - 1) / kMinSlabRows * kMinSlabRows);
+}
+// Floats of one of the two partial arrays for either element type: at least slabs * H, and never less for fewer
+// rows or columns, so that a workspace of the largest call serves the smaller ones.
+int64_t slab_floats_for(int64_t rows, int64_t H)
+{
+    const int64_t most = (rows + kMinSlabRows - 1) / kMinSlabRows * H, least = (rows + kMaxSlabRows - 1) / kMaxSlabRows * H;
+    const int64_t fill = kSlabWorkgroups * kGroupVecs * 8 + H;
+    return fill < least ? least : (fill < most ? fill : (most > 0 ? most : H));
+}
 
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
 param_grad_partials_kernel(const T *__restrict__ x, const float *__restrict__ mean, const float *__restrict__ rstd,
-                           const T *__restrict__ dy, int64_t rows, int H, int groups, float *__restrict__ partials)
+                           const T *__restrict__ dy, int64_t rows, int H, int groups, int slab_rows,
+                           float *__restrict__ partials)
 {
     constexpr int E = RowIO<T>::E;
     __shared__ float red_g[kWaves][kWave][E], red_b[kWaves][kWave][E];
@@ -522,8 +547,8 @@ param_grad_partials_kernel(const T *__restrict__ x, const float *__restrict__ me
     const int group = blockIdx.x % groups;
     const int q = group * kGroupVecs + lane;                   // this lane's column vector
     const bool mine = q < nvec;
-    const int64_t r0 = slab * kSlabRows;
-    const int n_rows = (int)min((int64_t)kSlabRows, rows - r0);
+    const int64_t r0 = slab * slab_rows;
+    const int n_rows = (int)min((int64_t)slab_rows, rows - r0);
     float sg[E], sb[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) sg[e] = sb[e] = 0.0f;
@@ -577,11 +602,12 @@ param_grad_partials_kernel(const T *__restrict__ x, const float *__restrict__ me
     }
 }
 
-// 32 columns (of the 2H outputs: gamma^ then beta^) per workgroup; the 8 groups of 32 threads take every
-// eighth slab each and their fp64 sums are added in group order.
+// 32 columns (of the 2H outputs: gamma^ then beta^) per workgroup; the 32 groups of 32 threads take every
+// 32nd slab each and their fp64 sums are added in group order.
 constexpr int kFinishCols = 32;
-constexpr int kFinishGroups = kThreads / kFinishCols;
-__global__ void __launch_bounds__(kThreads)
+constexpr int kFinishThreads = 1024;
+constexpr int kFinishGroups = kFinishThreads / kFinishCols;
+__global__ void __launch_bounds__(kFinishThreads)
 param_grad_finish_kernel(const float *__restrict__ partials, int64_t slabs, int H, float *__restrict__ dgamma,
                          float *__restrict__ dbeta)
 {
@@ -590,6 +616,7 @@ param_grad_finish_kernel(const float *__restrict__ partials, int64_t slabs, int 
     const int col = blockIdx.x * kFinishCols + c;               // 0 .. 2H-1; 2H is a multiple of 8, not always of 32
     double acc = 0.0;
     if (col < 2 * H)
+#pragma unroll 4
         for (int64_t s = grp; s < slabs; s += kFinishGroups) acc += (double)partials[s * 2 * H + col];
     part[grp][c] = acc;
     __syncthreads();
@@ -715,8 +742,7 @@ extern "C" int32_t slimfit_layernorm_param_grads_workspace(int64_t rows, int64_t
     int32_t rc = validate(rows, H);
     if (rc != SLIMFIT_OK) return rc;
     if (!bytes) return SLIMFIT_ERR_INVALID_ARG;
-    const int64_t slabs = (rows + kSlabRows - 1) / kSlabRows;
-    *bytes = (size_t)(slabs > 0 ? slabs : 1) * 2 * (size_t)H * 4;
+    *bytes = (size_t)slab_floats_for(rows, H) * 2 * 4;
     return SLIMFIT_OK;
 }
 
@@ -731,9 +757,13 @@ extern "C" int32_t slimfit_layernorm_param_grads(const void *x, int32_t dt, cons
     if (!aligned_to(dgamma, 4) || !aligned_to(dbeta, 4) || !aligned_to(workspace, 16) ||
         (rows > 0 && (!aligned_to(x, 16) || !aligned_to(dy, 16) || !aligned_to(mean, 4) || !aligned_to(rstd, 4))))
         return SLIMFIT_ERR_ALIGNMENT;
-    size_t need = 0;
-    slimfit_layernorm_param_grads_workspace(rows, H, &need);
-    if (workspace_bytes < need) return SLIMFIT_ERR_WORKSPACE;
+    // (a workspace below the reported size but large enough for the fewest slabs is served with the slabs that fit)
+    const int64_t least = (rows + kMaxSlabRows - 1) / kMaxSlabRows;
+    if (workspace_bytes < (size_t)(least > 0 ? least : 1) * 2 * (size_t)H * 4) return SLIMFIT_ERR_WORKSPACE;
+    const int64_t room = (int64_t)(workspace_bytes / (2 * (size_t)H * 4));
+    const int slab_rows = slab_rows_for(rows, H, dt == SLIMFIT_F32 ? 4 : 8, room);
+    const int64_t slabs = (rows + slab_rows - 1) / slab_rows;
+    const size_t need = (size_t)(slabs > 0 ? slabs : 1) * 2 * (size_t)H * 4;
     if ((rc = check_device_range(dgamma, (size_t)H * 4)) != SLIMFIT_OK) return rc;
     if ((rc = check_device_range(dbeta, (size_t)H * 4)) != SLIMFIT_OK) return rc;
     if ((rc = check_device_range(workspace, need)) != SLIMFIT_OK) return rc;
@@ -745,21 +775,21 @@ extern "C" int32_t slimfit_layernorm_param_grads(const void *x, int32_t dt, cons
         if ((rc = check_device_range(rstd, (size_t)rows * 4)) != SLIMFIT_OK) return rc;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t slabs = (rows + kSlabRows - 1) / kSlabRows;
     float *partials = static_cast<float *>(workspace);
     const int64_t epv = dt == SLIMFIT_F32 ? 4 : 8;
     const int groups = (int)((H / epv + kGroupVecs - 1) / kGroupVecs);
     if (slabs > 0) {
         if (dt == SLIMFIT_F32)
             param_grad_partials_kernel<float><<<(unsigned)(slabs * groups), kThreads, 0, s>>>(
-                static_cast<const float *>(x), mean, rstd, static_cast<const float *>(dy), rows, (int)H, groups, partials);
+                static_cast<const float *>(x), mean, rstd, static_cast<const float *>(dy), rows, (int)H, groups, slab_rows,
+                partials);
         else
             param_grad_partials_kernel<uint16_t><<<(unsigned)(slabs * groups), kThreads, 0, s>>>(
                 static_cast<const uint16_t *>(x), mean, rstd, static_cast<const uint16_t *>(dy), rows, (int)H, groups,
-                partials);
+                slab_rows, partials);
     }
     const unsigned fgrid = (unsigned)((2 * H + kFinishCols - 1) / kFinishCols);
-    param_grad_finish_kernel<<<fgrid, kThreads, 0, s>>>(partials, slabs, (int)H, dgamma, dbeta);
+    param_grad_finish_kernel<<<fgrid, kFinishThreads, 0, s>>>(partials, slabs, (int)H, dgamma, dbeta);
     return launch_status();
 }
 

@@ -241,3 +241,35 @@ def test_layernorm_input_at_full_size(ci):
     k = sf.keep_count(x.numel(), 100000)
     vals, idx, ptr = _prune_both(x, mean, rstd, k)
     _backward_both(vals, idx, ptr, k, rstd, gamma, dy)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,H,slabs", [(16, 256, 0), (17, 256, 0), (4096, 768, 0), (4100, 520, 1), (8200, 256, 0),
+                                          (8200, 264, 40), (70001, 8, 0)])
+def test_param_grads_slab_counts(rows, H, slabs, dtype):
+    """Slabs of every size the rule picks, and workspaces between the smallest accepted one (256-row slabs) and the
+    reported size; each column sum of at most 70 001 terms in fp32 slab sums of at most 256 rows."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(rows + H)
+    x = torch.randn(rows, H, generator=g, device="cuda").to(dtype)
+    dy = torch.randn(rows, H, generator=g, device="cuda").to(dtype)
+    mean = 0.1 * torch.randn(rows, generator=g, device="cuda")
+    rstd = 0.5 + torch.rand(rows, generator=g, device="cuda")
+    least = (rows + 255) // 256
+    room = (max(slabs, least) if slabs else 0) * 2 * H * 4
+    xt = (x.double() - mean.double()[:, None]) * rstd.double()[:, None]
+    dg, db = Guarded(H, torch.float32), Guarded(H, torch.float32)
+    ws = Guarded(room, torch.uint8) if room else None
+    sf.layernorm_param_grads(x, mean, rstd, dy, dg.t, db.t, ws.t if ws else None)
+    torch.cuda.synchronize()
+    dg.check(); db.check()
+    if ws:
+        ws.check()
+    # 2 roundings of x~, one product, at most 64 + 4 additions: under 4.3e-6 of the absolute sums, seen 1e-7
+    want_g, want_b = (xt * dy.double()).sum(0), dy.double().sum(0)
+    assert bool(((dg.t.double() - want_g).abs() <= 4.3e-6 * (xt * dy.double()).abs().sum(0)).all())
+    assert bool(((db.t.double() - want_b).abs() <= 4.3e-6 * dy.double().abs().sum(0)).all())
+    too_small = torch.empty(least * 2 * H * 4 - 4, dtype=torch.uint8, device="cuda")
+    with pytest.raises(sf.SlimfitError) as e:
+        sf.layernorm_param_grads(x, mean, rstd, dy, dg.t, db.t, too_small)
+    assert e.value.status == sf.ERR_WORKSPACE
