@@ -374,7 +374,7 @@ int32_t slimfit_softmax_backward_pruned(const void *vals, const uint16_t *idx, c
  *              restoring process builds every output tile once instead of
  *              filling zeros and scattering into them.
  *  workspace : DEVICE, 16-byte aligned, at least the byte count that
- *              slimfit_prune_global_workspace(n) reports (about n/2 bytes);
+ *              slimfit_prune_global_workspace(n) reports (about 1.3 n bytes);
  *              owned by the caller, contents need not be initialised and are
  *              overwritten.  Calls that share a workspace must not overlap.
  *  slimfit_restore_global : out (n elements of dt, 16-byte aligned) = zeros,

@@ -3,78 +3,96 @@
 // indices, restore by zeros + scatter).
 //
 // A full sort is not needed to know which k entries a descending sort would put
-// first: an exact radix select finds the k-th largest key T and how many keys
-// equal to T belong to the kept set, and one more sweep emits the survivors in
-// ascending index order (ties at T go to the lowest indices).
+// first: the k-th largest key T and the number of keys equal to T that belong to
+// the kept set decide it.  The survivors are emitted in ascending index order
+// (ties at T go to the lowest indices).
 //
 //   keys      order-preserving unsigned images of the elements: |x| as the IEEE
 //             bit pattern without its sign (by magnitude) or the usual signed
 //             fold with -0 mapped onto +0 (by value); 32 bits for fp32, 16 for
-//             bf16.
-//   digit 1   every workgroup histograms the top 12 key bits of its share of
-//             the tensor in LDS (ds_add) and adds the non-empty bins to one
-//             global histogram; a single workgroup walks the 4096 bins from the
-//             top and fixes the bin that holds T and the count still to take
-//             from it.
-//   bracket   if that bin is small enough (the usual case: a bin is 1/16 of a
-//             binade, 1-2 % of a bell-shaped tensor), one sweep counts, per
-//             tile, the keys above the bin and files the bin's own keys in the
-//             tile's slot of a key list (1/16 of the tile's size; slots are
-//             granted from an LDS counter, no global atomics).  The remaining
-//             digits (8+12 bits for fp32, 4 for bf16) and the per-tile counts
-//             of keys above / equal to T then read the lists only, a wave per
-//             tile.  A bin too large for the lists (heavy ties, constant
-//             tensors), or a tile whose slot overflows because the bin's keys
-//             are bunched, takes the plain route instead: every further digit
-//             and the count sweep read the tensor again.
-//   scan      one workgroup turns the tile counts into each tile's first output
-//             slot and the number of ties it may still keep.
-//   write     every tile ranks its survivors with a packed wave prefix sum and
-//             stores (value, index) pairs at their final places, plus the
-//             optional tile pointers (survivors ahead of every 4096 elements)
-//             that let the restoring process run as one pass.
+//             bf16.  A key's top 12 bits name its bin (1/16 of a binade by
+//             magnitude, 1/8 by value).
+//   sample    16 workgroups histogram the bins of up to 16384 vectors drawn one
+//             from each equal stretch of the tensor; one workgroup adds the
+//             histograms and fixes the bracket, the bins that hold the sample's
+//             k-th largest entry give or take six standard deviations of its
+//             rank.  Nothing depends on the sample being right: the counts of the
+//             next pass show whether T lies inside the bracket.
+//   sweep     one pass over the tensor, a workgroup per tile of 4096 elements:
+//             the candidates (keys not below the bracket) are collected in index
+//             order in LDS and leave as a contiguous run of (value, position)
+//             records, 6 bytes each; the keys inside the bracket (1.5 - 3 % of a
+//             bell-shaped tensor) are also filed in the tile's key list.
+//   digits    T from the key lists, first in 2^9 .. 2^12 steps of the bracket's
+//             width, then to the last bit (at most 2^14 steps).
+//   count     keys above T and equal to T, per tile and per group of tiles.
+//   write     a wave per tile reads the tile's records, drops those that T
+//             rejects, and stores (value, index) pairs at their final places,
+//             with the optional tile and row pointers.  The first output slot of a
+//             tile is the sum of the group counts and of the counts of its own
+//             group's earlier tiles.  A tile that holds more candidates than it has
+//             record slots is read from the tensor instead (so are all tiles when
+//             more than one entry in nine is kept: no records are made then).
 //
-// Both routes run the same launches; a kernel looks at the route flag in the
-// state block and either returns or picks its source.  No kernel waits on
-// another workgroup, and the single-workgroup steps (digit selection, scan) are
-// launches of their own: letting the last workgroup of a sweep do them needs an
-// agent-scope release in every workgroup, which on this part writes back the
-// XCD's whole L2 and made the sweeps 2-25x slower when it was tried.  The tensor is read three times on the list route (digit
-// 1, bracket, write) and 2 + number of digits times on the plain one.
+// Plain route: a bracket that holds too much of the sample (heavy ties), a list
+// that overflows (bunched keys) or a sample that missed T leaves the lists
+// unused; the same launches then read the tensor once per digit (12 | 8 | 12
+// bits, bf16 12 | 4), once for the counts and once to write, and the last launch,
+// which otherwise returns at once, is the write.  When k / n is too close to 0 or
+// to 1 for a sample to bracket T, the tensor's own histogram takes its place.
+//
+// No kernel waits on another workgroup: every step that needs the whole of the
+// one before is a launch of its own (a last-workgroup ticket needs an agent-scope
+// release in every workgroup, which on this part writes back the XCD's whole L2
+// and made the sweeps 2-25x slower when it was tried), but a step that one
+// workgroup could do is done by every workgroup of the next launch for itself.
 #include "common.hpp"
 
+#include <cmath>
 #include <type_traits>
 
 namespace slimfit {
 namespace {
 
-constexpr int kTileThreads = 256;          // tile kernels: 4 waves
-constexpr int kVecPerThread = 4;           // 16-byte vectors a thread holds
-constexpr int kDigitBits = 12;
-constexpr int kMaxBins = 1 << kDigitBits;
-constexpr int kHistThreads = 1024;
-constexpr int kSelectThreads = 1024;
-constexpr int kScanThreads = 1024;
-constexpr int64_t kPtrTile = SLIMFIT_GLOBAL_TILE;   // granularity of the tile pointers; smallest kernel tile
+constexpr int kTileThreads = 256;          // sweep and write: 4 waves
+constexpr int kVecPerThread = 4;           // 16-byte vectors a thread holds in a tensor histogram
+constexpr int kWideThreads = 1024;         // histogram, count and single-workgroup kernels
+constexpr int kWideWaves = kWideThreads / kWave;
+constexpr int kTop = 12;                   // leading key bits that name a bin
+constexpr int kTopBins = 1 << kTop;
+constexpr int64_t kPtrTile = SLIMFIT_GLOBAL_TILE;   // granularity of the tile pointers, and the tile of every kernel
+constexpr int kTileElems = (int)kPtrTile;
+constexpr int kWaveElems = kTileElems / 4; // a tile is four rounds of 1024 elements, one a wave of the sweep
 
-struct State {                             // first 64 bytes of the workspace
-    uint32_t prefix;                       // key bits fixed so far
-    uint32_t mask;                         // which bits those are
-    uint32_t k_rem;                        // entries still to take among the keys matching prefix
-    uint32_t T;                            // k-th largest key (after the last digit)
-    uint32_t take_eq;                      // how many keys equal to T are kept
-    uint32_t route;                        // 1: digits after the first and the counts read the candidate list
-    uint32_t overflow;                     // 1: a tile's list ran out of slots; the lists are not used after all
-    uint32_t pad[9];
+constexpr int kSampleWgs = 16;             // at most
+constexpr int kSampleVecs = 1;             // vectors a thread of them takes
+constexpr int kListSlots = kTileElems * 3 / 32;     // a tile's key list
+constexpr int kRecSlots = 640;             // a tile's records: 10 % kept and 3 % more in the bracket, plus 5 standard deviations
+constexpr int kRecShare = 9;               // records are made when k * 9 <= n
+constexpr int kMaxBracketBins = 64;
+constexpr int kMaxDigit3 = 14;             // bits of the last digit over the lists
+constexpr int kListGrid = 128;             // workgroups that add a first-digit histogram of the lists (each adds its non-empty bins with global atomics)
+constexpr int kWideGrid = 256;
+constexpr unsigned kPlainGrid = 2048;      // plain route: workgroups that count and write (those of the last launch usually return at once)
+constexpr int kCounters = 64;              // the sweep's totals, spread over as many cache lines
+constexpr int kMaxGroups = kWideGrid;      // groups of tiles whose counts are summed ahead of the write
+constexpr int kMaxGroupTiles = 2048;       // 2^31 elements are 2^19 tiles
+
+struct State {                             // first 128 bytes of the workspace
+    uint32_t plain;                        // set ahead of the sweep: the lists will not be used
+    uint32_t overflow;                     // set by the sweep: a tile's key list ran out of slots
+    uint32_t lo;                           // the bracket: keys lo .. lo + 2^range_bits - 1, as far as they exist
+    uint32_t last;                         // its largest key
+    uint32_t digit2, shift2;               // bits of the first digit over the lists, and where it starts
+    uint32_t use_plain;                    // set after the sweep: what every later launch goes by
+    uint32_t prefix;                       // plain route: the top digit
+    uint32_t lo2;                          // list route: lower edge of the first digit's step that holds T
+    uint32_t k_rem, k_rem2, k_rem3;        // entries still to take ahead of each digit
+    uint32_t prefix3;                      // plain route: all key bits but the last digit's
+    uint32_t T, take_eq;                   // k-th largest key; how many keys equal to T are kept
+    uint32_t pad[17];
 };
-#ifndef SLIMFIT_PG_HIST_GRID
-#define SLIMFIT_PG_HIST_GRID 256          // workgroups of a histogram sweep: each adds its non-empty bins with global atomics
-#endif
-#ifndef SLIMFIT_PG_NT
-#define SLIMFIT_PG_NT 0
-#endif
-constexpr int kListShare = 16;             // a tile's key list holds 1/16 of the tile's element count
-__device__ __forceinline__ bool use_list(const State *st) { return st->route != 0u && st->overflow == 0u; }
+static_assert(sizeof(State) == 128, "state size");
 
 // bf16 elements that enter the selection widened to fp32: the rows of a bf16 tensor that is standardised
 // on the way in (the standardised values are fp32, and so are the kept values)
@@ -195,7 +213,8 @@ __device__ __forceinline__ int load_tile_vec(const T *x, int64_t n, int64_t nvec
 struct Std {
     const float *mean, *rstd;
     uint32_t magic, shift;
-    uint32_t wave_uniform;       // H is a multiple of 64 vectors: the 64 vectors a wave loads together share a row
+    uint32_t wave_uniform;       // H is a multiple of 64: 64 consecutive elements from a multiple of 64 share a row
+    uint32_t vec_uniform;        // H is a multiple of 64 vectors: the 64 vectors a wave loads together share a row
     uint32_t last_row;
     uint32_t H;
     int32_t *row_ptr;            // optional output: survivors ahead of every row (rows + 1 entries)
@@ -212,7 +231,7 @@ __device__ __forceinline__ void standardise(uint32_t (&bits)[Elem<T>::EPV], int 
         // all of a thread's vectors can be issued together.
         (void)valid;
         uint32_t row = min(__umulhi((uint32_t)(v * EPV), sd.magic) >> sd.shift, sd.last_row);
-        if (sd.wave_uniform) row = (uint32_t)__builtin_amdgcn_readfirstlane((int)row);   // scalar loads
+        if (sd.vec_uniform) row = (uint32_t)__builtin_amdgcn_readfirstlane((int)row);    // scalar loads
         const float mu = sd.mean[row], rs = sd.rstd[row];
 #pragma unroll
         for (int e = 0; e < EPV; ++e)
@@ -241,94 +260,32 @@ __device__ __forceinline__ uint32_t wave_total_u32(uint32_t inclusive)
     return (uint32_t)__builtin_amdgcn_readlane((int)inclusive, 63);
 }
 
-// ---- state / histogram reset ------------------------------------------------------
-__global__ void __launch_bounds__(kSelectThreads) init_kernel(State *st, uint32_t *hist, uint32_t k)
+__device__ __forceinline__ uint32_t row_of(uint32_t e, const Std &sd) { return __umulhi(e, sd.magic) >> sd.shift; }
+
+// vector (tile, round, group j, lane): a round is kGroups * 64 consecutive vectors
+template <typename T> constexpr int kGroups = kWaveElems / (kWave * Elem<T>::EPV);      // 4 (fp32) or 2 (bf16)
+template <typename T>
+__device__ __forceinline__ int64_t round_vec(int64_t tile, int round, int j, int lane)
 {
-    for (int i = threadIdx.x; i < kMaxBins; i += kSelectThreads) hist[i] = 0u;
-    if (threadIdx.x == 0) {
-        st->prefix = 0u;
-        st->mask = 0u;
-        st->k_rem = k;
-        st->T = 0u;
-        st->take_eq = 0u;
-        st->route = 0u;
-        st->overflow = 0u;
-    }
+    return tile * (int64_t)(kTileElems / Elem<T>::EPV) + (int64_t)((round * kGroups<T> + j) * kWave + lane);
+}
+// a wave's round of a tile, standardised; INSIDE: the whole tile lies below n
+template <typename T, bool STD, bool INSIDE, bool NT = false>
+__device__ __forceinline__ void load_round(const T *__restrict__ x, int64_t n, int64_t tile, int round, int lane,
+                                           uint32_t (&bits)[kGroups<T>][Elem<T>::EPV], int (&valid)[kGroups<T>],
+                                           const Std &sd)
+{
+    const int64_t nvec = (n + Elem<T>::EPV - 1) / Elem<T>::EPV;
+#pragma unroll
+    for (int j = 0; j < kGroups<T>; ++j)
+        valid[j] = load_tile_vec<T, INSIDE, NT>(x, n, nvec, round_vec<T>(tile, round, j, lane), bits[j]);
+#pragma unroll
+    for (int j = 0; j < kGroups<T>; ++j) standardise<T, STD>(bits[j], valid[j], round_vec<T>(tile, round, j, lane), sd);
 }
 
-// ---- one digit of the select: histogram of the keys that match the prefix ------------
-// Source: the tensor (first digit, and every digit on the plain route) or the
-// candidate list.
-template <typename T, bool MAG, bool STD, bool FIRST>
-__global__ void __launch_bounds__(kHistThreads)
-hist_kernel(const T *__restrict__ x, int64_t n, const State *__restrict__ st, uint32_t *__restrict__ hist,
-            const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, int64_t ntiles, int shift, int nbins, Std sd)
-{
-    constexpr int EPV = Elem<T>::EPV;
-    __shared__ uint32_t bins[kMaxBins];
-    for (int i = threadIdx.x; i < nbins; i += kHistThreads) bins[i] = 0u;
-    const uint32_t prefix = st->prefix, mask = st->mask;
-    const uint32_t digit_mask = (uint32_t)nbins - 1u;
-    const bool listed = use_list(st);
-    __syncthreads();
-
-    if (listed) {
-        // a wave per tile list; the tile's count sits in the second word of its counters
-        constexpr int64_t kSlot = (int64_t)kTileThreads * kVecPerThread * EPV / kListShare;
-        const int lane = threadIdx.x & (kWave - 1);
-        const int64_t waves = (int64_t)gridDim.x * (kHistThreads / kWave);
-        for (int64_t t = (int64_t)blockIdx.x * (kHistThreads / kWave) + (threadIdx.x >> 6); t < ntiles; t += waves) {
-            const uint32_t cnt = min(tile_cnt[t].y, (uint32_t)kSlot);
-            const uint32_t *keys = lists + t * kSlot;
-            for (uint32_t i = lane; i < cnt; i += kWave) {
-                const uint32_t key = keys[i];
-                if ((key & mask) == prefix) atomicAdd(&bins[(key >> shift) & digit_mask], 1u);
-            }
-        }
-    } else {
-        const int64_t nvec = (n + EPV - 1) / EPV;
-        const int64_t nfull = n / EPV;                            // vectors wholly below n
-        const int64_t chunk = (int64_t)kHistThreads * kVecPerThread;
-        auto sweep = [&](auto inside_tag, int64_t base) {
-            constexpr bool INSIDE = decltype(inside_tag)::value;
-            uint32_t bits[kVecPerThread][EPV];
-            int valid[kVecPerThread];
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j) {
-                const int64_t v = base + (int64_t)j * kHistThreads + threadIdx.x;
-                valid[j] = load_tile_vec<T, INSIDE, SLIMFIT_PG_NT != 0>(x, n, nvec, v, bits[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j)
-                standardise<T, STD>(bits[j], valid[j], base + (int64_t)j * kHistThreads + threadIdx.x, sd);
-#pragma unroll
-            for (int j = 0; j < kVecPerThread; ++j) {
-#pragma unroll
-                for (int e = 0; e < EPV; ++e) {
-                    if (INSIDE || e < valid[j]) {
-                        const uint32_t key = make_key<T, MAG>(bits[j][e]);
-                        // the first digit counts every key: no prefix to match, no branch around the ds_add
-                        if (FIRST || (key & mask) == prefix) atomicAdd(&bins[(key >> shift) & digit_mask], 1u);
-                    }
-                }
-            }
-        };
-        for (int64_t base = (int64_t)blockIdx.x * chunk; base < nvec; base += (int64_t)gridDim.x * chunk) {
-            if (base + chunk <= nfull) sweep(std::true_type{}, base);      // workgroup-uniform
-            else sweep(std::false_type{}, base);
-        }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nbins; i += kHistThreads) {
-        const uint32_t c = bins[i];
-        if (c) atomicAdd(&hist[i], c);
-    }
-}
-
-// exclusive prefix sum of one value per thread over a workgroup of NT threads
-// (NT/64 waves); `total` receives the workgroup's sum.  Two barriers.
+// exclusive prefix sum of one value per thread over a workgroup of NT threads; two barriers
 template <int NT>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *wave_sums, uint32_t &total)
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *wave_sums)
 {
     constexpr int NW = NT / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
@@ -336,124 +293,260 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *w
     __syncthreads();                                       // wave_sums may still be read from a previous call
     if (lane == kWave - 1) wave_sums[wave] = incl;
     __syncthreads();
-    uint32_t before = 0u, sum = 0u;
+    uint32_t before = 0u;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const uint32_t s = wave_sums[w];
-        before += (w < wave) ? s : 0u;
-        sum += s;
-    }
-    total = sum;
+    for (int w = 0; w < NW; ++w) before += (w < wave) ? wave_sums[w] : 0u;
     return before + incl - v;
 }
 
-// Walk the bins from the highest digit down: the digit of the k-th largest key
-// is the first one whose running count reaches k_rem.  Clears the histogram.
-// After the first digit it also picks the route: the candidate list is used
-// when the chosen bin fits into it.
-__global__ void __launch_bounds__(kSelectThreads)
-select_kernel(State *st, uint32_t *hist, int shift, int nbins, int first, int last, uint32_t cap)
+// The bin, counted from the top of a histogram of 2^bits bins, at which the running count reaches k_rem, and how
+// many of its entries are still to take.  Every thread of the workgroup (NT threads, bits <= 14, 2^bits <= 16 NT)
+// gets the answer.
+struct Choice {
+    uint32_t bin, left;
+};
+template <int NT, int PER>
+__device__ __forceinline__ Choice select_bin_per(const uint32_t *hist, int bits, uint32_t k_rem)
 {
-    __shared__ uint32_t wave_sums[kSelectThreads / kWave];
-    constexpr int PER = kMaxBins / kSelectThreads;         // 4 bins a thread, highest first
-    const uint32_t prefix = st->prefix, mask = st->mask, k_rem = st->k_rem;
+    __shared__ uint32_t wave_sums[NT / kWave];
+    __shared__ Choice found;
+    const int top = (1 << bits) - 1 - (int)threadIdx.x * PER;              // this thread's highest bin
     uint32_t h[PER];
     uint32_t mine = 0u;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int r = threadIdx.x * PER + j;               // rank from the top
-        const int b = nbins - 1 - r;
-        h[j] = 0u;
-        if (b >= 0) {
-            h[j] = hist[b];
-            hist[b] = 0u;
-        }
+        h[j] = hist[max(top - j, 0)];
+        h[j] = top - j >= 0 ? h[j] : 0u;
         mine += h[j];
     }
-    uint32_t total;
-    uint32_t above = block_exclusive_scan<kSelectThreads>(mine, wave_sums, total);
-    (void)total;
+    if (threadIdx.x == 0) found = Choice{0u, 1u};
+    uint32_t above = block_exclusive_scan<NT>(mine, wave_sums);
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int b = nbins - 1 - (threadIdx.x * PER + j);
-        if (b >= 0 && above < k_rem && k_rem <= above + h[j]) {     // exactly one (thread, j) when k_rem <= #matching keys
-            const uint32_t new_prefix = prefix | ((uint32_t)b << shift);
-            const uint32_t left = k_rem - above;
-            st->prefix = new_prefix;
-            st->mask = mask | (((uint32_t)nbins - 1u) << shift);
-            st->k_rem = left;
-            if (first) st->route = (!last && h[j] <= cap) ? 1u : 0u;
-            if (last) {
-                st->T = new_prefix;
-                st->take_eq = left;
-            }
-        }
+        if (above < k_rem && k_rem <= above + h[j]) found = Choice{(uint32_t)(top - j), k_rem - above};   // one thread, one j
         above += h[j];
     }
+    __syncthreads();
+    return found;
 }
-
-// vector index of (tile, wave, group j, lane): a wave owns 4 x 64 consecutive vectors
-__device__ __forceinline__ int64_t tile_vec(int64_t tile, int wave, int j, int lane)
+template <int NT>
+__device__ __forceinline__ Choice select_bin(const uint32_t *hist, int bits, uint32_t k_rem)
 {
-    return tile * (int64_t)(kTileThreads * kVecPerThread) + (int64_t)((wave * kVecPerThread + j) * kWave + lane);
+    if ((1 << bits) <= NT) return select_bin_per<NT, 1>(hist, bits, k_rem);
+    if ((1 << bits) <= 4 * NT) return select_bin_per<NT, 4>(hist, bits, k_rem);
+    return select_bin_per<NT, 16>(hist, bits, k_rem);
 }
 
-// ---- list route: per tile, keys above the chosen bin; the bin's own keys go to the tile's list ----
-// Leaves tile_cnt[tile] = (keys above the bin, keys filed).
-template <typename T, bool MAG, bool STD, bool INSIDE>
-__device__ __forceinline__ void
-bracket_tile(const T *__restrict__ x, int64_t n, State *st, u32x2 *__restrict__ tile_cnt, uint32_t *__restrict__ lists, Std sd)
+// the counters, group sums and histograms, one contiguous piece of the workspace
+__device__ __forceinline__ void clear_block(u32x4 *zero, int n16)
+{
+    for (int i = blockIdx.x * kWideThreads + threadIdx.x; i < n16; i += gridDim.x * kWideThreads) zero[i] = u32x4{0u, 0u, 0u, 0u};
+}
+__global__ void __launch_bounds__(kWideThreads) clear_kernel(u32x4 *zero, int n16) { clear_block(zero, n16); }
+
+// ---- the sample ------------------------------------------------------------------------
+// One vector of each of `total` equal stretches of the tensor (all vectors when there are no more than that), for
+// stretch i at a place in it that depends on i only.  step: length of a stretch times 2^16.
+template <typename T, bool MAG, bool STD>
+__global__ void __launch_bounds__(kWideThreads)
+sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, u32x2 *__restrict__ sample, u32x4 *zero, int n16, Std sd)
 {
     constexpr int EPV = Elem<T>::EPV;
-    constexpr uint32_t kSlot = kTileThreads * kVecPerThread * EPV / kListShare;
-    __shared__ uint32_t wave_gt[kTileThreads / kWave];
-    __shared__ uint32_t filed;
-    if (st->route == 0u) return;
-    const uint32_t prefix = st->prefix, mask = st->mask;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int64_t nvec = (n + EPV - 1) / EPV;
-    if (threadIdx.x == 0) filed = 0u;
-    uint32_t bits[kVecPerThread][EPV];
-    int valid[kVecPerThread];
+    __shared__ uint32_t bins[kTopBins];
+    const uint32_t first = blockIdx.x * kWideThreads + threadIdx.x, stride = gridDim.x * kWideThreads;
+    uint32_t bits[kSampleVecs][EPV];
+    int64_t at[kSampleVecs];
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-        const int64_t v = tile_vec(blockIdx.x, wave, j, lane);
-        valid[j] = load_tile_vec<T, INSIDE>(x, n, nvec, v, bits[j]);
+    for (int u = 0; u < kSampleVecs; ++u) {
+        const uint32_t i = min(first + (uint32_t)u * stride, total - 1u);
+        const uint64_t v0 = (i * step) >> 16, v1 = ((i + 1) * step) >> 16;
+        uint32_t h = i * 0x9E3779B1u;
+        h ^= h >> 15;
+        h *= 0x85EBCA77u;
+        h ^= h >> 13;
+        at[u] = (int64_t)v0 + __umulhi(h, (uint32_t)(v1 - v0));
+        load_tile_vec<T, true>(x, 0, 0, at[u], bits[u]);
     }
+    for (int b = threadIdx.x; b < kTopBins; b += kWideThreads) bins[b] = 0u;
+    clear_block(zero, n16);
+    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) standardise<T, STD>(bits[j], valid[j], tile_vec(blockIdx.x, wave, j, lane), sd);
-    uint32_t gt = 0u, in_bin = 0u;
+    for (int u = 0; u < kSampleVecs; ++u) {
+        if (first + (uint32_t)u * stride < total) {
+            standardise<T, STD>(bits[u], EPV, at[u], sd);
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
+            for (int e = 0; e < EPV; ++e) atomicAdd(&bins[make_key<T, MAG>(bits[u][e]) >> (Elem<T>::KEYBITS - kTop)], 1u);
+        }
+    }
+    __syncthreads();
+    // 16-bit counts (a workgroup holds at most 16384 entries), four bins a thread
+    const uint32_t *b = bins + 4 * threadIdx.x;
+    sample[blockIdx.x * kWideThreads + threadIdx.x] = u32x2{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
+}
+
+// One workgroup: the bracket from the sample's histograms (FULL: from the tensor's own, which is cleared again).
+// rank_hi <= rank_lo: the ranks, counted from the largest, whose bins bound it; size: entries counted.
+template <bool FULL>
+__global__ void __launch_bounds__(kWideThreads)
+bracket_kernel(State *st, const u32x2 *__restrict__ sample, int wgs, uint32_t *full, int key_bits, uint32_t rank_hi, uint32_t rank_lo,
+               uint32_t size)
+{
+    __shared__ uint32_t wave_sums[kWideWaves];
+    __shared__ uint32_t edge[4];                           // highest bin, entries above it, lowest bin, entries down to it
+    constexpr int PER = kTopBins / kWideThreads;           // 4
+    const int slot = kWideThreads - 1 - (int)threadIdx.x;  // bins 4 * slot .. 4 * slot + 3, highest first
+    uint32_t h[PER] = {0u, 0u, 0u, 0u};
+    if (FULL) {
+        const u32x4 f = reinterpret_cast<const u32x4 *>(full)[slot];
+        h[0] = f.w; h[1] = f.z; h[2] = f.y; h[3] = f.x;
+        reinterpret_cast<u32x4 *>(full)[slot] = u32x4{0u, 0u, 0u, 0u};
+    } else {
+        u32x2 s[kSampleWgs];
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            if (INSIDE || e < valid[j]) {
-                const uint32_t top = make_key<T, MAG>(bits[j][e]) & mask;
-                gt += top > prefix ? 1u : 0u;
-                in_bin += top == prefix ? 1u : 0u;
+        for (int w = 0; w < kSampleWgs; ++w) s[w] = sample[min(w, wgs - 1) * kWideThreads + slot];
+#pragma unroll
+        for (int w = 0; w < kSampleWgs; ++w) {
+            if (w < wgs) {
+                h[0] += s[w].y >> 16; h[1] += s[w].y & 0xFFFFu;
+                h[2] += s[w].x >> 16; h[3] += s[w].x & 0xFFFFu;
             }
         }
     }
-    const uint32_t packed = gt | (in_bin << 16);            // a wave holds at most 2048 elements
-    const uint32_t incl = wave_scan_u32(packed);
-    const uint32_t wave_total = wave_total_u32(incl);
-    if (lane == 0) wave_gt[wave] = wave_total & 0xFFFFu;
-    const uint32_t wave_filed = wave_total >> 16;
-    __syncthreads();                                        // `filed` is zero
-    if (wave_filed) {                                       // wave-uniform
-        uint32_t base = 0u;
-        if (lane == 0) base = atomicAdd(&filed, wave_filed);
-        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-        uint32_t slot = base + ((incl - packed) >> 16);
-        uint32_t *keys = lists + (int64_t)blockIdx.x * kSlot;
+    if (threadIdx.x < 4) edge[threadIdx.x] = 0u;           // ranks outside the sample leave a bracket at the bottom: T is missed
+    uint32_t above = block_exclusive_scan<kWideThreads>(h[0] + h[1] + h[2] + h[3], wave_sums);
 #pragma unroll
-        for (int j = 0; j < kVecPerThread; ++j) {
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t bin = (uint32_t)(4 * slot + PER - 1 - j);
+        if (above < rank_hi && rank_hi <= above + h[j]) { edge[0] = bin; edge[1] = above; }
+        if (above < rank_lo && rank_lo <= above + h[j]) { edge[2] = bin; edge[3] = above + h[j]; }
+        above += h[j];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int shift = key_bits - kTop;
+        const uint32_t nb = edge[0] - edge[2] + 1u;
+        int log_nb = 0;
+        while ((1u << log_nb) < nb && log_nb < 12) ++log_nb;
+        // too wide for the digits, or too much for the lists (1/14 of the tensor on average, 1/10.7 of a tile)
+        const bool plain = nb > (uint32_t)kMaxBracketBins || (uint64_t)(edge[3] - edge[1]) * 14u > size;
+        const int range_bits = log_nb + shift;
+        const int digit2 = min(range_bits, max(9, log_nb + 6));            // the rest is at most 14 bits
+        st->plain = plain ? 1u : 0u;
+        st->overflow = 0u;
+        st->lo = edge[2] << shift;
+        st->last = (edge[2] << shift) + ((nb << shift) - 1u);
+        st->digit2 = (uint32_t)digit2;
+        st->shift2 = (uint32_t)(range_bits - digit2);
+    }
+}
+
+// ---- the sweep: records, key lists and totals --------------------------------------------
+// Bound by the read of the tensor and the records (0.7 bytes an element), with instruction issue close behind (bf16):
+// 50.3 M fp32 41.5 us, 5.7 TB/s; 51.6 M bf16 30 us, 4.6 TB/s.  A candidate's place comes from prefix sums over the
+// lanes' counts; a lane per element and two v_mbcnt each instead (4-byte loads, no counts) took 50 and 52 us.  The
+// records pass through LDS so that they leave in whole lines: 37 MB written here and read by the write below in
+// place of a second read of the tensor with one scattered store per survivor (42 us, bf16 44).
+// Leaves tile_cnt[tile] = (keys above the bracket | candidates << 16, keys filed).
+constexpr uint32_t kTooMany = 0x8000u;                      // in place of a tile's candidate count: it has no records
+// REC: make records; the tensor is not read again then, and its loads are non-temporal.
+template <typename T, bool MAG, bool STD, bool INSIDE, bool REC>
+__device__ __forceinline__ void
+sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
+           uint32_t *__restrict__ lists, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, const Std &sd)
+{
+    constexpr int EPV = Elem<T>::EPV, G = kGroups<T>;
+    __shared__ u32x2 stage[REC ? kRecSlots : 1];                      // (element bits, place in the tile)
+    __shared__ uint32_t wave_cnt[kTileThreads / kWave];
+    __shared__ uint32_t filed;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int64_t tile = blockIdx.x;
+    if (threadIdx.x == 0) filed = 0u;
+    uint32_t bits[G][EPV];
+    int valid[G];
+    load_round<T, STD, INSIDE, REC>(x, n, tile, wave, lane, bits, valid, sd);
+    const uint32_t lo = st->lo, last = st->last;
+
+    // candidates per group of 64 vectors: three 10-bit fields (at most 512 each) in one prefix sum
+    uint32_t packed[2] = {0u, 0u};
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        uint32_t c = 0u;
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) c += ((INSIDE || e < valid[j]) && make_key<T, MAG>(bits[j][e]) >= lo) ? 1u : 0u;
+        packed[j / 3] += c << (10 * (j % 3));
+    }
+    uint32_t incl[2], total[2];
+#pragma unroll
+    for (int w = 0; w < (G + 2) / 3; ++w) {
+        incl[w] = wave_scan_u32(packed[w]);
+        total[w] = wave_total_u32(incl[w]);
+    }
+    uint32_t wave_total = 0u;
+#pragma unroll
+    for (int j = 0; j < G; ++j) wave_total += (total[j / 3] >> (10 * (j % 3))) & 1023u;
+    if (lane == 0) wave_cnt[wave] = wave_total;
+    __syncthreads();                                        // `filed` is zero as well
+    uint32_t pos = 0u, n_cand = 0u;
+#pragma unroll
+    for (int w = 0; w < kTileThreads / kWave; ++w) {
+        pos += (w < wave) ? wave_cnt[w] : 0u;
+        n_cand += wave_cnt[w];
+    }
+    uint32_t *keys = lists + tile * kListSlots;
+    const bool whole = REC && n_cand <= (uint32_t)kRecSlots;       // workgroup-uniform
+    if (whole) {
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            uint32_t at = pos + (((incl[j / 3] - packed[j / 3]) >> (10 * (j % 3))) & 1023u);
 #pragma unroll
             for (int e = 0; e < EPV; ++e) {
-                if (INSIDE || e < valid[j]) {
+                if ((INSIDE || e < valid[j]) && make_key<T, MAG>(bits[j][e]) >= lo)
+                    stage[at++] = u32x2{bits[j][e], (uint32_t)(((wave * G + j) * kWave + lane) * EPV + e)};
+            }
+            pos += (total[j / 3] >> (10 * (j % 3))) & 1023u;
+        }
+        __syncthreads();
+        uint32_t *rv = rec_val + tile * kRecSlots;
+        uint16_t *rp = rec_pos + tile * kRecSlots;
+        for (uint32_t base = 0u; base < n_cand; base += kTileThreads) {
+            const uint32_t t = base + threadIdx.x;
+            const bool in = t < n_cand;
+            const u32x2 r = stage[min(t, n_cand - 1u)];
+            const uint32_t key = make_key<T, MAG>(r.x);
+            if (in) {
+                rv[t] = r.x;
+                rp[t] = (uint16_t)r.y;
+            }
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in && key <= last);
+            if (m != 0) {                                   // wave-uniform
+                uint32_t slot = 0u;
+                if (lane == 0) slot = atomicAdd(&filed, (uint32_t)__builtin_popcountll(m));
+                slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + lanes_below(m);
+                if (in && key <= last && slot < (uint32_t)kListSlots) keys[slot] = key;
+            }
+        }
+    } else {
+        uint32_t in_bracket = 0u;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) {
+                const uint32_t key = make_key<T, MAG>(bits[j][e]);
+                in_bracket += ((INSIDE || e < valid[j]) && key >= lo && key <= last) ? 1u : 0u;
+            }
+        }
+        const uint32_t upto = wave_scan_u32(in_bracket), all = wave_total_u32(upto);
+        if (all) {                                          // wave-uniform
+            uint32_t slot = 0u;
+            if (lane == 0) slot = atomicAdd(&filed, all);
+            slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + upto - in_bracket;
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
                     const uint32_t key = make_key<T, MAG>(bits[j][e]);
-                    if ((key & mask) == prefix) {
-                        if (slot < kSlot) keys[slot] = key;
+                    if ((INSIDE || e < valid[j]) && key >= lo && key <= last) {
+                        if (slot < (uint32_t)kListSlots) keys[slot] = key;
                         ++slot;
                     }
                 }
@@ -462,314 +555,595 @@ bracket_tile(const T *__restrict__ x, int64_t n, State *st, u32x2 *__restrict__ 
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        u32x2 c = {0u, min(filed, kSlot)};
-#pragma unroll
-        for (int w = 0; w < kTileThreads / kWave; ++w) c.x += wave_gt[w];
-        tile_cnt[blockIdx.x] = c;
-        if (filed > kSlot) st->overflow = 1u;
+        const uint32_t f = filed, gt = n_cand - f;
+        tile_cnt[tile] = u32x2{gt | ((whole ? n_cand : kTooMany) << 16), min(f, (uint32_t)kListSlots)};
+        if (f > (uint32_t)kListSlots) st->overflow = 1u;
+        atomicAdd(reinterpret_cast<unsigned long long *>(counters + (tile & (kCounters - 1)) * 8),
+                  (unsigned long long)gt | ((unsigned long long)f << 32));
     }
 }
 
-template <typename T, bool MAG, bool STD>
+template <typename T, bool MAG, bool STD, bool REC>
 __global__ void __launch_bounds__(kTileThreads)
-bracket_kernel(const T *__restrict__ x, int64_t n, State *st, u32x2 *__restrict__ tile_cnt, uint32_t *__restrict__ lists, Std sd)
+sweep_kernel(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
+             uint32_t *__restrict__ lists, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, Std sd)
 {
-    // workgroup-uniform: the whole tile lies below n
-    constexpr int64_t kTileElems = (int64_t)kTileThreads * kVecPerThread * Elem<T>::EPV;
-    if (((int64_t)blockIdx.x + 1) * kTileElems <= n)
-        bracket_tile<T, MAG, STD, true>(x, n, st, tile_cnt, lists, sd);
+    if (st->plain) return;
+    if (((int64_t)blockIdx.x + 1) * kTileElems <= n)        // workgroup-uniform: the whole tile lies below n
+        sweep_tile<T, MAG, STD, true, REC>(x, n, st, counters, tile_cnt, lists, rec_val, rec_pos, sd);
     else
-        bracket_tile<T, MAG, STD, false>(x, n, st, tile_cnt, lists, sd);
+        sweep_tile<T, MAG, STD, false, REC>(x, n, st, counters, tile_cnt, lists, rec_val, rec_pos, sd);
 }
 
-// ---- per tile: keys above T, keys equal to T -------------------------------------------
-// plain route: from the tensor; list route: the list's keys are added to the
-// counts that bracket_kernel left.
-template <typename T, bool MAG, bool STD, bool INSIDE>
-__device__ __forceinline__ void
-count_tile(const T *__restrict__ x, int64_t n, const State *__restrict__ st, u32x2 *__restrict__ tile_cnt,
-             const uint32_t *__restrict__ lists, int64_t ntiles, Std sd)
+// ---- one digit: LDS histogram of the matching keys, non-empty bins added to the global one ----
+// Of the tensor; FIRST: the top digit, every key matches and there is no branch around the ds_add.  The top digit
+// keeps kCopies histograms, one per lane modulo kCopies: the plain route is the one of tensors with few distinct
+// values, whose lanes would queue for a handful of LDS words (50.3 M fp32 multiples of a half: 89 us with one, 62 with
+// four, 58 with eight).
+constexpr int kCopies = 8;
+template <typename T, bool MAG, bool STD, bool FIRST>
+__device__ __forceinline__ void tensor_hist(const T *__restrict__ x, int64_t n, uint32_t prefix, uint32_t mask, int shift,
+                                            int nbins, uint32_t *bins, const Std &sd)
 {
     constexpr int EPV = Elem<T>::EPV;
-    constexpr uint32_t kTileElems = kTileThreads * kVecPerThread * EPV;
-    __shared__ uint32_t wave_gt[kTileThreads / kWave], wave_eq[kTileThreads / kWave];
-    const uint32_t Tk = st->T;
-    if (use_list(st)) {                                     // a wave per tile list
-        constexpr int64_t kSlot = (int64_t)kTileElems / kListShare;
-        const int64_t t = (int64_t)blockIdx.x * (kTileThreads / kWave) + (threadIdx.x >> 6);
-        if (t >= ntiles) return;
-        const int lane_ = threadIdx.x & (kWave - 1);
-        const u32x2 c = tile_cnt[t];
-        const uint32_t cnt = min(c.y, (uint32_t)kSlot);
-        const uint32_t *keys = lists + t * kSlot;
-        uint32_t gt_ = 0u, eq_ = 0u;
-        for (uint32_t i = lane_; i < cnt; i += kWave) {
-            const uint32_t key = keys[i];
-            gt_ += key > Tk ? 1u : 0u;
-            eq_ += key == Tk ? 1u : 0u;
+    const int64_t nvec = (n + EPV - 1) / EPV;
+    const int64_t nfull = n / EPV;                            // vectors wholly below n
+    const int64_t chunk = (int64_t)kWideThreads * kVecPerThread;
+    const uint32_t copy = (threadIdx.x % kCopies) * kTopBins;
+    auto sweep = [&](auto inside_tag, int64_t base) {
+        constexpr bool INSIDE = decltype(inside_tag)::value;
+        uint32_t bits[kVecPerThread][EPV];
+        int valid[kVecPerThread];
+#pragma unroll
+        for (int j = 0; j < kVecPerThread; ++j)
+            valid[j] = load_tile_vec<T, INSIDE>(x, n, nvec, base + (int64_t)j * kWideThreads + threadIdx.x, bits[j]);
+#pragma unroll
+        for (int j = 0; j < kVecPerThread; ++j)
+            standardise<T, STD>(bits[j], valid[j], base + (int64_t)j * kWideThreads + threadIdx.x, sd);
+#pragma unroll
+        for (int j = 0; j < kVecPerThread; ++j) {
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) {
+                if (INSIDE || e < valid[j]) {
+                    const uint32_t key = make_key<T, MAG>(bits[j][e]);
+                    if (FIRST) atomicAdd(&bins[copy + (key >> shift)], 1u);
+                    else if ((key & mask) == prefix) atomicAdd(&bins[(key >> shift) & (uint32_t)(nbins - 1)], 1u);
+                }
+            }
         }
-        const uint32_t sums = wave_total_u32(wave_scan_u32(gt_ | (eq_ << 16)));
-        if (lane_ == 0) {
-            u32x2 r;
-            r.x = c.x + (sums & 0xFFFFu);
-            r.y = sums >> 16;
-            tile_cnt[t] = r;
+    };
+    for (int64_t base = (int64_t)blockIdx.x * chunk; base < nvec; base += (int64_t)gridDim.x * chunk) {
+        if (base + chunk <= nfull) sweep(std::true_type{}, base);      // workgroup-uniform
+        else sweep(std::false_type{}, base);
+    }
+}
+// The key lists of four tiles t, t + stride, ...: counts and first 128 slots (those past the count hold anything).
+struct FourLists {
+    u32x2 cnt[4];
+    uint32_t a[4], b[4];
+    __device__ __forceinline__ void load(const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, int64_t t,
+                                         int64_t stride, int64_t end)
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t at = min(t + u * stride, end - 1);
+            cnt[u] = tile_cnt[at];
+            a[u] = lists[at * kListSlots + lane];
+            b[u] = lists[at * kListSlots + lane + kWave];
         }
+    }
+    template <typename F>
+    __device__ __forceinline__ void each(int u, const uint32_t *__restrict__ keys, F f) const
+    {
+        const uint32_t lane = threadIdx.x & (kWave - 1), n = cnt[u].y;
+        if (lane < n) f(a[u]);
+        if (lane + kWave < n) f(b[u]);
+        for (uint32_t i = lane + 2 * kWave; i < n; i += kWave) f(keys[i]);
+    }
+};
+// f(key) for every filed key, a wave per tile; first: the wave's first four, loaded ahead by the caller
+template <typename F>
+__device__ __forceinline__ void for_each_filed(FourLists &first, const u32x2 *__restrict__ tile_cnt,
+                                               const uint32_t *__restrict__ lists, int64_t ntiles, int grid, F f)
+{
+    const int64_t waves = (int64_t)grid * kWideWaves;
+    for (int64_t t = (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6); t < ntiles;) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (t + u * waves < ntiles) first.each(u, lists + (t + u * waves) * kListSlots, f);
+        t += 4 * waves;
+        if (t < ntiles) first.load(tile_cnt, lists, t, waves, ntiles);
+    }
+}
+__device__ __forceinline__ void clear_bins(uint32_t *bins, int nbins)
+{
+    for (int i = threadIdx.x; i < nbins; i += kWideThreads) bins[i] = 0u;
+}
+template <int COPIES = 1>
+__device__ __forceinline__ void add_bins(const uint32_t *bins, uint32_t *__restrict__ hist, int nbins)
+{
+    for (int i = threadIdx.x; i < nbins; i += kWideThreads) {
+        uint32_t c = 0u;
+#pragma unroll
+        for (int u = 0; u < COPIES; ++u) c += bins[u * kTopBins + i];
+        if (c) atomicAdd(&hist[i], c);
+    }
+}
+
+// the tensor's own top digit, in place of the sample
+template <typename T, bool MAG, bool STD>
+__global__ void __launch_bounds__(kWideThreads)
+top_digit_kernel(const T *__restrict__ x, int64_t n, uint32_t *__restrict__ hist, Std sd)
+{
+    __shared__ uint32_t bins[kCopies * kTopBins];
+    clear_bins(bins, kCopies * kTopBins);
+    __syncthreads();
+    tensor_hist<T, MAG, STD, true>(x, n, 0u, 0u, Elem<T>::KEYBITS - kTop, kTopBins, bins, sd);
+    __syncthreads();
+    add_bins<kCopies>(bins, hist, kTopBins);
+}
+
+// The verdict on the bracket, and the first digit (list route: of the bracket; plain route: the top one).
+template <typename T, bool MAG, bool STD>
+__global__ void __launch_bounds__(kWideThreads)
+digit_kernel(const T *__restrict__ x, int64_t n, State *st, const uint64_t *__restrict__ counters,
+             const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, uint32_t *__restrict__ hist2, int64_t ntiles,
+             uint32_t k, Std sd)
+{
+    __shared__ uint32_t bins[kCopies * kTopBins];
+    const int lane = threadIdx.x & (kWave - 1);
+    static_assert(kCounters == kWave, "a lane per counter");
+    const int grid = min((int)gridDim.x, kListGrid);
+    FourLists first;
+    first.load(tile_cnt, lists, (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6), (int64_t)grid * kWideWaves, ntiles);
+    const uint64_t c = counters[lane * 8];
+    const uint32_t gt = wave_total_u32(wave_scan_u32((uint32_t)c)), in = wave_total_u32(wave_scan_u32((uint32_t)(c >> 32)));
+    const bool plain = st->plain || st->overflow || gt >= k || k - gt > in;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->use_plain = plain ? 1u : 0u;
+        st->k_rem = plain ? k : k - gt;
+    }
+    if (!plain && (int)blockIdx.x >= grid) return;
+    const int nbins = plain ? kTopBins : 1 << st->digit2;
+    clear_bins(bins, plain ? kCopies * kTopBins : nbins);
+    __syncthreads();
+    if (plain) {
+        tensor_hist<T, MAG, STD, true>(x, n, 0u, 0u, Elem<T>::KEYBITS - kTop, kTopBins, bins, sd);
+    } else {
+        const uint32_t lo = st->lo, shift = st->shift2, top = (uint32_t)nbins - 1u;
+        for_each_filed(first, tile_cnt, lists, ntiles, grid, [&](uint32_t key) { atomicAdd(&bins[min((key - lo) >> shift, top)], 1u); });
+    }
+    __syncthreads();
+    if (plain) add_bins<kCopies>(bins, hist2, kTopBins);
+    else add_bins(bins, hist2, nbins);
+}
+
+// 32-bit keys: the second digit (list route: the rest of the key).
+template <typename T, bool MAG, bool STD>
+__global__ void __launch_bounds__(kWideThreads)
+second_digit_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *__restrict__ tile_cnt,
+                    const uint32_t *__restrict__ lists, const uint32_t *__restrict__ hist2, uint32_t *__restrict__ hist3,
+                    int64_t ntiles, Std sd)
+{
+    __shared__ uint32_t bins[1 << kMaxDigit3];
+    FourLists first;
+    first.load(tile_cnt, lists, (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6), (int64_t)gridDim.x * kWideWaves, ntiles);
+    const bool plain = st->use_plain != 0u;
+    const Choice c = select_bin<kWideThreads>(hist2, plain ? kTop : (int)st->digit2, st->k_rem);
+    const uint32_t shift = st->shift2;
+    const uint32_t lo2 = st->lo + (c.bin << shift);
+    const uint32_t prefix = c.bin << (32 - kTop), mask = ~0u << (32 - kTop);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->k_rem2 = c.left;
+        st->lo2 = lo2;
+        st->prefix = prefix;
+    }
+    const int nbins = plain ? 256 : 1 << shift;
+    clear_bins(bins, nbins);
+    __syncthreads();
+    if (plain)
+        tensor_hist<T, MAG, STD, false>(x, n, prefix, mask, 12, nbins, bins, sd);
+    else
+        for_each_filed(first, tile_cnt, lists, ntiles, (int)gridDim.x, [&](uint32_t key) {
+            if (key - lo2 < (uint32_t)nbins) atomicAdd(&bins[key - lo2], 1u);
+        });
+    __syncthreads();
+    add_bins(bins, hist3, nbins);
+}
+
+// List route: T, then the keys above T and equal to T per group of tiles and, inside a group, ahead of every tile.
+// Plain route: the last digit.
+template <typename T, bool MAG, bool STD>
+__global__ void __launch_bounds__(kWideThreads)
+count_kernel(const T *__restrict__ x, int64_t numel, State *st, const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists,
+             const uint32_t *__restrict__ hist2, const uint32_t *__restrict__ hist3, uint32_t *__restrict__ hist4,
+             u32x2 *__restrict__ tile_sum, u32x2 *__restrict__ group_sum, int64_t ntiles, int group_tiles, Std sd)
+{
+    constexpr bool WIDE_KEY = Elem<T>::KEYBITS == 32;
+    __shared__ uint32_t bins[kTopBins];                     // list route: the group's tiles' sums
+    __shared__ uint32_t wave_sums[kWideWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int64_t t0 = (int64_t)blockIdx.x * group_tiles, t1 = min(t0 + group_tiles, ntiles);
+    FourLists four;
+    four.load(tile_cnt, lists, t0 + wave, kWideWaves, t1);
+    const bool plain = st->use_plain != 0u;
+    const Choice c = WIDE_KEY ? select_bin<kWideThreads>(hist3, plain ? 8 : (int)st->shift2, st->k_rem2)
+                              : select_bin<kWideThreads>(hist2, plain ? kTop : (int)st->digit2, st->k_rem);
+    if (plain) {
+        const uint32_t prefix = WIDE_KEY ? st->prefix | (c.bin << 12) : c.bin << 4;
+        constexpr uint32_t low = WIDE_KEY ? 0xFFFu : 0xFu;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st->prefix3 = prefix;
+            st->k_rem3 = c.left;
+        }
+        clear_bins(bins, (int)low + 1);
+        __syncthreads();
+        tensor_hist<T, MAG, STD, false>(x, numel, prefix, ~low, 0, (int)low + 1, bins, sd);
+        __syncthreads();
+        add_bins(bins, hist4, (int)low + 1);
         return;
     }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int64_t nvec = (n + EPV - 1) / EPV;
-    uint32_t bits[kVecPerThread][EPV];
-    int valid[kVecPerThread];
-#pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-        const int64_t v = tile_vec(blockIdx.x, wave, j, lane);
-        valid[j] = load_tile_vec<T, INSIDE>(x, n, nvec, v, bits[j]);
+    const uint32_t Tk = (WIDE_KEY ? st->lo2 : st->lo) + c.bin;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->T = Tk;
+        st->take_eq = c.left;
     }
+    u32x2 *sum = reinterpret_cast<u32x2 *>(bins);
+    for (int64_t t = t0 + wave; t < t1;) {
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) standardise<T, STD>(bits[j], valid[j], tile_vec(blockIdx.x, wave, j, lane), sd);
-    uint32_t gt = 0u, eq = 0u;
-#pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            if (INSIDE || e < valid[j]) {
-                const uint32_t key = make_key<T, MAG>(bits[j][e]);
+        for (int u = 0; u < 4; ++u) {
+            const int64_t tile = t + u * kWideWaves;
+            if (tile >= t1) break;                          // wave-uniform
+            uint32_t gt = 0u, eq = 0u;
+            four.each(u, lists + tile * kListSlots, [&](uint32_t key) {
                 gt += key > Tk ? 1u : 0u;
                 eq += key == Tk ? 1u : 0u;
-            }
+            });
+            const uint32_t both = wave_total_u32(wave_scan_u32(gt | (eq << 16)));
+            if (lane == 0) sum[tile - t0] = u32x2{(four.cnt[u].x & 0xFFFFu) + (both & 0xFFFFu), both >> 16};
         }
-    }
-    const uint32_t packed = wave_total_u32(wave_scan_u32(gt | (eq << 16)));     // a wave holds at most 2048 elements
-    if (lane == 0) {
-        wave_gt[wave] = packed & 0xFFFFu;
-        wave_eq[wave] = packed >> 16;
+        t += 4 * kWideWaves;
+        if (t < t1) four.load(tile_cnt, lists, t, kWideWaves, t1);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        u32x2 c = {0u, 0u};
-#pragma unroll
-        for (int w = 0; w < kTileThreads / kWave; ++w) {
-            c.x += wave_gt[w];
-            c.y += wave_eq[w];
-        }
-        tile_cnt[blockIdx.x] = c;
-    }
-}
-
-template <typename T, bool MAG, bool STD>
-__global__ void __launch_bounds__(kTileThreads)
-count_kernel(const T *__restrict__ x, int64_t n, const State *__restrict__ st, u32x2 *__restrict__ tile_cnt,
-             const uint32_t *__restrict__ lists, int64_t ntiles, Std sd)
-{
-    // workgroup-uniform: the whole tile lies below n
-    constexpr int64_t kTileElems = (int64_t)kTileThreads * kVecPerThread * Elem<T>::EPV;
-    if (((int64_t)blockIdx.x + 1) * kTileElems <= n)
-        count_tile<T, MAG, STD, true>(x, n, st, tile_cnt, lists, ntiles, sd);
-    else
-        count_tile<T, MAG, STD, false>(x, n, st, tile_cnt, lists, ntiles, sd);
-}
-
-// ---- tile counts -> first output slot and tie budget of every tile ----------------------
-// One workgroup.  Loads and stores are 16 bytes a lane, lanes side by side (a
-// lane that fetched 16 consecutive tiles of its own made the kernel's one CU
-// request every cache line 16 times over and took twice as long).  A pass covers
-// 2 * kScanThreads tiles, thread t owning tiles 2t and 2t+1 of it; a round
-// issues the loads of kScanPasses passes at once and then scans them in turn,
-// carrying the totals.
-constexpr int kScanPasses = 8;
-__device__ __forceinline__ void block_exclusive_scan2(uint32_t a, uint32_t b, uint32_t *sums_a, uint32_t *sums_b,
-                                                      uint32_t &before_a, uint32_t &before_b, uint32_t &total_a,
-                                                      uint32_t &total_b)
-{
-    constexpr int NW = kScanThreads / kWave;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const uint32_t ia = wave_scan_u32(a), ib = wave_scan_u32(b);
-    __syncthreads();                                       // the sums of the previous pass have been read
-    if (lane == kWave - 1) {
-        sums_a[wave] = ia;
-        sums_b[wave] = ib;
-    }
-    __syncthreads();
-    uint32_t ba = 0u, bb = 0u, ta = 0u, tb = 0u;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const uint32_t sa = sums_a[w], sb = sums_b[w];
-        ba += (w < wave) ? sa : 0u;
-        bb += (w < wave) ? sb : 0u;
-        ta += sa;
-        tb += sb;
-    }
-    before_a = ba + ia - a;
-    before_b = bb + ib - b;
-    total_a = ta;
-    total_b = tb;
-}
-__global__ void __launch_bounds__(kScanThreads)
-scan_kernel(const State *__restrict__ st, const u32x2 *__restrict__ tile_cnt, u32x2 *__restrict__ tile_base,
-            int64_t ntiles)
-{
-    __shared__ uint32_t sums_gt[kScanThreads / kWave], sums_eq[kScanThreads / kWave];
-    const uint32_t take_eq = st->take_eq;
-    auto base_of = [&](uint32_t gt_b, uint32_t eq_b) {
-        u32x2 r;
-        r.x = gt_b + min(eq_b, take_eq);
-        r.y = take_eq > eq_b ? take_eq - eq_b : 0u;
-        return r;
-    };
-    uint32_t gt_carry = 0u, eq_carry = 0u;
-    for (int64_t base = 0; base < ntiles; base += (int64_t)kScanPasses * 2 * kScanThreads) {
-        u32x2 c0[kScanPasses], c1[kScanPasses];
-#pragma unroll
-        for (int p = 0; p < kScanPasses; ++p) {
-            const int64_t t = base + (int64_t)p * 2 * kScanThreads + 2 * threadIdx.x;
-            c0[p] = u32x2{0u, 0u};
-            c1[p] = u32x2{0u, 0u};
-            if (t + 1 < ntiles) {                           // tile_cnt is 128-byte aligned and t is even
-                const u32x4 v = *reinterpret_cast<const u32x4 *>(tile_cnt + t);
-                c0[p] = u32x2{v.x, v.y};
-                c1[p] = u32x2{v.z, v.w};
-            } else if (t < ntiles) {
-                c0[p] = tile_cnt[t];
-            }
-        }
-#pragma unroll
-        for (int p = 0; p < kScanPasses; ++p) {
-            const int64_t t = base + (int64_t)p * 2 * kScanThreads + 2 * threadIdx.x;
-            if (base + (int64_t)p * 2 * kScanThreads >= ntiles) break;          // uniform
-            uint32_t gt_before, eq_before, gt_total, eq_total;
-            block_exclusive_scan2(c0[p].x + c1[p].x, c0[p].y + c1[p].y, sums_gt, sums_eq, gt_before, eq_before, gt_total,
-                                  eq_total);
-            gt_before += gt_carry;
-            eq_before += eq_carry;
-            const u32x2 b0 = base_of(gt_before, eq_before);
-            const u32x2 b1 = base_of(gt_before + c0[p].x, eq_before + c0[p].y);
-            if (t + 1 < ntiles) {
-                *reinterpret_cast<u32x4 *>(tile_base + t) = u32x4{b0.x, b0.y, b1.x, b1.y};
-            } else if (t < ntiles) {
-                tile_base[t] = b0;
-            }
-            gt_carry += gt_total;
-            eq_carry += eq_total;
-        }
-    }
+    // the sums ahead of every tile of the group, and the group's own; two tiles a thread
+    static_assert(kMaxGroupTiles <= 2 * kWideThreads && kMaxGroupTiles * 2 <= kTopBins, "group size");
+    const int n = (int)(t1 - t0), i = 2 * (int)threadIdx.x;
+    const u32x2 zero = {0u, 0u}, s0 = i < n ? sum[i] : zero, s1 = i + 1 < n ? sum[i + 1] : zero;
+    const u32x2 a = {block_exclusive_scan<kWideThreads>(s0.x + s1.x, wave_sums), block_exclusive_scan<kWideThreads>(s0.y + s1.y, wave_sums)};
+    if (i < n) tile_sum[t0 + i] = a;
+    if (i + 1 < n) tile_sum[t0 + i + 1] = a + s0;
+    if (i < n && i + 2 >= n) group_sum[blockIdx.x] = a + s0 + s1;
 }
 
 template <typename T> __device__ __forceinline__ void store_raw(T *p, uint32_t bits);
 template <> __device__ __forceinline__ void store_raw<float>(float *p, uint32_t bits) { *p = __builtin_bit_cast(float, bits); }
 template <> __device__ __forceinline__ void store_raw<uint16_t>(uint16_t *p, uint32_t bits) { *p = (uint16_t)bits; }
 
-// ---- emit the survivors of a tile in ascending index order ------------------------------
-template <typename T, bool MAG, bool STD, bool INSIDE>
-__device__ __forceinline__ void
-write_tile(const T *__restrict__ x, int64_t n, const State *__restrict__ st, const u32x2 *__restrict__ tile_base,
-             typename Elem<T>::Out *__restrict__ vals, int32_t *__restrict__ idx, int32_t *__restrict__ tile_ptr, uint32_t k,
-             Std sd)
-{
-    constexpr int EPV = Elem<T>::EPV;
-    constexpr int NW = kTileThreads / kWave;
-    constexpr int64_t kWaveElems = (int64_t)kWave * kVecPerThread * EPV;       // 1024 (fp32) / 2048 (bf16)
-    __shared__ uint32_t wave_gt[NW], wave_eq[NW];
-    const uint32_t Tk = st->T;
-    const u32x2 tb = tile_base[blockIdx.x];
-    const uint32_t out_base = tb.x, budget = tb.y;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int64_t nvec = (n + EPV - 1) / EPV;
+__device__ __forceinline__ void stream_raw(float *p, uint32_t bits) { __builtin_nontemporal_store(__builtin_bit_cast(float, bits), p); }
+__device__ __forceinline__ void stream_raw(uint16_t *p, uint32_t bits) { __builtin_nontemporal_store((uint16_t)bits, p); }
 
-    uint32_t bits[kVecPerThread][EPV];
-    int valid[kVecPerThread];
-    uint32_t packed[kVecPerThread];                         // per vector: keys above T | keys equal T << 16
+// Where the outputs go.
+template <typename T>
+struct Out {
+    typename Elem<T>::Out *vals;
+    int32_t *idx, *tile_ptr;
+    uint32_t k;
+};
+
+// keys above T / equal to T of a tile, from the tensor (a workgroup, a wave a round); the sums are thread 0's
+template <typename T, bool MAG, bool STD, bool INSIDE>
+__device__ __forceinline__ u32x2 count_tensor_tile(const T *__restrict__ x, int64_t n, int64_t tile, uint32_t Tk, const Std &sd)
+{
+    constexpr int EPV = Elem<T>::EPV, G = kGroups<T>;
+    __shared__ uint32_t part[kTileThreads / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    uint32_t bits[G][EPV];
+    int valid[G];
+    load_round<T, STD, INSIDE>(x, n, tile, wave, lane, bits, valid, sd);
+    uint32_t packed = 0u;
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-        const int64_t v = tile_vec(blockIdx.x, wave, j, lane);
-        valid[j] = load_tile_vec<T, INSIDE>(x, n, nvec, v, bits[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) standardise<T, STD>(bits[j], valid[j], tile_vec(blockIdx.x, wave, j, lane), sd);
-    uint32_t incl[kVecPerThread];
-    uint32_t wave_packed = 0u;
-#pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-        uint32_t gt = 0u, eq = 0u;
+    for (int j = 0; j < G; ++j) {
 #pragma unroll
         for (int e = 0; e < EPV; ++e) {
-            if (INSIDE || e < valid[j]) {
-                const uint32_t key = make_key<T, MAG>(bits[j][e]);
-                gt += key > Tk ? 1u : 0u;
-                eq += key == Tk ? 1u : 0u;
-            }
+            const uint32_t key = make_key<T, MAG>(bits[j][e]);
+            if (INSIDE || e < valid[j]) packed += (key > Tk ? 1u : 0u) + (key == Tk ? 1u << 16 : 0u);
         }
-        packed[j] = gt | (eq << 16);
-        incl[j] = wave_scan_u32(packed[j]);                 // at most 512 per group and field
-        wave_packed += wave_total_u32(incl[j]);
     }
-    if (lane == 0) {
-        wave_gt[wave] = wave_packed & 0xFFFFu;
-        wave_eq[wave] = wave_packed >> 16;
-    }
+    const uint32_t sum = wave_total_u32(wave_scan_u32(packed));    // at most 1024 in either half
+    __syncthreads();                                        // the previous tile's sums have been read
+    if (lane == 0) part[wave] = sum;
     __syncthreads();
+    u32x2 r = {0u, 0u};
+#pragma unroll
+    for (int w = 0; w < kTileThreads / kWave; ++w) {
+        r.x += part[w] & 0xFFFFu;
+        r.y += part[w] >> 16;
+    }
+    return r;
+}
+
+// the survivors of a tile in ascending index order, from the tensor: a wave, round by round, or (WG) a workgroup, a
+// wave a round
+template <typename T, bool MAG, bool STD, bool INSIDE, bool WG>
+__device__ __forceinline__ void write_tensor_tile(const T *__restrict__ x, int64_t n, int64_t tile, uint32_t Tk, uint32_t out_base,
+                                                  uint32_t budget, const Out<T> &out, const Std &sd)
+{
+    constexpr int EPV = Elem<T>::EPV, G = kGroups<T>;
+    const int lane = threadIdx.x & (kWave - 1);
+    __shared__ uint32_t part[WG ? kTileThreads / kWave : 1];
+    const int wave = threadIdx.x >> 6;
     uint32_t run_gt = 0u, run_eq = 0u;                      // survivors / ties of this tile ahead of the current group
+#pragma unroll 1
+    for (int step = 0; step < (WG ? 1 : 4); ++step) {
+        const int round = WG ? wave : step;
+        uint32_t bits[G][EPV];
+        int valid[G];
+        load_round<T, STD, INSIDE>(x, n, tile, round, lane, bits, valid, sd);
+        uint32_t packed[G], incl[G];                        // keys above T | keys equal T << 16: at most 512 per group and field
+        uint32_t mine = 0u;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        run_gt += (w < wave) ? wave_gt[w] : 0u;
-        run_eq += (w < wave) ? wave_eq[w] : 0u;
-    }
-    if (tile_ptr) {
-        const int64_t wave_start = (int64_t)blockIdx.x * (kWaveElems * NW) + wave * kWaveElems;
-        if (lane == 0 && wave_start % kPtrTile == 0 && wave_start < n)
-            tile_ptr[wave_start / kPtrTile] = (int32_t)(out_base + run_gt + min(run_eq, budget));
-        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) tile_ptr[(n + kPtrTile - 1) / kPtrTile] = (int32_t)k;
-    }
-    if constexpr (STD) {
-        if (sd.row_ptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) sd.row_ptr[sd.last_row + 1u] = (int32_t)k;
-    }
+        for (int j = 0; j < G; ++j) {
+            packed[j] = 0u;
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-        const uint32_t excl = incl[j] - packed[j];
-        uint32_t my_gt = run_gt + (excl & 0xFFFFu);
-        uint32_t my_eq = run_eq + (excl >> 16);
-        const int64_t e0 = tile_vec(blockIdx.x, wave, j, lane) * EPV;
-        if constexpr (STD) {
-            if (sd.row_ptr && valid[j]) {                       // rows start on vector boundaries
-                const uint32_t row = __umulhi((uint32_t)e0, sd.magic) >> sd.shift;
-                if ((uint32_t)e0 == row * sd.H) sd.row_ptr[row] = (int32_t)(out_base + my_gt + min(my_eq, budget));
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            if (INSIDE || e < valid[j]) {
+            for (int e = 0; e < EPV; ++e) {
                 const uint32_t key = make_key<T, MAG>(bits[j][e]);
-                const bool above = key > Tk;
-                const bool tie = key == Tk;
-                if (above || (tie && my_eq < budget)) {
-                    const uint32_t pos = out_base + my_gt + min(my_eq, budget);
-                    if (pos < k) {                          // always true for consistent counts; guards the stores
-                        store_raw<typename Elem<T>::Out>(vals + pos, bits[j][e]);
-                        idx[pos] = (int32_t)(e0 + e);
-                    }
-                }
-                my_gt += above ? 1u : 0u;
-                my_eq += tie ? 1u : 0u;
+                if (INSIDE || e < valid[j]) packed[j] += (key > Tk ? 1u : 0u) + (key == Tk ? 1u << 16 : 0u);
+            }
+            incl[j] = wave_scan_u32(packed[j]);
+            mine += wave_total_u32(incl[j]);
+        }
+        if constexpr (WG) {
+            __syncthreads();                                // the previous tile's sums have been read
+            if (lane == 0) part[wave] = mine;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kTileThreads / kWave; ++w) {
+                run_gt += w < wave ? part[w] & 0xFFFFu : 0u;
+                run_eq += w < wave ? part[w] >> 16 : 0u;
             }
         }
-        const uint32_t group = wave_total_u32(incl[j]);
-        run_gt += group & 0xFFFFu;
-        run_eq += group >> 16;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const uint32_t excl = incl[j] - packed[j], group = wave_total_u32(incl[j]);
+            uint32_t my_gt = run_gt + (excl & 0xFFFFu);
+            uint32_t my_eq = run_eq + (excl >> 16);
+            const int64_t e0 = round_vec<T>(tile, round, j, lane) * EPV;
+            if constexpr (STD) {
+                if (sd.row_ptr && valid[j]) {               // rows start on vector boundaries
+                    const uint32_t row = row_of((uint32_t)e0, sd);
+                    if ((uint32_t)e0 == row * sd.H) sd.row_ptr[row] = (int32_t)(out_base + my_gt + min(my_eq, budget));
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) {
+                if (INSIDE || e < valid[j]) {
+                    const uint32_t key = make_key<T, MAG>(bits[j][e]);
+                    const bool above = key > Tk;
+                    const bool tie = key == Tk;
+                    if (above || (tie && my_eq < budget)) {
+                        const uint32_t pos = out_base + my_gt + min(my_eq, budget);
+                        if (pos < out.k) {                  // always true for consistent counts; guards the stores
+                            store_raw<typename Elem<T>::Out>(out.vals + pos, bits[j][e]);
+                            out.idx[pos] = (int32_t)(e0 + e);
+                        }
+                    }
+                    my_gt += above ? 1u : 0u;
+                    my_eq += tie ? 1u : 0u;
+                }
+            }
+            run_gt += group & 0xFFFFu;
+            run_eq += group >> 16;
+        }
     }
 }
 
+// the survivors of a tile from its records (a wave; n_cand <= kRecSlots of them, 64 a register).  Bound by latency
+// (a wave's one round of loads, 1.7 waves a slot): 50.3 M fp32 entries, 5.03 M kept, 18 us for 80 MB.
+constexpr int kRecChunks = kRecSlots / kWave;
+constexpr int kFirstChunks = 8;            // loaded before the count is known
+template <typename T, bool MAG, bool STD>
+__device__ __forceinline__ void write_record_tile(const uint32_t (&v)[kRecChunks], const uint32_t (&p)[kRecChunks], uint32_t n_cand,
+                                                  int64_t n, int64_t tile, uint32_t Tk, uint32_t out_base, uint32_t budget,
+                                                  const Out<T> &out, const Std &sd)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t t0 = (uint32_t)(tile * kTileElems);
+    uint32_t kept = 0u, run_eq = 0u;
+    int row_run = -1;                                       // row of the last survivor (or the last row that began ahead of the tile)
+    const bool rows = STD && sd.row_ptr != nullptr;
+    if (rows && t0 > 0u) row_run = (int)row_of(t0 - 1u, sd);
+#pragma unroll
+    for (int u = 0; u < kRecChunks; ++u) {
+        const uint32_t i = (uint32_t)(u * kWave + lane);
+        if ((uint32_t)(u * kWave) >= n_cand) break;         // wave-uniform
+        const uint32_t key = make_key<T, MAG>(v[u]);
+        const bool tie = i < n_cand && key == Tk;
+        const uint64_t ties = __builtin_amdgcn_ballot_w64(tie);
+        const bool keep = i < n_cand && (key > Tk || (tie && run_eq + lanes_below(ties) < budget));
+        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+        const uint32_t pos = out_base + kept + lanes_below(m);
+        if (keep && pos < out.k) {                          // always below k for consistent counts; guards the stores
+            stream_raw(out.vals + pos, v[u]);
+            __builtin_nontemporal_store((int32_t)(t0 + p[u]), out.idx + pos);
+        }
+        if (rows) {
+            // row_ptr[r] for the rows that begin between the previous survivor and this one
+            const int row = (int)row_of(t0 + p[u], sd);
+            const uint64_t below = m & (((uint64_t)1 << lane) - 1u);
+            const int prev = __shfl(row, below ? 63 - __builtin_clzll(below) : lane, kWave);
+            if (keep)
+                for (int r = (below ? prev : row_run) + 1; r <= row; ++r) sd.row_ptr[r] = (int32_t)pos;
+            if (m) row_run = __builtin_amdgcn_readlane(row, 63 - __builtin_clzll(m));
+        }
+        kept += (uint32_t)__builtin_popcountll(m);
+        run_eq += (uint32_t)__builtin_popcountll(ties);
+    }
+    if (rows) {
+        const int end = (int)row_of((uint32_t)(min((int64_t)t0 + kTileElems, n) - 1), sd);
+        for (int r = row_run + 1 + lane; r <= end; r += kWave) sd.row_ptr[r] = (int32_t)(out_base + kept);
+    }
+}
+
+// List route: keys above T / equal to T ahead of a tile: those ahead of it in its group plus the sums of the groups
+// ahead (a wave, no barrier).
+__device__ __forceinline__ u32x2 sums_ahead(const u32x2 *__restrict__ tile_sum, const u32x2 *__restrict__ group_sum, int64_t tile,
+                                            int group_tiles)
+{
+    const int lane = threadIdx.x & (kWave - 1), group = (int)(tile / group_tiles);
+    u32x2 a = {0u, 0u};
+#pragma unroll
+    for (int u = 0; u < kMaxGroups / kWave; ++u) {
+        const u32x2 s = group_sum[u * kWave + lane];        // (past the last group: zeros)
+        a += u * kWave + lane < group ? s : u32x2{0u, 0u};
+    }
+    return tile_sum[tile] + u32x2{wave_total_u32(wave_scan_u32(a.x)), wave_total_u32(wave_scan_u32(a.y))};
+}
+// The same on the plain route, whose tile sums are the tiles' own (a workgroup).
+__device__ __forceinline__ u32x2 plain_sums_ahead(const u32x2 *__restrict__ tile_sum, const u32x2 *__restrict__ group_sum, int64_t first,
+                                            int group_tiles)
+{
+    __shared__ uint32_t part[2][kTileThreads / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int group = (int)(first / group_tiles);
+    u32x2 a = {0u, 0u};
+    static_assert(kMaxGroups <= kTileThreads, "a thread per group");
+    if ((int)threadIdx.x < group) a = group_sum[threadIdx.x];
+    for (int64_t t = (int64_t)group * group_tiles + threadIdx.x; t < first; t += kTileThreads) {
+        const u32x2 s = tile_sum[t];
+        a.x += s.x;
+        a.y += s.y;
+    }
+    const uint32_t gx = wave_total_u32(wave_scan_u32(a.x)), gy = wave_total_u32(wave_scan_u32(a.y));
+    __syncthreads();                                        // `part` may still be read from the previous tile
+    if (lane == 0) {
+        part[0][wave] = gx;
+        part[1][wave] = gy;
+    }
+    __syncthreads();
+    u32x2 sum = {0u, 0u};
+#pragma unroll
+    for (int w = 0; w < kTileThreads / kWave; ++w) {
+        sum.x += part[0][w];
+        sum.y += part[1][w];
+    }
+    return sum;
+}
+template <typename T>
+__device__ __forceinline__ void write_pointers(const Out<T> &out, int64_t tile, int64_t ntiles, uint32_t out_base, const Std &sd, bool std)
+{
+    if ((threadIdx.x & (kWave - 1)) != 0) return;
+    if (out.tile_ptr) {
+        out.tile_ptr[tile] = (int32_t)out_base;
+        if (tile == ntiles - 1) out.tile_ptr[ntiles] = (int32_t)out.k;
+    }
+    if (std && sd.row_ptr && tile == ntiles - 1) sd.row_ptr[sd.last_row + 1u] = (int32_t)out.k;
+}
+
+// Plain route: T, then the counts per tile and group (few enough workgroups that the search for T is amortised).
+template <typename T, bool MAG, bool STD>
+__device__ __forceinline__ void plain_count(const T *__restrict__ x, int64_t n, State *st, const uint32_t *__restrict__ hist4,
+                                            u32x2 *tile_sum, u32x2 *group_sum, int64_t ntiles, int group_tiles, const Std &sd)
+{
+    const int64_t grid = min((int64_t)gridDim.x, (int64_t)kPlainGrid);
+    if ((int64_t)blockIdx.x >= grid) return;
+    const Choice c = select_bin<kTileThreads>(hist4, Elem<T>::KEYBITS == 32 ? 12 : 4, st->k_rem3);
+    const uint32_t Tk = st->prefix3 | c.bin;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->T = Tk;
+        st->take_eq = c.left;
+    }
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += grid) {              // workgroup-uniform
+        const u32x2 r = (tile + 1) * kTileElems <= n ? count_tensor_tile<T, MAG, STD, true>(x, n, tile, Tk, sd)
+                                                     : count_tensor_tile<T, MAG, STD, false>(x, n, tile, Tk, sd);
+        if (threadIdx.x == 0) {
+            tile_sum[tile] = r;
+            uint32_t *g = reinterpret_cast<uint32_t *>(group_sum + tile / group_tiles);
+            atomicAdd(g, r.x);
+            atomicAdd(g + 1, r.y);
+        }
+    }
+}
+// the survivors of one tile, from the tensor (a workgroup)
+template <typename T, bool MAG, bool STD>
+__device__ __forceinline__ void dense_tile(const T *__restrict__ x, int64_t n, const State *st,
+                                           u32x2 ahead, int64_t tile, int64_t ntiles, const Out<T> &out, const Std &sd)
+{
+    const uint32_t Tk = st->T, take_eq = st->take_eq;
+    const uint32_t out_base = ahead.x + min(ahead.y, take_eq), budget = take_eq > ahead.y ? take_eq - ahead.y : 0u;
+    if (threadIdx.x < kWave) write_pointers<T>(out, tile, ntiles, out_base, sd, STD);
+    if ((tile + 1) * kTileElems <= n)
+        write_tensor_tile<T, MAG, STD, true, true>(x, n, tile, Tk, out_base, budget, out, sd);
+    else
+        write_tensor_tile<T, MAG, STD, false, true>(x, n, tile, Tk, out_base, budget, out, sd);
+}
+
+// The survivors from the records (list route; on the plain route the counts).
 template <typename T, bool MAG, bool STD>
 __global__ void __launch_bounds__(kTileThreads)
-write_kernel(const T *__restrict__ x, int64_t n, const State *__restrict__ st, const u32x2 *__restrict__ tile_base,
-             typename Elem<T>::Out *__restrict__ vals, int32_t *__restrict__ idx, int32_t *__restrict__ tile_ptr, uint32_t k,
-             Std sd)
+write_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ rec_val,
+             const uint16_t *__restrict__ rec_pos, const uint32_t *__restrict__ hist4, u32x2 *tile_sum, u32x2 *group_sum, int64_t ntiles,
+             int group_tiles, Out<T> out, Std sd)
 {
-    // workgroup-uniform: the whole tile lies below n
-    constexpr int64_t kTileElems = (int64_t)kTileThreads * kVecPerThread * Elem<T>::EPV;
-    if (((int64_t)blockIdx.x + 1) * kTileElems <= n)
-        write_tile<T, MAG, STD, true>(x, n, st, tile_base, vals, idx, tile_ptr, k, sd);
+    if (st->use_plain != 0u) {
+        plain_count<T, MAG, STD>(x, n, st, hist4, tile_sum, group_sum, ntiles, group_tiles, sd);
+        return;
+    }
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
+    const uint32_t Tk = st->T, take_eq = st->take_eq;
+    // the records travel while the sums ahead are added up; no branch around any load
+    const int64_t here = min(tile, ntiles - 1);
+    const uint32_t n_cand = tile_cnt[here].x >> 16;
+    const uint32_t *rv = rec_val + here * kRecSlots;
+    const uint16_t *rp = rec_pos + here * kRecSlots;
+    uint32_t v[kRecChunks], p[kRecChunks];
+#pragma unroll
+    for (int u = 0; u < kFirstChunks; ++u) {                // (a list's unused slots hold anything)
+        v[u] = rv[u * kWave + lane];
+        p[u] = rp[u * kWave + lane];
+    }
+    const bool more = n_cand > (uint32_t)(kFirstChunks * kWave) && n_cand != kTooMany;
+#pragma unroll
+    for (int u = kFirstChunks; u < kRecChunks; ++u) {
+        v[u] = p[u] = 0u;
+        if (more) {
+            v[u] = rv[u * kWave + lane];
+            p[u] = rp[u * kWave + lane];
+        }
+    }
+    const u32x2 ahead = sums_ahead(tile_sum, group_sum, here, group_tiles);
+    if (tile >= ntiles) return;
+    const uint32_t out_base = ahead.x + min(ahead.y, take_eq), budget = take_eq > ahead.y ? take_eq - ahead.y : 0u;
+    write_pointers<T>(out, tile, ntiles, out_base, sd, STD);
+    if (n_cand != kTooMany)
+        write_record_tile<T, MAG, STD>(v, p, n_cand, n, tile, Tk, out_base, budget, out, sd);
+    else if ((tile + 1) * kTileElems <= n)
+        write_tensor_tile<T, MAG, STD, true, false>(x, n, tile, Tk, out_base, budget, out, sd);
     else
-        write_tile<T, MAG, STD, false>(x, n, st, tile_base, vals, idx, tile_ptr, k, sd);
+        write_tensor_tile<T, MAG, STD, false, false>(x, n, tile, Tk, out_base, budget, out, sd);
+}
+
+// The same when the sweep has made no records: a workgroup per tile, from the tensor.
+template <typename T, bool MAG, bool STD>
+__global__ void __launch_bounds__(kTileThreads)
+dense_write_kernel(const T *__restrict__ x, int64_t n, State *st, const uint32_t *__restrict__ hist4, u32x2 *tile_sum, u32x2 *group_sum,
+                   int64_t ntiles, int group_tiles, Out<T> out, Std sd)
+{
+    if (st->use_plain != 0u) plain_count<T, MAG, STD>(x, n, st, hist4, tile_sum, group_sum, ntiles, group_tiles, sd);
+    else dense_tile<T, MAG, STD>(x, n, st, sums_ahead(tile_sum, group_sum, blockIdx.x, group_tiles), blockIdx.x, ntiles, out, sd);
+}
+
+// Plain route: the survivors.
+template <typename T, bool MAG, bool STD>
+__global__ void __launch_bounds__(kTileThreads)
+plain_write_kernel(const T *__restrict__ x, int64_t n, const State *st, const u32x2 *__restrict__ tile_sum,
+                   const u32x2 *__restrict__ group_sum, int64_t ntiles, int group_tiles, Out<T> out, Std sd)
+{
+    if (st->use_plain == 0u) return;
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x)           // workgroup-uniform
+        dense_tile<T, MAG, STD>(x, n, st, plain_sums_ahead(tile_sum, group_sum, tile, group_tiles), tile, ntiles, out, sd);
 }
 
 // ---- restore without tile pointers: zeros, then scatter -----------------------------------
@@ -848,19 +1222,24 @@ restore_tiles_kernel(const T *__restrict__ vals, const int32_t *__restrict__ idx
     for (int e = full * PER16 + tid; e < m; e += kTileThreads) out[t0 + e] = tile[e];
 }
 
-// Workspace: state | histogram | tile counts | tile bases | tile key lists.
+// Workspace: state | counters | group sums | three histograms | sample | tile counts | tile sums | key lists | records.
+// From the counters to the histograms everything has to be zero at the start.
 struct Workspace {
     State *st;
-    uint32_t *hist;
-    u32x2 *tile_cnt, *tile_base;
-    uint32_t *lists;
-    uint32_t route_cap;                    // largest bin that is sent to the lists: half of their slots
+    uint64_t *counters;
+    u32x2 *group_sum;
+    uint32_t *hist2, *hist3, *hist4;
+    u32x2 *sample;
+    u32x2 *tile_cnt, *tile_sum;
+    uint32_t *lists, *rec_val;
+    uint16_t *rec_pos;
     size_t bytes;
 };
+constexpr size_t kZeroBytes = kCounters * 64 + kMaxGroups * 8 + (size_t)(kTopBins + (1 << kMaxDigit3) + kTopBins) * 4;
 Workspace carve(void *base, int64_t n)
 {
     Workspace w;
-    const size_t slots = (size_t)((n + kPtrTile - 1) / kPtrTile);        // >= kernel tiles of either dtype
+    const size_t tiles = (size_t)((n + kPtrTile - 1) / kPtrTile);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char *p = static_cast<char *>(base) + off;
@@ -868,12 +1247,17 @@ Workspace carve(void *base, int64_t n)
         return p;
     };
     w.st = reinterpret_cast<State *>(take(sizeof(State)));
-    w.hist = reinterpret_cast<uint32_t *>(take((size_t)kMaxBins * 4));
-    w.tile_cnt = reinterpret_cast<u32x2 *>(take(slots * 8));
-    w.tile_base = reinterpret_cast<u32x2 *>(take(slots * 8));
-    // a bf16 tile spans two pointer tiles and owns both their list slots
-    w.lists = reinterpret_cast<uint32_t *>(take((slots + 1) * (size_t)(kPtrTile / kListShare) * 4));
-    w.route_cap = (uint32_t)(n / (2 * kListShare));
+    w.counters = reinterpret_cast<uint64_t *>(take(kCounters * 64));
+    w.group_sum = reinterpret_cast<u32x2 *>(take(kMaxGroups * 8));
+    w.hist2 = reinterpret_cast<uint32_t *>(take((size_t)kTopBins * 4));
+    w.hist3 = reinterpret_cast<uint32_t *>(take((size_t)4 << kMaxDigit3));
+    w.hist4 = reinterpret_cast<uint32_t *>(take((size_t)kTopBins * 4));
+    w.sample = reinterpret_cast<u32x2 *>(take((size_t)kSampleWgs * kTopBins * 2));
+    w.tile_cnt = reinterpret_cast<u32x2 *>(take(tiles * 8));
+    w.tile_sum = reinterpret_cast<u32x2 *>(take(tiles * 8));
+    w.lists = reinterpret_cast<uint32_t *>(take(tiles * kListSlots * 4));
+    w.rec_val = reinterpret_cast<uint32_t *>(take(tiles * kRecSlots * 4));
+    w.rec_pos = reinterpret_cast<uint16_t *>(take(tiles * kRecSlots * 2));
     w.bytes = off;
     return w;
 }
@@ -883,55 +1267,85 @@ size_t workspace_bytes_for(int64_t n)
     return carve(origin, n).bytes;
 }
 
-// digits from the top: fp32 12 | 8 | 12, bf16 12 | 4.  The middle digit is kept
-// narrow because every workgroup adds its non-empty bins to the global
-// histogram with atomics, and on the list route the second digit still sees
-// every filed key.
-template <typename T> struct Digits;
-template <> struct Digits<float> {
-    static constexpr int N = 3;
-    static constexpr int bits[3] = {12, 8, 12};
+// Which ranks of the sample bound the bracket.  The rank of T in a sample of `size` unlike entries has a standard
+// deviation of at most sqrt(size f (1 - f)), f = k / n: six of them either way, 0.7 % of the tensor at f = 0.1.  (All
+// of a vector's four entries alike: three.)
+struct SamplePlan {
+    bool use;                              // false: T's rank is too close to an end, the tensor's own histogram is taken
+    uint32_t total, hi, lo, size;
+    uint64_t step;
 };
-template <> struct Digits<uint16_t> {
-    static constexpr int N = 2;
-    static constexpr int bits[3] = {12, 4, 0};
-};
+SamplePlan plan_sample(int64_t n, int64_t k, int epv)
+{
+    SamplePlan p = {false, 0u, 0u, 0u, 0u, 0u};
+    const int64_t vectors = n / epv, most = (int64_t)kSampleWgs * kSampleVecs * kWideThreads;
+    if (vectors == 0) return p;
+    const int64_t total = vectors < most ? vectors : most, size = total * epv, rest = n - vectors * epv;
+    p.total = (uint32_t)total;
+    p.size = (uint32_t)size;
+    p.step = ((uint64_t)vectors << 16) / (uint64_t)total;
+    int64_t hi, lo;
+    if (total == vectors) {                // every vector: only the last few entries were not seen
+        hi = k - rest;
+        lo = k;
+    } else {
+        const double f = (double)k / (double)n;
+        const int64_t r = (int64_t)(f * (double)size), margin = (int64_t)(6.0 * std::sqrt((double)size * f * (1.0 - f))) + rest + 1;
+        if (r < 256 || size - r < 256) return p;
+        hi = r - margin;
+        lo = r + margin;
+    }
+    p.use = true;
+    p.hi = (uint32_t)(hi < 1 ? 1 : hi);
+    p.lo = (uint32_t)(lo > size ? size : lo);
+    if (p.hi > p.lo) p.hi = p.lo;
+    return p;
+}
 
 template <typename T, bool MAG, bool STD>
 void launch_select(const T *x, int64_t n, uint32_t k, typename Elem<T>::Out *vals, int32_t *idx, int32_t *tile_ptr,
                    const Workspace &w, const Std &sd, hipStream_t s)
 {
-    using DigitPlan = Digits<typename Elem<T>::Key>;
-    constexpr int EPV = Elem<T>::EPV;
-    const int64_t nvec = (n + EPV - 1) / EPV;
-    const int64_t chunk = (int64_t)kHistThreads * kVecPerThread;
-    const int64_t nchunks = (nvec + chunk - 1) / chunk;
-    const unsigned hist_grid = (unsigned)(nchunks < SLIMFIT_PG_HIST_GRID ? nchunks : SLIMFIT_PG_HIST_GRID);
-    const int64_t tile_vecs = (int64_t)kTileThreads * kVecPerThread;
-    const int64_t ntiles = (nvec + tile_vecs - 1) / tile_vecs;
+    const int64_t ntiles = (n + kTileElems - 1) / kTileElems;
+    // at most kMaxGroups groups of tiles; also the workgroups of the digit and count launches
+    const int group_tiles = (int)(((ntiles + kMaxGroups - 1) / kMaxGroups + 3) / 4 * 4);
+    const unsigned groups = (unsigned)((ntiles + group_tiles - 1) / group_tiles);
+    const bool records = (int64_t)k * kRecShare <= n;
+    u32x4 *zero = reinterpret_cast<u32x4 *>(w.counters);
+    const int zero16 = (int)(kZeroBytes / 16);
+    const SamplePlan plan = plan_sample(n, (int64_t)k, Elem<T>::EPV);
 
-    init_kernel<<<1, kSelectThreads, 0, s>>>(w.st, w.hist, k);
-    int hi = Elem<T>::KEYBITS;
-    for (int d = 0; d < DigitPlan::N; ++d) {
-        const int bits = DigitPlan::bits[d];
-        const int shift = hi - bits;
-        const bool first = d == 0, last = d == DigitPlan::N - 1;
-        if (first)
-            hist_kernel<T, MAG, STD, true><<<hist_grid, kHistThreads, 0, s>>>(x, n, w.st, w.hist, w.tile_cnt, w.lists,
-                                                                             ntiles, shift, 1 << bits, sd);
-        else
-            hist_kernel<T, MAG, STD, false><<<hist_grid, kHistThreads, 0, s>>>(x, n, w.st, w.hist, w.tile_cnt, w.lists,
-                                                                              ntiles, shift, 1 << bits, sd);
-        select_kernel<<<1, kSelectThreads, 0, s>>>(w.st, w.hist, shift, 1 << bits, first ? 1 : 0, last ? 1 : 0,
-                                                   w.route_cap);
-        if (first && !last)
-            bracket_kernel<T, MAG, STD><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, sd);
-        hi = shift;
+    if (plan.use) {
+        const uint32_t per = kSampleVecs * kWideThreads;
+        const int wgs = (int)((plan.total + per - 1) / per);
+        sample_kernel<T, MAG, STD><<<wgs, kWideThreads, 0, s>>>(x, plan.total, plan.step, w.sample, zero, zero16, sd);
+        bracket_kernel<false><<<1, kWideThreads, 0, s>>>(w.st, w.sample, wgs, nullptr, Elem<T>::KEYBITS, plan.hi, plan.lo,
+                                                         plan.size);
+    } else {
+        clear_kernel<<<1, kWideThreads, 0, s>>>(zero, zero16);
+        top_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.hist4, sd);
+        bracket_kernel<true><<<1, kWideThreads, 0, s>>>(w.st, nullptr, 0, w.hist4, Elem<T>::KEYBITS, k, k, (uint32_t)n);
     }
-    count_kernel<T, MAG, STD><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, ntiles, sd);
-    scan_kernel<<<1, kScanThreads, 0, s>>>(w.st, w.tile_cnt, w.tile_base, ntiles);
-    write_kernel<T, MAG, STD><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.tile_base, vals, idx, tile_ptr, k,
-                                                                         sd);
+    if (records)
+        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.rec_val,
+                                                                                 w.rec_pos, sd);
+    else
+        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, nullptr,
+                                                                                  nullptr, sd);
+    digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.hist2, ntiles, k, sd);
+    if constexpr (Elem<T>::KEYBITS == 32)
+        second_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.hist2, w.hist3, ntiles, sd);
+    count_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.hist2, w.hist3, w.hist4, w.tile_sum,
+                                                              w.group_sum, ntiles, group_tiles, sd);
+    const Out<T> out = {vals, idx, tile_ptr, k};
+    if (records)
+        write_kernel<T, MAG, STD><<<(unsigned)((ntiles + 3) / 4), kTileThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.rec_val, w.rec_pos, w.hist4,
+                                                                                       w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
+    else
+        dense_write_kernel<T, MAG, STD><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.hist4, w.tile_sum, w.group_sum, ntiles,
+                                                                                 group_tiles, out, sd);
+    plain_write_kernel<T, MAG, STD><<<(unsigned)(ntiles < kPlainGrid ? ntiles : kPlainGrid), kTileThreads, 0, s>>>(
+        x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
 }
 
 }  // namespace
@@ -982,7 +1396,7 @@ int32_t prune_global_entry(const void *x, int32_t dt, int64_t n, int64_t H, cons
     if ((rc = check_device_range(workspace, w.bytes)) != SLIMFIT_OK) return rc;
     if (tile_ptr && (rc = check_device_range(tile_ptr, (size_t)slimfit_global_tile_ptr_len(n) * 4)) != SLIMFIT_OK)
         return rc;
-    Std sd = {nullptr, nullptr, 0u, 0u, 0u, 0u, 0u, nullptr};
+    Std sd = {nullptr, nullptr, 0u, 0u, 0u, 0u, 0u, 0u, nullptr};
     if (standardised) {
         const size_t rows = (size_t)(n / H);
         if ((rc = check_device_range(mean, rows * 4)) != SLIMFIT_OK) return rc;
@@ -995,7 +1409,8 @@ int32_t prune_global_entry(const void *x, int32_t dt, int64_t n, int64_t H, cons
         sd.rstd = rstd;
         sd.magic = (uint32_t)((pow + (uint64_t)H - 1) / (uint64_t)H);   // < 2^32 because H > 2^(l-1)
         sd.shift = (uint32_t)(l - 1);
-        sd.wave_uniform = (H % (kWave * epv) == 0) ? 1u : 0u;           // the 64 vectors a wave loads together share a row
+        sd.wave_uniform = (H % kWave == 0) ? 1u : 0u;
+        sd.vec_uniform = (H % (kWave * epv) == 0) ? 1u : 0u;
         sd.last_row = (uint32_t)(rows - 1);
         sd.H = (uint32_t)H;
         sd.row_ptr = row_ptr;

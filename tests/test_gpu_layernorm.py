@@ -273,3 +273,19 @@ def test_param_grads_slab_counts(rows, H, slabs, dtype):
     with pytest.raises(sf.SlimfitError) as e:
         sf.layernorm_param_grads(x, mean, rstd, dy, dg.t, db.t, too_small)
     assert e.value.status == sf.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,H", [(40000, 8), (1700, 104), (700, 1000), (257, 4096), (9001, 64), (3, 4096)])
+def test_standardised_pruning_rows_and_tiles(rows, H, dtype):
+    """Rows shorter and longer than a tile, and not aligned with it: row pointers from the records (a tenth kept,
+    many rows with no survivor at all) and from the tensor (a quarter)."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(rows + H)
+    x = torch.randn(rows, H, generator=g, device="cuda")
+    x[rows // 3: rows // 3 + rows // 5] *= 0.01                       # rows without survivors
+    x = x.to(dtype)
+    mean = 0.05 * torch.randn(rows, generator=g, device="cuda")
+    rstd = 0.9 + 0.2 * torch.rand(rows, generator=g, device="cuda")
+    for k in (rows * H // 10, rows * H // 4):
+        _prune_both(x, mean, rstd, k)

@@ -203,3 +203,68 @@ def test_layernorm_input_at_full_size(ci):
     k = sf.keep_count(x.numel(), 100000)
     assert k == int(x.numel() * 0.1)
     _run_both(x, k, True)
+
+
+# ---- sizes past the sample (65 536 entries) and the edges of the record route ----
+
+def _signs(g, n):
+    return torch.where(torch.rand(n, generator=g, device="cuda") < 0.5, -1.0, 1.0)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,k", [(200003, 200003 // 9), (200003, 200003 // 9 + 1), (300000, 1), (300001, 299999), (300001, 700),
+                                 (1 << 19, 1 << 18), ((1 << 19) + 4095, 52428)])
+def test_records_and_sample_rule(n, k, dtype):
+    """One entry in nine is where records stop; ranks near either end take the tensor's own first digit."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    x = torch.randn(n, generator=g, device="cuda").to(dtype)
+    _run_both(x, k, True, restore=False)
+    _run_both(x, k, False, restore=False)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tiles_with_more_candidates_than_records(dtype):
+    """Two tiles are all candidates (read from the tensor again), the others hold hardly any; then one in which a
+    single tile's keys crowd the bracket."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(31)
+    n = 40 * 4096 + 77
+    x = torch.rand(n, generator=g, device="cuda") * 0.5
+    x[3 * 4096:4 * 4096] += 4.0
+    x[-3000:] += 2.0
+    x = (x * _signs(g, n)).to(dtype)
+    for k in (4096 + 1500, 4096 + 3000, 4096 + 3000 + 9000):
+        _run_both(x, k, True, restore=False)
+    x = torch.exp2(torch.rand(n, generator=g, device="cuda") * 60 - 50)          # many binades wide
+    _run_both((x * _signs(g, n)).to(dtype), n // 10, True, restore=False)
+
+
+def _sampled_vectors(n, epv):
+    """The vectors the bracket is estimated from: one of each of 16 384 stretches, at a hashed place."""
+    vectors, total = n // epv, 16384
+    i = np.arange(total, dtype=np.uint64)
+    step = np.uint64((vectors << 16) // total)
+    v0, v1 = (i * step) >> np.uint64(16), ((i + np.uint64(1)) * step) >> np.uint64(16)
+    h = (i * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)
+    h ^= h >> np.uint64(15)
+    h = (h * np.uint64(0x85EBCA77)) & np.uint64(0xFFFFFFFF)
+    h ^= h >> np.uint64(13)
+    return (v0 + ((h * (v1 - v0)) >> np.uint64(32))).astype(np.int64)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("scale", [0.25, 4.0])
+def test_sample_that_misses_the_cut(dtype, scale):
+    """Every entry the sample sees is four times smaller (larger) than the rest: T lies above (below) the bracket."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(41)
+    epv = 4 if dtype == torch.float32 else 8
+    n = 70000 * epv + 3
+    x = torch.randn(n, generator=g, device="cuda")
+    at = torch.from_numpy((_sampled_vectors(n, epv)[:, None] * epv + np.arange(epv)).reshape(-1)).cuda()
+    x[at] *= scale
+    x = x.to(dtype)
+    for k in (n // 10, n // 2):
+        _run_both(x, k, True, restore=False)
+        _run_both(x, k, False, restore=False)
