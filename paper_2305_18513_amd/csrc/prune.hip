@@ -57,8 +57,11 @@ __device__ __forceinline__ int popc64(uint64_t m) { return __builtin_popcountll(
 // Finding the cut value T (the k-th largest entry of the row):
 //   1. lane-local, then wave-wide minimum and maximum (DPP butterflies);
 //   2. a 256-bin histogram of the row in the wave's private LDS region, bins
-//      of equal width in the order-preserving integer image of the floats,
-//      bin 0 holding the largest values (ds_add, one per element);
+//      of equal width in the order-preserving integer image of the floats
+//      (of logits: in their values), bin 0 holding the largest (ds_add, one per
+//      element).  A score row's entries are all positive and span binades, which
+//      the integer image suits (in value bins peaked rows took 261 us for 67);
+//      logits lie around 0, where the image has a gap of 2^31 values;
 //   3. a wave prefix sum over the bins locates the bin that holds the k-th
 //      largest entry; if the entries above that bin plus the bin's own are
 //      exactly k, its lower edge separates the kept set and the search is over
@@ -68,11 +71,11 @@ __device__ __forceinline__ int popc64(uint64_t m) { return __builtin_popcountll(
 //      lane mask is popcounted on the scalar unit, ending as soon as a probe is
 //      passed by exactly k entries or the bracket is a single value (ties).
 // Survivors are compacted in ascending column order with mask-prefix counts
-// (mbcnt) into (value, column) records in LDS when k <= 64; a wave owns 8
+// (mbcnt) into (value, column) records in LDS when k <= 64; a wave owns up to 8
 // consecutive rows and stores their records as two contiguous runs, so the
 // output leaves in full cache lines instead of a dozen masked stores per row.
-// Launch shape: one 8-row unit per wave (no persistent loop; the chip streams
-// best with many short workgroups).
+// Launch shape: one unit per wave (no persistent loop; the chip streams best with
+// many short workgroups).
 constexpr int kBins = 256;
 constexpr int kStage = 64;           // largest k whose output is staged in LDS
 #ifndef SLIMFIT_PRUNE_ROWS_PER_UNIT
@@ -158,13 +161,14 @@ template <> __device__ __forceinline__ float load_elem_stream<uint16_t>(const ui
 }
 
 // LDS staging of one wave: the (value bits, column) records of the kept entries
-// of kRowsPerUnit consecutive rows, in output order (row stride k).
-struct StageRec {
+// of the unit's rows, in output order (row stride k).
+struct alignas(8) StageRec {            // one 8-byte LDS store
     uint32_t v, c;
 };
-struct alignas(16) WaveStage {
-    StageRec rec[kRowsPerUnit * kStage];
-};
+__host__ __device__ inline size_t row_lds_bytes(bool softmax, bool staged, int unit_rows, int k)      // LDS of one wave
+{
+    return (softmax ? 2 : 1) * kBins * 4 + (staged ? ((size_t)(unit_rows * k) * sizeof(StageRec) + 15) / 16 * 16 : 0);
+}
 
 // Places the kept entries of one row in ascending column order, either as
 // records in the staging area (STAGED; at most k <= kStage per row) or directly
@@ -214,24 +218,24 @@ template <typename T, int M, bool FULL, bool STAGED, bool SOFTMAX>
 __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__restrict__ p, int64_t rows, int cols, int k,
                                                               int mode, float tau, T *__restrict__ vals,
                                                               uint16_t *__restrict__ idx, int32_t *__restrict__ counts,
-                                                              T *__restrict__ probs)
+                                                              T *__restrict__ probs, int unit_rows, int64_t n_units)
 {
     // keys of bf16 inputs have 16 zero low bits: work in units of 2^16 there
     constexpr int KEY_SHIFT = sizeof(T) == 2 ? 16 : 0;
     constexpr uint32_t UNIT = 1u << KEY_SHIFT;
     constexpr uint32_t KEY_MASK = ~(UNIT - 1u);
-    __shared__ uint32_t s_hist[kRowWaves][kBins];
-    __shared__ WaveStage s_stage[STAGED ? kRowWaves : 1];
+    extern __shared__ __align__(16) uint32_t row_lds[];      // a wave's bins and unit_rows * k records
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);      // uniform: rows and pointers stay scalar
-    uint32_t *hist = s_hist[wave];
-    StageRec *rec = s_stage[STAGED ? wave : 0].rec;
+    int lds_at = wave * (int)row_lds_bytes(SOFTMAX, STAGED, unit_rows, k), rec_at = lds_at + (SOFTMAX ? 2 : 1) * kBins * 4;
+    asm("" : "+s"(lds_at), "+s"(rec_at));      // two plain bases: their common part folded into every address costs an addition each
+    uint32_t *hist = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(row_lds) + lds_at);
+    StageRec *rec = reinterpret_cast<StageRec *>(reinterpret_cast<char *>(row_lds) + rec_at);
     const float ninf = -__builtin_inff(), pinf = __builtin_inff(), qnan = __builtin_nanf("");
 
-    // a unit is kRowsPerUnit consecutive rows owned by one wave; a workgroup owns
+    // a unit is unit_rows (at most kRowsPerUnit) consecutive rows owned by one wave; a workgroup owns
     // kRowWaves consecutive units, so its output is one contiguous run
-    const int64_t n_units = (rows + kRowsPerUnit - 1) / kRowsPerUnit;
     const int64_t unit0 = (int64_t)blockIdx.x * kRowWaves + wave;
     const int64_t unit_stride = (int64_t)gridDim.x * kRowWaves;
 
@@ -251,8 +255,8 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
 
     float nxt[M];
     for (int64_t unit = unit0; unit < n_units; unit += unit_stride) {        // wave-uniform trip counts
-        const int64_t row0 = unit * kRowsPerUnit;
-        const int n_here = (int)min((int64_t)kRowsPerUnit, rows - row0);
+        const int64_t row0 = unit * unit_rows;
+        const int n_here = (int)min((int64_t)unit_rows, rows - row0);
         int my_count = 0;                                                    // lane i keeps row i's count
         // the launch gives every wave one unit (the loop only runs on for row counts beyond the grid
         // limit), so rows are prefetched inside a unit only
@@ -273,12 +277,20 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 for (int j = 0; j < M; ++j) nxt[j] = load_col(next_src, j);
             }
 
-            float pv[M];                 // SOFTMAX: the row's probabilities, in the output dtype's values
-            if constexpr (SOFTMAX) {
-                float lm = ninf;
+            // the largest entry as an order-preserving integer key (lane, then wave), -0 folded onto +0
+            float lmax = ninf;
+            uint32_t hi = 0u;
+            auto find_largest = [&]() {
 #pragma unroll
-                for (int j = 0; j < M; ++j) lm = fmaxf(lm, f[j]);
-                const float row_max = key_to_float(wave_umax(float_to_key(lm)));
+                for (int j = 0; j < M; ++j) lmax = fmaxf(lmax, f[j]);
+                hi = wave_umax(float_to_key(lmax));
+                if (hi == 0x7FFFFFFFu) hi = 0x80000000u;
+            };
+            float pv[M];                 // SOFTMAX: the row's probabilities, in the output dtype's values
+            float row_max = 0.0f;
+            if constexpr (SOFTMAX) {
+                find_largest();
+                row_max = key_to_float(hi);
                 float part = 0.0f;
 #pragma unroll
                 for (int j = 0; j < M; ++j) {
@@ -315,33 +327,62 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 if (c_tau <= k) { kk = c_tau; T_cut = T_exact = tau; c_ge = c_tau; have_cut = true; }
             }
             if (!have_cut) {
-                // 1. extrema as order-preserving keys (the minimum as a maximum of complements)
-                float lmax = ninf, lmin = pinf;
+                // 1. the range to search, as keys.  Its lower end is the row's minimum, or, for logits (BOUND), of the 64
+                //    lanes' largest entries the smallest: they are 64 entries of the row, so the kk-th largest is no
+                //    smaller, the bins get finer and masked entries (far below the rest) do not stretch them.  A range
+                //    that masked entries stretch all the same (fewer than 64 others, or kk > 64) is cut to the entries
+                //    within 128 of the largest if kk lie there (49 152 rows of 1000, 600 not masked, k = 100: 205 -> 110 us)
+                constexpr bool BOUND = SOFTMAX;
+                if constexpr (!SOFTMAX) find_largest();
+                float low = lmax;
+                if (!BOUND || kk > kWave || (!FULL && M == 1)) {
+                    low = pinf;
 #pragma unroll
-                for (int j = 0; j < M; ++j) {
-                    lmax = fmaxf(lmax, f[j]);
-                    lmin = fminf(lmin, f[j]);
+                    for (int j = 0; j < M; ++j) low = fminf(low, f[j]);
                 }
-                uint32_t hi = wave_umax(float_to_key(lmax));
-                uint32_t lo = ~wave_umax(~float_to_key(lmin));
+                uint32_t lo = ~wave_umax(~float_to_key(low));
                 // a key below that of +0 means a set sign bit somewhere in the row
                 const bool any_neg = lo < 0x80000000u;
                 // -0 is folded onto +0 so that integer order agrees with float comparison
-                if (hi == 0x7FFFFFFFu) hi = 0x80000000u;
                 if (lo == 0x7FFFFFFFu) lo = 0x80000000u;
+                float low_value = key_to_float(lo);
+                if (BOUND && row_max - low_value > 128.0f) {
+                    const float near = row_max - 128.0f;
+                    if (count_ge(near) >= kk) {
+                        low = pinf;
+#pragma unroll
+                        for (int j = 0; j < M; ++j) low = fminf(low, f[j] >= near ? f[j] : pinf);
+                        lo = ~wave_umax(~float_to_key(low));
+                        if (lo == 0x7FFFFFFFu) lo = 0x80000000u;
+                        low_value = key_to_float(lo);
+                    }
+                }
                 // bf16: the keys of negative values end in 0xFFFF, those of the others in 0x0000;
                 // dropping the low bits keeps the order and puts every key on a multiple of UNIT
-                hi &= KEY_MASK;
+                const uint32_t top = hi & KEY_MASK;
                 lo &= KEY_MASK;
-                const uint32_t range = (hi - lo) >> KEY_SHIFT;
+                const uint32_t range = (top - lo) >> KEY_SHIFT;
                 const int width_bits = 32 - __builtin_clz(range | 1u);
                 const int sh = KEY_SHIFT + (width_bits > 8 ? width_bits - 8 : 0);   // bin = (hi - key) >> sh < 256
+                const float width = (row_max - low_value) * (1.0f / 255.5f);        // BOUND: bins of this width in value
 
                 // 2. histogram
                 reinterpret_cast<uint4 *>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
                 __builtin_amdgcn_wave_barrier();
-                if (!any_neg) {
-                    const uint32_t hi_bits = hi ^ 0x80000000u;   // keys of non-negative floats are their bits
+                if constexpr (BOUND) {
+                    // bins of equal width in the values: the keys of a range around 0 hold two sets of all binades, and a
+                    // cut in a bin that wide took five more probes a row.  A rounded difference times a positive scale is
+                    // monotone, which is all that a bin has to be.  What lies below the bound goes, spread out, to 256
+                    // further bins which nothing reads (in one bin those entries queue for its word: 8 -> 25 conflict
+                    // cycles a ds_add)
+                    const float scale = __builtin_amdgcn_rcpf(width);
+#pragma unroll
+                    for (int j = 0; j < M; ++j) {
+                        const uint32_t b = (uint32_t)fminf((row_max - f[j]) * scale, 2.0f * kBins - 1.0f);
+                        if (FULL || valid[j]) atomicAdd(&hist[b], 1u);
+                    }
+                } else if (!any_neg) {
+                    const uint32_t hi_bits = top ^ 0x80000000u;      // keys of non-negative floats are their bits
 #pragma unroll
                     for (int j = 0; j < M; ++j) {
                         const uint32_t b = ((hi_bits - __builtin_bit_cast(uint32_t, f[j])) >> sh) & (kBins - 1);
@@ -350,7 +391,7 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 } else {
 #pragma unroll
                     for (int j = 0; j < M; ++j) {
-                        const uint32_t b = ((hi - (float_to_key(f[j] + 0.0f) & KEY_MASK)) >> sh) & (kBins - 1);
+                        const uint32_t b = ((top - (float_to_key(f[j] + 0.0f) & KEY_MASK)) >> sh) & (kBins - 1);
                         if (FULL || valid[j]) atomicAdd(&hist[b], 1u);
                     }
                 }
@@ -370,12 +411,45 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 const int sub = c0 >= kk ? 0 : (c1 >= kk ? 1 : (c2 >= kk ? 2 : 3));
                 const int c_bin = sub == 0 ? c0 : (sub == 1 ? c1 : (sub == 2 ? c2 : c3));   // entries >= the bin's lower edge
                 const int B = 4 * L + sub;
-                // keys of bin B: (hi - (B+1)<<sh, hi - B<<sh]
-                const uint64_t span = (uint64_t)(B + 1) << sh;
-                uint32_t blo = span > (uint64_t)(hi - lo) ? lo : (uint32_t)(hi - (uint32_t)span + UNIT);
-                uint32_t bhi = hi - ((uint32_t)B << sh) + UNIT;  // exclusive
-                c_ge = c_bin;
-                // 4. bisection inside the bin
+
+                // 4. the bracket [blo, bhi) of the cut's key, and the entries >= blo
+                uint32_t blo, bhi;
+                if constexpr (!BOUND) {
+                    // keys of bin B: (hi - (B+1)<<sh, hi - B<<sh]
+                    const uint64_t span = (uint64_t)(B + 1) << sh;
+                    blo = span > (uint64_t)(top - lo) ? lo : (uint32_t)(top - (uint32_t)span + UNIT);
+                    bhi = top - ((uint32_t)B << sh) + UNIT;
+                    c_ge = c_bin;
+                } else {
+                    // the bin's edges, apart by more than the binning rounds: an entry's place is off by at most 5 parts in
+                    // 2^23 of the range, the edges by 2 of the larger bound.  A width that is not an ordinary number (all
+                    // lanes' maxima alike, infinities) gives no edges.
+                    const bool ordinary = width > 1e-37f && width < 1e37f;
+                    const float edge = row_max - (float)(B + 1) * width;
+                    const float slack = 1e-6f * (row_max - low_value) + 3e-7f * fmaxf(fabsf(row_max), fabsf(low_value));
+                    blo = lo;
+                    bhi = top + UNIT;
+                    c_ge = -1;                                       // not counted yet (kk or more)
+                    if (!ordinary) {
+                        // the cut may well be the range's lower end (masked entries among the kept, equal maxima)
+                        if (blo + UNIT < bhi && count_ge(key_to_float(blo + UNIT)) < kk) bhi = blo + UNIT;
+                    } else if (reached) {
+                        blo = max(float_to_key(edge - slack) & KEY_MASK, lo);
+                        bhi = min(float_to_key(row_max - (float)B * width + slack) & KEY_MASK, top) + UNIT;
+                        // first the lower edge itself, which usually separates a bin that ends at kk
+                        const uint32_t at = float_to_key(edge) & KEY_MASK;
+                        if (c_bin == kk && at > blo && at < bhi) {
+                            const int c = count_ge(key_to_float(at));
+                            if (c >= kk) {
+                                blo = at;
+                                c_ge = c;
+                            } else {
+                                bhi = at;
+                            }
+                        }
+                    }
+                }
+                // bisection
                 if (c_ge != kk) {
                     while (bhi - blo > UNIT) {                    // at most 32 probes
                         const uint32_t mid = blo + (((bhi - blo) >> (KEY_SHIFT + 1)) << KEY_SHIFT);
@@ -388,6 +462,7 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                             bhi = mid;
                         }
                     }
+                    if (BOUND && c_ge < 0) c_ge = count_ge(key_to_float(blo));
                 }
                 T_cut = key_to_float(blo);
                 // the value itself when blo is the key of a row entry (negative bf16 values
@@ -399,8 +474,7 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
             uint16_t *oi = idx + row * (int64_t)k;
             const uint32_t first = STAGED ? (uint32_t)(i * k) : 0u;
             if (c_ge == kk) {
-                emit_row<T, M, STAGED>([&](int j) { return f[j] >= T_cut; }, kept_value, lane, k, kk, ov, oi, rec,
-                                       first);
+                emit_row<T, M, STAGED>([&](int j) { return f[j] >= T_cut; }, kept_value, lane, k, kk, ov, oi, rec, first);
             } else {
                 // more than kk entries reach the cut value: all above it, then the
                 // equal ones by ascending column until kk are taken
@@ -1076,6 +1150,31 @@ __global__ __launch_bounds__(kThreads) void softmax_backward_small_kernel(const 
     for (int e = n_vec * PER16 + tid; e < n; e += kThreads) dst[e] = tile[e];
 }
 
+// Rows a wave takes.  A wave works on one row at a time, so a call of few rows is spread over all of the chip's 8192
+// wave slots before any wave gets a second row (2048 rows of 384 fp32 columns, 8 rows a wave against one: 11.8 -> 6.8 us,
+// the host's time for a launch; 16384 rows with two: 14.0 -> 10.0; fp32 softmax 21.4 -> 12.6).  With rows enough, eight
+// share a wave's setup and leave as one run (786 432 rows of 384 columns pruned: 342 us with one row a wave, 240 with
+// eight), unless the call is bound by the dense rows it moves and not by instructions, where shorter waves stream better:
+//   fp32 softmax, whole slots   786 432 x 384: 441 us with one row, 482 with eight; 196 608 x 512 142 / 165, 768 142 / 169,
+//                               1024 142 / 164
+//   fp32 softmax, ragged slots  196 608 x 352: 110 us with four rows, 116 with eight; 448 134 / 144, 1000 179 / 185
+//   pruning, >= 512 whole       196 608 rows, fp32 with two 512: 87 / 89 us, 768 93.5 / 101, 1024 94 / 101; bf16 with four
+//                               768: 81 / 83, its softmax 121 / 125
+// Rows past 1024 columns hold the most instructions per byte: eight again.
+template <typename T, bool SOFTMAX>
+int unit_rows_for(int64_t rows, int cols)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    const bool whole = cols == 384 || cols == 512 || cols == 768 || cols == 1024;      // no absent columns, no ragged slots
+    int most = kRowsPerUnit;
+    if (cols <= 1024) {
+        if (SOFTMAX && F32) most = whole ? 1 : (cols > 256 ? 4 : most);
+        else if (whole && cols >= 512) most = F32 && !SOFTMAX ? 2 : 4;
+    }
+    const int64_t fill = rows / (256 * 32);
+    return fill < 1 ? 1 : (fill < most ? (int)fill : most);
+}
+
 template <typename T, bool SOFTMAX>
 void launch_prune(const void *p, int64_t rows, int cols, int k, int mode, float tau, void *vals, uint16_t *idx,
                   int32_t *counts, void *probs, hipStream_t st)
@@ -1106,11 +1205,12 @@ void launch_prune(const void *p, int64_t rows, int cols, int k, int mode, float 
         }
         return;
     }
-    const int64_t rows_per_block = (int64_t)kRowWaves * kRowsPerUnit;
-    const int64_t blocks_needed = (rows + rows_per_block - 1) / rows_per_block;
+    const int unit_rows = unit_rows_for<T, SOFTMAX>(rows, cols);
+    const int64_t n_units = (rows + unit_rows - 1) / unit_rows;       // (a division the kernel's scalar unit would take 150 instructions for)
+    const int64_t blocks_needed = (n_units + kRowWaves - 1) / kRowWaves;
     const unsigned grid = (unsigned)(blocks_needed < kMaxPruneBlocks ? blocks_needed : kMaxPruneBlocks);
 #define SLIMFIT_PRUNE_LAUNCH(MM, FF, SS)                                                                       \
-    prune_rows_kernel<T, MM, FF, SS, SOFTMAX><<<grid, kRowThreads, 0, st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts, pr)
+    prune_rows_kernel<T, MM, FF, SS, SOFTMAX><<<grid, kRowThreads, kRowWaves * row_lds_bytes(SOFTMAX, SS, unit_rows, k), st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts, pr, unit_rows, n_units)
 #define SLIMFIT_PRUNE_CASE(MM)                                                                                  \
     do {                                                                                                        \
         const bool full = cols == MM * kWave, staged = k <= kStage;                                             \

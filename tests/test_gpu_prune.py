@@ -168,3 +168,16 @@ def test_unaligned_row_start_is_accepted():
     ov, oi, _ = ref.prune_scores(to_np(p), 9)
     np.testing.assert_array_equal(to_np(idx), oi)
     np.testing.assert_array_equal(to_np(vals), ov)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols,k", [(8192 * 2 + 5, 72, 20), (8192 * 3 + 1, 64, 33), (8192 * 7 + 3, 40, 18),
+                                         (8192 * 8 - 1, 65, 17), (8192 * 2 + 1, 512, 51), (8192 * 4 + 2, 576, 20)])
+def test_rows_a_wave_takes(rows, cols, k, dtype):
+    """Row counts at which a wave takes two, three, seven and eight rows, ragged last units, staged and threshold runs."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    p = torch.softmax(torch.randn(rows, cols, generator=g, device="cuda"), dim=-1).to(dtype)
+    _run_both(p, k, restore=False)
+    _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=float(p.float().quantile(1.0 - k / cols) if p.numel() < 1 << 24 else 1.6 / cols),
+              restore=False)

@@ -159,3 +159,37 @@ def test_fused_kept_sets_differ_from_the_two_step_form_only_on_rounding_ties(ci)
         assert torch.equal(a, b)                                   # same kept values: only tied columns were swapped
     # fp32 probabilities of 384 random logits almost never tie; bf16 ones (about 300 distinct values a row) often do
     assert n_differ < (rows // 1000 if cfg.act_dtype == torch.float32 else rows)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols,k", [(8192 * 2 + 5, 72, 20), (8192 * 5 + 3, 224, 22), (8192 * 8 + 1, 65, 17),
+                                         (8192 * 2 + 1, 384, 38)])
+def test_rows_a_wave_takes(rows, cols, k, dtype):
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    _run_both(torch.randn(rows, cols, generator=g, device="cuda").to(dtype), k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols,k", [(40, 17), (64, 20), (130, 17), (384, 38), (512, 64), (700, 65), (1100, 110)])
+def test_hard_rows_for_the_value_bins(cols, k, dtype):
+    """Rows whose range says nothing about the cut: masked entries, one far outlier, constant rows and maxima, ranges
+    of a few denormals or of the whole type, values closer together than a bin can tell."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    l = torch.randn(260, cols, generator=g, device="cuda")
+    l[0:20, cols * 7 // 10:] = -1e9
+    l[20:40, k + 1:] = -3e38                                           # hardly more left than are kept
+    l[40:50, 5] = 300.0
+    l[50:60] = 1.25
+    l[60:70] = l[60:70].clamp(max=0.5)                                 # many equal maxima
+    l[70:80] = l[70:80] * 1e-41
+    l[80:90] = torch.sign(l[80:90]) * 3e38
+    l[90:100] = 1000.0 + l[90:100] * 1e-3
+    l[100:110] = -1000.0 + (l[100:110] * 4).round() * 2.0 ** -13
+    l[110:120] = (l[110:120] * 2).round() / 2
+    l[120:130] = torch.where(l[120:130] > 0, 0.0, -0.0)
+    l[130:140] = l[130:140].abs() + 1e-3
+    l[140:150] = -l[140:150].abs()
+    l[150:160] = torch.exp(l[150:160] * 8.0).clamp(max=1e30)
+    _run_both(l.to(dtype), k)
