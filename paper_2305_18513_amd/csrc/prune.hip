@@ -77,6 +77,7 @@ __device__ __forceinline__ int popc64(uint64_t m) { return __builtin_popcountll(
 // Launch shape: one unit per wave (no persistent loop; the chip streams best with
 // many short workgroups).
 constexpr int kBins = 256;
+constexpr uint32_t kNearKeys = 64u << 23;      // 64 binades: further below the largest entry lie zeros of masked columns
 constexpr int kStage = 64;           // largest k whose output is staged in LDS
 #ifndef SLIMFIT_PRUNE_ROWS_PER_UNIT
 #define SLIMFIT_PRUNE_ROWS_PER_UNIT 8
@@ -165,9 +166,9 @@ template <> __device__ __forceinline__ float load_elem_stream<uint16_t>(const ui
 struct alignas(8) StageRec {            // one 8-byte LDS store
     uint32_t v, c;
 };
-__host__ __device__ inline size_t row_lds_bytes(bool softmax, bool staged, int unit_rows, int k)      // LDS of one wave
+__host__ __device__ inline size_t row_lds_bytes(bool spill, bool staged, int unit_rows, int k)      // LDS of one wave
 {
-    return (softmax ? 2 : 1) * kBins * 4 + (staged ? ((size_t)(unit_rows * k) * sizeof(StageRec) + 15) / 16 * 16 : 0);
+    return (kBins + (spill ? kWave : 0)) * 4 + (staged ? ((size_t)(unit_rows * k) * sizeof(StageRec) + 15) / 16 * 16 : 0);
 }
 
 // Places the kept entries of one row in ascending column order, either as
@@ -224,11 +225,12 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
     constexpr int KEY_SHIFT = sizeof(T) == 2 ? 16 : 0;
     constexpr uint32_t UNIT = 1u << KEY_SHIFT;
     constexpr uint32_t KEY_MASK = ~(UNIT - 1u);
+    constexpr bool SPILL = SOFTMAX || sizeof(T) == 4;
     extern __shared__ __align__(16) uint32_t row_lds[];      // a wave's bins and unit_rows * k records
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);      // uniform: rows and pointers stay scalar
-    int lds_at = wave * (int)row_lds_bytes(SOFTMAX, STAGED, unit_rows, k), rec_at = lds_at + (SOFTMAX ? 2 : 1) * kBins * 4;
+    int lds_at = wave * (int)row_lds_bytes(SPILL, STAGED, unit_rows, k), rec_at = lds_at + (kBins + (SPILL ? kWave : 0)) * 4;
     asm("" : "+s"(lds_at), "+s"(rec_at));      // two plain bases: their common part folded into every address costs an addition each
     uint32_t *hist = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(row_lds) + lds_at);
     StageRec *rec = reinterpret_cast<StageRec *>(reinterpret_cast<char *>(row_lds) + rec_at);
@@ -330,9 +332,11 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 // 1. the range to search, as keys.  Its lower end is the row's minimum, or, for logits (BOUND), of the 64
                 //    lanes' largest entries the smallest: they are 64 entries of the row, so the kk-th largest is no
                 //    smaller, the bins get finer and masked entries (far below the rest) do not stretch them.  A range
-                //    that masked entries stretch all the same (fewer than 64 others, or kk > 64) is cut to the entries
-                //    within 128 of the largest if kk lie there (49 152 rows of 1000, 600 not masked, k = 100: 205 -> 110 us)
-                constexpr bool BOUND = SOFTMAX;
+                //    that masked entries stretch all the same (fewer than 64 others, kk > 64, probabilities that are 0) is
+                //    cut to the entries near the largest if kk lie there: 196 608 rows of 384 pruned, 268 not masked, 193 ->
+                //    79 us; 49 152 logit rows of 1000, 600 not masked, k = 100, 124 -> 96.  Not for bf16 scores: plain rows
+                //    lose 2 % to the test (237 -> 242 us at 786 432 x 384).
+                constexpr bool BOUND = SOFTMAX, NEAR = sizeof(T) == 4;
                 if constexpr (!SOFTMAX) find_largest();
                 float low = lmax;
                 if (!BOUND || kk > kWave || (!FULL && M == 1)) {
@@ -342,21 +346,21 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 }
                 uint32_t lo = ~wave_umax(~float_to_key(low));
                 // a key below that of +0 means a set sign bit somewhere in the row
-                const bool any_neg = lo < 0x80000000u;
+                uint32_t lo_sign = lo;
                 // -0 is folded onto +0 so that integer order agrees with float comparison
                 if (lo == 0x7FFFFFFFu) lo = 0x80000000u;
-                float low_value = key_to_float(lo);
-                if (BOUND && row_max - low_value > 128.0f) {
-                    const float near = row_max - 128.0f;
+                if (BOUND ? row_max - key_to_float(lo) > 128.0f : NEAR && hi - lo > kNearKeys) {
+                    const float near = BOUND ? row_max - 128.0f : key_to_float(hi - kNearKeys);
                     if (count_ge(near) >= kk) {
                         low = pinf;
 #pragma unroll
                         for (int j = 0; j < M; ++j) low = fminf(low, f[j] >= near ? f[j] : pinf);
                         lo = ~wave_umax(~float_to_key(low));
                         if (lo == 0x7FFFFFFFu) lo = 0x80000000u;
-                        low_value = key_to_float(lo);
+                        lo_sign = 0u;
                     }
                 }
+                const float low_value = key_to_float(lo);
                 // bf16: the keys of negative values end in 0xFFFF, those of the others in 0x0000;
                 // dropping the low bits keeps the order and puts every key on a multiple of UNIT
                 const uint32_t top = hi & KEY_MASK;
@@ -366,22 +370,22 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 const int sh = KEY_SHIFT + (width_bits > 8 ? width_bits - 8 : 0);   // bin = (hi - key) >> sh < 256
                 const float width = (row_max - low_value) * (1.0f / 255.5f);        // BOUND: bins of this width in value
 
-                // 2. histogram
+                // 2. histogram.  What lies below the range goes to a word of the lane's own past the bins, which nothing
+                //    reads: in one common bin those entries queue for its word, which is what masked rows took their time for
+                const uint32_t spill = kBins + lane;
                 reinterpret_cast<uint4 *>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
                 __builtin_amdgcn_wave_barrier();
                 if constexpr (BOUND) {
                     // bins of equal width in the values: the keys of a range around 0 hold two sets of all binades, and a
                     // cut in a bin that wide took five more probes a row.  A rounded difference times a positive scale is
-                    // monotone, which is all that a bin has to be.  What lies below the bound goes, spread out, to 256
-                    // further bins which nothing reads (in one bin those entries queue for its word: 8 -> 25 conflict
-                    // cycles a ds_add)
+                    // monotone, which is all that a bin has to be
                     const float scale = __builtin_amdgcn_rcpf(width);
 #pragma unroll
                     for (int j = 0; j < M; ++j) {
-                        const uint32_t b = (uint32_t)fminf((row_max - f[j]) * scale, 2.0f * kBins - 1.0f);
+                        const uint32_t b = (uint32_t)fminf((row_max - f[j]) * scale, (float)spill);
                         if (FULL || valid[j]) atomicAdd(&hist[b], 1u);
                     }
-                } else if (!any_neg) {
+                } else if (lo_sign >= 0x80000000u) {
                     const uint32_t hi_bits = top ^ 0x80000000u;      // keys of non-negative floats are their bits
 #pragma unroll
                     for (int j = 0; j < M; ++j) {
@@ -391,7 +395,7 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                 } else {
 #pragma unroll
                     for (int j = 0; j < M; ++j) {
-                        const uint32_t b = ((top - (float_to_key(f[j] + 0.0f) & KEY_MASK)) >> sh) & (kBins - 1);
+                        const uint32_t b = min((top - (float_to_key(f[j] + 0.0f) & KEY_MASK)) >> sh, NEAR ? spill : kBins - 1u);
                         if (FULL || valid[j]) atomicAdd(&hist[b], 1u);
                     }
                 }
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(kRowThreads) void prune_rows_kernel(const T *__rest
                     bhi = top + UNIT;
                     c_ge = -1;                                       // not counted yet (kk or more)
                     if (!ordinary) {
-                        // the cut may well be the range's lower end (masked entries among the kept, equal maxima)
+                        // again the lower end first
                         if (blo + UNIT < bhi && count_ge(key_to_float(blo + UNIT)) < kk) bhi = blo + UNIT;
                     } else if (reached) {
                         blo = max(float_to_key(edge - slack) & KEY_MASK, lo);
@@ -1210,7 +1214,7 @@ void launch_prune(const void *p, int64_t rows, int cols, int k, int mode, float 
     const int64_t blocks_needed = (n_units + kRowWaves - 1) / kRowWaves;
     const unsigned grid = (unsigned)(blocks_needed < kMaxPruneBlocks ? blocks_needed : kMaxPruneBlocks);
 #define SLIMFIT_PRUNE_LAUNCH(MM, FF, SS)                                                                       \
-    prune_rows_kernel<T, MM, FF, SS, SOFTMAX><<<grid, kRowThreads, kRowWaves * row_lds_bytes(SOFTMAX, SS, unit_rows, k), st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts, pr, unit_rows, n_units)
+    prune_rows_kernel<T, MM, FF, SS, SOFTMAX><<<grid, kRowThreads, kRowWaves * row_lds_bytes(SOFTMAX || sizeof(T) == 4, SS, unit_rows, k), st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts, pr, unit_rows, n_units)
 #define SLIMFIT_PRUNE_CASE(MM)                                                                                  \
     do {                                                                                                        \
         const bool full = cols == MM * kWave, staged = k <= kStage;                                             \

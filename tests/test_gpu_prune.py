@@ -181,3 +181,30 @@ def test_rows_a_wave_takes(rows, cols, k, dtype):
     _run_both(p, k, restore=False)
     _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=float(p.float().quantile(1.0 - k / cols) if p.numel() < 1 << 24 else 1.6 / cols),
               restore=False)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols,k", [(40, 17), (64, 20), (130, 17), (384, 38), (512, 64), (700, 65), (1100, 110)])
+def test_rows_of_masked_entries(cols, k, dtype):
+    """Rows whose range is stretched: zeros of masked columns (more and fewer others than are kept), both zeros, both
+    signs, denormals, entries on either side of the 64 binades that the bins may cover, constant rows."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    p = torch.rand(170, cols, generator=g, device="cuda") + 1e-3
+    p[0:20, cols * 7 // 10:] = 0.0
+    p[20:40, k + 1:] = 0.0
+    p[40:50, k:] = 0.0
+    p[50:60, k // 2:] = 0.0
+    p[60:70, k // 2::2] = -0.0
+    p[70:80] = (torch.rand(10, cols, generator=g, device="cuda") - 0.5) * 1e-20
+    p[80:90, 3] = 1e30
+    p[90:100] = p[90:100] * 2.0 ** -126
+    p[100:110, ::2] = p[100:110, ::2] * 2.0 ** -63
+    p[110:120, ::2] = p[110:120, ::2] * 2.0 ** -65
+    p[120:130] = 0.25
+    p[120:130, k + 2:] = 0.0
+    p[130:140] = 0.0
+    p[140:150] = -p[140:150] * 2.0 ** torch.randint(-90, 90, (10, cols), generator=g, device="cuda")
+    p[150:160, k + 3:] = -1e30
+    p[160:170] = torch.where(torch.rand(10, cols, generator=g, device="cuda") < 0.5, -1.0, 1.0) * p[160:170]
+    _run_both(p.to(dtype), k, restore=False)
