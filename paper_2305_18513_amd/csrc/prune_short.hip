@@ -668,14 +668,32 @@ void launch_short_k(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int3
 
 }  // namespace
 
-// Measured against the wave-per-row kernel on 64 .. 250 columns: bf16 rows gain at every k <= 16 (1.2 - 4 times
-// faster), fp32 rows up to k = 9 (1.2 - 1.8 times); fp32 rows that keep 12 or 16 entries lose 15 - 45 %, the
-// list insertion growing with k.
-bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k)
+// Which short rows come here rather than to the wave-per-row kernel (prune.hip), both measured on 40 .. 256 columns at
+// 16 384 and 196 608 rows:
+//  - few enough kept entries: the list insertion grows with k (fp32 rows that keep 12 or 16 lose 15 - 45 %);
+//  - strides that spread over the LDS banks: the lanes of a wave read the same entry of 16 rows at once, and at a
+//    stride of a multiple of 32 dwords those lie in one or two banks (fp32 softmax on 256 columns 524 us against 70, 128
+//    columns 265 against 53, 64 columns 68 against 48; pruning, which walks the rows once, 98 against 42 at 256 and 54
+//    against 37 at 128, but 17 against 33 at 64; bf16, whose stride is half, softmax on 256 columns 84 against 72);
+//  - enough rows: a wave takes 16 (32) of them and needs 8 - 15 us whatever their number, while the other kernel gives
+//    few rows a wave each (16 384 rows of 197 columns: fp32 softmax 16.3 us against 10.3, pruning 11.5 against 9.3, bf16
+//    softmax 15.6 against 10.8); the two meet at 24 576 rows (fp32 pruning, 13.3 and 11.9, but peaked rows 10.2 and 11.6;
+//    bf16 softmax 16.1 and 14.8, on 128 columns 10.5 and 12.4) and at 65 536 (fp32 softmax, 32.5 and 33.5); at 196 608
+//    this one is ahead (72.7 against 84, 40.6 against 48.9, 61.5 against 75.8).
+constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 60000;
+
+bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, bool softmax)
 {
-    const int k_max = dt == SLIMFIT_BF16 ? kShortPruneMaxK : kShortPruneMaxKF32;
-    // (the rows are staged with 16-byte loads)
-    return cols <= kShortPruneMaxCols && k <= k_max && aligned_to(p, 16) && rows <= (int64_t)0x7FFFFFFF * 16;
+    const bool bf16 = dt == SLIMFIT_BF16;
+    if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32) || rows > (int64_t)0x7FFFFFFF * 16) return false;
+    if (!aligned_to(p, 16)) return false;              // (the rows are staged with 16-byte loads)
+    if (bf16) {
+        if (softmax && cols == 256) return false;
+        if (softmax) return cols < 128 || rows >= kShortMinRows;
+        return k <= 12 || rows >= kShortMinRows;
+    }
+    if (softmax) return !(cols >= 64 && cols % 32 == 0) && (cols < 128 || rows >= kShortMinRowsSoftmaxF32);
+    return !(cols >= 128 && cols % 64 == 0) && (cols < 128 || rows >= kShortMinRows);
 }
 
 void launch_softmax_prune_short(const void *logits, int32_t dt, int64_t rows, int cols, int k, void *probs, void *vals,

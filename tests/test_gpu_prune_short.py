@@ -96,3 +96,25 @@ def test_misaligned_rows_take_the_other_kernel_and_agree():
     sf.prune_scores(base, 9, sf.PRUNE_TOPK, 0.0, vals2, idx2, None)
     torch.cuda.synchronize()
     assert torch.equal(vals, vals2) and torch.equal(idx.view(torch.int16), idx2.view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype,cols,k,rows", [
+    (torch.float32, 197, 9, 20000), (torch.float32, 197, 9, 19999), (torch.float32, 130, 3, 20011), (torch.float32, 250, 8, 20001),
+    (torch.float32, 160, 9, 20007), (torch.float32, 192, 9, 20000), (torch.bfloat16, 197, 16, 20001), (torch.bfloat16, 33, 16, 19999)])
+def test_rows_enough_for_several_a_wave(dtype, cols, k, rows):
+    """Both sides of the row counts and strides at which the kernel changes; fp32 rows of every hard kind among many."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols * 7 + k)
+    p = torch.softmax(torch.randn(rows, cols, generator=g, device="cuda") * 0.5, dim=-1)
+    low = torch.randint(0, 256, (600, cols), generator=g, device="cuda", dtype=torch.int32)
+    p[1000:1600] = (0x3C000000 + low).view(torch.float32)            # entries that agree in their upper 24 bits
+    p[1100:1200] = -p[1100:1200]
+    p[1200:1300] = p[1200:1300, :1]
+    p[1300:1400] = (torch.randn(100, cols, generator=g, device="cuda") * 2).round() / 2
+    p[1400:1450] = 0.0
+    p[1400:1450, ::2] = -0.0
+    p[1450:1500] = p[1450:1500].abs() * 1e-41
+    p = p.to(dtype)
+    _run_both(p, k, restore=False)
+    for tau in (1.3 / cols, 0.0, float(torch.tensor(0x3C000080, dtype=torch.int32).view(torch.float32))):
+        _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=tau, restore=False)

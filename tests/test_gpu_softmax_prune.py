@@ -170,6 +170,19 @@ def test_rows_a_wave_takes(rows, cols, k, dtype):
     _run_both(torch.randn(rows, cols, generator=g, device="cuda").to(dtype), k)
 
 
+@pytest.mark.parametrize("dtype,cols,k,rows", [(torch.float32, 197, 9, 60000), (torch.float32, 197, 9, 59999), (torch.float32, 160, 8, 60003),
+                                               (torch.float32, 64, 6, 1000), (torch.float32, 250, 5, 60001), (torch.bfloat16, 197, 16, 20001),
+                                               (torch.bfloat16, 256, 12, 20000), (torch.bfloat16, 150, 3, 19999)])
+def test_short_rows_by_row_count_and_stride(dtype, cols, k, rows):
+    """Both sides of the row counts and strides at which short rows change kernels."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols + rows)
+    l = torch.randn(rows, cols, generator=g, device="cuda")
+    l[100:200] = (l[100:200] * 2).round() / 2                          # ties
+    l[200:300] = -l[200:300].abs() - 1.0
+    _run_both(l.to(dtype), k)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("cols,k", [(40, 17), (64, 20), (130, 17), (384, 38), (512, 64), (700, 65), (1100, 110)])
 def test_hard_rows_for_the_value_bins(cols, k, dtype):
