@@ -220,8 +220,9 @@ struct Std {
     int32_t *row_ptr;            // optional output: survivors ahead of every row (rows + 1 entries)
 };
 // Applied to a vector after all of the thread's loads have been issued, so that
-// the loads still overlap.
-template <typename T, bool STD>
+// the loads still overlap.  SCATTERED: the wave's vectors are not 64 consecutive
+// ones, so every lane has a row of its own whatever H is.
+template <typename T, bool STD, bool SCATTERED = false>
 __device__ __forceinline__ void standardise(uint32_t (&bits)[Elem<T>::EPV], int valid, int64_t v, const Std &sd)
 {
     constexpr int EPV = Elem<T>::EPV;
@@ -231,7 +232,7 @@ __device__ __forceinline__ void standardise(uint32_t (&bits)[Elem<T>::EPV], int 
         // all of a thread's vectors can be issued together.
         (void)valid;
         uint32_t row = min(__umulhi((uint32_t)(v * EPV), sd.magic) >> sd.shift, sd.last_row);
-        if (sd.vec_uniform) row = (uint32_t)__builtin_amdgcn_readfirstlane((int)row);    // scalar loads
+        if (!SCATTERED && sd.vec_uniform) row = (uint32_t)__builtin_amdgcn_readfirstlane((int)row);    // scalar loads
         const float mu = sd.mean[row], rs = sd.rstd[row];
 #pragma unroll
         for (int e = 0; e < EPV; ++e)
@@ -373,7 +374,7 @@ sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, u32x2 *__r
 #pragma unroll
     for (int u = 0; u < kSampleVecs; ++u) {
         if (first + (uint32_t)u * stride < total) {
-            standardise<T, STD>(bits[u], EPV, at[u], sd);
+            standardise<T, STD, true>(bits[u], EPV, at[u], sd);
 #pragma unroll
             for (int e = 0; e < EPV; ++e) atomicAdd(&bins[make_key<T, MAG>(bits[u][e]) >> (Elem<T>::KEYBITS - kTop)], 1u);
         }

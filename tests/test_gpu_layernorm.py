@@ -289,3 +289,26 @@ def test_standardised_pruning_rows_and_tiles(rows, H, dtype):
     rstd = 0.9 + 0.2 * torch.rand(rows, generator=g, device="cuda")
     for k in (rows * H // 10, rows * H // 4):
         _prune_both(x, mean, rstd, k)
+
+
+@pytest.mark.parametrize("rows,H,dtype", [(600, 256, torch.float32), (300, 768, torch.float32), (200, 1024, torch.float32),
+                                          (600, 512, torch.bfloat16), (301, 1024, torch.bfloat16), (900, 264, torch.bfloat16)])
+def test_sample_is_standardised_row_by_row(rows, H, dtype):
+    """Past 16 384 vectors the lanes of a wave sample different rows.  With rows of unlike mean and scale the bracket
+    only holds the cut if each vector takes its own row's statistics; the results are right either way, so the route
+    that was taken (word 6 of the workspace) is looked at."""
+    require_gpu()
+    x, _, _, _ = _inputs(rows + H, rows, H)
+    # offsets in proportion to the scale: bf16 rows far from 0 would hold few distinct values, which take the other route
+    x = ((x + (torch.arange(rows, device="cuda") % 5)[:, None]) * torch.exp2(torch.arange(rows, device="cuda") % 7 - 3.0)[:, None]).to(dtype)
+    xd = x.double()
+    mean, rstd = xd.mean(1).float(), (1.0 / (xd.var(1, unbiased=False) + 1e-5).sqrt()).float()
+    n = rows * H
+    assert n // (4 if dtype == torch.float32 else 8) > 16384
+    for k in (n // 10, n // 3):
+        for by_mag in (True, False):
+            _prune_both(x, mean, rstd, k, by_mag)
+            vals, idx = torch.empty(k, device="cuda"), torch.empty(k, dtype=torch.int32, device="cuda")
+            ws = torch.full((sf.prune_global_workspace(n),), 0xFF, dtype=torch.uint8, device="cuda")
+            sf.prune_global_standardized(x, mean, rstd, k, vals, idx, by_mag, None, None, ws)
+            assert int(ws[24:28].view(torch.int32)) == 0, "the sampled bracket missed the cut"
