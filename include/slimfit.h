@@ -373,10 +373,15 @@ int32_t slimfit_softmax_backward_pruned(const void *vals, const uint16_t *idx, c
  *              t * SLIMFIT_GLOBAL_TILE, the last entry = k.  With it the
  *              restoring process builds every output tile once instead of
  *              filling zeros and scattering into them.
- *  workspace : DEVICE, 16-byte aligned, at least the byte count that
- *              slimfit_prune_global_workspace(n) reports (about 1.3 n bytes);
- *              owned by the caller, contents need not be initialised and are
- *              overwritten.  Calls that share a workspace must not overlap.
+ *  workspace : DEVICE, 16-byte aligned, of the byte count that
+ *              slimfit_prune_global_workspace(n) reports (about 1.3 n bytes: 66 MB
+ *              for 50 M elements, a third of an fp32 tensor, two thirds of a bf16
+ *              one, at the time of the call); owned by the caller, contents need
+ *              not be initialised and are overwritten.  Calls that share a
+ *              workspace must not overlap.  A smaller one is served with the same
+ *              results, more slowly, down to
+ *              16512 + 2 * r(8 t) + 1024 * (t + 1) bytes, about n / 4, where
+ *              t = ceil(n / SLIMFIT_GLOBAL_TILE) and r rounds up to 128.
  *  slimfit_restore_global : out (n elements of dt, 16-byte aligned) = zeros,
  *              then out[idx[s]] = vals[s] for s < k; an index outside [0, n) is
  *              skipped; indices must be distinct.  tile_ptr == NULL accepts the

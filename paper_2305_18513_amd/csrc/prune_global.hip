@@ -66,7 +66,8 @@ constexpr int kWaveElems = kTileElems / 4; // a tile is four rounds of 1024 elem
 
 constexpr int kSampleWgs = 16;             // at most
 constexpr int kSampleVecs = 1;             // vectors a thread of them takes
-constexpr int kListSlots = kTileElems * 3 / 32;     // a tile's key list
+constexpr int kListSlots = kTileElems * 3 / 32;     // a tile's key list (in a workspace without records: fewer)
+constexpr int kMinListSlots = 192;         // fewer are not worth the sweep; the readers load 128 ahead
 constexpr int kRecSlots = 640;             // a tile's records: 10 % kept and 3 % more in the bracket, plus 5 standard deviations
 constexpr int kRecShare = 9;               // records are made when k * 9 <= n
 constexpr int kMaxBracketBins = 64;
@@ -343,7 +344,11 @@ __device__ __forceinline__ void clear_block(u32x4 *zero, int n16)
 {
     for (int i = blockIdx.x * kWideThreads + threadIdx.x; i < n16; i += gridDim.x * kWideThreads) zero[i] = u32x4{0u, 0u, 0u, 0u};
 }
-__global__ void __launch_bounds__(kWideThreads) clear_kernel(u32x4 *zero, int n16) { clear_block(zero, n16); }
+__global__ void __launch_bounds__(kWideThreads) clear_kernel(u32x4 *zero, int n16, State *plain)      // plain: no sample and no sweep follow
+{
+    clear_block(zero, n16);
+    if (plain && blockIdx.x == 0 && threadIdx.x == 0) plain->plain = 1u;      // (the thread that cleared it)
+}
 
 // ---- the sample ------------------------------------------------------------------------
 // One vector of each of `total` equal stretches of the tensor (all vectors when there are no more than that), for
@@ -390,7 +395,7 @@ sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, u32x2 *__r
 template <bool FULL>
 __global__ void __launch_bounds__(kWideThreads)
 bracket_kernel(State *st, const u32x2 *__restrict__ sample, int wgs, uint32_t *full, int key_bits, uint32_t rank_hi, uint32_t rank_lo,
-               uint32_t size)
+               uint32_t size, int list_slots)
 {
     __shared__ uint32_t wave_sums[kWideWaves];
     __shared__ uint32_t edge[4];                           // highest bin, entries above it, lowest bin, entries down to it
@@ -428,8 +433,9 @@ bracket_kernel(State *st, const u32x2 *__restrict__ sample, int wgs, uint32_t *f
         const uint32_t nb = edge[0] - edge[2] + 1u;
         int log_nb = 0;
         while ((1u << log_nb) < nb && log_nb < 12) ++log_nb;
-        // too wide for the digits, or too much for the lists (1/14 of the tensor on average, 1/10.7 of a tile)
-        const bool plain = nb > (uint32_t)kMaxBracketBins || (uint64_t)(edge[3] - edge[1]) * 14u > size;
+        // too wide for the digits, or too much for the lists (on average 1/14 of the tensor where they hold 1/10.7 of a tile)
+        const bool plain = nb > (uint32_t)kMaxBracketBins ||
+                           (uint64_t)(edge[3] - edge[1]) * (14 * kListSlots) > (uint64_t)size * (uint32_t)list_slots;
         const int range_bits = log_nb + shift;
         const int digit2 = min(range_bits, max(9, log_nb + 6));            // the rest is at most 14 bits
         st->plain = plain ? 1u : 0u;
@@ -453,7 +459,7 @@ constexpr uint32_t kTooMany = 0x8000u;                      // in place of a til
 template <typename T, bool MAG, bool STD, bool INSIDE, bool REC>
 __device__ __forceinline__ void
 sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
-           uint32_t *__restrict__ lists, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, const Std &sd)
+           uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, const Std &sd)
 {
     constexpr int EPV = Elem<T>::EPV, G = kGroups<T>;
     __shared__ u32x2 stage[REC ? kRecSlots : 1];                      // (element bits, place in the tile)
@@ -493,7 +499,7 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
         pos += (w < wave) ? wave_cnt[w] : 0u;
         n_cand += wave_cnt[w];
     }
-    uint32_t *keys = lists + tile * kListSlots;
+    uint32_t *keys = lists + tile * list_slots;
     const bool whole = REC && n_cand <= (uint32_t)kRecSlots;       // workgroup-uniform
     if (whole) {
 #pragma unroll
@@ -523,7 +529,7 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
                 uint32_t slot = 0u;
                 if (lane == 0) slot = atomicAdd(&filed, (uint32_t)__builtin_popcountll(m));
                 slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + lanes_below(m);
-                if (in && key <= last && slot < (uint32_t)kListSlots) keys[slot] = key;
+                if (in && key <= last && slot < (uint32_t)list_slots) keys[slot] = key;
             }
         }
     } else {
@@ -547,7 +553,7 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
                 for (int e = 0; e < EPV; ++e) {
                     const uint32_t key = make_key<T, MAG>(bits[j][e]);
                     if ((INSIDE || e < valid[j]) && key >= lo && key <= last) {
-                        if (slot < (uint32_t)kListSlots) keys[slot] = key;
+                        if (slot < (uint32_t)list_slots) keys[slot] = key;
                         ++slot;
                     }
                 }
@@ -557,8 +563,8 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
     __syncthreads();
     if (threadIdx.x == 0) {
         const uint32_t f = filed, gt = n_cand - f;
-        tile_cnt[tile] = u32x2{gt | ((whole ? n_cand : kTooMany) << 16), min(f, (uint32_t)kListSlots)};
-        if (f > (uint32_t)kListSlots) st->overflow = 1u;
+        tile_cnt[tile] = u32x2{gt | ((whole ? n_cand : kTooMany) << 16), min(f, (uint32_t)list_slots)};
+        if (f > (uint32_t)list_slots) st->overflow = 1u;
         atomicAdd(reinterpret_cast<unsigned long long *>(counters + (tile & (kCounters - 1)) * 8),
                   (unsigned long long)gt | ((unsigned long long)f << 32));
     }
@@ -567,13 +573,13 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
 template <typename T, bool MAG, bool STD, bool REC>
 __global__ void __launch_bounds__(kTileThreads)
 sweep_kernel(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
-             uint32_t *__restrict__ lists, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, Std sd)
+             uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, Std sd)
 {
     if (st->plain) return;
     if (((int64_t)blockIdx.x + 1) * kTileElems <= n)        // workgroup-uniform: the whole tile lies below n
-        sweep_tile<T, MAG, STD, true, REC>(x, n, st, counters, tile_cnt, lists, rec_val, rec_pos, sd);
+        sweep_tile<T, MAG, STD, true, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd);
     else
-        sweep_tile<T, MAG, STD, false, REC>(x, n, st, counters, tile_cnt, lists, rec_val, rec_pos, sd);
+        sweep_tile<T, MAG, STD, false, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd);
 }
 
 // ---- one digit: LDS histogram of the matching keys, non-empty bins added to the global one ----
@@ -622,16 +628,16 @@ __device__ __forceinline__ void tensor_hist(const T *__restrict__ x, int64_t n, 
 struct FourLists {
     u32x2 cnt[4];
     uint32_t a[4], b[4];
-    __device__ __forceinline__ void load(const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, int64_t t,
-                                         int64_t stride, int64_t end)
+    __device__ __forceinline__ void load(const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, int list_slots,
+                                         int64_t t, int64_t stride, int64_t end)
     {
         const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int64_t at = min(t + u * stride, end - 1);
             cnt[u] = tile_cnt[at];
-            a[u] = lists[at * kListSlots + lane];
-            b[u] = lists[at * kListSlots + lane + kWave];
+            a[u] = lists[at * list_slots + lane];
+            b[u] = lists[at * list_slots + lane + kWave];
         }
     }
     template <typename F>
@@ -646,15 +652,15 @@ struct FourLists {
 // f(key) for every filed key, a wave per tile; first: the wave's first four, loaded ahead by the caller
 template <typename F>
 __device__ __forceinline__ void for_each_filed(FourLists &first, const u32x2 *__restrict__ tile_cnt,
-                                               const uint32_t *__restrict__ lists, int64_t ntiles, int grid, F f)
+                                               const uint32_t *__restrict__ lists, int list_slots, int64_t ntiles, int grid, F f)
 {
     const int64_t waves = (int64_t)grid * kWideWaves;
     for (int64_t t = (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6); t < ntiles;) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (t + u * waves < ntiles) first.each(u, lists + (t + u * waves) * kListSlots, f);
+            if (t + u * waves < ntiles) first.each(u, lists + (t + u * waves) * list_slots, f);
         t += 4 * waves;
-        if (t < ntiles) first.load(tile_cnt, lists, t, waves, ntiles);
+        if (t < ntiles) first.load(tile_cnt, lists, list_slots, t, waves, ntiles);
     }
 }
 __device__ __forceinline__ void clear_bins(uint32_t *bins, int nbins)
@@ -689,15 +695,15 @@ top_digit_kernel(const T *__restrict__ x, int64_t n, uint32_t *__restrict__ hist
 template <typename T, bool MAG, bool STD>
 __global__ void __launch_bounds__(kWideThreads)
 digit_kernel(const T *__restrict__ x, int64_t n, State *st, const uint64_t *__restrict__ counters,
-             const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, uint32_t *__restrict__ hist2, int64_t ntiles,
-             uint32_t k, Std sd)
+             const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ hist2,
+             int64_t ntiles, uint32_t k, Std sd)
 {
     __shared__ uint32_t bins[kCopies * kTopBins];
     const int lane = threadIdx.x & (kWave - 1);
     static_assert(kCounters == kWave, "a lane per counter");
     const int grid = min((int)gridDim.x, kListGrid);
     FourLists first;
-    first.load(tile_cnt, lists, (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6), (int64_t)grid * kWideWaves, ntiles);
+    first.load(tile_cnt, lists, list_slots, (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6), (int64_t)grid * kWideWaves, ntiles);
     const uint64_t c = counters[lane * 8];
     const uint32_t gt = wave_total_u32(wave_scan_u32((uint32_t)c)), in = wave_total_u32(wave_scan_u32((uint32_t)(c >> 32)));
     const bool plain = st->plain || st->overflow || gt >= k || k - gt > in;
@@ -713,7 +719,7 @@ digit_kernel(const T *__restrict__ x, int64_t n, State *st, const uint64_t *__re
         tensor_hist<T, MAG, STD, true>(x, n, 0u, 0u, Elem<T>::KEYBITS - kTop, kTopBins, bins, sd);
     } else {
         const uint32_t lo = st->lo, shift = st->shift2, top = (uint32_t)nbins - 1u;
-        for_each_filed(first, tile_cnt, lists, ntiles, grid, [&](uint32_t key) { atomicAdd(&bins[min((key - lo) >> shift, top)], 1u); });
+        for_each_filed(first, tile_cnt, lists, list_slots, ntiles, grid, [&](uint32_t key) { atomicAdd(&bins[min((key - lo) >> shift, top)], 1u); });
     }
     __syncthreads();
     if (plain) add_bins<kCopies>(bins, hist2, kTopBins);
@@ -724,12 +730,12 @@ digit_kernel(const T *__restrict__ x, int64_t n, State *st, const uint64_t *__re
 template <typename T, bool MAG, bool STD>
 __global__ void __launch_bounds__(kWideThreads)
 second_digit_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *__restrict__ tile_cnt,
-                    const uint32_t *__restrict__ lists, const uint32_t *__restrict__ hist2, uint32_t *__restrict__ hist3,
-                    int64_t ntiles, Std sd)
+                    const uint32_t *__restrict__ lists, int list_slots, const uint32_t *__restrict__ hist2,
+                    uint32_t *__restrict__ hist3, int64_t ntiles, Std sd)
 {
     __shared__ uint32_t bins[1 << kMaxDigit3];
     FourLists first;
-    first.load(tile_cnt, lists, (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6), (int64_t)gridDim.x * kWideWaves, ntiles);
+    first.load(tile_cnt, lists, list_slots, (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6), (int64_t)gridDim.x * kWideWaves, ntiles);
     const bool plain = st->use_plain != 0u;
     const Choice c = select_bin<kWideThreads>(hist2, plain ? kTop : (int)st->digit2, st->k_rem);
     const uint32_t shift = st->shift2;
@@ -746,7 +752,7 @@ second_digit_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *
     if (plain)
         tensor_hist<T, MAG, STD, false>(x, n, prefix, mask, 12, nbins, bins, sd);
     else
-        for_each_filed(first, tile_cnt, lists, ntiles, (int)gridDim.x, [&](uint32_t key) {
+        for_each_filed(first, tile_cnt, lists, list_slots, ntiles, (int)gridDim.x, [&](uint32_t key) {
             if (key - lo2 < (uint32_t)nbins) atomicAdd(&bins[key - lo2], 1u);
         });
     __syncthreads();
@@ -758,6 +764,7 @@ second_digit_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *
 template <typename T, bool MAG, bool STD>
 __global__ void __launch_bounds__(kWideThreads)
 count_kernel(const T *__restrict__ x, int64_t numel, State *st, const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists,
+             int list_slots,
              const uint32_t *__restrict__ hist2, const uint32_t *__restrict__ hist3, uint32_t *__restrict__ hist4,
              u32x2 *__restrict__ tile_sum, u32x2 *__restrict__ group_sum, int64_t ntiles, int group_tiles, Std sd)
 {
@@ -767,7 +774,7 @@ count_kernel(const T *__restrict__ x, int64_t numel, State *st, const u32x2 *__r
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int64_t t0 = (int64_t)blockIdx.x * group_tiles, t1 = min(t0 + group_tiles, ntiles);
     FourLists four;
-    four.load(tile_cnt, lists, t0 + wave, kWideWaves, t1);
+    four.load(tile_cnt, lists, list_slots, t0 + wave, kWideWaves, t1);
     const bool plain = st->use_plain != 0u;
     const Choice c = WIDE_KEY ? select_bin<kWideThreads>(hist3, plain ? 8 : (int)st->shift2, st->k_rem2)
                               : select_bin<kWideThreads>(hist2, plain ? kTop : (int)st->digit2, st->k_rem);
@@ -797,7 +804,7 @@ count_kernel(const T *__restrict__ x, int64_t numel, State *st, const u32x2 *__r
             const int64_t tile = t + u * kWideWaves;
             if (tile >= t1) break;                          // wave-uniform
             uint32_t gt = 0u, eq = 0u;
-            four.each(u, lists + tile * kListSlots, [&](uint32_t key) {
+            four.each(u, lists + tile * list_slots, [&](uint32_t key) {
                 gt += key > Tk ? 1u : 0u;
                 eq += key == Tk ? 1u : 0u;
             });
@@ -805,7 +812,7 @@ count_kernel(const T *__restrict__ x, int64_t numel, State *st, const u32x2 *__r
             if (lane == 0) sum[tile - t0] = u32x2{(four.cnt[u].x & 0xFFFFu) + (both & 0xFFFFu), both >> 16};
         }
         t += 4 * kWideWaves;
-        if (t < t1) four.load(tile_cnt, lists, t, kWideWaves, t1);
+        if (t < t1) four.load(tile_cnt, lists, list_slots, t, kWideWaves, t1);
     }
     __syncthreads();
     // the sums ahead of every tile of the group, and the group's own; two tiles a thread
@@ -1225,6 +1232,13 @@ restore_tiles_kernel(const T *__restrict__ vals, const int32_t *__restrict__ idx
 
 // Workspace: state | counters | group sums | three histograms | sample | tile counts | tile sums | key lists | records.
 // From the counters to the histograms everything has to be zero at the start.
+//
+// That is 1.3 bytes an element.  Before the records there was a quarter of a byte, and a caller may hold a workspace of
+// that size: it is still served, in one of two smaller layouts.
+//   lists   no records (the survivors are written from the tensor), the sample where the lists will be, and as many list
+//           slots as there is room for;
+//   plain   where not even 192 slots fit beside the histograms (below 4 - 6 M elements): no sample and no sweep, the
+//           plain route's launches alone, with the state, two histograms and the sums.
 struct Workspace {
     State *st;
     uint64_t *counters;
@@ -1234,38 +1248,93 @@ struct Workspace {
     u32x2 *tile_cnt, *tile_sum;
     uint32_t *lists, *rec_val;
     uint16_t *rec_pos;
+    int list_slots;                        // 0: the plain layout
+    bool records;
+    u32x4 *zero;
+    int zero16;
     size_t bytes;
 };
-constexpr size_t kZeroBytes = kCounters * 64 + kMaxGroups * 8 + (size_t)(kTopBins + (1 << kMaxDigit3) + kTopBins) * 4;
-Workspace carve(void *base, int64_t n)
-{
-    Workspace w;
-    const size_t tiles = (size_t)((n + kPtrTile - 1) / kPtrTile);
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        char *p = static_cast<char *>(base) + off;
+struct Carver {
+    char *base;
+    size_t off;
+    template <typename P> P *take(size_t bytes)
+    {
+        char *p = base + off;
         off += (bytes + 127) / 128 * 128;
-        return p;
-    };
-    w.st = reinterpret_cast<State *>(take(sizeof(State)));
-    w.counters = reinterpret_cast<uint64_t *>(take(kCounters * 64));
-    w.group_sum = reinterpret_cast<u32x2 *>(take(kMaxGroups * 8));
-    w.hist2 = reinterpret_cast<uint32_t *>(take((size_t)kTopBins * 4));
-    w.hist3 = reinterpret_cast<uint32_t *>(take((size_t)4 << kMaxDigit3));
-    w.hist4 = reinterpret_cast<uint32_t *>(take((size_t)kTopBins * 4));
-    w.sample = reinterpret_cast<u32x2 *>(take((size_t)kSampleWgs * kTopBins * 2));
-    w.tile_cnt = reinterpret_cast<u32x2 *>(take(tiles * 8));
-    w.tile_sum = reinterpret_cast<u32x2 *>(take(tiles * 8));
-    w.lists = reinterpret_cast<uint32_t *>(take(tiles * kListSlots * 4));
-    w.rec_val = reinterpret_cast<uint32_t *>(take(tiles * kRecSlots * 4));
-    w.rec_pos = reinterpret_cast<uint16_t *>(take(tiles * kRecSlots * 2));
-    w.bytes = off;
+        return reinterpret_cast<P *>(p);
+    }
+};
+size_t tiles_of(int64_t n) { return (size_t)((n + kPtrTile - 1) / kPtrTile); }
+int group_tiles_for(int64_t ntiles) { return (int)(((ntiles + kMaxGroups - 1) / kMaxGroups + 3) / 4 * 4); }
+constexpr size_t kSampleBytes = (size_t)kSampleWgs * kTopBins * 2;
+Workspace carve(void *base, int64_t n, int list_slots, bool records)
+{
+    Workspace w = {};
+    Carver c = {static_cast<char *>(base), 0};
+    const size_t tiles = tiles_of(n);
+    w.list_slots = list_slots;
+    w.records = records;
+    w.st = c.take<State>(sizeof(State));
+    w.counters = c.take<uint64_t>(kCounters * 64);
+    w.group_sum = c.take<u32x2>(kMaxGroups * 8);
+    w.hist2 = c.take<uint32_t>((size_t)kTopBins * 4);
+    w.hist3 = c.take<uint32_t>((size_t)4 << kMaxDigit3);
+    w.hist4 = c.take<uint32_t>((size_t)kTopBins * 4);
+    w.zero = reinterpret_cast<u32x4 *>(w.counters);
+    w.zero16 = (int)((c.off - sizeof(State)) / 16);
+    if (records) w.sample = c.take<u32x2>(kSampleBytes);
+    w.tile_cnt = c.take<u32x2>(tiles * 8);
+    w.tile_sum = c.take<u32x2>(tiles * 8);
+    const size_t list_bytes = tiles * (size_t)list_slots * 4;
+    w.lists = c.take<uint32_t>(records || list_bytes > kSampleBytes ? list_bytes : kSampleBytes);
+    if (records) {
+        w.rec_val = c.take<uint32_t>(tiles * kRecSlots * 4);
+        w.rec_pos = c.take<uint16_t>(tiles * kRecSlots * 2);
+    } else {
+        w.sample = reinterpret_cast<u32x2 *>(w.lists);      // (read before the sweep files the first key)
+    }
+    w.bytes = c.off;
     return w;
 }
-size_t workspace_bytes_for(int64_t n)
+Workspace carve_plain(void *base, int64_t n)
 {
-    static char origin[1];                 // only offsets are taken
-    return carve(origin, n).bytes;
+    Workspace w = {};
+    Carver c = {static_cast<char *>(base), 0};
+    const int64_t tiles = (int64_t)tiles_of(n);
+    const int per = group_tiles_for(tiles);
+    w.st = c.take<State>(sizeof(State));
+    w.group_sum = c.take<u32x2>((size_t)((tiles + per - 1) / (per > 0 ? per : 1)) * 8);
+    w.hist2 = c.take<uint32_t>((size_t)kTopBins * 4);
+    w.hist3 = c.take<uint32_t>(256 * 4);
+    w.zero = reinterpret_cast<u32x4 *>(w.st);
+    w.zero16 = (int)(c.off / 16);
+    w.tile_sum = c.take<u32x2>((size_t)tiles * 8);
+    w.bytes = c.off;
+    return w;
+}
+char origin[1];                            // where only offsets are wanted
+size_t workspace_bytes_for(int64_t n) { return carve(origin, n, kListSlots, true).bytes; }
+// The least that is accepted: state, one histogram, two words and 256 list slots a tile.  (The plain layout is smaller.)
+size_t least_workspace_for(int64_t n)
+{
+    Carver c = {origin, 0};
+    const size_t tiles = tiles_of(n);
+    c.take<char>(sizeof(State) + (size_t)kTopBins * 4);
+    c.take<char>(tiles * 8);
+    c.take<char>(tiles * 8);
+    c.take<char>((tiles + 1) * 1024);
+    return c.off;
+}
+Workspace carve_room(void *base, int64_t n, size_t room)            // room >= least_workspace_for(n)
+{
+    if (room >= workspace_bytes_for(n)) return carve(base, n, kListSlots, true);
+    const size_t bare = carve(origin, n, 0, false).bytes - kSampleBytes, tiles = tiles_of(n);
+    if (room >= bare + kSampleBytes) {
+        const size_t fit = (room - bare) / (tiles * 4);             // (whole lines: a multiple of 32)
+        const int slots = (int)(fit < (size_t)kListSlots ? fit / 32 * 32 : (size_t)kListSlots);
+        if (slots >= kMinListSlots) return carve(base, n, slots, false);
+    }
+    return carve_plain(base, n);
 }
 
 // Which ranks of the sample bound the bracket.  The rank of T in a sample of `size` unlike entries has a standard
@@ -1309,44 +1378,66 @@ void launch_select(const T *x, int64_t n, uint32_t k, typename Elem<T>::Out *val
 {
     const int64_t ntiles = (n + kTileElems - 1) / kTileElems;
     // at most kMaxGroups groups of tiles; also the workgroups of the digit and count launches
-    const int group_tiles = (int)(((ntiles + kMaxGroups - 1) / kMaxGroups + 3) / 4 * 4);
+    const int group_tiles = group_tiles_for(ntiles);
     const unsigned groups = (unsigned)((ntiles + group_tiles - 1) / group_tiles);
-    const bool records = (int64_t)k * kRecShare <= n;
-    u32x4 *zero = reinterpret_cast<u32x4 *>(w.counters);
-    const int zero16 = (int)(kZeroBytes / 16);
+    const Out<T> out = {vals, idx, tile_ptr, k};
+    const unsigned plain_grid = (unsigned)(ntiles < kPlainGrid ? ntiles : kPlainGrid);
+    if (w.list_slots == 0) {
+        // The plain layout.  The digit launches look at a list's head before they know the route: they are told of one
+        // tile and given the histogram to look at.  The first digit's histogram serves again as the last one's.
+        const u32x2 *no_cnt = reinterpret_cast<const u32x2 *>(w.hist2);
+        clear_kernel<<<1, kWideThreads, 0, s>>>(w.zero, w.zero16, w.st);
+        digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, reinterpret_cast<const uint64_t *>(w.hist2), no_cnt, w.hist2,
+                                                                  0, w.hist2, 1, k, sd);
+        uint32_t *last = w.hist3;
+        if constexpr (Elem<T>::KEYBITS == 32) {
+            second_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, no_cnt, w.hist2, 0, w.hist2, w.hist3, 1, sd);
+            last = w.hist2;
+            clear_kernel<<<1, kWideThreads, 0, s>>>(reinterpret_cast<u32x4 *>(last), kTopBins / 4, nullptr);
+        }
+        count_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, no_cnt, w.hist2, 0, w.hist2, w.hist3, last, w.tile_sum,
+                                                                  w.group_sum, 1, group_tiles, sd);
+        dense_write_kernel<T, MAG, STD><<<plain_grid, kTileThreads, 0, s>>>(x, n, w.st, last, w.tile_sum, w.group_sum, ntiles, group_tiles,
+                                                                            out, sd);
+        plain_write_kernel<T, MAG, STD><<<plain_grid, kTileThreads, 0, s>>>(x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out,
+                                                                            sd);
+        return;
+    }
+    const bool records = w.records && (int64_t)k * kRecShare <= n;
     const SamplePlan plan = plan_sample(n, (int64_t)k, Elem<T>::EPV);
 
     if (plan.use) {
         const uint32_t per = kSampleVecs * kWideThreads;
         const int wgs = (int)((plan.total + per - 1) / per);
-        sample_kernel<T, MAG, STD><<<wgs, kWideThreads, 0, s>>>(x, plan.total, plan.step, w.sample, zero, zero16, sd);
+        sample_kernel<T, MAG, STD><<<wgs, kWideThreads, 0, s>>>(x, plan.total, plan.step, w.sample, w.zero, w.zero16, sd);
         bracket_kernel<false><<<1, kWideThreads, 0, s>>>(w.st, w.sample, wgs, nullptr, Elem<T>::KEYBITS, plan.hi, plan.lo,
-                                                         plan.size);
+                                                         plan.size, w.list_slots);
     } else {
-        clear_kernel<<<1, kWideThreads, 0, s>>>(zero, zero16);
+        clear_kernel<<<1, kWideThreads, 0, s>>>(w.zero, w.zero16, nullptr);
         top_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.hist4, sd);
-        bracket_kernel<true><<<1, kWideThreads, 0, s>>>(w.st, nullptr, 0, w.hist4, Elem<T>::KEYBITS, k, k, (uint32_t)n);
+        bracket_kernel<true><<<1, kWideThreads, 0, s>>>(w.st, nullptr, 0, w.hist4, Elem<T>::KEYBITS, k, k, (uint32_t)n,
+                                                        w.list_slots);
     }
     if (records)
-        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.rec_val,
+        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, w.rec_val,
                                                                                  w.rec_pos, sd);
     else
-        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, nullptr,
+        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, nullptr,
                                                                                   nullptr, sd);
-    digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.hist2, ntiles, k, sd);
+    digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, w.hist2,
+                                                              ntiles, k, sd);
     if constexpr (Elem<T>::KEYBITS == 32)
-        second_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.hist2, w.hist3, ntiles, sd);
-    count_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.hist2, w.hist3, w.hist4, w.tile_sum,
+        second_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.list_slots, w.hist2, w.hist3,
+                                                                         ntiles, sd);
+    count_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.list_slots, w.hist2, w.hist3, w.hist4, w.tile_sum,
                                                               w.group_sum, ntiles, group_tiles, sd);
-    const Out<T> out = {vals, idx, tile_ptr, k};
     if (records)
         write_kernel<T, MAG, STD><<<(unsigned)((ntiles + 3) / 4), kTileThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.rec_val, w.rec_pos, w.hist4,
                                                                                        w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
     else
         dense_write_kernel<T, MAG, STD><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.hist4, w.tile_sum, w.group_sum, ntiles,
                                                                                  group_tiles, out, sd);
-    plain_write_kernel<T, MAG, STD><<<(unsigned)(ntiles < kPlainGrid ? ntiles : kPlainGrid), kTileThreads, 0, s>>>(
-        x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
+    plain_write_kernel<T, MAG, STD><<<plain_grid, kTileThreads, 0, s>>>(x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
 }
 
 }  // namespace
@@ -1388,8 +1479,8 @@ int32_t prune_global_entry(const void *x, int32_t dt, int64_t n, int64_t H, cons
         (tile_ptr && !aligned_to(tile_ptr, 4)) || (row_ptr && !aligned_to(row_ptr, 4)) ||
         (standardised && (!aligned_to(mean, 4) || !aligned_to(rstd, 4))))
         return SLIMFIT_ERR_ALIGNMENT;
-    const Workspace w = carve(workspace, n);
-    if (workspace_bytes < w.bytes) return SLIMFIT_ERR_WORKSPACE;
+    if (workspace_bytes < least_workspace_for(n)) return SLIMFIT_ERR_WORKSPACE;
+    const Workspace w = carve_room(workspace, n, workspace_bytes);
     int32_t rc;
     if ((rc = check_device_range(x, (size_t)n * esz)) != SLIMFIT_OK) return rc;
     if ((rc = check_device_range(vals, (size_t)k * vsz)) != SLIMFIT_OK) return rc;

@@ -59,14 +59,14 @@ def _forward_both(x, gamma, beta, eps=1e-5):
     return torch.from_numpy(om).cuda(), torch.from_numpy(orr).cuda()
 
 
-def _prune_both(x, mean, rstd, k, by_mag=True):
+def _prune_both(x, mean, rstd, k, by_mag=True, room=None):
     rows, H = x.shape
     n = rows * H
     vals = Guarded(k, torch.float32)
     idx = Guarded(k, torch.int32)
     ptr = Guarded(sf.global_tile_ptr_len(n), torch.int32)
     rptr = Guarded(rows + 1, torch.int32)
-    ws = Guarded(sf.prune_global_workspace(n), torch.uint8)
+    ws = Guarded(room or sf.prune_global_workspace(n), torch.uint8)
     sf.prune_global_standardized(x, mean, rstd, k, vals.t, idx.t, by_mag, ptr.t, rptr.t, ws.t)
     torch.cuda.synchronize()
     vals.check(); idx.check(); ptr.check(); rptr.check(); ws.check()
@@ -312,3 +312,18 @@ def test_sample_is_standardised_row_by_row(rows, H, dtype):
             ws = torch.full((sf.prune_global_workspace(n),), 0xFF, dtype=torch.uint8, device="cuda")
             sf.prune_global_standardized(x, mean, rstd, k, vals, idx, by_mag, None, None, ws)
             assert int(ws[24:28].view(torch.int32)) == 0, "the sampled bracket missed the cut"
+
+
+@pytest.mark.parametrize("rows,H,dtype", [(3, 8, torch.float32), (700, 96, torch.float32), (700, 1000, torch.bfloat16),
+                                          (6300, 1024, torch.float32), (6300, 1024, torch.bfloat16)])
+def test_standardised_pruning_in_a_small_workspace(rows, H, dtype):
+    """The smallest workspace that is accepted: without lists below some 5 M elements, with short ones above."""
+    require_gpu()
+    x, _, _, _ = _inputs(rows * 3 + H, rows, H)
+    x = x.to(dtype)
+    xd = x.double()
+    mean, rstd = xd.mean(1).float(), (1.0 / (xd.var(1, unbiased=False) + 1e-5).sqrt()).float()
+    tiles = (rows * H + sf.GLOBAL_TILE - 1) // sf.GLOBAL_TILE
+    room = 16512 + 2 * ((8 * tiles + 127) // 128 * 128) + 1024 * (tiles + 1)
+    for k in (rows * H // 10, rows * H // 3):
+        _prune_both(x, mean, rstd, k, room=room)

@@ -268,3 +268,34 @@ def test_sample_that_misses_the_cut(dtype, scale):
     for k in (n // 10, n // 2):
         _run_both(x, k, True, restore=False)
         _run_both(x, k, False, restore=False)
+
+
+def _least_workspace(n):
+    tiles = (n + sf.GLOBAL_TILE - 1) // sf.GLOBAL_TILE
+    return 16512 + 2 * ((8 * tiles + 127) // 128 * 128) + 1024 * (tiles + 1)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,k,room", [(1, 1, 0), (5, 2, 0), (4096, 409, 0), (4097, 4097, 0), (70001, 7000, 0), ((1 << 20) + 3, 104857, 0),
+                                      (300000, 30000, 150000), (2000003, 200000, 1000001), (2000003, 1500000, 700000),
+                                      (6500003, 650000, 0), (6500003, 5, 0), (6500003, 3000000, 0)])
+def test_smaller_workspaces(n, k, room, dtype):
+    """From the smallest accepted size up: without lists, with short ones, without records."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    least = _least_workspace(n)
+    assert least <= (room or least) < sf.prune_global_workspace(n)
+    x = torch.randn(n, generator=g, device="cuda").to(dtype)
+    for by_mag in (True, False):
+        _run_both(x, k, by_mag, restore=False, workspace=Guarded(room or least, torch.uint8))
+    _run_both((x * 2).round() / 2, k, True, restore=False, workspace=Guarded(room or least, torch.uint8))
+    vals, idx = torch.empty(k, dtype=dtype, device="cuda"), torch.empty(k, dtype=torch.int32, device="cuda")
+    with pytest.raises(sf.SlimfitError) as e:
+        sf.prune_global(x, k, vals, idx, True, workspace=torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+    assert e.value.status == sf.ERR_WORKSPACE
+
+
+def test_smaller_workspaces_hold_what_was_reported_before_there_were_records():
+    """The sizes that slimfit_prune_global_workspace used to report."""
+    for n, want in ((1, 18816), (4096, 18816), (4097, 19840), (100000, 43648), (6500003, 1668224), (50331648, 12797056)):
+        assert _least_workspace(n) == want
