@@ -872,78 +872,70 @@ __device__ __forceinline__ u32x2 count_tensor_tile(const T *__restrict__ x, int6
     return r;
 }
 
-// the survivors of a tile in ascending index order, from the tensor: a wave, round by round, or (WG) a workgroup, a
-// wave a round
-template <typename T, bool MAG, bool STD, bool INSIDE, bool WG>
+// the survivors of a tile in ascending index order, from the tensor (a workgroup, a wave a round)
+template <typename T, bool MAG, bool STD, bool INSIDE>
 __device__ __forceinline__ void write_tensor_tile(const T *__restrict__ x, int64_t n, int64_t tile, uint32_t Tk, uint32_t out_base,
                                                   uint32_t budget, const Out<T> &out, const Std &sd)
 {
     constexpr int EPV = Elem<T>::EPV, G = kGroups<T>;
-    const int lane = threadIdx.x & (kWave - 1);
-    __shared__ uint32_t part[WG ? kTileThreads / kWave : 1];
-    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    __shared__ uint32_t part[kTileThreads / kWave];
+    uint32_t bits[G][EPV];
+    int valid[G];
+    load_round<T, STD, INSIDE>(x, n, tile, wave, lane, bits, valid, sd);
+    uint32_t packed[G], incl[G];                            // keys above T | keys equal T << 16: at most 512 per group and field
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        packed[j] = 0u;
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            const uint32_t key = make_key<T, MAG>(bits[j][e]);
+            if (INSIDE || e < valid[j]) packed[j] += (key > Tk ? 1u : 0u) + (key == Tk ? 1u << 16 : 0u);
+        }
+        incl[j] = wave_scan_u32(packed[j]);
+        mine += wave_total_u32(incl[j]);
+    }
+    __syncthreads();                                        // the previous tile's sums have been read
+    if (lane == 0) part[wave] = mine;
+    __syncthreads();
     uint32_t run_gt = 0u, run_eq = 0u;                      // survivors / ties of this tile ahead of the current group
-#pragma unroll 1
-    for (int step = 0; step < (WG ? 1 : 4); ++step) {
-        const int round = WG ? wave : step;
-        uint32_t bits[G][EPV];
-        int valid[G];
-        load_round<T, STD, INSIDE>(x, n, tile, round, lane, bits, valid, sd);
-        uint32_t packed[G], incl[G];                        // keys above T | keys equal T << 16: at most 512 per group and field
-        uint32_t mine = 0u;
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
-            packed[j] = 0u;
+    for (int w = 0; w < kTileThreads / kWave; ++w) {
+        run_gt += w < wave ? part[w] & 0xFFFFu : 0u;
+        run_eq += w < wave ? part[w] >> 16 : 0u;
+    }
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) {
+    for (int j = 0; j < G; ++j) {
+        const uint32_t excl = incl[j] - packed[j], group = wave_total_u32(incl[j]);
+        uint32_t my_gt = run_gt + (excl & 0xFFFFu);
+        uint32_t my_eq = run_eq + (excl >> 16);
+        const int64_t e0 = round_vec<T>(tile, wave, j, lane) * EPV;
+        if constexpr (STD) {
+            if (sd.row_ptr && valid[j]) {                   // rows start on vector boundaries
+                const uint32_t row = row_of((uint32_t)e0, sd);
+                if ((uint32_t)e0 == row * sd.H) sd.row_ptr[row] = (int32_t)(out_base + my_gt + min(my_eq, budget));
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            if (INSIDE || e < valid[j]) {
                 const uint32_t key = make_key<T, MAG>(bits[j][e]);
-                if (INSIDE || e < valid[j]) packed[j] += (key > Tk ? 1u : 0u) + (key == Tk ? 1u << 16 : 0u);
-            }
-            incl[j] = wave_scan_u32(packed[j]);
-            mine += wave_total_u32(incl[j]);
-        }
-        if constexpr (WG) {
-            __syncthreads();                                // the previous tile's sums have been read
-            if (lane == 0) part[wave] = mine;
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < kTileThreads / kWave; ++w) {
-                run_gt += w < wave ? part[w] & 0xFFFFu : 0u;
-                run_eq += w < wave ? part[w] >> 16 : 0u;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-            const uint32_t excl = incl[j] - packed[j], group = wave_total_u32(incl[j]);
-            uint32_t my_gt = run_gt + (excl & 0xFFFFu);
-            uint32_t my_eq = run_eq + (excl >> 16);
-            const int64_t e0 = round_vec<T>(tile, round, j, lane) * EPV;
-            if constexpr (STD) {
-                if (sd.row_ptr && valid[j]) {               // rows start on vector boundaries
-                    const uint32_t row = row_of((uint32_t)e0, sd);
-                    if ((uint32_t)e0 == row * sd.H) sd.row_ptr[row] = (int32_t)(out_base + my_gt + min(my_eq, budget));
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) {
-                if (INSIDE || e < valid[j]) {
-                    const uint32_t key = make_key<T, MAG>(bits[j][e]);
-                    const bool above = key > Tk;
-                    const bool tie = key == Tk;
-                    if (above || (tie && my_eq < budget)) {
-                        const uint32_t pos = out_base + my_gt + min(my_eq, budget);
-                        if (pos < out.k) {                  // always true for consistent counts; guards the stores
-                            store_raw<typename Elem<T>::Out>(out.vals + pos, bits[j][e]);
-                            out.idx[pos] = (int32_t)(e0 + e);
-                        }
+                const bool above = key > Tk;
+                const bool tie = key == Tk;
+                if (above || (tie && my_eq < budget)) {
+                    const uint32_t pos = out_base + my_gt + min(my_eq, budget);
+                    if (pos < out.k) {                      // always true for consistent counts; guards the stores
+                        store_raw<typename Elem<T>::Out>(out.vals + pos, bits[j][e]);
+                        out.idx[pos] = (int32_t)(e0 + e);
                     }
-                    my_gt += above ? 1u : 0u;
-                    my_eq += tie ? 1u : 0u;
                 }
+                my_gt += above ? 1u : 0u;
+                my_eq += tie ? 1u : 0u;
             }
-            run_gt += group & 0xFFFFu;
-            run_eq += group >> 16;
         }
+        run_gt += group & 0xFFFFu;
+        run_eq += group >> 16;
     }
 }
 
@@ -1082,9 +1074,9 @@ __device__ __forceinline__ void dense_tile(const T *__restrict__ x, int64_t n, c
     const uint32_t out_base = ahead.x + min(ahead.y, take_eq), budget = take_eq > ahead.y ? take_eq - ahead.y : 0u;
     if (threadIdx.x < kWave) write_pointers<T>(out, tile, ntiles, out_base, sd, STD);
     if ((tile + 1) * kTileElems <= n)
-        write_tensor_tile<T, MAG, STD, true, true>(x, n, tile, Tk, out_base, budget, out, sd);
+        write_tensor_tile<T, MAG, STD, true>(x, n, tile, Tk, out_base, budget, out, sd);
     else
-        write_tensor_tile<T, MAG, STD, false, true>(x, n, tile, Tk, out_base, budget, out, sd);
+        write_tensor_tile<T, MAG, STD, false>(x, n, tile, Tk, out_base, budget, out, sd);
 }
 
 // The survivors from the records (list route; on the plain route the counts).
@@ -1122,15 +1114,27 @@ write_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *__restr
         }
     }
     const u32x2 ahead = sums_ahead(tile_sum, group_sum, here, group_tiles);
-    if (tile >= ntiles) return;
     const uint32_t out_base = ahead.x + min(ahead.y, take_eq), budget = take_eq > ahead.y ? take_eq - ahead.y : 0u;
-    write_pointers<T>(out, tile, ntiles, out_base, sd, STD);
-    if (n_cand != kTooMany)
-        write_record_tile<T, MAG, STD>(v, p, n_cand, n, tile, Tk, out_base, budget, out, sd);
-    else if ((tile + 1) * kTileElems <= n)
-        write_tensor_tile<T, MAG, STD, true, false>(x, n, tile, Tk, out_base, budget, out, sd);
-    else
-        write_tensor_tile<T, MAG, STD, false, false>(x, n, tile, Tk, out_base, budget, out, sd);
+    // A tile that holds more candidates than records (18 % of them where the rows' scale has a log-normal spread of 0.3) is
+    // written from the tensor by the whole workgroup, whose waves read a quarter each.  By its own wave alone, a quarter
+    // after another, the launch waited for it: such rows 50432 x 1024 bf16 100.8 us in all against 96.6, 49152 x 1024 fp32
+    // 113.6 against 111.3.
+    __shared__ u32x2 left[4];                               // such tiles: first output slot, ties to keep
+    if (lane == 0) left[wave] = tile < ntiles && n_cand == kTooMany ? u32x2{out_base, budget} : u32x2{~0u, 0u};
+    if (tile < ntiles) {
+        write_pointers<T>(out, tile, ntiles, out_base, sd, STD);
+        if (n_cand != kTooMany) write_record_tile<T, MAG, STD>(v, p, n_cand, n, tile, Tk, out_base, budget, out, sd);
+    }
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        const u32x2 at = left[w];
+        if (at.x == ~0u) continue;                          // workgroup-uniform
+        const int64_t t = (int64_t)blockIdx.x * 4 + w;
+        if ((t + 1) * kTileElems <= n)
+            write_tensor_tile<T, MAG, STD, true>(x, n, t, Tk, at.x, at.y, out, sd);
+        else
+            write_tensor_tile<T, MAG, STD, false>(x, n, t, Tk, at.x, at.y, out, sd);
+    }
 }
 
 // The same when the sweep has made no records: a workgroup per tile, from the tensor.
