@@ -601,6 +601,8 @@ sweep_kernel(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict
 // values, whose lanes would queue for a handful of LDS words (50.3 M fp32 multiples of a half: 89 us with one, 62 with
 // four, 58 with eight).
 constexpr int kCopies = 8;
+constexpr int kCopyStride = kTopBins + 8;      // a bin's copies lie in banks of their own (at kTopBins all in one: bf16 ties 59.4 us, now 38.2)
+constexpr int kCopyWords = kCopies * kCopyStride;
 template <typename T, bool MAG, bool STD, bool FIRST>
 __device__ __forceinline__ void tensor_hist(const T *__restrict__ x, int64_t n, uint32_t prefix, uint32_t mask, int shift,
                                             int nbins, uint32_t *bins, const Std &sd)
@@ -609,7 +611,7 @@ __device__ __forceinline__ void tensor_hist(const T *__restrict__ x, int64_t n, 
     const int64_t nvec = (n + EPV - 1) / EPV;
     const int64_t nfull = n / EPV;                            // vectors wholly below n
     const int64_t chunk = (int64_t)kWideThreads * kVecPerThread;
-    const uint32_t copy = (threadIdx.x % kCopies) * kTopBins;
+    const uint32_t copy = (threadIdx.x % kCopies) * kCopyStride;
     auto sweep = [&](auto inside_tag, int64_t base) {
         constexpr bool INSIDE = decltype(inside_tag)::value;
         uint32_t bits[kVecPerThread][EPV];
@@ -686,7 +688,7 @@ __device__ __forceinline__ void add_bins(const uint32_t *bins, uint32_t *__restr
     for (int i = threadIdx.x; i < nbins; i += kWideThreads) {
         uint32_t c = 0u;
 #pragma unroll
-        for (int u = 0; u < COPIES; ++u) c += bins[u * kTopBins + i];
+        for (int u = 0; u < COPIES; ++u) c += bins[u * kCopyStride + i];
         if (c) atomicAdd(&hist[i], c);
     }
 }
@@ -696,8 +698,8 @@ template <typename T, bool MAG, bool STD>
 __global__ void __launch_bounds__(kWideThreads)
 top_digit_kernel(const T *__restrict__ x, int64_t n, uint32_t *__restrict__ hist, Std sd)
 {
-    __shared__ uint32_t bins[kCopies * kTopBins];
-    clear_bins(bins, kCopies * kTopBins);
+    __shared__ uint32_t bins[kCopyWords];
+    clear_bins(bins, kCopyWords);
     __syncthreads();
     tensor_hist<T, MAG, STD, true>(x, n, 0u, 0u, Elem<T>::KEYBITS - kTop, kTopBins, bins, sd);
     __syncthreads();
@@ -711,7 +713,7 @@ digit_kernel(const T *__restrict__ x, int64_t n, State *st, const uint64_t *__re
              const u32x2 *__restrict__ tile_cnt, const uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ hist2,
              int64_t ntiles, uint32_t k, Std sd)
 {
-    __shared__ uint32_t bins[kCopies * kTopBins];
+    __shared__ uint32_t bins[kCopyWords];
     const int lane = threadIdx.x & (kWave - 1);
     static_assert(kCounters == kWave, "a lane per counter");
     const int grid = min((int)gridDim.x, kListGrid);
@@ -726,7 +728,7 @@ digit_kernel(const T *__restrict__ x, int64_t n, State *st, const uint64_t *__re
     }
     if (!plain && (int)blockIdx.x >= grid) return;
     const int nbins = plain ? kTopBins : 1 << st->digit2;
-    clear_bins(bins, plain ? kCopies * kTopBins : nbins);
+    clear_bins(bins, plain ? kCopyWords : nbins);
     __syncthreads();
     if (plain) {
         tensor_hist<T, MAG, STD, true>(x, n, 0u, 0u, Elem<T>::KEYBITS - kTop, kTopBins, bins, sd);
