@@ -510,14 +510,17 @@ layernorm_backward_dequant_kernel(const uint8_t *__restrict__ codes, const float
 // (the four waves' four rows in flight) or over 256.  The time of a small call is the chip left idle: with
 // 256-row slabs throughout, 4096 x 768 fp32 has 48 workgroups and took 21.7 us (bf16 52.5) against 9.8 now,
 // which is the host's two launches (24 us of kernels to 6); 25216 x 768 34.2 -> 29.0; 49152 x 1024
-// 69.9 -> 65.2 (6.2 TB/s), bf16 68.4 -> 39.2.  Half as many workgroups: bf16 62.6; twice: fp32 30.6 and 66.3.
+// 69.9 -> 65.2 (6.2 TB/s), bf16 68.4 -> 39.2.  Half as many workgroups: bf16 62.6; twice: fp32 30.6 and 66.3.  Rows under
+// 256 columns count as 256: slabs in proportion to their width are so many that the second kernel's one workgroup reads
+// them for longer than the rows take (500 000 x 8 fp32 122.7 us, with 256-row slabs 107.7, now 50.8; bf16 169, 137, 87).
 constexpr int kMaxSlabRows = 256, kMinSlabRows = 16;
 constexpr int64_t kSlabWorkgroups = 1024;
 constexpr int kGroupVecs = kWave;           // column vectors per workgroup: 256 columns (fp32), 512 (bf16)
+constexpr int64_t kGroupCols = 256;
 int slab_rows_for(int64_t rows, int64_t H, int epv, int64_t room)      // room >= least: slabs the workspace holds
 {
     const int64_t most = (rows + kMinSlabRows - 1) / kMinSlabRows, least = (rows + kMaxSlabRows - 1) / kMaxSlabRows;
-    const int64_t fill = (kSlabWorkgroups * kGroupVecs * epv + H - 1) / H;
+    const int64_t cols = H < kGroupCols ? kGroupCols : H, fill = (kSlabWorkgroups * kGroupVecs * epv + cols - 1) / cols;
     int64_t slabs = fill < least ? least : (fill < most ? fill : most);
     if (slabs > room) slabs = room;
     const int64_t per = slabs > 0 ? (rows + slabs - 1) / slabs : kMinSlabRows;
