@@ -464,8 +464,12 @@ int32_t slimfit_layernorm_backward(const void *x, int32_t dt, const float *mean,
  * x~ = (x - mean[r]) * rstd[r] from the statistics slimfit_layernorm_forward returned.
  * fp32 products and slab sums (16 to 256 rows, four interleaved quarters), fp64 across slabs, fixed order (no atomics):
  * within 4e-6 * sum_r |x~ * y^| (resp. |y^|) of the fp64 value.
- * dgamma, dbeta : DEVICE float[H].  workspace: DEVICE, 16-byte aligned, at least
- * slimfit_layernorm_param_grads_workspace(rows, H) bytes; contents overwritten. */
+ * The slabs depend on rows, H and dt alone: the same call gives the same bits in every workspace of
+ * the reported size or more.
+ * dgamma, dbeta : DEVICE float[H].  workspace: DEVICE, 16-byte aligned, of
+ * slimfit_layernorm_param_grads_workspace(rows, H) bytes; contents overwritten.  A smaller one is
+ * served with slabs of 256 rows, more slowly and with sums grouped in that other way, down to
+ * max(1, ceil(rows / 256)) * 8 * H bytes. */
 int32_t slimfit_layernorm_param_grads_workspace(int64_t rows, int64_t H, size_t *bytes);
 
 int32_t slimfit_layernorm_param_grads(const void *x, int32_t dt, const float *mean, const float *rstd,

@@ -517,12 +517,11 @@ constexpr int kMaxSlabRows = 256, kMinSlabRows = 16;
 constexpr int64_t kSlabWorkgroups = 1024;
 constexpr int kGroupVecs = kWave;           // column vectors per workgroup: 256 columns (fp32), 512 (bf16)
 constexpr int64_t kGroupCols = 256;
-int slab_rows_for(int64_t rows, int64_t H, int epv, int64_t room)      // room >= least: slabs the workspace holds
+int slab_rows_for(int64_t rows, int64_t H, int epv)
 {
     const int64_t most = (rows + kMinSlabRows - 1) / kMinSlabRows, least = (rows + kMaxSlabRows - 1) / kMaxSlabRows;
     const int64_t cols = H < kGroupCols ? kGroupCols : H, fill = (kSlabWorkgroups * kGroupVecs * epv + cols - 1) / cols;
-    int64_t slabs = fill < least ? least : (fill < most ? fill : most);
-    if (slabs > room) slabs = room;
+    const int64_t slabs = fill < least ? least : (fill < most ? fill : most);
     const int64_t per = slabs > 0 ? (rows + slabs - 1) / slabs : kMinSlabRows;
     return (int)((per + kMinSlabRows - 1) / kMinSlabRows * kMinSlabRows);
 }
@@ -760,11 +759,13 @@ extern "C" int32_t slimfit_layernorm_param_grads(const void *x, int32_t dt, cons
     if (!aligned_to(dgamma, 4) || !aligned_to(dbeta, 4) || !aligned_to(workspace, 16) ||
         (rows > 0 && (!aligned_to(x, 16) || !aligned_to(dy, 16) || !aligned_to(mean, 4) || !aligned_to(rstd, 4))))
         return SLIMFIT_ERR_ALIGNMENT;
-    // (a workspace below the reported size but large enough for the fewest slabs is served with the slabs that fit)
+    // A workspace below the reported size that holds the partials of 256-row slabs is served with those, whatever its
+    // size: the sums' grouping, and with it their last bits, go by one comparison and not by the bytes that happen to fit.
     const int64_t least = (rows + kMaxSlabRows - 1) / kMaxSlabRows;
     if (workspace_bytes < (size_t)(least > 0 ? least : 1) * 2 * (size_t)H * 4) return SLIMFIT_ERR_WORKSPACE;
-    const int64_t room = (int64_t)(workspace_bytes / (2 * (size_t)H * 4));
-    const int slab_rows = slab_rows_for(rows, H, dt == SLIMFIT_F32 ? 4 : 8, room);
+    size_t reported = 0;
+    slimfit_layernorm_param_grads_workspace(rows, H, &reported);
+    const int slab_rows = workspace_bytes >= reported ? slab_rows_for(rows, H, dt == SLIMFIT_F32 ? 4 : 8) : kMaxSlabRows;
     const int64_t slabs = (rows + slab_rows - 1) / slab_rows;
     const size_t need = (size_t)(slabs > 0 ? slabs : 1) * 2 * (size_t)H * 4;
     if ((rc = check_device_range(dgamma, (size_t)H * 4)) != SLIMFIT_OK) return rc;

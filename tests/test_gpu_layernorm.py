@@ -327,3 +327,30 @@ def test_standardised_pruning_in_a_small_workspace(rows, H, dtype):
     room = 16512 + 2 * ((8 * tiles + 127) // 128 * 128) + 1024 * (tiles + 1)
     for k in (rows * H // 10, rows * H // 3):
         _prune_both(x, mean, rstd, k, room=room)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,H", [(1000, 8), (4100, 520), (8200, 256)])
+def test_param_grads_bits_do_not_depend_on_the_room(rows, H, dtype):
+    """One grouping of the sums for every workspace of the reported size or more, one for every smaller one."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randn(rows, H, generator=g, device="cuda").to(dtype)
+    dy = torch.randn(rows, H, generator=g, device="cuda").to(dtype)
+    mean = 0.1 * torch.randn(rows, generator=g, device="cuda")
+    rstd = 0.5 + torch.rand(rows, generator=g, device="cuda")
+    slab, least = 8 * H, (rows + 255) // 256
+    reported = torch.zeros(1, dtype=torch.int64)
+    import ctypes
+    assert sf.lib().slimfit_layernorm_param_grads_workspace(ctypes.c_int64(rows), ctypes.c_int64(H), ctypes.c_void_p(reported.data_ptr())) == 0
+    reported = int(reported)
+
+    def grads(nbytes):
+        dg, db = torch.empty(H, device="cuda"), torch.empty(H, device="cuda")
+        sf.layernorm_param_grads(x, mean, rstd, dy, dg, db, torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        return torch.cat([dg, db])
+
+    for sizes in ((least * slab, (least + 1) * slab, 2 * least * slab + 4, reported - 4), (reported, reported + slab, 2 * reported)):
+        first = grads(sizes[0])
+        for nbytes in sizes[1:]:
+            assert torch.equal(grads(nbytes), first), "workspace of %d bytes" % nbytes
