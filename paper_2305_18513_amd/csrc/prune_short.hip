@@ -668,18 +668,28 @@ void launch_short_k(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int3
 
 }  // namespace
 
-// Which short rows come here rather than to the wave-per-row kernel (prune.hip), both measured on 40 .. 256 columns at
-// 16 384 and 196 608 rows:
+// Which short rows come here rather than to the wave-per-row kernel (prune.hip).  Both were measured on 33 .. 256 columns
+// and 2048 .. 196 608 rows; times are this kernel's against the other's, in us:
 //  - few enough kept entries: the list insertion grows with k (fp32 rows that keep 12 or 16 lose 15 - 45 %);
 //  - strides that spread over the LDS banks: the lanes of a wave read the same entry of 16 rows at once, and at a
-//    stride of a multiple of 32 dwords those lie in one or two banks (fp32 softmax on 256 columns 524 us against 70, 128
-//    columns 265 against 53, 64 columns 68 against 48; pruning, which walks the rows once, 98 against 42 at 256 and 54
-//    against 37 at 128, but 17 against 33 at 64; bf16, whose stride is half, softmax on 256 columns 84 against 72);
+//    stride of a multiple of 32 dwords those lie in one or two banks (196 608 rows, fp32 softmax on 256 columns 528
+//    against 75, 128 columns 267 against 57, 160 90 against 62, 64 68 against 52, but 96 57 against 57; pruning, which
+//    walks the rows once, only at multiples of 64 dwords from 128 on: 105 against 47 at 256, 54 against 38 at 128, but 18
+//    against 34 at 64).  bf16 strides are half of that; softmax alone loses, on 256 columns alone (98 against 77 at k = 16,
+//    78 against 76 at 9; on 128 columns 30 against 63);
 //  - enough rows: a wave takes 16 (32) of them and needs 8 - 15 us whatever their number, while the other kernel gives
-//    few rows a wave each (16 384 rows of 197 columns: fp32 softmax 16.3 us against 10.3, pruning 11.5 against 9.3, bf16
-//    softmax 15.6 against 10.8); the two meet at 24 576 rows (fp32 pruning, 13.3 and 11.9, but peaked rows 10.2 and 11.6;
-//    bf16 softmax 16.1 and 14.8, on 128 columns 10.5 and 12.4) and at 65 536 (fp32 softmax, 32.5 and 33.5); at 196 608
-//    this one is ahead (72.7 against 84, 40.6 against 48.9, 61.5 against 75.8).
+//    few rows a wave each.  From 128 columns on, at 16 384 rows of 197 columns: fp32 pruning 11.2 against 8.3, softmax 16.2
+//    against 11.4, bf16 softmax 15.4 against 11.1.  fp32 pruning: 12.7 against 10.0 at 24 576 rows, 17.6 against 15.9 at
+//    49 152 (peaked 16.2 against 19.1, nine tenths masked 14.9 against 17.7), 40 against 47 at 196 608.  bf16 softmax:
+//    15.8 against 14.6 at 24 576 (128 columns 10.1 against 12.2), 16.2 against 18.0 at 32 768.  fp32 softmax: 32.3 against
+//    33.6 at 65 536, 25.8 against 25.4 at 49 152.
+//    Below 128 columns the two are within 1 us of one another for few rows (fp32 pruning of 16 384 x 112 7.1 against 7.2,
+//    softmax 10.1 against 9.2, bf16 8.8 against 9.8; at 2048 rows, where the host's launch is most of it, 7.9 against 6.5) and
+//    this one is ahead from 24 576 on, so their number is not looked at.  Nor is it for bf16 pruning: plain rows gain in the
+//    other kernel at k = 16 (16 384 x 197 9.5 against 8.1), but rows with masked columns, whose zeros share one histogram
+//    bin there, lose more (9.6 against 14.8; peaked 9.5 against 9.7).
+// What stays slower here or there: fp32 rows of few distinct values (logits in steps of a half) take the other kernel's
+// bisection to the last bit, 98 304 x 192 pruned 62 us here, 85 there, 16 384 x 197 12 and 20; constant rows 61 and 70, 12 and 16.
 constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 60000;
 
 bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, bool softmax)
@@ -687,11 +697,7 @@ bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int
     const bool bf16 = dt == SLIMFIT_BF16;
     if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32) || rows > (int64_t)0x7FFFFFFF * 16) return false;
     if (!aligned_to(p, 16)) return false;              // (the rows are staged with 16-byte loads)
-    if (bf16) {
-        if (softmax && cols == 256) return false;
-        if (softmax) return cols < 128 || rows >= kShortMinRows;
-        return k <= 12 || rows >= kShortMinRows;
-    }
+    if (bf16) return !softmax || (cols != 256 && (cols < 128 || rows >= kShortMinRows));
     if (softmax) return !(cols >= 64 && cols % 32 == 0) && (cols < 128 || rows >= kShortMinRowsSoftmaxF32);
     return !(cols >= 128 && cols % 64 == 0) && (cols < 128 || rows >= kShortMinRows);
 }
