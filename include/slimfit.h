@@ -318,7 +318,7 @@ int32_t slimfit_restore_scores(const void *vals, const uint16_t *idx, const int3
  *     fp32 (hardware exp2, a sum in a fixed order, one IEEE division per row):
  *     p_j within p_j * (2e-6 + 2e-7 * (max l - l_j)) of the exact value (a
  *     subnormal p_j may be flushed to zero), bf16 results within one further
- *     bf16 rounding.  The order of the sum is one of two, by dt, rows, cols, k and
+ *     bf16 rounding.  The order of the sum goes by dt, rows, cols, k and
  *     the pointers' alignment: calls that agree in those give the same bits, and a
  *     row's last bits may differ between calls that don't.
  *
