@@ -1165,11 +1165,18 @@ __global__ __launch_bounds__(kThreads) void softmax_backward_small_kernel(const 
 //   pruning, >= 512 whole       196 608 rows, fp32 with two 512: 87 / 89 us, 768 93.5 / 101, 1024 94 / 101; bf16 with four
 //                               768: 81 / 83, its softmax 121 / 125
 // Rows past 1024 columns hold the most instructions per byte: eight again.
+constexpr int kSlotCounts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};           // the kernel's instances
+int slots_held(int cols)
+{
+    int i = 0;
+    while (kSlotCounts[i] * kWave < cols) ++i;                                       // cols <= 64 * kMaxRegSlots
+    return kSlotCounts[i];
+}
 template <typename T, bool SOFTMAX>
 int unit_rows_for(int64_t rows, int cols)
 {
     constexpr bool F32 = sizeof(T) == 4;
-    const bool whole = cols == 384 || cols == 512 || cols == 768 || cols == 1024;      // no absent columns, no ragged slots
+    const bool whole = cols > 256 && cols == slots_held(cols) * kWave;               // no absent columns, no ragged slots
     int most = kRowsPerUnit;
     if (cols <= 1024) {
         if (SOFTMAX && F32) most = whole ? 1 : (cols > 256 ? 4 : most);
@@ -1223,22 +1230,24 @@ void launch_prune(const void *p, int64_t rows, int cols, int k, int mode, float 
         else if (staged) SLIMFIT_PRUNE_LAUNCH(MM, false, true);                                                 \
         else SLIMFIT_PRUNE_LAUNCH(MM, false, false);                                                            \
     } while (0)
-    if (slots <= 1) SLIMFIT_PRUNE_CASE(1);
-    else if (slots <= 2) SLIMFIT_PRUNE_CASE(2);
-    else if (slots <= 3) SLIMFIT_PRUNE_CASE(3);
-    else if (slots <= 4) SLIMFIT_PRUNE_CASE(4);
-    else if (slots <= 6) SLIMFIT_PRUNE_CASE(6);
-    else if (slots <= 8) SLIMFIT_PRUNE_CASE(8);
-    else if (slots <= 12) SLIMFIT_PRUNE_CASE(12);
-    else if (slots <= 16) SLIMFIT_PRUNE_CASE(16);
+    switch (slots_held(cols)) {
+    case 1: SLIMFIT_PRUNE_CASE(1); break;
+    case 2: SLIMFIT_PRUNE_CASE(2); break;
+    case 3: SLIMFIT_PRUNE_CASE(3); break;
+    case 4: SLIMFIT_PRUNE_CASE(4); break;
+    case 6: SLIMFIT_PRUNE_CASE(6); break;
+    case 8: SLIMFIT_PRUNE_CASE(8); break;
+    case 12: SLIMFIT_PRUNE_CASE(12); break;
+    case 16: SLIMFIT_PRUNE_CASE(16); break;
 #if SLIMFIT_PRUNE_WAVE_SLOTS >= 32
-    else if (slots <= 24) SLIMFIT_PRUNE_LAUNCH(24, false, false);       // wide rows: no staging, ragged or not
-    else if (slots <= 32) SLIMFIT_PRUNE_LAUNCH(32, false, false);
+    case 24: SLIMFIT_PRUNE_LAUNCH(24, false, false); break;       // wide rows: no staging, ragged or not
+    case 32: SLIMFIT_PRUNE_LAUNCH(32, false, false); break;
 #endif
 #if SLIMFIT_PRUNE_WAVE_SLOTS >= 64
-    else if (slots <= 48) SLIMFIT_PRUNE_LAUNCH(48, false, false);
-    else if (slots <= 64) SLIMFIT_PRUNE_LAUNCH(64, false, false);
+    case 48: SLIMFIT_PRUNE_LAUNCH(48, false, false); break;
+    case 64: SLIMFIT_PRUNE_LAUNCH(64, false, false); break;
 #endif
+    }
 #undef SLIMFIT_PRUNE_CASE
 #undef SLIMFIT_PRUNE_LAUNCH
 }
