@@ -64,8 +64,7 @@ constexpr int64_t kPtrTile = SLIMFIT_GLOBAL_TILE;   // granularity of the tile p
 constexpr int kTileElems = (int)kPtrTile;
 constexpr int kWaveElems = kTileElems / 4; // a tile is four rounds of 1024 elements, one a wave of the sweep
 
-constexpr int kSampleWgs = 16;             // at most
-constexpr int kSampleVecs = 1;             // vectors a thread of them takes
+constexpr int kSampleWgs = 16;             // at most; a thread of them takes one vector
 constexpr int kListSlots = kTileElems * 3 / 32;     // a tile's key list (in a workspace without records: fewer)
 constexpr int kMinListSlots = 192;         // fewer are not worth the sweep; the readers load 128 ahead
 constexpr int kRecSlots = 640;             // a tile's records: 10 % kept and 3 % more in the bracket, plus 5 standard deviations
@@ -215,7 +214,6 @@ __device__ __forceinline__ int load_tile_vec(const T *x, int64_t n, int64_t nvec
 struct Std {
     const float *mean, *rstd;
     uint32_t magic, shift;
-    uint32_t wave_uniform;       // H is a multiple of 64: 64 consecutive elements from a multiple of 64 share a row
     uint32_t vec_uniform;        // H is a multiple of 64 vectors: the 64 vectors a wave loads together share a row
     uint32_t last_row;
     uint32_t H;
@@ -370,30 +368,22 @@ sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, u32x2 *__r
 {
     constexpr int EPV = Elem<T>::EPV;
     __shared__ uint32_t bins[kTopBins];
-    const uint32_t first = blockIdx.x * kWideThreads + threadIdx.x, stride = gridDim.x * kWideThreads;
-    uint32_t bits[kSampleVecs][EPV];
-    int64_t at[kSampleVecs];
-#pragma unroll
-    for (int u = 0; u < kSampleVecs; ++u) {
-        const uint32_t i = min(first + (uint32_t)u * stride, total - 1u);
-        const uint64_t v0 = (i * step) >> 16, v1 = ((i + 1) * step) >> 16;
-        uint32_t h = i * 0x9E3779B1u;
-        h ^= h >> 15;
-        h *= 0x85EBCA77u;
-        h ^= h >> 13;
-        at[u] = (int64_t)v0 + __umulhi(h, (uint32_t)(v1 - v0));
-        load_tile_vec<T, true>(x, 0, 0, at[u], bits[u]);
-    }
+    const uint32_t mine = blockIdx.x * kWideThreads + threadIdx.x, i = min(mine, total - 1u);
+    const uint64_t v0 = (i * step) >> 16, v1 = ((i + 1) * step) >> 16;
+    uint32_t h = i * 0x9E3779B1u;
+    h ^= h >> 15;
+    h *= 0x85EBCA77u;
+    h ^= h >> 13;
+    const int64_t at = (int64_t)v0 + __umulhi(h, (uint32_t)(v1 - v0));
+    uint32_t bits[EPV];
+    load_tile_vec<T, true>(x, 0, 0, at, bits);
     for (int b = threadIdx.x; b < kTopBins; b += kWideThreads) bins[b] = 0u;
     clear_block(zero, n16);
     __syncthreads();
+    if (mine < total) {
+        standardise<T, STD, true>(bits, EPV, at, sd);
 #pragma unroll
-    for (int u = 0; u < kSampleVecs; ++u) {
-        if (first + (uint32_t)u * stride < total) {
-            standardise<T, STD, true>(bits[u], EPV, at[u], sd);
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) atomicAdd(&bins[make_key<T, MAG>(bits[u][e]) >> (Elem<T>::KEYBITS - kTop)], 1u);
-        }
+        for (int e = 0; e < EPV; ++e) atomicAdd(&bins[make_key<T, MAG>(bits[e]) >> (Elem<T>::KEYBITS - kTop)], 1u);
     }
     __syncthreads();
     // 16-bit counts (a workgroup holds at most 16384 entries), four bins a thread
@@ -1372,7 +1362,7 @@ struct SamplePlan {
 SamplePlan plan_sample(int64_t n, int64_t k, int epv)
 {
     SamplePlan p = {false, 0u, 0u, 0u, 0u, 0u};
-    const int64_t vectors = n / epv, most = (int64_t)kSampleWgs * kSampleVecs * kWideThreads;
+    const int64_t vectors = n / epv, most = (int64_t)kSampleWgs * kWideThreads;
     if (vectors == 0) return p;
     const int64_t total = vectors < most ? vectors : most, size = total * epv, rest = n - vectors * epv;
     p.total = (uint32_t)total;
@@ -1431,8 +1421,7 @@ void launch_select(const T *x, int64_t n, uint32_t k, typename Elem<T>::Out *val
     const SamplePlan plan = plan_sample(n, (int64_t)k, Elem<T>::EPV);
 
     if (plan.use) {
-        const uint32_t per = kSampleVecs * kWideThreads;
-        const int wgs = (int)((plan.total + per - 1) / per);
+        const int wgs = (int)((plan.total + kWideThreads - 1) / kWideThreads);
         sample_kernel<T, MAG, STD><<<wgs, kWideThreads, 0, s>>>(x, plan.total, plan.step, w.sample, w.zero, w.zero16, sd);
         bracket_kernel<false><<<1, kWideThreads, 0, s>>>(w.st, w.sample, wgs, nullptr, Elem<T>::KEYBITS, plan.hi, plan.lo,
                                                          plan.size, w.list_slots);
@@ -1512,7 +1501,7 @@ int32_t prune_global_entry(const void *x, int32_t dt, int64_t n, int64_t H, cons
     if ((rc = check_device_range(workspace, w.bytes)) != SLIMFIT_OK) return rc;
     if (tile_ptr && (rc = check_device_range(tile_ptr, (size_t)slimfit_global_tile_ptr_len(n) * 4)) != SLIMFIT_OK)
         return rc;
-    Std sd = {nullptr, nullptr, 0u, 0u, 0u, 0u, 0u, 0u, nullptr};
+    Std sd = {nullptr, nullptr, 0u, 0u, 0u, 0u, 0u, nullptr};
     if (standardised) {
         const size_t rows = (size_t)(n / H);
         if ((rc = check_device_range(mean, rows * 4)) != SLIMFIT_OK) return rc;
@@ -1525,7 +1514,6 @@ int32_t prune_global_entry(const void *x, int32_t dt, int64_t n, int64_t H, cons
         sd.rstd = rstd;
         sd.magic = (uint32_t)((pow + (uint64_t)H - 1) / (uint64_t)H);   // < 2^32 because H > 2^(l-1)
         sd.shift = (uint32_t)(l - 1);
-        sd.wave_uniform = (H % kWave == 0) ? 1u : 0u;
         sd.vec_uniform = (H % (kWave * epv) == 0) ? 1u : 0u;
         sd.last_row = (uint32_t)(rows - 1);
         sd.H = (uint32_t)H;
