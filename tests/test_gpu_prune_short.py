@@ -1,6 +1,8 @@
 """GPU parity of slimfit_prune_scores on short rows that keep few entries (the kernel with several rows per
 wavefront): every route of it -- keys that carry the column, the exact route for rows whose cut cannot be
-told from 24 value bits, signed keys -- against the CPU oracle, bit for bit."""
+told from 24 value bits, signed keys -- against the CPU oracle, bit for bit.  fp32 rows of 128 columns and more take
+that kernel from 20 000 rows on (and at no stride of a multiple of 64 columns), so there the rows that a test is about
+stand among enough plain ones."""
 import numpy as np
 import pytest
 import torch
@@ -10,6 +12,15 @@ from tests.gpu_util import require_gpu
 from tests.test_gpu_prune import _run_both
 
 pytestmark = pytest.mark.gpu
+
+ENOUGH = 20000             # a multiple of the rows a wave takes: the remainder is the test's own
+
+
+def _among_many(p, g):
+    if p.dtype != torch.float32 or p.shape[1] < 128:
+        return p
+    return torch.cat([p, torch.softmax(torch.randn(ENOUGH, p.shape[1], generator=g, device="cuda") * 0.5, dim=-1)])
+
 
 ROWS = [1, 15, 16, 17, 31, 32, 33, 64, 1000, 1037]
 COLS_K = [(1, 1), (2, 1), (3, 3), (5, 2), (16, 4), (17, 9), (63, 6), (64, 6), (65, 7), (100, 9), (128, 9),
@@ -25,6 +36,10 @@ def test_shapes_and_ragged_row_counts(cols, k, dtype):
         p = torch.softmax(torch.randn(rows, cols, generator=g, device="cuda") * 0.5, dim=-1).to(dtype)
         _run_both(p, k, restore=False)
         _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=1.3 / cols, restore=False)
+        if rows in (1, 17, 1037) and dtype == torch.float32 and cols >= 128:
+            many = _among_many(p, g)
+            _run_both(many, k, restore=False)
+            _run_both(many, k, mode=sf.PRUNE_THRESHOLD, tau=1.3 / cols, restore=False)
 
 
 @pytest.mark.parametrize("cols,k", [(197, 9), (128, 12), (250, 16), (64, 13), (33, 16)])
@@ -49,11 +64,10 @@ def test_fp32_cut_inside_one_bucket_of_24_bits(k):
     p[20:30, 5] = 1.0                                               # one far above
     p[30:40] = p[30:40, :1]                                         # constant rows
     p[40:50, 100:] = p[40:50, 99:100]                               # long runs of equal entries across lanes
-    _run_both(p, k)
     tau = float(torch.tensor(0x3C000080, dtype=torch.int32).view(torch.float32))        # a threshold inside the bucket
-    _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=tau)
-    _run_both(-p, k)                                                # the same among negative entries
-    _run_both(-p, k, mode=sf.PRUNE_THRESHOLD, tau=-tau)
+    for q, t in ((p, tau), (_among_many(p, g), tau), (-p, -tau), (_among_many(-p, g), -tau)):      # and among negative entries
+        _run_both(q, k)
+        _run_both(q, k, mode=sf.PRUNE_THRESHOLD, tau=t)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
@@ -74,23 +88,23 @@ def test_signs_zeros_and_ties(cols, k, dtype):
     p[90:100, 3] = float("inf")
     p[100:110, 4] = float("-inf")
     p = p.to(dtype)
-    _run_both(p, k)
-    _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=0.0)
-    _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=-0.0)
-    _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=-0.75)
-    _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=0.5)
+    for q in (p, _among_many(p, g)) if dtype == torch.float32 and cols >= 128 else (p,):
+        _run_both(q, k)
+        for tau in (0.0, -0.0, -0.75, 0.5):
+            _run_both(q, k, mode=sf.PRUNE_THRESHOLD, tau=tau)
 
 
 def test_misaligned_rows_take_the_other_kernel_and_agree():
     require_gpu()
     g = torch.Generator(device="cuda").manual_seed(5)
-    base = torch.softmax(torch.randn(77, 197, generator=g, device="cuda"), dim=-1)
-    flat = torch.empty(77 * 197 + 1, device="cuda")
+    rows = ENOUGH + 77
+    base = torch.softmax(torch.randn(rows, 197, generator=g, device="cuda"), dim=-1)
+    flat = torch.empty(rows * 197 + 1, device="cuda")
     flat[1:] = base.reshape(-1)
-    p = flat[1:].view(77, 197)
+    p = flat[1:].view(rows, 197)
     assert p.data_ptr() % 16 != 0
-    vals = torch.empty(77, 9, device="cuda")
-    idx = torch.empty(77, 9, dtype=torch.uint16, device="cuda")
+    vals = torch.empty(rows, 9, device="cuda")
+    idx = torch.empty(rows, 9, dtype=torch.uint16, device="cuda")
     vals2, idx2 = torch.empty_like(vals), torch.empty_like(idx)
     sf.prune_scores(p, 9, sf.PRUNE_TOPK, 0.0, vals, idx, None)
     sf.prune_scores(base, 9, sf.PRUNE_TOPK, 0.0, vals2, idx2, None)

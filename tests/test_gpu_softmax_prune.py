@@ -79,7 +79,9 @@ def test_random_rows_ties_and_ranges(rows, cols, k, dtype):
                                          (31, 100, 6), (1037, 197, 9), (129, 3, 2), (70, 65, 4)])
 def test_short_rows_several_rows_a_wavefront(rows, cols, k, dtype):
     """Rows of at most 256 columns that keep few entries take the kernel that gives a wavefront 16 or 32 rows at
-    once: ragged row counts, logits of either sign, ties, and fp32 logits that only their lowest bits tell apart."""
+    once: ragged row counts, logits of either sign, ties, and fp32 logits that only their lowest bits tell apart.
+    From 128 columns on it takes them from 60 000 rows (fp32) or 20 000 (bf16), so there the rows are run alone and
+    among that many (multiples of 32: the remainder is the test's own); 256 columns always take the other kernel."""
     require_gpu()
     g = torch.Generator(device="cuda").manual_seed(rows * 7 + cols * 3 + k)
     l = torch.randn(rows, cols, generator=g, device="cuda") * 3
@@ -92,14 +94,18 @@ def test_short_rows_several_rows_a_wavefront(rows, cols, k, dtype):
         l[5] = -l[4]
         l[6] = l[6] + 300.0
     _run_both(l.to(dtype), k)
+    if 128 <= cols < 256:
+        more = torch.randn(60000 if dtype == torch.float32 else 20000, cols, generator=g, device="cuda") * 3
+        _run_both(torch.cat([l, more]).to(dtype), k)
 
 
 @pytest.mark.parametrize("cols,k", [(197, 12), (128, 16), (250, 13)])
 def test_short_bf16_rows_keep_up_to_sixteen(cols, k):
     require_gpu()
     g = torch.Generator(device="cuda").manual_seed(cols + k)
-    l = (torch.randn(200, cols, generator=g, device="cuda") * 0.5).to(torch.bfloat16)        # many tied logits
+    l = (torch.randn(20200, cols, generator=g, device="cuda") * 0.5).to(torch.bfloat16)      # many tied logits; enough rows
     _run_both(l, k)
+    _run_both(l[:200], k)
 
 
 def test_argument_errors():
