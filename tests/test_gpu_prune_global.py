@@ -256,7 +256,8 @@ def _sampled_vectors(n, epv):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("scale", [0.25, 4.0])
 def test_sample_that_misses_the_cut(dtype, scale):
-    """Every entry the sample sees is four times smaller (larger) than the rest: T lies above (below) the bracket."""
+    """Every entry the sample sees is four times smaller (larger) than the rest: T lies above (below) the bracket, and
+    the plain route is taken (word 6 of the workspace), or the sample is no longer where this test thinks it is."""
     require_gpu()
     g = torch.Generator(device="cuda").manual_seed(41)
     epv = 4 if dtype == torch.float32 else 8
@@ -266,8 +267,10 @@ def test_sample_that_misses_the_cut(dtype, scale):
     x[at] *= scale
     x = x.to(dtype)
     for k in (n // 10, n // 2):
-        _run_both(x, k, True, restore=False)
-        _run_both(x, k, False, restore=False)
+        for by_mag in (True, False):
+            ws = Guarded(sf.prune_global_workspace(n), torch.uint8)
+            _run_both(x, k, by_mag, restore=False, workspace=ws)
+            assert int(ws.t[24:28].view(torch.int32)) == 1, (k, by_mag)
 
 
 def _least_workspace(n):
