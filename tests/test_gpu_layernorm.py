@@ -265,10 +265,10 @@ def test_param_grads_slab_counts(rows, H, slabs, dtype):
     dg.check(); db.check()
     if ws:
         ws.check()
-    # 2 roundings of x~, one product, at most 64 + 4 additions: under 4.3e-6 of the absolute sums, seen 1e-7
+    # the header's bound on the sums (2 roundings of x~, one product, at most 64 + 4 additions; seen 1e-7)
     want_g, want_b = (xt * dy.double()).sum(0), dy.double().sum(0)
-    assert bool(((dg.t.double() - want_g).abs() <= 4.3e-6 * (xt * dy.double()).abs().sum(0)).all())
-    assert bool(((db.t.double() - want_b).abs() <= 4.3e-6 * dy.double().abs().sum(0)).all())
+    assert bool(((dg.t.double() - want_g).abs() <= 4e-6 * (xt * dy.double()).abs().sum(0)).all())
+    assert bool(((db.t.double() - want_b).abs() <= 4e-6 * dy.double().abs().sum(0)).all())
     too_small = torch.empty(least * 2 * H * 4 - 4, dtype=torch.uint8, device="cuda")
     with pytest.raises(sf.SlimfitError) as e:
         sf.layernorm_param_grads(x, mean, rstd, dy, dg.t, db.t, too_small)
