@@ -46,11 +46,13 @@ KERNELS = {
 }
 
 
-# bench.py's extras -> (kernels of one call, the kernel that runs once per call)
+# bench.py's extras -> (kernels of one call, the kernel that runs once per call).  The whole-tensor pruner's bracket and
+# clear kernels, which are the same for its plain and its standardised form, are left out: they read at most 128 KB.
+_GLOBAL = r"(sample|top_digit|sweep|digit|second_digit|count|write|dense_write|plain_write)_kernel"
 EXTRAS = {
     "restore_scores": (r"restore_tile_kernel", r"restore_tile_kernel"),
     "quant_pack[scores, fixed 4.4]": (r"quant_pack_kernel<\w+, 8, false", r"quant_pack_kernel<\w+, 8, false"),
-    "prune_global[ln_in, 10%]": (r"(hist|bracket|count|write)_kernel<\w+, true, false", r"write_kernel<\w+, true, false"),
+    "prune_global[ln_in, 10%]": (_GLOBAL + r"<\w+, true, false", r"sweep_kernel<\w+, true, false"),
     "restore_global[ln_in, tile pointers]": (r"restore_tiles_kernel", r"restore_tiles_kernel"),
     "restore_global[ln_in, zeros+scatter]": (r"(zero|scatter)_kernel", r"scatter_kernel"),
     "gelu_quant_pack[gelu_in]": (r"quant_pack_kernel<[^>]*, true>", r"quant_pack_kernel<[^>]*, true>"),
@@ -58,7 +60,7 @@ EXTRAS = {
     "softmax_prune[scores as logits]": (r"prune_rows_kernel<\w+, \d+, \w+, \w+, true>", r"prune_rows_kernel<\w+, \d+, \w+, \w+, true>"),
     "softmax_backward_pruned[scores]": (r"softmax_backward_(tile|small)_kernel", r"softmax_backward_(tile|small)_kernel"),
     "layernorm_forward[ln_in]": (r"layernorm_forward_kernel", r"layernorm_forward_kernel"),
-    "prune_global_standardized[ln_in, 10%]": (r"(hist|bracket|count|write)_kernel<\w+, true, true", r"write_kernel<\w+, true, true"),
+    "prune_global_standardized[ln_in, 10%]": (_GLOBAL + r"<\w+, true, true", r"sweep_kernel<\w+, true, true"),
     "layernorm_backward_pruned[ln_in]": (r"layernorm_backward_pruned_kernel", r"layernorm_backward_pruned_kernel"),
     "layernorm_forward_quant_pack[ln_in]": (r"layernorm_forward_quant_kernel", r"layernorm_forward_quant_kernel"),
     "layernorm_backward_dequant[ln_in]": (r"layernorm_backward_dequant_kernel", r"layernorm_backward_dequant_kernel"),
@@ -96,7 +98,9 @@ def summarise_extras(root):
         if f is None or w is None:
             continue
         fb, wb = f * fs * 1024.0, w * wsc * 1024.0
-        lines.append("  %-46s fetched %.1f MB + written %.1f MB = %.1f MB (mean of %d calls)" % (name, fb / 1e6, wb / 1e6, (fb + wb) / 1e6, calls))
+        seen = sorted({m.group(1) for r in fetch if re.search(pat_all, r["Kernel_Name"]) for m in [re.search(r"(\w+_kernel)\b", r["Kernel_Name"])] if m})
+        lines.append("  %-46s fetched %.1f MB + written %.1f MB = %.1f MB (mean of %d calls; kernels: %s)"
+                     % (name, fb / 1e6, wb / 1e6, (fb + wb) / 1e6, calls, ", ".join(seen)))
         data.append("DATA config=-1 kernel=%s fetch_bytes=%.6g write_bytes=%.6g launches=%d" % (name.replace(" ", "_"), fb, wb, calls))
     lines.append("")
     return lines, data

@@ -1,7 +1,9 @@
 """The counter summariser on a hand-made rocprofv3 folder: per-row instruction counts, byte counters scaled by the
 copy calibration, and the DATA lines bench.py reads."""
 import csv
+import glob
 import os
+import re
 
 from paper_2305_18513_amd import profile_counters as pc
 from paper_2305_18513_amd import synth
@@ -62,3 +64,32 @@ def test_bench_reads_the_tracked_summary():
     bound, t_issue = bench.classify_bound(0.247, 1387266048, cnt)
     assert bound in ("issue", "hbm") and t_issue is not None
     assert bench.classify_bound(0.01, 1 << 20, {})[0] == "launch"
+
+
+def _kernels_of_the_library():
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    found = set()
+    for path in glob.glob(os.path.join(root, "paper_2305_18513_amd", "csrc", "*.hip")):
+        with open(path) as fh:
+            found.update(re.findall(r"\b(\w+_kernel)\(", fh.read()))
+    return found
+
+
+def test_the_summary_names_kernels_that_exist():
+    """The patterns of the summariser, and the operations of the tracked summary: counters of a kernel that is no
+    longer there would be divided by the times of what replaced it."""
+    known = _kernels_of_the_library()
+    for pats in list(pc.EXTRAS.values()) + [(p,) for p in pc.KERNELS.values()]:
+        for pat in pats:
+            parts = re.split(r"\(([a-z_|]+)\)(\??)", pat.split("<")[0])          # text, alternatives, "?", text, ...
+            names = [parts[0]]
+            for alts, optional, text in zip(parts[1::3], parts[2::3], parts[3::3]):
+                names = [n + a + text for n in names for a in alts.split("|") + ([""] if optional else [])]
+            assert set(names) <= known, (pat, names)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    with open(os.path.join(root, "profiles", "kernel_counters.txt")) as fh:
+        found = [line for line in fh if " calls" in line and " fetched " in line]
+    assert len(found) == len(pc.EXTRAS)
+    for line in found:
+        names = re.search(r"kernels: ([\w, ]+)\)", line)
+        assert names and set(names.group(1).split(", ")) <= known, line
