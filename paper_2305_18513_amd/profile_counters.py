@@ -69,16 +69,22 @@ EXTRAS = {
 
 
 def _per_call(rows, counter, pat_all, pat_once):
-    """Sum of the counter over a call's kernels, averaged over the calls of the run."""
-    total, calls = 0.0, 0
+    """The counter over the kernels of one call of the largest size, and the number of such calls.  The run also holds
+    the same operation on smaller tensors (the frozen encoder block's): of each kernel only the launches with the
+    largest grid count."""
+    by_kernel = collections.defaultdict(lambda: collections.defaultdict(list))
     for r in rows:
-        if r.get("Counter_Name") != counter:
-            continue
-        if re.search(pat_all, r["Kernel_Name"]):
-            total += float(r["Counter_Value"])
-        if re.search(pat_once, r["Kernel_Name"]):
-            calls += 1
-    return (total / calls, calls) if calls else (None, 0)
+        if r.get("Counter_Name") == counter and re.search(pat_all, r["Kernel_Name"]):
+            by_kernel[r["Kernel_Name"]][int(r.get("Grid_Size", 0) or 0)].append(float(r["Counter_Value"]))
+    once = [g for name, g in by_kernel.items() if re.search(pat_once, name)]
+    if not once:
+        return None, 0
+    launched = sum(len(v) for g in once for v in g.values())
+    total = 0.0
+    for g in by_kernel.values():
+        largest = g[max(g)]
+        total += sum(largest) / len(largest) * sum(len(v) for v in g.values()) / launched
+    return total, sum(len(g[max(g)]) for g in once)
 
 
 def summarise_extras(root):

@@ -66,6 +66,15 @@ def test_bench_reads_the_tracked_summary():
     assert bench.classify_bound(0.01, 1 << 20, {})[0] == "launch"
 
 
+def test_an_operation_is_counted_at_its_largest_size():
+    """Two kernels a call, three full-size calls and one of a quarter, whose first kernel has the same grid in both."""
+    rows = [dict(Kernel_Name="void a_kernel<float>", Grid_Size="64", Counter_Name="FETCH_SIZE", Counter_Value=v) for v in (8, 8, 8, 8)]
+    rows += [dict(Kernel_Name="void b_kernel<float>", Grid_Size=g, Counter_Name="FETCH_SIZE", Counter_Value=v)
+             for g, v in (("400", 100), ("100", 25), ("400", 104), ("400", 102))]
+    total, calls = pc._per_call(rows, "FETCH_SIZE", r"(a|b)_kernel", r"b_kernel")
+    assert calls == 3 and abs(total - 110.0) < 1e-9
+
+
 def _kernels_of_the_library():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     found = set()
