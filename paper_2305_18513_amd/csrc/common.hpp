@@ -67,7 +67,8 @@ constexpr int kDppMirror = 0x140;     // lane i <-> 15-i inside each 16
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+    // every source lane exists, so `old` is never seen; bound_ctrl lets the move fold into the instruction that uses it
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v)
@@ -75,30 +76,22 @@ __device__ __forceinline__ float dpp_f32(float v)
     return __builtin_bit_cast(float, dpp_u32<CTRL>(__builtin_bit_cast(uint32_t, v)));
 }
 
-// max over groups of G consecutive lanes (G = 4..64, power of two); every lane
-// of a group receives the group's result.
-template <int G>
-__device__ __forceinline__ float group_max_f32(float v)
+// max over groups of G consecutive lanes (G = 4 .. 64, a power of two; it need not be a constant, but is wave-uniform);
+// every lane of a group receives the group's result.
+__device__ __forceinline__ uint32_t group_max_u32(uint32_t v, int G)
 {
-    static_assert(G == 4 || G == 8 || G == 16 || G == 32 || G == 64, "group size");
-    v = fmaxf(v, dpp_f32<kDppXor1>(v));
-    v = fmaxf(v, dpp_f32<kDppXor2>(v));
-    if (G >= 8) v = fmaxf(v, dpp_f32<kDppHalfMirror>(v));
-    if (G >= 16) v = fmaxf(v, dpp_f32<kDppMirror>(v));
-    if (G >= 32) v = fmaxf(v, __shfl_xor(v, 16, kWave));
-    if (G >= 64) v = fmaxf(v, __shfl_xor(v, 32, kWave));
-    return v;
-}
-
-// the same with the group size a wave-uniform run-time value (4, 8, 16, 32 or 64)
-__device__ __forceinline__ float group_max_f32_dyn(float v, int G)
-{
-    v = fmaxf(v, dpp_f32<kDppXor1>(v));
-    v = fmaxf(v, dpp_f32<kDppXor2>(v));
-    if (G >= 8) v = fmaxf(v, dpp_f32<kDppHalfMirror>(v));
-    if (G >= 16) v = fmaxf(v, dpp_f32<kDppMirror>(v));
-    if (G >= 32) v = fmaxf(v, __shfl_xor(v, 16, kWave));
-    if (G >= 64) v = fmaxf(v, __shfl_xor(v, 32, kWave));
+    v = max(v, dpp_u32<kDppXor1>(v));
+    v = max(v, dpp_u32<kDppXor2>(v));
+    if (G >= 8) v = max(v, dpp_u32<kDppHalfMirror>(v));
+    if (G >= 16) v = max(v, dpp_u32<kDppMirror>(v));
+    if (G >= 32) {                                          // exchanges rows of 16 lanes, then halves of the wave
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = max(r[0], r[1]);
+    }
+    if (G >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = max(r[0], r[1]);
+    }
     return v;
 }
 
@@ -106,26 +99,66 @@ __device__ __forceinline__ float group_max_f32_dyn(float v, int G)
 // -- one fp32 multiply -- where mult = qmax / a and the stored scale = a / qmax for a
 // block whose largest magnitude is a (two IEEE fp32 divisions); a block of zeros, or one
 // whose multiplier would overflow, gets scale 0 and codes 0.
+//
+// The code is left in the low BITS bits of the result (two's complement), whatever is above them: clamping to whole
+// numbers commutes with rounding, and adding 1.5 * 2^23 rounds to a whole number (half to even) in the low mantissa bits.
+constexpr uint32_t kRoundBits = 0x4B400000u;               // 1.5 * 2^23
 template <int BITS>
-__device__ __forceinline__ int quantise_one(float x, float mult)
+__device__ __forceinline__ uint32_t quantise_one(float x, float mult)
 {
     constexpr float qmax = (float)((1 << (BITS - 1)) - 1);
     constexpr float qmin = -(float)(1 << (BITS - 1));
-    float r = __builtin_rintf(x * mult);
-    r = fminf(fmaxf(r, qmin), qmax);
-    return (int)r;
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(x * mult, qmin, qmax) + __builtin_bit_cast(float, kRoundBits));
+}
+// the E codes of a vector, element i in bits [i*BITS, (i+1)*BITS) of the 64-bit result (two words)
+template <int BITS, int E>
+__device__ __forceinline__ void pack_codes(const float (&f)[E], float mult, uint32_t (&w)[2])
+{
+    static_assert(E == 4 || E == 8, "a 16-byte vector");
+    uint32_t b[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) b[i] = quantise_one<BITS>(f[i], mult);
+    w[0] = w[1] = 0u;
+    if constexpr (BITS == 8) {
+#pragma unroll
+        for (int i = 0; i < E; i += 4)                      // the low bytes of four words
+            w[i / 4] = __builtin_amdgcn_perm(b[i + 1], b[i], 0x0C0C0400u) | __builtin_amdgcn_perm(b[i + 3], b[i + 2], 0x04000C0Cu);
+    } else {
+        // sum of (kRoundBits + c_i) 16^i, the kRoundBits' share taken out; with 8 added to every c_i the fields borrow
+        // nothing from one another, and flipping their top bits takes the 8 away again
+        constexpr uint32_t ones = E == 4 ? 0x1111u : 0x11111111u;
+        uint32_t v = b[E - 1];
+#pragma unroll
+        for (int i = E - 2; i >= 0; --i) v = (v << 4) + b[i];
+        v = (v + (8u - kRoundBits) * ones) ^ (8u * ones);
+        w[0] = E == 4 ? v & 0xFFFFu : v;
+    }
 }
 template <int BITS>
-__device__ __forceinline__ void block_scale(float a, float &mult, float &scale)
+__device__ __forceinline__ void block_scale(float a, float &mult, float &scale)       // a >= 0, not NaN
 {
     constexpr float qmax = (float)((1 << (BITS - 1)) - 1);
-    mult = 0.0f;
-    scale = 0.0f;
-    if (a > 0.0f) {
-        mult = qmax / a;
-        if (__builtin_isinf(mult)) mult = 0.0f;
-        else scale = a / qmax;
-    }
+    const float m = qmax / a, s = a / qmax;
+    const bool ok = !__builtin_isinf(m);                   // a of 0 as well
+    mult = ok ? m : 0.0f;
+    scale = ok ? s : 0.0f;
+}
+// The same for N <= 4 blocks whose maxima all lanes of a quad hold: lane l of the quad does the divisions of block l and
+// the quad exchanges the multipliers; `scale` is that of block (lane & 3), meant for lanes with (lane & 3) < N.  (Every
+// lane's divisions for every block were a quarter of the quantiser's instructions.)
+template <int BITS, int N>
+__device__ __forceinline__ void quad_scales(const uint32_t (&a)[N], int lane, float (&mult)[N], float &scale)
+{
+    static_assert(N >= 1 && N <= 4, "a quad");
+    const uint32_t a0 = a[0], a1 = a[N >= 2 ? 1 : 0], a2 = a[N >= 3 ? 2 : 0], a3 = a[N - 1];
+    const uint32_t low = (lane & 1) ? a1 : a0, high = (lane & 1) ? a3 : a2;
+    const uint32_t mine = N >= 3 && (lane & 2) ? high : low;
+    float m;
+    block_scale<BITS>(__builtin_bit_cast(float, mine), m, scale);
+    mult[0] = dpp_f32<0x00>(m);                            // quad_perm: lane 0's to all four, and so on
+    if constexpr (N >= 2) mult[1] = dpp_f32<0x55>(m);
+    if constexpr (N >= 3) mult[2] = dpp_f32<0xAA>(m);
+    if constexpr (N >= 4) mult[3] = dpp_f32<0xFF>(m);
 }
 // field i of BITS bits of a packed word, sign-extended
 template <int BITS>

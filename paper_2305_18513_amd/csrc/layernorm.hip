@@ -384,18 +384,6 @@ layernorm_backward_kernel(const T *__restrict__ x, const float *__restrict__ mea
 // and the codes are those of the flat quantiser.
 // Backward: x^ = code * scale is rebuilt in registers and goes straight into the dense
 // input-gradient formula; it is never stored.
-// the E codes of a vector, element i in bits [i*BITS, (i+1)*BITS) of the 64-bit result (two words)
-template <int BITS, int E>
-__device__ __forceinline__ void pack_codes(const float (&f)[E], float mult, uint32_t (&w)[2])
-{
-    w[0] = w[1] = 0u;
-#pragma unroll
-    for (int i = 0; i < E; ++i) {
-        const uint32_t c = (uint32_t)quantise_one<BITS>(f[i], mult) & ((1u << BITS) - 1u);
-        w[(i * BITS) / 32] |= c << ((i * BITS) % 32);
-    }
-}
-
 template <typename T, int NV, int BITS>
 __global__ void __launch_bounds__(kThreads)
 layernorm_forward_quant_kernel(const T *__restrict__ x, const float *__restrict__ gamma,
@@ -415,25 +403,35 @@ layernorm_forward_quant_kernel(const T *__restrict__ x, const float *__restrict_
     load_params<E, NV>(gamma, nvec, lane, ga);
     load_params<E, NV>(beta, nvec, lane, be);
 
-    // the cache: codes and scales of this row's blocks (writing it after y instead makes no measurable difference)
+    // the cache: codes and scales of this row's blocks (writing it after y instead makes no measurable difference),
+    // up to four vectors at a time
+    constexpr int N = NV < 4 ? NV : 4;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int q = i * kWave + lane;
-        float a = 0.0f;
+    for (int i0 = 0; i0 < NV; i0 += N) {
+        uint32_t a[N];
 #pragma unroll
-        for (int e = 0; e < E; ++e) a = fmaxf(a, fabsf(v[i][e]));
-        a = group_max_f32_dyn(a, G);
-        float mult, scale;
-        block_scale<BITS>(a, mult, scale);
-        if (q < nvec) {
-            const int64_t el = e0 + (int64_t)q * E;
-            if ((lane & (G - 1)) == 0) scales[el >> block_shift] = scale;
-            uint32_t w[2];
-            pack_codes<BITS, E>(v[i], mult, w);
-            uint8_t *dst = codes + (el * BITS) / 8;
-            if (OUT_BYTES == 2) __builtin_nontemporal_store((uint16_t)w[0], reinterpret_cast<uint16_t *>(dst));
-            else if (OUT_BYTES == 4) __builtin_nontemporal_store(w[0], reinterpret_cast<uint32_t *>(dst));
-            else __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2 *>(dst));
+        for (int u = 0; u < N; ++u) {
+            float m = 0.0f;
+#pragma unroll
+            for (int e = 0; e < E; ++e) m = fmaxf(m, fabsf(v[i0 + u][e]));
+            a[u] = group_max_u32(__builtin_bit_cast(uint32_t, m), G);
+        }
+        float mult[N], scale;
+        quad_scales<BITS, N>(a, lane, mult, scale);
+        const int own = lane & (G - 1), q_own = (i0 + own) * kWave + lane;     // lanes 0 .. N - 1 of a group store a block's scale each
+        if (own < N && q_own < nvec) scales[(e0 + (int64_t)q_own * E) >> block_shift] = scale;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int q = (i0 + u) * kWave + lane;
+            if (q < nvec) {
+                const int64_t el = e0 + (int64_t)q * E;
+                uint32_t w[2];
+                pack_codes<BITS, E>(v[i0 + u], mult[u], w);
+                uint8_t *dst = codes + (el * BITS) / 8;
+                if (OUT_BYTES == 2) __builtin_nontemporal_store((uint16_t)w[0], reinterpret_cast<uint16_t *>(dst));
+                else if (OUT_BYTES == 4) __builtin_nontemporal_store(w[0], reinterpret_cast<uint32_t *>(dst));
+                else __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2 *>(dst));
+            }
         }
     }
 

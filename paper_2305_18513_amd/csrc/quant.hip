@@ -9,6 +9,16 @@
 // pass over the data.  A workgroup covers kUnroll such steps so that each lane
 // has kUnroll independent 128-bit loads in flight.
 //
+// What bounds the quantiser: HBM on large tensors, the vector pipe on those of a
+// few MB.  With the two divisions of a block done by one lane of a quad for each
+// of the lane's blocks, codes rounded and packed without conversions, and the
+// butterfly on integer images (its lane moves fold into the maxima), a wave
+// issues 40 vector instructions a 16-byte vector against 80, and two vectors a
+// lane (128 threads) stream better than four (256): 201.3 M fp32 143 -> 139.5 us
+// (6.6 TB/s), 12.6 M 10.8 -> 9.9, 12.6 M bf16 7.7 -> 6.4, with GELU 77.5 M fp32
+// 116 -> 112 (5.9 TB/s), 12.6 M 20.2 -> 18.3.  Four vectors with the same code
+// 148, one 157 (201.3 M); 256 threads the same within 1 %, but GELU 12.6 M 19.0.
+//
 // Producer fusion: the same tiles can also carry the GELU whose input is being
 // cached.  Forward, the lane that holds x for the quantiser also writes
 // GELU(x), so the activation is read once for both; backward, the dequantised
@@ -22,7 +32,7 @@ namespace {
 // Tunables (compile-time): vectors per lane in the two kernels, and whether
 // the bulk streams bypass the caches' retention (each byte is touched once).
 #ifndef SLIMFIT_QUANT_UNROLL
-#define SLIMFIT_QUANT_UNROLL 4
+#define SLIMFIT_QUANT_UNROLL 2
 #endif
 #ifndef SLIMFIT_DEQUANT_UNROLL
 #define SLIMFIT_DEQUANT_UNROLL 2
@@ -32,14 +42,14 @@ namespace {
 #endif
 
 #ifndef SLIMFIT_QUANT_THREADS
-#define SLIMFIT_QUANT_THREADS 256
+#define SLIMFIT_QUANT_THREADS 128
 #endif
 #ifndef SLIMFIT_DEQUANT_THREADS
 #define SLIMFIT_DEQUANT_THREADS 512
 #endif
 constexpr int kThreads = SLIMFIT_QUANT_THREADS;      // quantiser workgroup
 constexpr int kThreadsD = SLIMFIT_DEQUANT_THREADS;   // dequantiser workgroup
-constexpr int kUnrollQ = SLIMFIT_QUANT_UNROLL;
+constexpr int kUnrollQ = SLIMFIT_QUANT_UNROLL;      // at most 4: a quad of lanes shares their blocks' divisions
 constexpr int kUnrollD = SLIMFIT_DEQUANT_UNROLL;
 constexpr bool kNT = SLIMFIT_QUANT_NT != 0;
 
@@ -154,27 +164,32 @@ __device__ __forceinline__ void quant_tile(const T *__restrict__ x, int64_t n, f
         }
     }
 
+    float mult[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) mult[u] = fixed_mult;
+    if constexpr (BLOCKED) {
+        uint32_t a[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            float m = 0.0f;
+#pragma unroll
+            for (int i = 0; i < V; ++i) m = fmaxf(m, fabsf(f[u][i]));
+            a[u] = group_max_u32(__builtin_bit_cast(uint32_t, m), G);       // all lanes take part (no divergence above)
+        }
+        float scale;
+        quad_scales<BITS, kUnroll>(a, (int)threadIdx.x, mult, scale);
+        const int own = threadIdx.x & (G - 1);             // lanes 0 .. kUnroll - 1 of a group store a block's scale each
+        const int64_t e_own = (first_vec + (int64_t)own * kThreads) * V;
+        if (own < kUnroll && (INSIDE || e_own - own * V < n)) scales[e_own / (V * G)] = scale;
+    }
+
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         const int64_t e0 = (first_vec + (int64_t)u * kThreads) * V;
-        float mult = fixed_mult;
-        if (BLOCKED) {
-            float a = 0.0f;
-#pragma unroll
-            for (int i = 0; i < V; ++i) a = fmaxf(a, fabsf(f[u][i]));
-            a = group_max_f32<G>(a);                   // all lanes take part (no divergence above)
-            float scale;
-            block_scale<BITS>(a, mult, scale);
-            if ((threadIdx.x & (G - 1)) == 0 && (INSIDE || e0 < n)) scales[e0 / (V * G)] = scale;
-        }
         if (!INSIDE && e0 >= n) continue;
 
-        uint32_t w[2] = {0u, 0u};
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
-            const uint32_t c = (uint32_t)quantise_one<BITS>(f[u][i], mult) & ((1u << BITS) - 1u);
-            w[(i * BITS) / 32] |= c << ((i * BITS) % 32);
-        }
+        uint32_t w[2];
+        pack_codes<BITS, V>(f[u], mult[u], w);
         uint8_t *dst = codes + (e0 * BITS) / 8;
         if (INSIDE || e0 + V <= n) {
             if (OUT_BYTES == 2) store_global<kNT>(reinterpret_cast<uint16_t *>(dst), (uint16_t)w[0]);

@@ -150,3 +150,38 @@ def test_pointer_checks_reject_host_memory_and_short_buffers():
     assert rc == sf.ERR_POINTER
     sf.quant_pack(x, sf.Q_BLOCK, 4, 64, 0, codes, scales)      # still usable afterwards
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits,block", [(4, 32), (8, 64), (4, 128), (8, 256)])
+def test_whole_and_partial_tiles_with_infinities_and_nan(dtype, bits, block):
+    """Sizes around a workgroup's tile (1024 fp32 or 2048 bf16 elements), where the straight-line and the guarded path
+    meet, with entries that are no numbers: a block's maximum passes NaN over, a NaN product takes the lowest code."""
+    require_gpu()
+    tile = 1024 if dtype == torch.float32 else 2048
+    g = torch.Generator(device="cuda").manual_seed(bits * 100 + block)
+    for n in (tile - 1, tile, tile + 1, 2 * tile - block, 3 * tile + block // 2):
+        x = torch.randn(n, generator=g, device="cuda").to(dtype)
+        _run_both(x, sf.Q_BLOCK, bits, block, 0)
+        x[5], x[block + 3], x[block + 4], x[n - 1] = float("nan"), float("inf"), float("-inf"), float("nan")
+        codes = Guarded(sf.packed_bytes(n, bits), torch.uint8)
+        scales = Guarded(sf.num_blocks(n, block), torch.float32)
+        sf.quant_pack(x, sf.Q_BLOCK, bits, block, 0, codes.t, scales.t)
+        torch.cuda.synchronize()
+        codes.check(); scales.check()
+        rows = -(-n // block)
+        xb = np.zeros(rows * block, dtype=np.float32)
+        xb[:n] = x.float().cpu().numpy()
+        xb = xb.reshape(rows, block)
+        qmax, qmin = np.float32(2 ** (bits - 1) - 1), np.float32(-(2 ** (bits - 1)))
+        with np.errstate(all="ignore"):
+            a = np.fmax.reduce(np.abs(xb), axis=1)
+            mult = qmax / a
+            want_scale = np.where(np.isinf(mult), np.float32(0), a / qmax)
+            prod = xb * np.where(np.isinf(mult), np.float32(0), mult)[:, None]
+            want = np.where(np.isnan(prod), qmin, np.clip(np.rint(prod), qmin, qmax)).astype(np.int64).reshape(-1)[:n]
+        np.testing.assert_array_equal(to_np(scales.t).view(np.uint32), want_scale.astype(np.float32).view(np.uint32))
+        got = to_np(codes.t)
+        if bits == 4:
+            got = np.stack([got & 15, got >> 4], 1).reshape(-1)[:n]
+        np.testing.assert_array_equal(got, want & (2 ** bits - 1))
