@@ -5,7 +5,7 @@
 // With 197-column rows a wave that owns one row at a time spends most of its
 // instructions on per-row bookkeeping (wave reductions, a bin scan, scalar
 // popcounts) that does not shrink with the row.  Here nothing is done per row by
-// a whole wave.  G lanes (2 or 4) share a row, so a wave works on R = 64 / G
+// a whole wave.  G lanes (2 or 4; 4 or 8 of wide softmax rows) share a row, so a wave works on R = 64 / G
 // consecutive rows at once, and every lane owns one contiguous segment of its
 // row (E = ceil(cols / G) entries):
 //
@@ -101,9 +101,14 @@ __device__ __forceinline__ void merge_row(int (&m)[CH])
 #pragma unroll
     for (int i = 0; i < CH; ++i) b[i] = (int)dpp_u32<kDppXor1>((uint32_t)m[i]);
     chain_merge<CH>(m, b);
-    if constexpr (G == 4) {
+    if constexpr (G >= 4) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) b[i] = (int)dpp_u32<kDppXor2>((uint32_t)m[i]);
+        chain_merge<CH>(m, b);
+    }
+    if constexpr (G >= 8) {                                // (the lanes of a quad hold the same list by now)
+#pragma unroll
+        for (int i = 0; i < CH; ++i) b[i] = (int)dpp_u32<kDppHalfMirror>((uint32_t)m[i]);
         chain_merge<CH>(m, b);
     }
 }
@@ -157,7 +162,8 @@ struct ShortRows {
     static constexpr bool BF = sizeof(T) == 2;
     static constexpr int R = kWave / G;
     static constexpr int CHP = BF ? K : K + 1;                 // list length: fp32 also wants the (k+1)-th largest
-    static constexpr int TAG_BITS = BF ? 7 : 6;                // entry's rank inside the lane's segment
+    static constexpr int LANE_BITS = G == 2 ? 1 : (G == 4 ? 2 : 3);
+    static constexpr int TAG_BITS = 8 - LANE_BITS;             // entry's rank inside the lane's segment (at most 256 columns)
     static constexpr int N_OUT = (R * K + kWave - 1) / kWave;  // output pairs a lane stores
 
     // Visits the lane's entries e = 0 .. E-1 in column order: f(e, bits, ok) with the entry's bits (fp32: its
@@ -213,15 +219,14 @@ struct ShortRows {
     // the positive entries correctly and puts everything else (zeros of either sign, negative values in reversed
     // order) below them: enough whenever every kept entry is positive.  The plain pass notices when that fails for
     // one of the wave's rows and returns false before it has written anything; the caller then runs the signed pass.
-    // between(): called once, after the kept columns are staged and before the kept values are fetched from the
-    // staged rows (FROM_ROWS: always from there); the fused softmax rewrites the rows in between.
-    struct Nothing {
-        __device__ void operator()() const {}
+    // Held: entries that are in registers already: each_held(f) visits the lane's as f(e, bits), those that it does not
+    // have as -inf (below every kept entry of a plain pass).  The kept columns are left in oc, kept is the row's count.
+    struct NotHeld {
+        static constexpr bool HELD = false;
     };
-    template <bool NEG, bool FROM_ROWS = false, typename Between = Nothing>
-    static __device__ bool run(const ShortArgs &a, const T *rows_lds, uint32_t *oc, int lane, int n_here, int64_t row0,
-                               T *__restrict__ vals, uint16_t *__restrict__ idx, int32_t *__restrict__ counts,
-                               Between between = Between())
+    template <bool NEG, typename Held>
+    static __device__ __forceinline__ bool select(const ShortArgs &a, const T *rows_lds, uint32_t *oc, int lane, int &kept,
+                                                  const Held &held)
     {
         const int cols = a.cols, k = a.k;
         const int r = lane / G, q = lane % G;
@@ -230,7 +235,7 @@ struct ShortRows {
         const int e_all = max(cols - (G - 1) * E, 0);      // the last lane's: the shortest segment
         const T *seg = rows_lds + r * cols + q * E;
         constexpr int TAG_TOP = (1 << TAG_BITS) - 1;
-        constexpr uint32_t COL_MASK = (1u << (TAG_BITS + 2)) - 1u;      // rank in the segment, lane of the row
+        constexpr uint32_t COL_MASK = (1u << (TAG_BITS + LANE_BITS)) - 1u;      // rank in the segment, lane of the row
 
         // ---- selection on keys that carry the column ---------------------------------
         int m[CHP];
@@ -238,10 +243,16 @@ struct ShortRows {
         for (int i = 0; i < CHP; ++i) m[i] = INT_MIN;
         int value_mask = (int)~COL_MASK;
         asm("" : "+v"(value_mask));                        // in a register, not a literal at every use
-        for_each_entry<NEG>(seg, E, len, e_all, [&](int e, int bits, bool ok) {
+        // f(e, bits, ok) for the lane's entries, from registers if they are there
+        auto walk = [&](auto f) {
+            if constexpr (!NEG && Held::HELD) held.each_held([&](int e, int bits) { f(e, bits, true); });
+            else for_each_entry<NEG>(seg, E, len, e_all, f);
+        };
+        walk([&](int e, int bits, bool ok) {
             // the tag is wave-uniform: the earlier entry of the segment ranks higher
             int key;
             if constexpr (BF) key = (int)(((uint32_t)(NEG ? signed_key_16(bits) : bits) << 16) | (uint32_t)(TAG_TOP - e));
+            else if constexpr (!NEG && Held::HELD) key = (bits & value_mask) | (TAG_TOP - e);      // (e is a constant)
             else key = and_or_i32(NEG ? signed_key_f32((uint32_t)bits) : bits, value_mask, TAG_TOP - e);
             chain_insert<CHP>(m, ok ? key : INT_MIN);
         });
@@ -260,7 +271,7 @@ struct ShortRows {
             // all kept entries positive?  With k entries kept: the k-th largest is; with fewer (a threshold run): tau is.
             int cut_value = 0;
 #pragma unroll
-            for (int i = 0; i < K; ++i) cut_value = (i == k - 1) ? m[i] >> (BF ? 16 : TAG_BITS + 2) : cut_value;
+            for (int i = 0; i < K; ++i) cut_value = (i == k - 1) ? m[i] >> (BF ? 16 : TAG_BITS + LANE_BITS) : cut_value;
             const bool plain_ok = cut_value > 0 || (a.mode == SLIMFIT_PRUNE_THRESHOLD && a.tau > 0.0f);
             if (__builtin_amdgcn_ballot_w64(!plain_ok) != 0) return false;
         }
@@ -283,17 +294,17 @@ struct ShortRows {
             int cut_v = INT_MIN, next_v = INT_MIN;          // value bits of the k-th and the (k+1)-th largest
 #pragma unroll
             for (int i = 0; i < CHP; ++i) {
-                cut_v = (i == k - 1) ? m[i] >> (TAG_BITS + 2) : cut_v;
-                next_v = (i == k) ? m[i] >> (TAG_BITS + 2) : next_v;
+                cut_v = (i == k - 1) ? m[i] >> (TAG_BITS + LANE_BITS) : cut_v;
+                next_v = (i == k) ? m[i] >> (TAG_BITS + LANE_BITS) : next_v;
             }
             exact = cut_v == next_v;
             if (a.mode == SLIMFIT_PRUNE_THRESHOLD) {
-                const int tau_v = signed_key_f32(__builtin_bit_cast(uint32_t, a.tau)) >> (TAG_BITS + 2);
+                const int tau_v = signed_key_f32(__builtin_bit_cast(uint32_t, a.tau)) >> (TAG_BITS + LANE_BITS);
                 int n = 0;
                 bool unsure = false;
 #pragma unroll
                 for (int i = 0; i < K; ++i) {
-                    const int v = m[i] >> (TAG_BITS + 2);
+                    const int v = m[i] >> (TAG_BITS + LANE_BITS);
                     n += (i < k && v > tau_v) ? 1 : 0;
                     unsure = unsure || (i < k && v == tau_v);
                 }
@@ -321,8 +332,7 @@ struct ShortRows {
 #pragma unroll
                 for (int i = 0; i < CH; ++i) s[i] = INT_MIN;
                 auto full_key = [&](int bits) { return NEG ? signed_key_f32((uint32_t)bits) : bits; };
-                for_each_entry<NEG>(seg, E, len, e_all,
-                                    [&](int e, int bits, bool ok) { chain_insert<CH>(s, ok ? full_key(bits) : INT_MIN); });
+                walk([&](int e, int bits, bool ok) { chain_insert<CH>(s, ok ? full_key(bits) : INT_MIN); });
                 int mm[CH];
 #pragma unroll
                 for (int i = 0; i < CH; ++i) mm[i] = s[i];
@@ -354,14 +364,10 @@ struct ShortRows {
                     eq += s[i] == cut ? 1 : 0;
                 }
                 int gt_of[G], eq_of[G];                     // the same of every lane of the row
-                if constexpr (G == 4) {
-                    gt_of[0] = (int)dpp_u32<0x00>((uint32_t)gt); gt_of[1] = (int)dpp_u32<0x55>((uint32_t)gt);
-                    gt_of[2] = (int)dpp_u32<0xAA>((uint32_t)gt); gt_of[3] = (int)dpp_u32<0xFF>((uint32_t)gt);
-                    eq_of[0] = (int)dpp_u32<0x00>((uint32_t)eq); eq_of[1] = (int)dpp_u32<0x55>((uint32_t)eq);
-                    eq_of[2] = (int)dpp_u32<0xAA>((uint32_t)eq); eq_of[3] = (int)dpp_u32<0xFF>((uint32_t)eq);
-                } else {
-                    gt_of[0] = (int)dpp_u32<0xA0>((uint32_t)gt); gt_of[1] = (int)dpp_u32<0xF5>((uint32_t)gt);
-                    eq_of[0] = (int)dpp_u32<0xA0>((uint32_t)eq); eq_of[1] = (int)dpp_u32<0xF5>((uint32_t)eq);
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    gt_of[g] = __shfl(gt, (lane & ~(G - 1)) + g, kWave);
+                    eq_of[g] = __shfl(eq, (lane & ~(G - 1)) + g, kWave);
                 }
                 int gt_all = 0;
 #pragma unroll
@@ -379,7 +385,7 @@ struct ShortRows {
                 uint32_t *out = orow + base;
                 const int col0 = q * E;
                 int seen = 0;
-                for_each_entry<NEG>(seg, E, len, e_all, [&](int e, int bits, bool ok) {
+                walk([&](int e, int bits, bool ok) {
                     const int key = full_key(bits);
                     const bool is_eq = ok && key == cut;
                     if ((ok && key > cut) || (is_eq && seen < take_eq)) *out++ = (uint32_t)(col0 + e) << 16;
@@ -388,13 +394,24 @@ struct ShortRows {
             }
         }
 
-        // ---- the wave's pairs in output order ----
+        kept = kk;
+        return true;
+    }
+    // LDS serves a wave's accesses in order
+    static __device__ __forceinline__ void settle()
+    {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        between();
+    }
+
+    // ---- the wave's pairs in output order; reread: the values come from the staged rows, not from oc ----
+    static __device__ __forceinline__ void write_pairs(const ShortArgs &a, const T *rows_lds, const uint32_t *oc, bool reread, int lane,
+                                                       int n_here, int64_t row0, int kept, T *__restrict__ vals,
+                                                       uint16_t *__restrict__ idx, int32_t *__restrict__ counts)
+    {
+        const int cols = a.cols, k = a.k;
         const int n_out = n_here * k;
-        constexpr bool REREAD = !BF || NEG || FROM_ROWS;    // values come from the staged rows again
         T *ov = vals + row0 * (int64_t)k;
         uint16_t *oi = idx + row0 * (int64_t)k;
         uint32_t w[N_OUT];
@@ -408,12 +425,10 @@ struct ShortRows {
         for (int it = 0; it < N_OUT; ++it) {
             const uint32_t t = (uint32_t)(it * kWave + lane);
             const uint32_t rl = min((t * a.div_magic) >> 16, (uint32_t)(R - 1));
-            v[it] = T(0);
-            if constexpr (REREAD) {
+            v[it] = (T)(w[it] & 0xFFFFu);                   // (0 of an unused slot)
+            if (!BF || reread) {                            // wave-uniform
                 const T x = rows_lds[rl * (uint32_t)cols + min(w[it] >> 16, (uint32_t)cols - 1u)];
-                if (w[it] != kNoPair) v[it] = x;
-            } else {
-                v[it] = (T)(w[it] & 0xFFFFu);
+                v[it] = w[it] != kNoPair ? x : T(0);
             }
         }
 #pragma unroll
@@ -424,8 +439,7 @@ struct ShortRows {
                 store_global<SLIMFIT_SHORT_NT_STORE != 0>(oi + t, (uint16_t)(w[it] >> 16));
             }
         }
-        if (counts && q == 0 && r < n_here) counts[row0 + r] = kk;
-        return true;
+        if (counts && lane % G == 0 && lane / G < n_here) counts[row0 + lane / G] = kept;
     }
 };
 
@@ -480,23 +494,130 @@ __global__ __launch_bounds__(kWave) void prune_rows_short_kernel(const T *__rest
     }
     // unused output slots read as "no pair"
     for (int t = lane; t < R * k; t += kWave) oc[t] = kNoPair;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    S::settle();
 
     const T *rows_lds = reinterpret_cast<const T *>(slab);
-    if (!S::template run<false>(a, rows_lds, oc, lane, n_here, row0, vals, idx, counts))
-        S::template run<true>(a, rows_lds, oc, lane, n_here, row0, vals, idx, counts);
+    int kept;
+    const typename S::NotHeld none;
+    const bool plain = S::template select<false>(a, rows_lds, oc, lane, kept, none);
+    if (!plain) S::template select<true>(a, rows_lds, oc, lane, kept, none);
+    S::settle();
+    S::write_pairs(a, rows_lds, oc, !plain, lane, n_here, row0, kept, vals, idx, counts);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
 // Row softmax and Alg. 5 in one pass over short rows of logits: the kept set is decided on the logits (which order
 // a row exactly as its probabilities do), the dense probabilities are written once, and the kept values are the
-// numbers the dense row holds.  The rows are staged and selected as above; before the kept values are fetched each
-// lane turns its part of its row into probabilities in place (row maximum and sum of exponentials by exchanges
-// between the row's G lanes; hardware exp2; four running sums a lane, so that no sum is longer than a quarter of
-// the lane's part; one IEEE division a row), and the wave's rows leave for `probs` as they came, as one contiguous
-// piece.
+// numbers the dense row holds.  The rows are staged as above; then every lane takes its part of its row into
+// registers (the LDS of the staged rows lets about 20 waves into a compute unit at 197 columns, so there are registers
+// enough for all of it), where selection, maximum, exponentials (hardware exp2), their sum (four running sums a lane, so that no
+// sum is longer than a quarter of the lane's part; exchanged between the row's G lanes) and the division by it (one IEEE
+// division a row) find it; the probabilities go back over the staged rows and leave for `probs` as one contiguous piece.
+// Bound by the waves' lifetime on few rows and by HBM on many: 87 468 x 197 fp32 37.2 us when selection, maximum,
+// exponentials and scaling each walked the staged rows, 34.2 from registers, 30.4 with eight lanes a row as well (4.7 TB/s);
+// 302 592 rows 100 -> 90 (5.3 TB/s); 806 912 x 197 bf16 202 -> 169 (3.9 TB/s, bound by the list insertion).
+template <typename T, int G, int K, int NV>
+struct HeldRows {
+    using S = ShortRows<T, G, K, NV>;
+    static constexpr bool BF = sizeof(T) == 2, HELD = true;
+    static constexpr int PER16 = 16 / (int)sizeof(T);
+    static constexpr int kMost = NV * kWave * 16 / (int)sizeof(T) / kWave, kBlk = 4;    // entries a lane may have
+    T *rows;                           // the staged rows (LDS)
+    T *seg;                            // the lane's part
+    T *out;                            // the wave's piece of the dense rows
+    int lane, n_elem, E, len, e_all;
+    float x[kMost];
+
+    __device__ __forceinline__ HeldRows(int cols, T *rows_, T *out_, int lane_, int n_elem_) : rows(rows_), out(out_), lane(lane_), n_elem(n_elem_)
+    {
+        const int r = lane / G, q = lane % G;
+        E = (cols + G - 1) / G;
+        len = min(max(cols - q * E, 0), E);
+        e_all = max(cols - (G - 1) * E, 0);                // entries every lane has
+        seg = rows + r * cols + q * E;
+        each_block([&](auto e0) {
+            // (a lane without some of a block's entries reads the next row's, or at most four entries past the rows)
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) x[e0 + u] = BF ? __builtin_bit_cast(float, (uint32_t)seg[e0 + u] << 16) : (float)seg[e0 + u];
+        });
+        each_block([&](auto e0) {
+            if (e0 + kBlk <= e_all) return;
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) x[e0 + u] = e0 + u < len ? x[e0 + u] : -__builtin_inff();
+        });
+    }
+    // f(first entry) for the blocks of kBlk entries that the widest lane has (unrolled as a pack: a loop this long would
+    // not be, and its registers would become memory)
+    template <typename F>
+    __device__ __forceinline__ void each_block(F f) const
+    {
+        static_for(std::make_integer_sequence<int, kMost / kBlk>{}, [&](auto i) {
+            if (i * kBlk < E) f(std::integral_constant<int, i * kBlk>{});          // wave-uniform
+        });
+    }
+    template <typename F>
+    __device__ __forceinline__ void each_held(F f) const
+    {
+        each_block([&](auto e0) {
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) f(e0 + u, (int)(__builtin_bit_cast(uint32_t, x[e0 + u]) >> (BF ? 16 : 0)));
+        });
+    }
+    __device__ __forceinline__ void to_probabilities()
+    {
+        constexpr float kLog2e = 1.44269504088896340736f;
+        float mx = -__builtin_inff();
+        each_block([&](auto e0) {
+            // the larger of two numbers (NaN is passed over)
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) mx = __builtin_amdgcn_fmed3f(x[e0 + u], mx, __builtin_inff());
+        });
+        mx = fmaxf(mx, dpp_f32<kDppXor1>(mx));
+        if constexpr (G >= 4) mx = fmaxf(mx, dpp_f32<kDppXor2>(mx));
+        if constexpr (G >= 8) mx = fmaxf(mx, dpp_f32<kDppHalfMirror>(mx));
+        // (a lane of a row past the tensor's end, or one without entries, holds -inf here: its results are not used)
+        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        each_block([&](auto e0) {
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) {
+                x[e0 + u] = __builtin_amdgcn_exp2f((x[e0 + u] - mx) * kLog2e);
+                s[u] += x[e0 + u];
+            }
+        });
+        float sum = (s[0] + s[1]) + (s[2] + s[3]);
+        sum += dpp_f32<kDppXor1>(sum);
+        if constexpr (G >= 4) sum += dpp_f32<kDppXor2>(sum);
+        if constexpr (G >= 8) sum += dpp_f32<kDppHalfMirror>(sum);
+        const float inv = 1.0f / sum;                       // IEEE division
+        each_block([&](auto e0) {
+            auto put = [&](int e) {
+                if constexpr (BF) seg[e] = (T)bf16_narrow(x[e] * inv);
+                else seg[e] = x[e] * inv;
+            };
+            if (e0 + kBlk <= e_all) {
+#pragma unroll
+                for (int u = 0; u < kBlk; ++u) put(e0 + u);
+            } else {
+#pragma unroll
+                for (int u = 0; u < kBlk; ++u)
+                    if (e0 + u < len) put(e0 + u);
+            }
+        });
+        S::settle();
+        // the dense rows leave as they came: one contiguous piece, 16 bytes a lane
+        const int n_vec = n_elem / PER16;
+        const u32x4 *src_v = reinterpret_cast<const u32x4 *>(rows);
+        u32x4 *dst_v = reinterpret_cast<u32x4 *>(out);
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const int v = u * kWave + lane;
+            if (v < n_vec) store_global<true>(dst_v + v, src_v[v]);
+        }
+        const int ei = n_vec * PER16 + lane;
+        if (ei < n_elem) out[ei] = rows[ei];
+    }
+};
+
 template <typename T, int G, int K, int NV>
 __global__ __launch_bounds__(kWave) void softmax_prune_short_kernel(const T *__restrict__ p, ShortArgs a,
                                                                     T *__restrict__ probs, T *__restrict__ vals,
@@ -504,7 +625,6 @@ __global__ __launch_bounds__(kWave) void softmax_prune_short_kernel(const T *__r
 {
     using S = ShortRows<T, G, K, NV>;
     extern __shared__ uint4 short_lds[];
-    constexpr bool BF = sizeof(T) == 2;
     constexpr int R = S::R;
     constexpr int PER16 = 16 / (int)sizeof(T);
     const int lane = threadIdx.x;
@@ -532,69 +652,23 @@ __global__ __launch_bounds__(kWave) void softmax_prune_short_kernel(const T *__r
         if (ei < n_elem) reinterpret_cast<T *>(slab)[ei] = p[row0 * (int64_t)cols + ei];
     }
     for (int t = lane; t < R * k; t += kWave) oc[t] = kNoPair;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    S::settle();
 
-    auto to_probabilities = [&]() {
-        const int r = lane / G, q = lane % G;
-        const int E = (cols + G - 1) / G;
-        const int len = min(max(cols - q * E, 0), E);
-        const int e_all = max(cols - (G - 1) * E, 0);
-        T *seg = reinterpret_cast<T *>(slab) + r * cols + q * E;
-        auto value = [](int bits) { return __builtin_bit_cast(float, BF ? (uint32_t)bits << 16 : (uint32_t)bits); };
-        constexpr float kLog2e = 1.44269504088896340736f;
-        float mx = -__builtin_inff();
-        S::template for_each_entry<false>(seg, E, len, e_all, [&](int, int bits, bool ok) {
-            const float x = value(bits);
-            mx = ok ? fmaxf(mx, x) : mx;
-        });
-        mx = fmaxf(mx, dpp_f32<kDppXor1>(mx));
-        if constexpr (G == 4) mx = fmaxf(mx, dpp_f32<kDppXor2>(mx));
-        // (a lane of a row past the tensor's end, or one without entries, holds -inf here: its results are not used)
-        float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-        S::template for_each_entry<false>(seg, E, len, e_all, [&](int e, int bits, bool ok) {
-            const float t = __builtin_amdgcn_exp2f((value(bits) - mx) * kLog2e);
-            const float s = s0 + (ok ? t : 0.0f);           // the four sums take turns
-            s0 = s1; s1 = s2; s2 = s3; s3 = s;
-            if constexpr (!BF) {
-                if (ok) seg[e] = t;                         // fp32 rows keep the exponential in place of the logit
-            }
-        });
-        float sum = (s0 + s1) + (s2 + s3);
-        sum += dpp_f32<kDppXor1>(sum);
-        if constexpr (G == 4) sum += dpp_f32<kDppXor2>(sum);
-        const float inv = 1.0f / sum;                       // IEEE division
-        if constexpr (!BF) {                                // (the lane reads back what it wrote itself: LDS keeps a wave's order)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        S::template for_each_entry<false>(seg, E, len, e_all, [&](int e, int bits, bool ok) {
-            const float pj = (BF ? __builtin_amdgcn_exp2f((value(bits) - mx) * kLog2e) : value(bits)) * inv;
-            if (ok) {
-                if constexpr (BF) seg[e] = (T)bf16_narrow(pj);
-                else seg[e] = pj;
-            }
-        });
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // the dense rows leave as they came: one contiguous piece, 16 bytes a lane
-        u32x4 *dst_v = reinterpret_cast<u32x4 *>(probs + row0 * (int64_t)cols);
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            const int v = u * kWave + lane;
-            if (v < n_vec) store_global<true>(dst_v + v, slab_v[v]);
-        }
-        const int ei = n_vec * PER16 + lane;
-        if (ei < n_elem) probs[row0 * (int64_t)cols + ei] = reinterpret_cast<const T *>(slab)[ei];
-    };
-
+    HeldRows<T, G, K, NV> held(cols, reinterpret_cast<T *>(slab), probs + row0 * (int64_t)cols, lane, n_elem);
     const T *rows_lds = reinterpret_cast<const T *>(slab);
-    if (!S::template run<false, true>(a, rows_lds, oc, lane, n_here, row0, vals, idx, nullptr, to_probabilities))
-        S::template run<true, true>(a, rows_lds, oc, lane, n_here, row0, vals, idx, nullptr, to_probabilities);
+    int kept;
+    if (!S::template select<false>(a, rows_lds, oc, lane, kept, held)) S::template select<true>(a, rows_lds, oc, lane, kept, held);
+    S::settle();
+    held.to_probabilities();
+    S::write_pairs(a, rows_lds, oc, true, lane, n_here, row0, kept, vals, idx, nullptr);
 }
+
+// Lanes to a softmax row: a wave that holds half as many rows lives half as long (and twice as many fit the LDS), which
+// wide rows gain more from than they lose to one more merge of the lists.  Eight lanes (fp32) against four, us:
+// 87 468 x 197 30.4 / 34.2, 49 152 x 197 20.1 / 22.8, 16 384 x 130 9.3 / 11.0, 8192 x 112 6.5 / 7.4, 98 304 x 112 18.7 / 17.9,
+// x 79 14.7 / 14.0, x 50 10.3 / 8.2.  bf16, four against two: 806 912 x 197 169 / 175, 32 768 x 250 16.2 / 21.1, 8192 x 96
+// 6.9 / 7.6, 98 304 x 96 12.9 / 12.6, x 79 14.2 / 13.4.  (bf16 with eight lanes: 183 at 806 912 x 197.)
+constexpr int kSoftmaxWideCols = 96;
 
 template <typename T, int G, int K, int NV>
 void launch_softmax_short(const T *p, const ShortArgs &a, T *probs, T *vals, uint16_t *idx, hipStream_t st)
@@ -605,28 +679,37 @@ void launch_softmax_short(const T *p, const ShortArgs &a, T *probs, T *vals, uin
     softmax_prune_short_kernel<T, G, K, NV><<<(unsigned)blocks, kWave, lds, st>>>(p, a, probs, vals, idx);
 }
 
-template <typename T, int G, int K>
+// WIDE: rows of at least kSoftmaxWideCols columns, and so many lanes to a row
+template <typename T, bool WIDE> constexpr int kSoftmaxLanes = (WIDE ? 2 : 1) * (sizeof(T) == 2 ? 2 : 4);
+
+template <typename T, bool WIDE, int K>
 void launch_softmax_short_nv(const T *p, const ShortArgs &a, T *probs, T *vals, uint16_t *idx, hipStream_t st)
 {
-    constexpr int R = kWave / G;
-    constexpr int S = R * (int)sizeof(T) / 64;
-    const int nv = (a.cols * S * 4 + kWave - 1) / kWave;
-    if (nv <= 4 * S) launch_softmax_short<T, G, K, 4 * S>(p, a, probs, vals, idx, st);
-    else if (nv <= 8 * S) launch_softmax_short<T, G, K, 8 * S>(p, a, probs, vals, idx, st);
-    else if (nv <= 12 * S + 1) launch_softmax_short<T, G, K, 12 * S + 1>(p, a, probs, vals, idx, st);
-    else launch_softmax_short<T, G, K, 16 * S>(p, a, probs, vals, idx, st);
+    // rounds of 64 vectors a piece takes when it is 64, 128, 208 (197 columns) or 256 columns wide
+    constexpr int G = kSoftmaxLanes<T, WIDE>;
+    constexpr int kFull = kWave / G * (int)sizeof(T) * 256 / 16 / kWave, kMost = (kFull * 13 + 15) / 16;
+    const int nv = (kWave / G * a.cols * (int)sizeof(T) / 16 + kWave - 1) / kWave;
+    if constexpr (WIDE) {
+        if (nv <= kFull / 2) launch_softmax_short<T, G, K, kFull / 2>(p, a, probs, vals, idx, st);
+        else if (nv <= kMost) launch_softmax_short<T, G, K, kMost>(p, a, probs, vals, idx, st);
+        else launch_softmax_short<T, G, K, kFull>(p, a, probs, vals, idx, st);
+    } else {
+        static_assert(kSoftmaxWideCols <= 128, "half the columns");
+        if (nv <= kFull / 4) launch_softmax_short<T, G, K, kFull / 4>(p, a, probs, vals, idx, st);
+        else launch_softmax_short<T, G, K, kFull / 2>(p, a, probs, vals, idx, st);
+    }
 }
 
-template <typename T, int G>
+template <typename T, bool WIDE>
 void launch_softmax_short_k(const T *p, const ShortArgs &a, T *probs, T *vals, uint16_t *idx, hipStream_t st)
 {
-    if (a.k <= 2) launch_softmax_short_nv<T, G, 2>(p, a, probs, vals, idx, st);
-    else if (a.k <= 4) launch_softmax_short_nv<T, G, 4>(p, a, probs, vals, idx, st);
-    else if (a.k <= 6) launch_softmax_short_nv<T, G, 6>(p, a, probs, vals, idx, st);
-    else if (a.k <= 9) launch_softmax_short_nv<T, G, 9>(p, a, probs, vals, idx, st);
+    if (a.k <= 2) launch_softmax_short_nv<T, WIDE, 2>(p, a, probs, vals, idx, st);
+    else if (a.k <= 4) launch_softmax_short_nv<T, WIDE, 4>(p, a, probs, vals, idx, st);
+    else if (a.k <= 6) launch_softmax_short_nv<T, WIDE, 6>(p, a, probs, vals, idx, st);
+    else if (a.k <= 9) launch_softmax_short_nv<T, WIDE, 9>(p, a, probs, vals, idx, st);
     else if constexpr (sizeof(T) == 2) {
-        if (a.k <= 12) launch_softmax_short_nv<T, G, 12>(p, a, probs, vals, idx, st);
-        else launch_softmax_short_nv<T, G, 16>(p, a, probs, vals, idx, st);
+        if (a.k <= 12) launch_softmax_short_nv<T, WIDE, 12>(p, a, probs, vals, idx, st);
+        else launch_softmax_short_nv<T, WIDE, 16>(p, a, probs, vals, idx, st);
     }
 }
 
@@ -672,33 +755,32 @@ void launch_short_k(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int3
 // and 2048 .. 196 608 rows; times are this kernel's against the other's, in us:
 //  - few enough kept entries: the list insertion grows with k (fp32 rows that keep 12 or 16 lose 15 - 45 %);
 //  - strides that spread over the LDS banks: the lanes of a wave read the same entry of 16 rows at once, and at a
-//    stride of a multiple of 32 dwords those lie in one or two banks (196 608 rows, fp32 softmax on 256 columns 528
-//    against 75, 128 columns 267 against 57, 160 90 against 62, 64 68 against 52, but 96 57 against 57; pruning, which
-//    walks the rows once, only at multiples of 64 dwords from 128 on: 105 against 47 at 256, 54 against 38 at 128, but 18
-//    against 34 at 64).  bf16 strides are half of that; softmax alone loses, on 256 columns alone (98 against 77 at k = 16,
-//    78 against 76 at 9; on 128 columns 30 against 63);
-//  - enough rows: a wave takes 16 (32) of them and needs 8 - 15 us whatever their number, while the other kernel gives
-//    few rows a wave each.  From 128 columns on, at 16 384 rows of 197 columns: fp32 pruning 11.2 against 8.3, softmax 16.2
-//    against 11.4, bf16 softmax 15.4 against 11.1.  fp32 pruning: 12.7 against 10.0 at 24 576 rows, 17.6 against 15.9 at
-//    49 152 (peaked 16.2 against 19.1, nine tenths masked 14.9 against 17.7), 40 against 47 at 196 608.  bf16 softmax:
-//    15.8 against 14.6 at 24 576 (128 columns 10.1 against 12.2), 16.2 against 18.0 at 32 768.  fp32 softmax: 32.3 against
-//    33.6 at 65 536, 25.8 against 25.4 at 49 152.
-//    Below 128 columns the two are within 1 us of one another for few rows (fp32 pruning of 16 384 x 112 7.1 against 7.2,
-//    softmax 10.1 against 9.2, bf16 8.8 against 9.8; at 2048 rows, where the host's launch is most of it, 7.9 against 6.5) and
-//    this one is ahead from 24 576 on, so their number is not looked at.  Nor is it for bf16 pruning: plain rows gain in the
-//    other kernel at k = 16 (16 384 x 197 9.5 against 8.1), but rows with masked columns, whose zeros share one histogram
-//    bin there, lose more (9.6 against 14.8; peaked 9.5 against 9.7).
-// What stays slower here or there: fp32 rows of few distinct values (logits in steps of a half) take the other kernel's
-// bisection to the last bit, 98 304 x 192 pruned 62 us here, 85 there, 16 384 x 197 12 and 20; constant rows 61 and 70, 12 and 16.
-constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 60000;
+//    stride of a multiple of 64 dwords those lie in one bank (196 608 rows, fp32 pruning, from 128 columns on: 105 against
+//    47 at 256, 54 against 38 at 128, but 18 against 34 at 64).  Softmax, whose fp32 waves hold 8 rows, loses on 256 columns
+//    alone (131 072 rows: fp32 123 against 51, bf16 63 against 53; fp32 224 columns 45 against 51, 192 40 / 42, 160 34 / 43,
+//    128 34 / 37, 96 20 / 39, 64 19 / 37);
+//  - enough rows: a wave takes 8 to 32 of them and needs 7 - 15 us whatever their number, while the other kernel gives
+//    few rows a wave each.  From 128 columns on, at 197 columns: fp32 pruning of 16 384 rows 11.2 against 8.3, 24 576 12.7 /
+//    10.0, 49 152 17.6 / 15.9 (peaked 16.2 against 19.1, nine tenths masked 14.9 against 17.7), 196 608 40 / 47.  bf16
+//    softmax of 16 384 rows 10.6 against 10.8 (250 columns 12.1 / 10.7), 20 000 12.5 / 15.5.  fp32 softmax of 20 000 rows
+//    12.6 against 11.8 (250 columns 13.9 / 12.3), 24 576 12.2 / 14.3, 32 768 14.9 / 17.4, 49 152 20.2 / 25.2.
+//    Below 128 columns the two are within 1 us of one another for few rows (fp32 pruning of 16 384 x 112 7.1 against 7.2)
+//    and this one is ahead from 24 576 on, so their number is not looked at.  Nor is it for bf16 pruning: plain rows gain in
+//    the other kernel at k = 16 (16 384 x 197 9.5 against 8.1), but rows with masked columns, whose zeros share one
+//    histogram bin there, lose more (9.6 against 14.8; peaked 9.5 against 9.7).
+// What stays slower here or there: pruned fp32 rows of few distinct values (logits in steps of a half) take the other kernel's
+// bisection to the last bit, 98 304 x 192 62 us here, 85 there, 16 384 x 197 12 and 20; constant rows 61 and 70, 12 and 16.
+// fp32 softmax rows of zeros take the signed pass and the exact route here, 24 576 x 197 20.6 us and 14.6 there (few distinct
+// logits the other way: 15.1 and 30.3).
+constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 24000;
 
 bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, bool softmax)
 {
     const bool bf16 = dt == SLIMFIT_BF16;
-    if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32) || rows > (int64_t)0x7FFFFFFF * 16) return false;
+    if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32) || rows > (int64_t)0x7FFFFFFF * 8) return false;
     if (!aligned_to(p, 16)) return false;              // (the rows are staged with 16-byte loads)
-    if (bf16) return !softmax || (cols != 256 && (cols < 128 || rows >= kShortMinRows));
-    if (softmax) return !(cols >= 64 && cols % 32 == 0) && (cols < 128 || rows >= kShortMinRowsSoftmaxF32);
+    if (softmax) return cols != 256 && (cols < 128 || rows >= (bf16 ? kShortMinRows : kShortMinRowsSoftmaxF32));
+    if (bf16) return true;
     return !(cols >= 128 && cols % 64 == 0) && (cols < 128 || rows >= kShortMinRows);
 }
 
@@ -712,12 +794,16 @@ void launch_softmax_prune_short(const void *logits, int32_t dt, int64_t rows, in
     a.mode = SLIMFIT_PRUNE_TOPK;
     a.tau = 0.0f;
     a.div_magic = 65536u / (uint32_t)k + 1u;
-    if (dt == SLIMFIT_F32)
-        launch_softmax_short_k<float, 4>(static_cast<const float *>(logits), a, static_cast<float *>(probs),
-                                         static_cast<float *>(vals), idx, st);
-    else
-        launch_softmax_short_k<uint16_t, 2>(static_cast<const uint16_t *>(logits), a, static_cast<uint16_t *>(probs),
-                                            static_cast<uint16_t *>(vals), idx, st);
+    const bool wide = cols >= kSoftmaxWideCols;
+    auto launch = [&](auto *x) {
+        using T = std::remove_pointer_t<decltype(x)>;
+        const T *in = static_cast<const T *>(logits);
+        T *pr = static_cast<T *>(probs), *v = static_cast<T *>(vals);
+        if (wide) launch_softmax_short_k<T, true>(in, a, pr, v, idx, st);
+        else launch_softmax_short_k<T, false>(in, a, pr, v, idx, st);
+    };
+    if (dt == SLIMFIT_F32) launch(static_cast<float *>(nullptr));
+    else launch(static_cast<uint16_t *>(nullptr));
 }
 
 void launch_prune_short(const void *p, int32_t dt, int64_t rows, int cols, int k, int mode, float tau, void *vals,

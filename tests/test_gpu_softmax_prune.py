@@ -80,8 +80,8 @@ def test_random_rows_ties_and_ranges(rows, cols, k, dtype):
 def test_short_rows_several_rows_a_wavefront(rows, cols, k, dtype):
     """Rows of at most 256 columns that keep few entries take the kernel that gives a wavefront 16 or 32 rows at
     once: ragged row counts, logits of either sign, ties, and fp32 logits that only their lowest bits tell apart.
-    From 128 columns on it takes them from 60 000 rows (fp32) or 20 000 (bf16), so there the rows are run alone and
-    among that many (multiples of 32: the remainder is the test's own); 256 columns always take the other kernel."""
+    From 128 columns on it takes them only in number, so there the rows are run alone and among 60 000 (fp32) or 20 000
+    (bf16; multiples of 32: the remainder is the test's own); 256 columns always take the other kernel."""
     require_gpu()
     g = torch.Generator(device="cuda").manual_seed(rows * 7 + cols * 3 + k)
     l = torch.randn(rows, cols, generator=g, device="cuda") * 3
@@ -212,3 +212,27 @@ def test_hard_rows_for_the_value_bins(cols, k, dtype):
     l[140:150] = -l[140:150].abs()
     l[150:160] = torch.exp(l[150:160] * 8.0).clamp(max=1e30)
     _run_both(l.to(dtype), k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols", [17, 64, 65, 95, 96, 97, 127, 128, 129, 192, 208, 209, 224, 225, 255])
+def test_short_rows_around_the_widths_that_change_kernels(cols, dtype):
+    """Lanes to a row change at 96 columns, the registers that hold a lane's part at 64, 128, 208 and 224; the last lane's
+    part is shorter or missing.  A ragged number of rows; from 128 columns on as many as the kernel is for, and one row
+    below that."""
+    require_gpu()
+    bf16 = dtype == torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    rows = (20000 if bf16 else 24000) + 5 if cols >= 128 else 77
+    for k in (1, 9, 16) if bf16 else (1, 9):
+        l = torch.randn(rows, cols, generator=g, device="cuda") * 3
+        l[1] = -l[1].abs() - 2.0
+        l[2] = torch.randint(-1, 2, (cols,), generator=g, device="cuda").float()
+        l[3], l[4] = 0.0, 2.5
+        l[5, cols // 2:] = -1e9                                            # masked columns
+        l[6, cols - 2:] = 40.0                                             # the largest in the last lane's part
+        l[7] = (torch.full((cols,), 0x3F800000, dtype=torch.int32, device="cuda")
+                + torch.arange(cols, dtype=torch.int32, device="cuda") % 7).view(torch.float32)     # 1 + j 2^-23
+        _run_both(l.to(dtype), k)
+        if cols in (129, 255) and k == 9:
+            _run_both(l[: rows - 6].to(dtype), k)
