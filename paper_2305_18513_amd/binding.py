@@ -1,4 +1,4 @@
-"""Thin ctypes binding of ``libslimfit.so`` (see ``include/slimfit.h``).
+"""Thin binding of ``libslimfit.so`` (see ``include/slimfit.h``).
 
 Argument marshalling only: every step of the hot path runs in the library's
 HIP kernels (or, for the ILS pair, in its host C++).  Functions carry the C
@@ -7,6 +7,10 @@ buffers (inputs and caller-allocated outputs) and NumPy arrays / sequences for
 host buffers.  Device work is enqueued on torch's current stream unless a
 stream handle is given.  A non-zero status raises :class:`SlimfitError`.
 There is no fallback: if the library has not been built, loading it raises.
+
+The calls of a training step go through ``_native`` (``csrc/native_binding.cpp``), which reads plain CUDA tensors
+without ctypes; a call that it does not take (it returns NotImplemented) is judged and served by the ctypes code
+below, which all other functions use as well.
 """
 from __future__ import annotations
 
@@ -17,8 +21,14 @@ from typing import Optional, Sequence
 import numpy as np
 import torch
 
+try:
+    from . import _native
+except ImportError:                # not built: lib() says so
+    _native = None
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libslimfit.so")
+_NATIVE_PATH = os.path.join(_PKG, "_native.so")
 
 F32, BF16 = 0, 1
 Q_FIXED, Q_BLOCK = 0, 1
@@ -60,7 +70,7 @@ _lib = None
 
 
 def is_built() -> bool:
-    return os.path.exists(LIB_PATH)
+    return os.path.exists(LIB_PATH) and os.path.exists(_NATIVE_PATH)
 
 
 def lib():
@@ -69,7 +79,7 @@ def lib():
     if _lib is None:
         if not is_built():
             raise RuntimeError(
-                "libslimfit.so is missing: build it with "
+                "libslimfit.so or its native binding is missing: build them with "
                 "`python -m paper_2305_18513_amd.build` (there is no fallback path)")
         L = C.CDLL(LIB_PATH)
         L.slimfit_status_string.restype = C.c_char_p
@@ -83,6 +93,8 @@ def lib():
             fn = getattr(L, name)
             if fn.restype is C.c_int:          # ctypes default
                 fn.restype = C.c_int32
+        from . import _native as native            # (built since this module was loaded: the wrappers stay with ctypes)
+        native.bind(*[C.cast(getattr(L, name), C.c_void_p).value for name in native.CALLS])
         _lib = L
     return _lib
 
@@ -94,6 +106,11 @@ def status_string(status: int) -> str:
 def _check(rc: int, where: str) -> None:
     if rc != OK:
         raise SlimfitError(rc, where)
+
+
+def _fast(name: str):
+    """The native form of a call; one that takes nothing where it has not been built."""
+    return getattr(_native, name) if _native is not None else lambda *args: NotImplemented
 
 
 def _dt(t: torch.Tensor) -> int:
@@ -181,8 +198,14 @@ def layer_delta_plan(w_prev: Sequence[torch.Tensor], w_cur: Sequence[torch.Tenso
     _check(rc, "layer_delta_plan")
 
 
+_native_layer_delta_run = _fast("layer_delta_run")
+
+
 def layer_delta_run(numel: Sequence[int], prev_dt: int, cur_dt: int, cur_is_delta: bool,
                     eps: float, d_out: torch.Tensor, workspace: torch.Tensor, stream=None) -> None:
+    rc = _native_layer_delta_run(numel, prev_dt, cur_dt, cur_is_delta, eps, d_out, workspace, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "layer_delta_run")
     n = _numel_array(numel)
     _require(d_out.dtype == torch.float32 and d_out.numel() >= n.size)
     rc = lib().slimfit_layer_delta_run(
@@ -293,8 +316,14 @@ def _cache_fits(n: int, mode: int, bits: int, block: int, codes: torch.Tensor, s
     return True
 
 
+_native_quant_pack = _fast("quant_pack")
+
+
 def quant_pack(x: torch.Tensor, mode: int, bits: int, block: int, frac_bits: int,
                codes: torch.Tensor, scales: Optional[torch.Tensor], stream=None) -> None:
+    rc = _native_quant_pack(x, mode, bits, block, frac_bits, codes, scales, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "quant_pack")
     _require(_cache_fits(x.numel(), mode, bits, block, codes, scales))
     rc = lib().slimfit_quant_pack(
         _dev(x), C.c_int32(_dt(x)), C.c_int64(x.numel()), C.c_int32(mode), C.c_int32(bits),
@@ -302,8 +331,14 @@ def quant_pack(x: torch.Tensor, mode: int, bits: int, block: int, frac_bits: int
     _check(rc, "quant_pack")
 
 
+_native_dequant_unpack = _fast("dequant_unpack")
+
+
 def dequant_unpack(codes: torch.Tensor, scales: Optional[torch.Tensor], mode: int, bits: int,
                    block: int, frac_bits: int, y: torch.Tensor, stream=None) -> None:
+    rc = _native_dequant_unpack(codes, scales, mode, bits, block, frac_bits, y, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "dequant_unpack")
     _require(_cache_fits(y.numel(), mode, bits, block, codes, scales))
     rc = lib().slimfit_dequant_unpack(
         _dev(codes), _dev(scales), C.c_int64(y.numel()), C.c_int32(mode), C.c_int32(bits),
@@ -313,9 +348,15 @@ def dequant_unpack(codes: torch.Tensor, scales: Optional[torch.Tensor], mode: in
 
 # ---------------------------------------------------------------- (b') the cache fused into GELU
 
+_native_gelu_quant_pack = _fast("gelu_quant_pack")
+
+
 def gelu_quant_pack(x: torch.Tensor, mode: int, bits: int, block: int, frac_bits: int, y: torch.Tensor,
                     codes: torch.Tensor, scales: Optional[torch.Tensor], stream=None) -> None:
     """y = GELU(x) and (codes, scales) = quant_pack(x) in one pass over x."""
+    rc = _native_gelu_quant_pack(x, mode, bits, block, frac_bits, y, codes, scales, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "gelu_quant_pack")
     _require(x.is_contiguous() and y.is_contiguous() and y.dtype == x.dtype and y.numel() == x.numel())
     _require(_cache_fits(x.numel(), mode, bits, block, codes, scales))
     rc = lib().slimfit_gelu_quant_pack(
@@ -324,9 +365,15 @@ def gelu_quant_pack(x: torch.Tensor, mode: int, bits: int, block: int, frac_bits
     _check(rc, "gelu_quant_pack")
 
 
+_native_gelu_backward_dequant = _fast("gelu_backward_dequant")
+
+
 def gelu_backward_dequant(codes: torch.Tensor, scales: Optional[torch.Tensor], mode: int, bits: int, block: int,
                           frac_bits: int, dy: torch.Tensor, dx: torch.Tensor, stream=None) -> None:
     """dx = dy * GELU'(dequantised cache); the dequantised values stay in registers."""
+    rc = _native_gelu_backward_dequant(codes, scales, mode, bits, block, frac_bits, dy, dx, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "gelu_backward_dequant")
     _require(dy.is_contiguous() and dx.is_contiguous() and dx.dtype == dy.dtype and dx.numel() == dy.numel())
     _require(_cache_fits(dx.numel(), mode, bits, block, codes, scales))
     rc = lib().slimfit_gelu_backward_dequant(
@@ -341,8 +388,14 @@ def keep_count(cols: int, keep_ppm: int) -> int:
     return int(lib().slimfit_keep_count(C.c_int32(cols), C.c_int32(keep_ppm)))
 
 
+_native_prune_scores = _fast("prune_scores")
+
+
 def prune_scores(p: torch.Tensor, k: int, mode: int, tau: float, vals: torch.Tensor,
                  idx: torch.Tensor, counts: Optional[torch.Tensor], stream=None) -> None:
+    rc = _native_prune_scores(p, k, mode, tau, vals, idx, counts, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "prune_scores")
     _require(p.dim() == 2 and vals.dtype == p.dtype and idx.dtype == torch.uint16)
     rows, cols = p.shape
     _require(k >= 0 and vals.numel() >= rows * k and idx.numel() >= rows * k)
@@ -353,8 +406,14 @@ def prune_scores(p: torch.Tensor, k: int, mode: int, tau: float, vals: torch.Ten
     _check(rc, "prune_scores")
 
 
+_native_restore_scores = _fast("restore_scores")
+
+
 def restore_scores(vals: torch.Tensor, idx: torch.Tensor, counts: Optional[torch.Tensor],
                    out: torch.Tensor, stream=None) -> None:
+    rc = _native_restore_scores(vals, idx, counts, out, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "restore_scores")
     _require(out.dim() == 2 and vals.dim() == 2 and vals.dtype == out.dtype and idx.dtype == torch.uint16)
     rows, cols = out.shape
     k = vals.shape[1]
@@ -366,9 +425,15 @@ def restore_scores(vals: torch.Tensor, idx: torch.Tensor, counts: Optional[torch
     _check(rc, "restore_scores")
 
 
+_native_softmax_prune = _fast("softmax_prune")
+
+
 def softmax_prune(logits: torch.Tensor, k: int, probs: torch.Tensor, vals: torch.Tensor, idx: torch.Tensor,
                   stream=None) -> None:
     """probs = softmax(logits) per row; (vals, idx) = the k largest of every row (decided on the logits)."""
+    rc = _native_softmax_prune(logits, k, probs, vals, idx, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "softmax_prune")
     _require(logits.dim() == 2 and logits.is_contiguous() and probs.is_contiguous())
     _require(probs.shape == logits.shape and probs.dtype == logits.dtype)
     _require(vals.dtype == logits.dtype and idx.dtype == torch.uint16)
@@ -380,9 +445,15 @@ def softmax_prune(logits: torch.Tensor, k: int, probs: torch.Tensor, vals: torch
     _check(rc, "softmax_prune")
 
 
+_native_softmax_backward_pruned = _fast("softmax_backward_pruned")
+
+
 def softmax_backward_pruned(vals: torch.Tensor, idx: torch.Tensor, counts: Optional[torch.Tensor],
                             dp: torch.Tensor, ds: torch.Tensor, stream=None) -> None:
     """ds = p^ * (dp - sum(p^ * dp)) per row, p^ being the rows that restore_scores would rebuild."""
+    rc = _native_softmax_backward_pruned(vals, idx, counts, dp, ds, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "softmax_backward_pruned")
     _require(dp.dim() == 2 and dp.is_contiguous() and ds.is_contiguous())
     _require(ds.shape == dp.shape and ds.dtype == dp.dtype)
     _require(vals.dim() == 2 and vals.dtype == dp.dtype and idx.dtype == torch.uint16 and vals.shape == idx.shape)
@@ -447,8 +518,14 @@ def restore_global(vals: torch.Tensor, idx: torch.Tensor, k: int, out: torch.Ten
 
 # ---------------------------------------------------------------- (c-ln) LayerNorm around the pruned cache
 
+_native_layernorm_forward = _fast("layernorm_forward")
+
+
 def layernorm_forward(x: torch.Tensor, gamma: torch.Tensor, beta: torch.Tensor, eps: float, y: torch.Tensor,
                       mean: torch.Tensor, rstd: torch.Tensor, stream=None) -> None:
+    rc = _native_layernorm_forward(x, gamma, beta, eps, y, mean, rstd, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "layernorm_forward")
     _require(x.dim() == 2 and x.is_contiguous() and y.is_contiguous() and y.shape == x.shape and y.dtype == x.dtype)
     _require(all(t.dtype == torch.float32 for t in (gamma, beta, mean, rstd)))
     rows, H = x.shape
@@ -459,11 +536,18 @@ def layernorm_forward(x: torch.Tensor, gamma: torch.Tensor, beta: torch.Tensor, 
     _check(rc, "layernorm_forward")
 
 
+_native_prune_global_standardized = _fast("prune_global_standardized")
+
+
 def prune_global_standardized(x: torch.Tensor, mean: torch.Tensor, rstd: torch.Tensor, k: int, vals: torch.Tensor,
                               idx: torch.Tensor, by_magnitude: bool = True, tile_ptr: Optional[torch.Tensor] = None,
                               row_ptr: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                               stream=None) -> None:
     """prune_global of the standardised rows of ``x`` (rows, H), formed on the fly from mean / rstd."""
+    rc = _native_prune_global_standardized(x, mean, rstd, k, vals, idx, by_magnitude, tile_ptr, row_ptr,
+                                           workspace, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "prune_global_standardized")
     _require(x.dim() == 2 and x.is_contiguous() and vals.dtype == torch.float32 and idx.dtype == torch.int32)
     _require(mean.dtype == torch.float32 and rstd.dtype == torch.float32)
     rows, H = x.shape
@@ -479,9 +563,15 @@ def prune_global_standardized(x: torch.Tensor, mean: torch.Tensor, rstd: torch.T
     _check(rc, "prune_global_standardized")
 
 
+_native_layernorm_backward = _fast("layernorm_backward")
+
+
 def layernorm_backward(x: torch.Tensor, mean: torch.Tensor, rstd: torch.Tensor, gamma: torch.Tensor,
                        dy: torch.Tensor, dx: torch.Tensor, stream=None) -> None:
     """Input gradient of an active LayerNorm (every standardised input present)."""
+    rc = _native_layernorm_backward(x, mean, rstd, gamma, dy, dx, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "layernorm_backward")
     _require(x.dim() == 2 and x.is_contiguous() and dy.is_contiguous() and dx.is_contiguous())
     _require(dy.shape == x.shape and dx.shape == x.shape and dy.dtype == x.dtype and dx.dtype == x.dtype)
     _require(all(t.dtype == torch.float32 for t in (mean, rstd, gamma)))
@@ -492,10 +582,16 @@ def layernorm_backward(x: torch.Tensor, mean: torch.Tensor, rstd: torch.Tensor, 
     _check(rc, "layernorm_backward")
 
 
+_native_layernorm_forward_quant_pack = _fast("layernorm_forward_quant_pack")
+
+
 def layernorm_forward_quant_pack(x: torch.Tensor, gamma: torch.Tensor, beta: torch.Tensor, eps: float, bits: int,
                                  block: int, y: torch.Tensor, mean: torch.Tensor, rstd: torch.Tensor,
                                  codes: torch.Tensor, scales: torch.Tensor, stream=None) -> None:
     """layernorm_forward plus, from the same read of x, the codes and scales of quant_pack(x) in BLOCK mode."""
+    rc = _native_layernorm_forward_quant_pack(x, gamma, beta, eps, bits, block, y, mean, rstd, codes, scales, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "layernorm_forward_quant_pack")
     _require(x.dim() == 2 and x.is_contiguous() and y.is_contiguous() and y.shape == x.shape)
     _require(all(t.dtype == torch.float32 for t in (gamma, beta, mean, rstd, scales)) and codes.dtype == torch.uint8)
     _require(y.dtype == x.dtype)
@@ -508,10 +604,16 @@ def layernorm_forward_quant_pack(x: torch.Tensor, gamma: torch.Tensor, beta: tor
     _check(rc, "layernorm_forward_quant_pack")
 
 
+_native_layernorm_backward_dequant = _fast("layernorm_backward_dequant")
+
+
 def layernorm_backward_dequant(codes: torch.Tensor, scales: torch.Tensor, bits: int, block: int, mean: torch.Tensor,
                                rstd: torch.Tensor, gamma: torch.Tensor, dy: torch.Tensor, dx: torch.Tensor,
                                stream=None) -> None:
     """Input gradient of a LayerNorm whose input was cached by layernorm_forward_quant_pack."""
+    rc = _native_layernorm_backward_dequant(codes, scales, bits, block, mean, rstd, gamma, dy, dx, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "layernorm_backward_dequant")
     _require(dy.dim() == 2 and dy.is_contiguous() and dx.is_contiguous() and dx.shape == dy.shape)
     _require(all(t.dtype == torch.float32 for t in (scales, mean, rstd, gamma)) and codes.dtype == torch.uint8)
     _require(dx.dtype == dy.dtype)
@@ -524,10 +626,16 @@ def layernorm_backward_dequant(codes: torch.Tensor, scales: torch.Tensor, bits: 
     _check(rc, "layernorm_backward_dequant")
 
 
+_native_layernorm_param_grads = _fast("layernorm_param_grads")
+
+
 def layernorm_param_grads(x: torch.Tensor, mean: torch.Tensor, rstd: torch.Tensor, dy: torch.Tensor,
                           dgamma: torch.Tensor, dbeta: torch.Tensor, workspace: Optional[torch.Tensor] = None,
                           stream=None) -> None:
     """gamma^ and beta^ of an active LayerNorm: column sums over the rows of ``x`` / ``dy`` (rows, H)."""
+    rc = _native_layernorm_param_grads(x, mean, rstd, dy, dgamma, dbeta, workspace, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "layernorm_param_grads")
     _require(x.dim() == 2 and x.is_contiguous() and dy.is_contiguous() and dy.shape == x.shape and dy.dtype == x.dtype)
     _require(all(t.dtype == torch.float32 for t in (mean, rstd, dgamma, dbeta)))
     rows, H = x.shape
@@ -543,9 +651,15 @@ def layernorm_param_grads(x: torch.Tensor, mean: torch.Tensor, rstd: torch.Tenso
     _check(rc, "layernorm_param_grads")
 
 
+_native_layernorm_backward_pruned = _fast("layernorm_backward_pruned")
+
+
 def layernorm_backward_pruned(vals: torch.Tensor, idx: torch.Tensor, row_ptr: torch.Tensor, k: int,
                               rstd: torch.Tensor, gamma: torch.Tensor, dy: torch.Tensor, dx: torch.Tensor,
                               stream=None) -> None:
+    rc = _native_layernorm_backward_pruned(vals, idx, row_ptr, k, rstd, gamma, dy, dx, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "layernorm_backward_pruned")
     _require(dy.dim() == 2 and dy.is_contiguous() and dx.is_contiguous() and dx.shape == dy.shape)
     _require(all(t.dtype == torch.float32 for t in (vals, rstd, gamma)) and dx.dtype == dy.dtype)
     _require(idx.dtype == torch.int32 and row_ptr.dtype == torch.int32)

@@ -1,4 +1,5 @@
-"""Builds ``libslimfit.so`` (the C-ABI library) for gfx950 with hipcc, in-tree.
+"""Builds ``libslimfit.so`` (the C-ABI library) for gfx950 with hipcc, and ``_native.so`` (the Python binding of the
+calls of a training step) with the host compiler, in-tree.
 
     python -m paper_2305_18513_amd.build            # rebuild
 
@@ -12,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +21,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libslimfit.so")
+NATIVE = os.path.join(PKG, "_native.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ("api.hip", "quant.hip", "layer_delta.hip", "prune.hip", "prune_short.hip", "prune_global.hip", "layernorm.hip", "probe.hip")
@@ -52,6 +55,25 @@ def _compile(src: str, extra_flags=(), obj_dir: str = OBJ_DIR) -> str:
     return obj
 
 
+def build_native(verbose: bool = True) -> str:
+    """Compile the native binding against the installed torch.  It finds the library's functions at run time
+    (``binding.lib`` hands it their addresses), so it links torch only."""
+    import torch
+    from torch.utils import cpp_extension
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    includes = [i for p in cpp_extension.include_paths("cuda") for i in ("-isystem", p)]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE, *includes,
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "native_binding.cpp"), "-o", tmp,
+           "-L", libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, NATIVE)
+    if verbose:
+        print("built", NATIVE)
+    return NATIVE
+
+
 def build_library(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
     """Compile every source and link the shared library.  Always rebuilds.
 
@@ -68,6 +90,8 @@ def build_library(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
     os.replace(tmp, out)
     if verbose:
         print("built", out)
+    if out == LIB:
+        build_native(verbose)
     return out
 
 
