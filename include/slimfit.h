@@ -504,6 +504,25 @@ int32_t slimfit_layernorm_backward_dequant(const uint8_t *codes, const float *sc
                                            void *stream);
 
 /* ------------------------------------------------------------------------
+ * (c-qkv) The rows of a QKV projection apart into the operands of attention's
+ *     products, and their gradients together again; each byte is read and
+ *     written once.
+ *
+ *  qkv : DEVICE [batch, tokens, 3, heads, head_dim], the three being q, k, v.
+ *  q, v: DEVICE [batch, heads, tokens, head_dim].
+ *  kt  : DEVICE [batch, heads, head_dim, tokens].
+ *        All contiguous, 16-byte aligned, of type dt, none overlapping.
+ *  slimfit_split_heads : q = q_scale * qkv[.., 0, ..], kt and v copied.
+ *  slimfit_merge_heads : qkv[.., 0, ..] = q_scale * q, the rest copied.
+ *        (q is the product rounded to dt: exact where q_scale is a power of two.)
+ *  head_dim has to be a multiple of 4 (fp32) or 8 (bf16): ERR_UNSUPPORTED.
+ * ---------------------------------------------------------------------- */
+int32_t slimfit_split_heads(const void *qkv, int32_t dt, int64_t batch, int32_t tokens, int32_t heads,
+                            int32_t head_dim, float q_scale, void *q, void *kt, void *v, void *stream);
+int32_t slimfit_merge_heads(const void *q, const void *kt, const void *v, int32_t dt, int64_t batch, int32_t tokens,
+                            int32_t heads, int32_t head_dim, float q_scale, void *qkv, void *stream);
+
+/* ------------------------------------------------------------------------
  * (d) Inter-layer scheduling on the host -- Alg. 1 and Sec. 3.2 / Fig. 4:
  *        idx = argsort(d)[: int(L*F)]   -> these layers are frozen;
  *     afterwards only the layers that were active take their new distance,

@@ -25,6 +25,8 @@ computes; the dense matrix products of the linear layer are torch's.
                      pairs and V are cached.  Backward: dP = dO @ V^T (dense
                      product, torch's), dV = P^^T @ dO with P^ restored from the
                      pairs, dlogits from the pairs as in SoftmaxFunction.
+  SplitHeadsFunction (q, k^T, v) of the attention products from the rows of a QKV
+                     projection in one pass, their gradients back in another.
   MatmulFunction     out = a @ b with both operands cached in 8 bits (the paper's
                      placement for MatMul's activations).
   LinearFunction     the freezing rule of Alg. 4: a layer whose weight does not
@@ -232,6 +234,7 @@ class SoftmaxMatmulFunction(torch.autograd.Function):
             vals, idx, v = ctx.saved_tensors
         cols = shape[-1]
         rows = vals.shape[0]
+        grad_output = grad_output.contiguous()              # (both products would lay out a transposed one for themselves)
         dp = torch.matmul(grad_output, v.transpose(-1, -2)).contiguous().view(rows, cols)
         p_hat = torch.empty(rows, cols, dtype=vals.dtype, device=vals.device)
         sf.restore_scores(vals, idx, None, p_hat)
@@ -239,6 +242,29 @@ class SoftmaxMatmulFunction(torch.autograd.Function):
         ds = torch.empty_like(dp)
         sf.softmax_backward_pruned(vals, idx, None, dp, ds)
         return ds.view(shape), dv, None, None, None
+
+
+class SplitHeadsFunction(torch.autograd.Function):
+    """(q, k^T, v) of the attention products from the rows (B, T, 3 * H) of a QKV projection, q times ``q_scale``; backward
+    lays the three gradients into one row buffer.  Nothing is kept."""
+
+    @staticmethod
+    def forward(ctx, qkv: torch.Tensor, heads: int, q_scale: float):
+        B, T, H3 = qkv.shape
+        D = H3 // (3 * heads)
+        q = torch.empty(B, heads, T, D, dtype=qkv.dtype, device=qkv.device)
+        kt = torch.empty(B, heads, D, T, dtype=qkv.dtype, device=qkv.device)
+        v = torch.empty_like(q)
+        sf.split_heads(qkv.contiguous(), q_scale, q, kt, v)
+        ctx.meta = (qkv.shape, q_scale)
+        return q, kt, v
+
+    @staticmethod
+    def backward(ctx, dq: torch.Tensor, dkt: torch.Tensor, dv: torch.Tensor):
+        shape, q_scale = ctx.meta
+        dqkv = torch.empty(shape, dtype=dq.dtype, device=dq.device)
+        sf.merge_heads(dq.contiguous(), dkt.contiguous(), dv.contiguous(), q_scale, dqkv)
+        return dqkv, None, None
 
 
 class LinearFunction(torch.autograd.Function):
@@ -274,6 +300,11 @@ class LinearFunction(torch.autograd.Function):
         return dx, dw, db, None, None
 
 
+def _halves(dim: int) -> bool:
+    """Whether sqrt(dim) is a power of two."""
+    return dim > 0 and dim & (dim - 1) == 0 and dim.bit_length() % 2 == 1
+
+
 def encoder_block_params(hidden: int, device="cuda", seed: int = 0, dtype=torch.float32):
     """Random weights of one encoder block (QKV, projection, two feed-forward matrices, two LayerNorms)."""
     g = torch.Generator(device=device).manual_seed(seed)
@@ -303,9 +334,16 @@ def frozen_encoder_block(x: torch.Tensor, p: dict, heads: int, wrapped: bool, ke
     if wrapped:
         w = {name: t.detach() for name, t in p.items()}    # frozen: the scheduler has switched their gradients off
         h = LayerNormFunction.apply(x, p["g1"], p["b1"], 1e-5, True, keep_ppm)
-        q, k_, v = LinearFunction.apply(h, w["wqkv"], None, 8, block).chunk(3, dim=-1)
-        s = MatmulFunction.apply(split(q).contiguous(), split(k_).transpose(-1, -2).contiguous(), 8, block) / D ** 0.5
-        a = SoftmaxMatmulFunction.apply(s, split(v).contiguous(), keep_ppm, 8, block).transpose(1, 2).reshape(B, T, H)
+        qkv = LinearFunction.apply(h, w["wqkv"], None, 8, block)
+        if _halves(D) and D * qkv.element_size() % 16 == 0:
+            # a power of two commutes with every rounding on the way: the same numbers as with the products divided
+            q, kt, v = SplitHeadsFunction.apply(qkv, heads, 1.0 / D ** 0.5)
+            s = MatmulFunction.apply(q, kt, 8, block)
+        else:
+            q, k_, v = qkv.chunk(3, dim=-1)
+            s = MatmulFunction.apply(split(q).contiguous(), split(k_).transpose(-1, -2).contiguous(), 8, block) / D ** 0.5
+            v = split(v).contiguous()
+        a = SoftmaxMatmulFunction.apply(s, v, keep_ppm, 8, block).transpose(1, 2).reshape(B, T, H)
         y = x + LinearFunction.apply(a, w["wo"], None, 8, block)
         h = LayerNormFunction.apply(y, p["g2"], p["b2"], 1e-5, True, keep_ppm)
         h = LinearFunction.apply(h, w["w1"], None, 8, block)

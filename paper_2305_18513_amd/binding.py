@@ -46,6 +46,7 @@ EXPORTS = (
     "slimfit_restore_scores", "slimfit_softmax_prune", "slimfit_softmax_backward_pruned", "slimfit_prune_global_workspace", "slimfit_global_tile_ptr_len", "slimfit_prune_global",
     "slimfit_restore_global", "slimfit_layernorm_forward", "slimfit_prune_global_standardized",
     "slimfit_layernorm_backward_pruned", "slimfit_layernorm_forward_quant_pack", "slimfit_layernorm_backward_dequant", "slimfit_layernorm_backward", "slimfit_layernorm_param_grads_workspace", "slimfit_layernorm_param_grads",
+    "slimfit_split_heads", "slimfit_merge_heads",
     "slimfit_freeze_count", "slimfit_ils_select", "slimfit_ils_select_blocks",
     "slimfit_ils_update", "slimfit_schedule_random", "slimfit_schedule_progressive",
 )
@@ -669,6 +670,47 @@ def layernorm_backward_pruned(vals: torch.Tensor, idx: torch.Tensor, row_ptr: to
         _dev(vals), _dev(idx), _dev(row_ptr), C.c_int64(k), _dev(rstd), _dev(gamma), _dev(dy), C.c_int32(_dt(dy)),
         C.c_int64(rows), C.c_int64(H), _dev(dx), _stream(stream))
     _check(rc, "layernorm_backward_pruned")
+
+
+# ---------------------------------------------------------------- (c-qkv) attention's operands
+
+def _heads_ok(qkv: torch.Tensor, q: torch.Tensor, kt: torch.Tensor, v: torch.Tensor) -> bool:
+    if q.dim() != 4 or qkv.numel() != 3 * q.numel():
+        return False
+    batch, heads, tokens, dim = q.shape
+    return (v.shape == q.shape and kt.shape == (batch, heads, dim, tokens) and qkv.shape[:2] == (batch, tokens)
+            and all(t.is_contiguous() and t.dtype == qkv.dtype for t in (qkv, q, kt, v)))
+
+
+_native_split_heads = _fast("split_heads")
+
+
+def split_heads(qkv: torch.Tensor, q_scale: float, q: torch.Tensor, kt: torch.Tensor, v: torch.Tensor, stream=None) -> None:
+    """The rows (batch, tokens, 3 * heads * dim) of a QKV projection apart into q_scale * q and v (batch, heads, tokens,
+    dim) and the transposed k (batch, heads, dim, tokens)."""
+    rc = _native_split_heads(qkv, q_scale, q, kt, v, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "split_heads")
+    _require(_heads_ok(qkv, q, kt, v))
+    batch, heads, tokens, dim = q.shape
+    rc = lib().slimfit_split_heads(_dev(qkv), C.c_int32(_dt(qkv)), C.c_int64(batch), C.c_int32(tokens), C.c_int32(heads), C.c_int32(dim),
+                                   C.c_float(q_scale), _dev(q), _dev(kt), _dev(v), _stream(stream))
+    _check(rc, "split_heads")
+
+
+_native_merge_heads = _fast("merge_heads")
+
+
+def merge_heads(q: torch.Tensor, kt: torch.Tensor, v: torch.Tensor, q_scale: float, qkv: torch.Tensor, stream=None) -> None:
+    """split_heads the other way round: q_scale * q, k and v (gradients) into the rows of qkv."""
+    rc = _native_merge_heads(q, kt, v, q_scale, qkv, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "merge_heads")
+    _require(_heads_ok(qkv, q, kt, v))
+    batch, heads, tokens, dim = q.shape
+    rc = lib().slimfit_merge_heads(_dev(q), _dev(kt), _dev(v), C.c_int32(_dt(qkv)), C.c_int64(batch), C.c_int32(tokens), C.c_int32(heads),
+                                   C.c_int32(dim), C.c_float(q_scale), _dev(qkv), _stream(stream))
+    _check(rc, "merge_heads")
 
 
 # ---------------------------------------------------------------- (d) Alg. 1 (host)

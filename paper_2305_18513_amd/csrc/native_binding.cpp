@@ -28,7 +28,8 @@ namespace {
     X(quant_pack) X(dequant_unpack) X(gelu_quant_pack) X(gelu_backward_dequant) X(prune_scores) X(restore_scores)      \
     X(softmax_prune) X(softmax_backward_pruned) X(prune_global_standardized) X(prune_global_workspace)                 \
     X(layernorm_forward) X(layernorm_backward) X(layernorm_backward_pruned) X(layernorm_forward_quant_pack)            \
-    X(layernorm_backward_dequant) X(layernorm_param_grads) X(layernorm_param_grads_workspace) X(layer_delta_run)
+    X(layernorm_backward_dequant) X(layernorm_param_grads) X(layernorm_param_grads_workspace) X(layer_delta_run)         \
+    X(split_heads) X(merge_heads)
 #define X(name) decltype(&slimfit_##name) name##_fn = nullptr;
 SLIMFIT_CALLS(X)
 #undef X
@@ -512,6 +513,47 @@ PyObject *layer_delta_run(PyObject *, PyObject *const *args, Py_ssize_t n_args)
     SLIMFIT_RUN(layer_delta_run_fn(sizes.data(), (int32_t)sizes.size(), prev_dt, cur_dt, is_delta, eps, dp, wp, bytes, st));
 }
 
+bool heads_ok(const at::Tensor *qkv, const at::Tensor *q, const at::Tensor *kt, const at::Tensor *v)
+{
+    if (q->dim() != 4 || kt->dim() != 4 || qkv->dim() < 2 || qkv->numel() != 3 * q->numel()) return false;
+    const int64_t batch = q->size(0), heads = q->size(1), tokens = q->size(2), dim = q->size(3);
+    return heads <= INT32_MAX && tokens <= INT32_MAX && dim <= INT32_MAX && v->sizes() == q->sizes() && kt->size(0) == batch &&
+           kt->size(1) == heads && kt->size(2) == dim && kt->size(3) == tokens && qkv->size(0) == batch && qkv->size(1) == tokens &&
+           activation(qkv) && same_type(qkv, q) && same_type(qkv, kt) && same_type(qkv, v);
+}
+
+PyObject *split_heads(PyObject *, PyObject *const *args, Py_ssize_t n_args)
+{
+    Args a(args, n_args, 6);
+    const at::Tensor *qkv = a.tensor();
+    const float scale = a.f32();
+    const at::Tensor *q = a.tensor(), *kt = a.tensor(), *v = a.tensor();
+    void *st = a.stream();
+    if (a.ok) a.need(heads_ok(qkv, q, kt, v));
+    if (!a.ok) return general();
+    const void *fp = ptr(qkv);
+    void *qp = ptr(q), *kp = ptr(kt), *vp = ptr(v);
+    const int64_t batch = q->size(0);
+    const int32_t heads = (int32_t)q->size(1), tokens = (int32_t)q->size(2), dim = (int32_t)q->size(3), dt = dtype_of(qkv);
+    SLIMFIT_RUN(split_heads_fn(fp, dt, batch, tokens, heads, dim, scale, qp, kp, vp, st));
+}
+
+PyObject *merge_heads(PyObject *, PyObject *const *args, Py_ssize_t n_args)
+{
+    Args a(args, n_args, 6);
+    const at::Tensor *q = a.tensor(), *kt = a.tensor(), *v = a.tensor();
+    const float scale = a.f32();
+    const at::Tensor *qkv = a.tensor();
+    void *st = a.stream();
+    if (a.ok) a.need(heads_ok(qkv, q, kt, v));
+    if (!a.ok) return general();
+    void *fp = ptr(qkv);
+    const void *qp = ptr(q), *kp = ptr(kt), *vp = ptr(v);
+    const int64_t batch = q->size(0);
+    const int32_t heads = (int32_t)q->size(1), tokens = (int32_t)q->size(2), dim = (int32_t)q->size(3), dt = dtype_of(qkv);
+    SLIMFIT_RUN(merge_heads_fn(qp, kp, vp, dt, batch, tokens, heads, dim, scale, fp, st));
+}
+
 // a C++ exception must not cross into the interpreter (torch's allocator raises one when memory runs out: the general
 // path, which asks again, raises torch's own)
 template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
@@ -554,7 +596,7 @@ PyMethodDef methods[] = {
     METHOD(quant_pack), METHOD(dequant_unpack), METHOD(gelu_quant_pack), METHOD(gelu_backward_dequant), METHOD(prune_scores),
     METHOD(restore_scores), METHOD(softmax_prune), METHOD(softmax_backward_pruned), METHOD(prune_global_standardized),
     METHOD(layernorm_forward), METHOD(layernorm_backward), METHOD(layernorm_backward_pruned), METHOD(layernorm_forward_quant_pack),
-    METHOD(layernorm_backward_dequant), METHOD(layernorm_param_grads), METHOD(layer_delta_run),
+    METHOD(layernorm_backward_dequant), METHOD(layernorm_param_grads), METHOD(layer_delta_run), METHOD(split_heads), METHOD(merge_heads),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
