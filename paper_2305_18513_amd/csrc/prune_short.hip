@@ -15,6 +15,8 @@
 //   select   each lane keeps the largest CH keys of its segment in a sorted
 //            register list: inserting a key is one v_max plus CH-1 v_med3
 //            (new s[i] = median(s[i-1], s[i], key)), no branch, no cross-lane step.
+//            Where a lane has many, only the larger of two neighbours is inserted,
+//            and the partners of those that stayed afterwards.
 //            A key carries the entry's column below its value (bf16: the 16 value
 //            bits and the column; fp32: the upper 24 bits of the value's image and
 //            the column), so ties go to the lower column and the list itself names
@@ -79,6 +81,15 @@ __device__ __forceinline__ void chain_insert(int (&s)[CH], int key)
 #pragma unroll
     for (int i = CH - 1; i >= 1; --i) s[i] = med3_i32(s[i - 1], s[i], key);
     s[0] = max(s[0], key);
+}
+
+// the same for a key that is not above s[J]
+template <int CH, int J>
+__device__ __forceinline__ void chain_insert_below(int (&s)[CH], int key)
+{
+#pragma unroll
+    for (int i = CH - 1; i >= J + 2; --i) s[i] = med3_i32(s[i - 1], s[i], key);
+    s[J + 1] = max(s[J + 1], key);
 }
 
 // the same for b[0] >= b[1] >= ...: b[j] cannot land above position j
@@ -165,6 +176,12 @@ struct ShortRows {
     static constexpr int LANE_BITS = G == 2 ? 1 : (G == 4 ? 2 : 3);
     static constexpr int TAG_BITS = 8 - LANE_BITS;             // entry's rank inside the lane's segment (at most 256 columns)
     static constexpr int N_OUT = (R * K + kWave - 1) / kWave;  // output pairs a lane stores
+    // Whether the larger of two neighbours stands for both in the selection's walk: where a lane has 65 (bf16) or 33 (fp32)
+    // entries or more (rows of more than 128 columns; NV is 4, 8, 13 or 16).  bf16 806 912 x 197, k = 9: 86.5 -> 78.0 us,
+    // 49 152 x 160, k = 16 12.5 -> 11.8, x 250, k = 12 14.1 -> 12.7; fp32 302 592 x 197 55.6 -> 54.2.  With fewer entries
+    // the partners cost as much or more: bf16 98 304 x 100 9.3 / 9.3, x 70 7.9 -> 8.1; fp32 x 50 8.0 -> 8.4, 196 608 x 33
+    // 9.7 -> 10.5.
+    static constexpr bool kPaired = NV >= 13;
 
     // Visits the lane's entries e = 0 .. E-1 in column order: f(e, bits, ok) with the entry's bits (fp32: its
     // 32; bf16: its 16, zero-extended, or sign-extended when SEXT) and ok = "this lane has an entry e".  seg:
@@ -248,14 +265,39 @@ struct ShortRows {
             if constexpr (!NEG && Held::HELD) held.each_held([&](int e, int bits) { f(e, bits, true); });
             else for_each_entry<NEG>(seg, E, len, e_all, f);
         };
+        // the earlier entry of the segment ranks higher
+        auto key_of = [&](int e, int bits) -> int {
+            if constexpr (BF) return (int)(((uint32_t)(NEG ? signed_key_16(bits) : bits) << 16) | (uint32_t)(TAG_TOP - e));
+            else return ((NEG ? signed_key_f32((uint32_t)bits) : bits) & value_mask) | (TAG_TOP - e);
+        };
+        // PAIRED: of entries 2i and 2i + 1 only the larger goes into the list.  A lane's largest entries are then those in
+        // the list or their partners: one that is not the larger of its pair has that one above it, so the pair is in the
+        // list or CHP larger entries are.  Half as many insertions, then CHP - 1 short ones.
+        constexpr bool PAIRED = kPaired && !Held::HELD;
+        int waiting = INT_MIN;
         walk([&](int e, int bits, bool ok) {
-            // the tag is wave-uniform: the earlier entry of the segment ranks higher
             int key;
-            if constexpr (BF) key = (int)(((uint32_t)(NEG ? signed_key_16(bits) : bits) << 16) | (uint32_t)(TAG_TOP - e));
-            else if constexpr (!NEG && Held::HELD) key = (bits & value_mask) | (TAG_TOP - e);      // (e is a constant)
-            else key = and_or_i32(NEG ? signed_key_f32((uint32_t)bits) : bits, value_mask, TAG_TOP - e);
-            chain_insert<CHP>(m, ok ? key : INT_MIN);
+            if constexpr (!BF && (NEG || !Held::HELD)) key = and_or_i32(NEG ? signed_key_f32((uint32_t)bits) : bits, value_mask, TAG_TOP - e);
+            else key = key_of(e, bits);                     // (fp32: e is a constant here, wave-uniform above)
+            key = ok ? key : INT_MIN;
+            if (!PAIRED) chain_insert<CHP>(m, key);
+            else if (e & 1) chain_insert<CHP>(m, max(waiting, key));
+            else waiting = key;
         });
+        if constexpr (PAIRED) {
+            if (E & 1) chain_insert<CHP>(m, waiting);
+            int partner[CHP - 1];
+#pragma unroll
+            for (int j = 0; j < CHP - 1; ++j) {
+                const int other = (TAG_TOP - (m[j] & TAG_TOP)) ^ 1;
+                const bool has = m[j] != INT_MIN && other < len;
+                int bits;
+                if constexpr (BF) bits = NEG ? (int)(int16_t)seg[has ? other : 0] : (int)seg[has ? other : 0];
+                else bits = (int)__builtin_bit_cast(uint32_t, seg[has ? other : 0]);
+                partner[j] = has ? key_of(other, bits) : INT_MIN;
+            }
+            static_for(std::make_integer_sequence<int, CHP - 1>{}, [&](auto j) { chain_insert_below<CHP, j>(m, partner[j]); });
+        }
 #pragma unroll
         for (int i = 0; i < CHP; ++i) m[i] |= (G - 1 - q) << TAG_BITS;     // lanes of lower columns rank higher
         merge_row<G, CHP>(m);

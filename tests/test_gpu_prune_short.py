@@ -132,3 +132,30 @@ def test_rows_enough_for_several_a_wave(dtype, cols, k, rows):
     _run_both(p, k, restore=False)
     for tau in (1.3 / cols, 0.0, float(torch.tensor(0x3C000080, dtype=torch.int32).view(torch.float32))):
         _run_both(p, k, mode=sf.PRUNE_THRESHOLD, tau=tau, restore=False)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols", [129, 130, 131, 160, 161, 197, 199, 207, 208, 209, 250, 255])
+def test_rows_whose_neighbours_are_selected_together(cols, dtype):
+    """More than 128 columns: the walk takes entries in twos.  Odd and even parts, the largest entries side by side, apart,
+    at the ends of the lanes' parts, equal to one another, all of them of one sign or the other."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    bf16 = dtype == torch.bfloat16
+    for k in (1, 2, 9, 16) if bf16 else (1, 2, 9):
+        x = torch.softmax(torch.randn(20000 + 5, cols, generator=g, device="cuda") * 3, -1)
+        lane = -(-cols // (2 if bf16 else 4))                              # entries of a lane
+        ends = [c for q in range(4) for c in (q * lane - 2, q * lane - 1, q * lane, q * lane + 1) if 0 <= c < cols] + [cols - 2, cols - 1]
+        x[1] = torch.arange(cols, device="cuda") / 1024.0                  # ascending: every pair's larger entry is its second
+        x[2] = x[1].flip(0)
+        x[3, :k] = 2.0 + torch.arange(k, device="cuda") / 64.0             # side by side
+        x[4, cols - k:] = 2.0
+        x[5, ::2] = 1.0                                                    # the first of every pair
+        x[6, 1::2] = 1.0
+        x[7, ends] = 3.0
+        x[8] = -x[8] - 1.0                                                 # no positive entry
+        x[9, k:] = -1.0                                                    # just as many positive ones as are kept
+        x[10], x[11], x[12] = 0.5, 0.0, -0.0
+        x[13, 1::2] = 0.0                                                  # masked neighbours
+        _run_both(x.to(dtype), k, sf.PRUNE_TOPK, 0.0)
+        _run_both(x.to(dtype), k, sf.PRUNE_THRESHOLD, 0.25)
