@@ -236,3 +236,29 @@ def test_short_rows_around_the_widths_that_change_kernels(cols, dtype):
         _run_both(l.to(dtype), k)
         if cols in (129, 255) and k == 9:
             _run_both(l[: rows - 6].to(dtype), k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols", [33, 64, 95, 127, 130, 197, 208, 255])
+def test_short_rows_whose_cut_is_at_or_below_zero(cols, dtype):
+    """Just as many, one more and one fewer unsigned logits than are kept: which selection runs goes by their number.  Zeros of
+    both signs at the cut, all rows of a wave and one of them, signed NaN-free extremes."""
+    require_gpu()
+    rows = 24000 + 7 if cols >= 128 else 45
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    k = 9
+    for base in (torch.randn(rows, cols, generator=g, device="cuda") * 3, -torch.rand(rows, cols, generator=g, device="cuda") - 0.5):
+        l = base.clone()
+        for r, n in ((1, k - 1), (2, k), (3, k + 1)):
+            l[r] = -l[r].abs() - 0.25
+            l[r, torch.randperm(cols, generator=g, device="cuda")[:n]] = torch.arange(1.0, n + 1, device="cuda")
+        l[4], l[5] = 0.0, -0.0
+        l[6, ::2] = 0.0
+        l[6, 1::2] = -0.0
+        l[7] = -l[7].abs() - 1.0
+        l[7, cols - k:] = 0.0
+        l[8] = -1e9
+        l[8, :k] = -1.0
+        l[9] = -3.0e38
+        l[rows - 1] = -l[rows - 1].abs() - 1.0
+        _run_both(l.to(dtype), k)
