@@ -27,7 +27,7 @@ int32_t launch_status();                                    // hipGetLastError -
 // short rows that keep few entries have a kernel of their own (prune_short.hip)
 constexpr int kShortPruneMaxCols = 256;
 constexpr int kShortPruneMaxK = 16;                     // bf16 rows
-constexpr int kShortPruneMaxKF32 = 9;                   // fp32 rows
+constexpr int kShortPruneMaxKF32 = 12;                  // fp32 rows
 bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, bool softmax);
 void launch_prune_short(const void *p, int32_t dt, int64_t rows, int cols, int k, int mode, float tau, void *vals,
                         uint16_t *idx, int32_t *counts, hipStream_t st);

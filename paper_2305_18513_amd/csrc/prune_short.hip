@@ -772,11 +772,11 @@ void launch_softmax_short_k(const T *p, const ShortArgs &a, T *probs, T *vals, u
     else if (a.k <= 4) launch_softmax_short_nv<T, WIDE, 4>(p, a, probs, vals, idx, st);
     else if (a.k <= 6) launch_softmax_short_nv<T, WIDE, 6>(p, a, probs, vals, idx, st);
     else if (a.k <= 9) launch_softmax_short_nv<T, WIDE, 9>(p, a, probs, vals, idx, st);
-    else if constexpr (sizeof(T) == 2) {
-        if (a.k <= 12) launch_softmax_short_nv<T, WIDE, 12>(p, a, probs, vals, idx, st);
-        else launch_softmax_short_nv<T, WIDE, 16>(p, a, probs, vals, idx, st);
-    }
+    else if (a.k <= 12) launch_softmax_short_nv<T, WIDE, 12>(p, a, probs, vals, idx, st);
+    else if constexpr (sizeof(T) == 2) launch_softmax_short_nv<T, WIDE, 16>(p, a, probs, vals, idx, st);
 }
+
+constexpr int kShortLongListF32 = 9;       // fp32 rows that keep more have lines of their own (prune_short_eligible)
 
 template <typename T, int G, int K, int NV>
 void launch_short(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int32_t *counts, hipStream_t st)
@@ -797,8 +797,10 @@ void launch_short_nv(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int
     const int nv = (R * a.cols * (int)sizeof(T) / 16 + kWave - 1) / kWave;      // rounds of 64 vectors a piece takes
     if (nv <= 4) launch_short<T, G, K, 4>(p, a, vals, idx, counts, st);
     else if (nv <= 8) launch_short<T, G, K, 8>(p, a, vals, idx, counts, st);
-    else if (nv <= 13) launch_short<T, G, K, 13>(p, a, vals, idx, counts, st);   // 197 columns
-    else launch_short<T, G, K, 16>(p, a, vals, idx, counts, st);
+    else if constexpr (sizeof(T) == 2 || K <= kShortLongListF32) {     // (fp32 rows of the longest lists have under 128 columns)
+        if (nv <= 13) launch_short<T, G, K, 13>(p, a, vals, idx, counts, st);   // 197 columns
+        else launch_short<T, G, K, 16>(p, a, vals, idx, counts, st);
+    }
 }
 
 template <typename T, int G>
@@ -808,17 +810,22 @@ void launch_short_k(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int3
     else if (a.k <= 4) launch_short_nv<T, G, 4>(p, a, vals, idx, counts, st);
     else if (a.k <= 6) launch_short_nv<T, G, 6>(p, a, vals, idx, counts, st);
     else if (a.k <= 9) launch_short_nv<T, G, 9>(p, a, vals, idx, counts, st);
-    else if constexpr (sizeof(T) == 2) {               // (fp32 rows that keep more than 9 entries are not routed here)
-        if (a.k <= 12) launch_short_nv<T, G, 12>(p, a, vals, idx, counts, st);
-        else launch_short_nv<T, G, 16>(p, a, vals, idx, counts, st);
-    }
+    else if (a.k <= 12) launch_short_nv<T, G, 12>(p, a, vals, idx, counts, st);
+    else if constexpr (sizeof(T) == 2) launch_short_nv<T, G, 16>(p, a, vals, idx, counts, st);
 }
 
 }  // namespace
 
 // Which short rows come here rather than to the wave-per-row kernel (prune.hip).  Both were measured on 33 .. 256 columns
 // and 2048 .. 196 608 rows; times are this kernel's against the other's, in us:
-//  - few enough kept entries: the list insertion grows with k (fp32 rows that keep 12 or 16 lose 15 - 45 %);
+//  - few enough kept entries: the list insertion grows with k.  fp32 rows that keep 13 to 16 lose (196 608 x 140, k = 14:
+//    softmax 74 against 63, pruning 46 against 44).  Those that keep 10 to 12 gain from 32 768 rows on up to 96 columns (98 304
+//    rows: softmax of 64 columns 18.9 against 29.8, pruning 14.4 / 19.5; 24 576 rows: pruning of 80 columns 8.0 / 8.8, softmax of
+//    90 10.6 / 11.2 but negative logits 13.6 / 11.2; 20 480 x 96 with a threshold 8.7 / 8.2) and on 65 536 rows of more: pruning of 97 to 127 columns (100 columns 13.4 / 16.3, 127 15.3 / 16.6, with a
+//    threshold 16.4 / 16.3; 49 152 x 127 13.4 / 13.6 and 14.1 / 13.5) and of no more (49 152 x 197 18.7 / 15.9), softmax of all
+//    but 128 and 192 (98 304 x 192 34.6 / 33.5; 196 608 rows: 100 columns 49 / 56, 160 59 / 63, 200 69 / 76, 255 82 / 115; 32 768
+//    rows: 160 14.3 / 14.3, 255 18.2 / 20.9 but negative logits 22.9 / 20.9).  There masked rows gain most (196 608 x 100 79 /
+//    134) and constant rows lose in softmax (96 / 52, x 200 129 / 75) and gain in pruning (98 304 x 112 31 / 43);
 //  - strides that spread over the LDS banks: the lanes of a wave read the same entry of 16 rows at once, and at a
 //    stride of a multiple of 64 dwords those lie in one bank (196 608 rows, fp32 pruning, from 128 columns on: 105 against
 //    47 at 256, 54 against 38 at 128, but 18 against 34 at 64).  Softmax, whose fp32 waves hold 8 rows, loses on 256 columns
@@ -837,13 +844,18 @@ void launch_short_k(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int3
 // bisection to the last bit, 98 304 x 192 62 us here, 85 there, 16 384 x 197 12 and 20; constant rows 61 and 70, 12 and 16.
 // fp32 softmax rows of zeros take the signed pass and the exact route here, 24 576 x 197 20.6 us and 14.6 there (few distinct
 // logits the other way: 15.1 and 30.3).
-constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 24000;
+constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 24000, kLongListMinRows = 65536,
+                  kLongListMinRowsNarrow = 32768;
 
 bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, bool softmax)
 {
     const bool bf16 = dt == SLIMFIT_BF16;
     if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32) || rows > (int64_t)0x7FFFFFFF * 8) return false;
     if (!aligned_to(p, 16)) return false;              // (the rows are staged with 16-byte loads)
+    if (!bf16 && k > kShortLongListF32) {
+        if (cols <= 96) return rows >= kLongListMinRowsNarrow;
+        return rows >= kLongListMinRows && (softmax ? cols % 64 != 0 : cols < 128);
+    }
     if (softmax) return cols != 256 && (cols < 128 || rows >= (bf16 ? kShortMinRows : kShortMinRowsSoftmaxF32));
     if (bf16) return true;
     return !(cols >= 128 && cols % 64 == 0) && (cols < 128 || rows >= kShortMinRows);

@@ -159,3 +159,24 @@ def test_rows_whose_neighbours_are_selected_together(cols, dtype):
         x[13, 1::2] = 0.0                                                  # masked neighbours
         _run_both(x.to(dtype), k, sf.PRUNE_TOPK, 0.0)
         _run_both(x.to(dtype), k, sf.PRUNE_THRESHOLD, 0.25)
+
+
+@pytest.mark.parametrize("cols,rows", [(12, 32769), (33, 32771), (64, 32768), (64, 32767), (95, 32770), (96, 32768), (97, 65536), (97, 65535),
+                                       (112, 65537), (127, 65539), (128, 65536)])
+def test_fp32_rows_that_keep_ten_to_twelve(cols, rows):
+    """Longer lists, on as many rows as the kernel takes them for and on one fewer; 24-bit buckets across the cut."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    for k in (10, 12):
+        x = torch.softmax(torch.randn(rows, cols, generator=g, device="cuda") * 3, -1)
+        x[1] = torch.arange(cols, device="cuda") / 1024.0
+        x[2] = x[1].flip(0)
+        x[3], x[4] = 0.5, -0.0
+        x[5] = -x[5] - 1.0
+        x[6, min(k, cols - 1):] = 0.0                                      # masked from there on
+        x[7, k - 1:] = -1.0
+        x[8] = (torch.full((cols,), 0x3F800000, dtype=torch.int32, device="cuda")
+                + torch.arange(cols, dtype=torch.int32, device="cuda") % 7).view(torch.float32)     # 1 + j 2^-23
+        x[rows - 1, cols - k:] = 2.0                                       # the last row, of a wave that is not full
+        _run_both(x, k, sf.PRUNE_TOPK, 0.0, restore=False)
+        _run_both(x, k, sf.PRUNE_THRESHOLD, 0.25, restore=False)

@@ -262,3 +262,21 @@ def test_short_rows_whose_cut_is_at_or_below_zero(cols, dtype):
         l[9] = -3.0e38
         l[rows - 1] = -l[rows - 1].abs() - 1.0
         _run_both(l.to(dtype), k)
+
+
+@pytest.mark.parametrize("cols,rows", [(12, 32769), (64, 32768), (64, 32767), (95, 32770), (96, 32771), (97, 65536), (97, 65535), (127, 65537),
+                                       (128, 65536), (129, 65538), (192, 65536), (197, 65536), (224, 65539), (255, 65541), (256, 65536)])
+def test_fp32_rows_that_keep_ten_to_twelve(cols, rows):
+    """Longer lists, on as many rows as the short-row kernel takes them for and on one fewer."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    for k in (10, 12):
+        l = torch.randn(rows, cols, generator=g, device="cuda") * 3
+        l[1] = -l[1].abs() - 2.0
+        l[2] = torch.randint(-1, 2, (cols,), generator=g, device="cuda").float()
+        l[3], l[4] = 0.0, 2.5
+        l[5, k:] = -1e9                                                    # as many columns as are kept, the rest masked
+        l[6, cols - 2:] = 40.0
+        l[7] = (torch.full((cols,), 0x3F800000, dtype=torch.int32, device="cuda")
+                + torch.arange(cols, dtype=torch.int32, device="cuda") % 7).view(torch.float32)     # 1 + j 2^-23
+        _run_both(l, k)
