@@ -236,8 +236,8 @@ struct ShortRows {
     // the positive entries correctly and puts everything else (zeros of either sign, negative values in reversed
     // order) below them: enough whenever every kept entry is positive.  The plain pass notices when that fails for
     // one of the wave's rows and returns false before it has written anything; the caller then runs the signed pass.
-    // Held: entries that are in registers already: each_held(f) visits the lane's as f(e, bits), those that it does not
-    // have as -inf (below every kept entry of a plain pass).  The kept columns are left in oc, kept is the row's count.
+    // Held: entries that are in registers already: each_held<NEG>(f) visits the lane's as f(e, bits, ok), and a row of one
+    // value (constant_rows) keeps its first columns: it neither starts the selection over nor takes the exact route.  The kept columns are left in oc, kept is the row's count.
     struct NotHeld {
         static constexpr bool HELD = false;
     };
@@ -262,7 +262,7 @@ struct ShortRows {
         asm("" : "+v"(value_mask));                        // in a register, not a literal at every use
         // f(e, bits, ok) for the lane's entries, from registers if they are there
         auto walk = [&](auto f) {
-            if constexpr (!NEG && Held::HELD) held.each_held([&](int e, int bits) { f(e, bits, true); });
+            if constexpr (Held::HELD) held.template each_held<NEG>(f);
             else for_each_entry<NEG>(seg, E, len, e_all, f);
         };
         // the earlier entry of the segment ranks higher
@@ -277,7 +277,7 @@ struct ShortRows {
         int waiting = INT_MIN;
         walk([&](int e, int bits, bool ok) {
             int key;
-            if constexpr (!BF && (NEG || !Held::HELD)) key = and_or_i32(NEG ? signed_key_f32((uint32_t)bits) : bits, value_mask, TAG_TOP - e);
+            if constexpr (!BF && !Held::HELD) key = and_or_i32(NEG ? signed_key_f32((uint32_t)bits) : bits, value_mask, TAG_TOP - e);
             else key = key_of(e, bits);                     // (fp32: e is a constant here, wave-uniform above)
             key = ok ? key : INT_MIN;
             if (!PAIRED) chain_insert<CHP>(m, key);
@@ -309,13 +309,14 @@ struct ShortRows {
         int kk = k;
         bool exact = false;                                 // this row has to take the exact route (fp32 only)
         uint32_t c[K];                                      // kept (column << 16 | bf16 value bits), kNoPair beyond kk
+        bool plain_ok = true;
         if constexpr (!NEG) {
             // all kept entries positive?  With k entries kept: the k-th largest is; with fewer (a threshold run): tau is.
             int cut_value = 0;
 #pragma unroll
             for (int i = 0; i < K; ++i) cut_value = (i == k - 1) ? m[i] >> (BF ? 16 : TAG_BITS + LANE_BITS) : cut_value;
-            const bool plain_ok = cut_value > 0 || (a.mode == SLIMFIT_PRUNE_THRESHOLD && a.tau > 0.0f);
-            if (__builtin_amdgcn_ballot_w64(!plain_ok) != 0) return false;
+            plain_ok = cut_value > 0 || (a.mode == SLIMFIT_PRUNE_THRESHOLD && a.tau > 0.0f);
+            if (!Held::HELD && __builtin_amdgcn_ballot_w64(!plain_ok) != 0) return false;
         }
         if constexpr (BF) {
             auto bits_of = [&](int key) -> uint32_t {
@@ -358,6 +359,15 @@ struct ShortRows {
             for (int i = 0; i < K; ++i) c[i] = i < kk ? (uint32_t)min(column_of(m[i]), cols - 1) << 16 : kNoPair;
         }
 
+        if constexpr (Held::HELD) {
+            if (__builtin_amdgcn_ballot_w64(exact || !plain_ok) != 0) {
+                const bool constant = held.constant_rows();
+                if (!NEG && __builtin_amdgcn_ballot_w64(!plain_ok && !constant) != 0) return false;
+                exact = exact && !constant;
+#pragma unroll
+                for (int i = 0; i < K; ++i) c[i] = constant ? (i < k ? (uint32_t)i << 16 : kNoPair) : c[i];
+            }
+        }
         uint32_t *orow = oc + r * k;
         const bool any_exact = !BF && (SLIMFIT_SHORT_FORCE_EXACT || __builtin_amdgcn_ballot_w64(exact) != 0);
         if (!any_exact) {
@@ -597,18 +607,55 @@ struct HeldRows {
             if (i * kBlk < E) f(std::integral_constant<int, i * kBlk>{});          // wave-uniform
         });
     }
-    template <typename F>
+    // f(entry, its bits, whether the lane has it): bf16 16 bits, sign-extended with NEG; entries that the lane lacks are
+    // -inf, below every kept entry of a plain pass, which is not told of them
+    template <bool NEG, typename F>
     __device__ __forceinline__ void each_held(F f) const
     {
         each_block([&](auto e0) {
+            const bool whole = !NEG || e0 + kBlk <= e_all;
 #pragma unroll
-            for (int u = 0; u < kBlk; ++u) f(e0 + u, (int)(__builtin_bit_cast(uint32_t, x[e0 + u]) >> (BF ? 16 : 0)));
+            for (int u = 0; u < kBlk; ++u) {
+                const int bits = __builtin_bit_cast(int, x[e0 + u]);
+                f(e0 + u, !BF ? bits : (NEG ? bits >> 16 : (int)((uint32_t)bits >> 16)), whole || e0 + u < len);
+            }
         });
+    }
+    // Is the row's every entry its first one?  Asked where a row would need a second pass, and so by the wave's whole; only
+    // where the first three entries of each lane of some row agree are the staged rows walked for it (few rows' waves decide
+    // how long a launch of few rows takes: 24 576 x 192 8.7 us without, 9.5 with the walk for all, 8.7 with this).
+    __device__ __forceinline__ bool constant_rows() const
+    {
+        auto bits_of = [](T v) -> uint32_t {
+            if constexpr (BF) return v;
+            else return __builtin_bit_cast(uint32_t, v);
+        };
+        auto held_bits = [&](int e) { return __builtin_bit_cast(uint32_t, x[e]); };
+        uint64_t alike = __builtin_amdgcn_ballot_w64(len < 3 || (held_bits(0) == held_bits(1) && held_bits(0) == held_bits(2)));
+        alike &= alike >> 1;                                // of all the lanes of a row
+        if (G >= 4) alike &= alike >> 2;
+        if (G >= 8) alike &= alike >> 4;
+        constexpr uint64_t firsts = G == 2 ? 0x5555555555555555u : (G == 4 ? 0x1111111111111111u : 0x0101010101010101u);
+        if ((alike & firsts) == 0) return false;
+        const uint32_t first = bits_of(seg[-(lane % G) * E]);
+        uint32_t differs = 0u;
+#pragma unroll 1
+        for (int e0 = 0; e0 < E; e0 += kBlk) {
+            uint32_t b[kBlk];
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) b[u] = bits_of(seg[e0 + u]) ^ first;
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) differs |= e0 + u < len ? b[u] : 0u;
+        }
+        differs |= dpp_u32<kDppXor1>(differs);
+        if constexpr (G >= 4) differs |= dpp_u32<kDppXor2>(differs);
+        if constexpr (G >= 8) differs |= dpp_u32<kDppHalfMirror>(differs);
+        return differs == 0u;
     }
     // Has some row of the wave fewer than k entries without a sign?  Its k-th largest is negative then, and the selection on
     // plain bit patterns would be for nothing.  One instruction an entry: the signs are shifted into a register.  us with
     // both selections / with this: negative logits 302 592 x 197 fp32 118 / 97, 806 912 x 197 bf16 213 / 195; nine tenths
-    // masked 108 / 88, 211 / 195; plain rows 89.5 / 92.0, 170 / 170.  (Constant rows of zeros still take both.)
+    // masked 108 / 88, 211 / 195; plain rows 89.5 / 92.0, 170 / 170.  (Zeros have no sign: a row that they cut takes both.)
     __device__ __forceinline__ bool cut_is_negative(int k) const
     {
         uint32_t signs[(kMost + 31) / 32] = {};

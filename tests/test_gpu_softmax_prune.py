@@ -280,3 +280,60 @@ def test_fp32_rows_that_keep_ten_to_twelve(cols, rows):
         l[7] = (torch.full((cols,), 0x3F800000, dtype=torch.int32, device="cuda")
                 + torch.arange(cols, dtype=torch.int32, device="cuda") % 7).view(torch.float32)     # 1 + j 2^-23
         _run_both(l, k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols", [12, 33, 64, 79, 96, 97, 128, 192, 197, 255])
+def test_rows_of_one_value_among_others(cols, dtype):
+    """One row of a wave, some and all of them constant (zeros of either sign, positive, negative); rows whose every lane
+    begins with equal entries and that differ later; masked rows of fewer finite entries than are kept, whose cut is -inf."""
+    require_gpu()
+    rows = 65536 + 9 if cols >= 128 else 40000 + 9
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    value = torch.tensor([0.0, -0.0, 2.5, -2.5], device="cuda")
+    for k in (1, 9, 12) if dtype == torch.float32 else (9, 16):
+        if k > cols:
+            continue
+        l = torch.randn(rows, cols, generator=g, device="cuda") * 3
+        l[8:264] = value.repeat_interleave(64)[:, None]                    # whole waves
+        l[264:520:16] = value.repeat(4)[:, None]                           # one row of each
+        l[520:776:2] = value.repeat(32)[:, None]
+        for lanes in (2, 4, 8):                                            # the first entries of every lane's part alike
+            part = -(-cols // lanes)
+            l[776 + lanes * 8: 784 + lanes * 8, (torch.arange(cols, device="cuda") % part) < 3] = 0.5
+        l[850:860] = -1.0
+        l[850:860, cols - 1] = torch.arange(-5.0, 5.0, device="cuda")      # constant but for the last
+        l[860:870, max(1, k // 2):] = float("-inf")
+        l[870:880] = -l[870:880].abs()
+        l[870:880, : cols - max(1, k // 2)] = float("-inf")
+        l[rows - 1] = 0.0
+        _run_both(l.to(dtype), k)
+
+
+def test_rows_of_one_value_cost_no_second_pass():
+    """Zeros, a value of either sign, and zeros in one row of sixteen: a wave that meets them selects once.  (With a second
+    selection and two more walks over the rows such calls took 1.5 to 2 times as long as plain ones.)"""
+    require_gpu()
+    rows, cols, k = 98304, 197, 9
+    plain = torch.randn(rows, cols, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    some = plain.clone()
+    some[::16] = 0.0
+    probs = torch.empty_like(plain)
+    vals, idx = torch.empty(rows, k, device="cuda"), torch.empty(rows, k, dtype=torch.uint16, device="cuda")
+
+    def least(l):
+        times = []
+        for _ in range(12):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(10):
+                sf.softmax_prune(l, k, probs, vals, idx)
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1))
+        return min(times)
+
+    least(plain)                                                           # clocks up
+    base = least(plain)
+    for l in (some, torch.zeros_like(plain), torch.full_like(plain, 2.5)):
+        assert least(l) < 1.3 * base
