@@ -28,7 +28,7 @@ int32_t launch_status();                                    // hipGetLastError -
 constexpr int kShortPruneMaxCols = 256;
 constexpr int kShortPruneMaxK = 16;                     // bf16 rows
 constexpr int kShortPruneMaxKF32 = 12;                  // fp32 rows
-bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, bool softmax);
+bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, int mode, bool softmax);
 void launch_prune_short(const void *p, int32_t dt, int64_t rows, int cols, int k, int mode, float tau, void *vals,
                         uint16_t *idx, int32_t *counts, hipStream_t st);
 void launch_softmax_prune_short(const void *logits, int32_t dt, int64_t rows, int cols, int k, void *probs, void *vals,

@@ -1194,11 +1194,11 @@ void launch_prune(const void *p, int64_t rows, int cols, int k, int mode, float 
     T *vv = static_cast<T *>(vals);
     T *pr = static_cast<T *>(probs);
     constexpr int32_t dt = sizeof(T) == 4 ? SLIMFIT_F32 : SLIMFIT_BF16;
-    if (!SOFTMAX && SLIMFIT_PRUNE_SHORT && prune_short_eligible(p, dt, rows, cols, k, SOFTMAX)) {
+    if (!SOFTMAX && SLIMFIT_PRUNE_SHORT && prune_short_eligible(p, dt, rows, cols, k, mode, SOFTMAX)) {
         launch_prune_short(p, dt, rows, cols, k, mode, tau, vals, idx, counts, st);
         return;
     }
-    if (SOFTMAX && SLIMFIT_SOFTMAX_SHORT && prune_short_eligible(p, dt, rows, cols, k, SOFTMAX) && aligned_to(probs, 16)) {
+    if (SOFTMAX && SLIMFIT_SOFTMAX_SHORT && prune_short_eligible(p, dt, rows, cols, k, mode, SOFTMAX) && aligned_to(probs, 16)) {
         launch_softmax_prune_short(p, dt, rows, cols, k, probs, vals, idx, st);      // (the dense rows leave in 16-byte stores)
         return;
     }

@@ -1,6 +1,6 @@
 // Pruning of short score rows that keep few entries (Alg. 5 applied per row; the
 // appendix on pruning), for gfx950: rows of at most 256 columns, k <= 16 (bf16)
-// or k <= 9 (fp32).
+// or k <= 12 (fp32).
 //
 // With 197-column rows a wave that owns one row at a time spends most of its
 // instructions on per-row bookkeeping (wave reductions, a bin scan, scalar
@@ -21,8 +21,8 @@
 //            bits and the column; fp32: the upper 24 bits of the value's image and
 //            the column), so ties go to the lower column and the list itself names
 //            the columns.
-//   merge    the G sorted lists of a row are merged by DPP exchanges inside the
-//            quad (the partner's j-th largest can only land at position >= j).
+//   merge    the G sorted lists of a row are merged by DPP exchanges between its
+//            lanes (the partner's j-th largest can only land at position >= j).
 //   fp32     24 value bits decide the kept set exactly unless the k-th and the
 //            (k+1)-th largest agree in all of them (or, with a threshold, an entry
 //            agrees with the threshold in all of them): about 0.1 % of 197-column
@@ -378,7 +378,7 @@ struct ShortRows {
         }
         if constexpr (!BF) {
             if (any_exact) {
-                // ---- the exact route: full 32-bit images, then a second walk over the registers ----
+                // ---- the exact route: full 32-bit images, then a second walk over the entries ----
                 constexpr int CH = K + 1;
                 int s[CH];
 #pragma unroll
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kWave) void prune_rows_short_kernel(const T *__rest
 // division a row) find it; the probabilities go back over the staged rows and leave for `probs` as one contiguous piece.
 // Bound by the waves' lifetime on few rows and by HBM on many: 87 468 x 197 fp32 37.2 us when selection, maximum,
 // exponentials and scaling each walked the staged rows, 34.2 from registers, 30.4 with eight lanes a row as well (4.7 TB/s);
-// 302 592 rows 100 -> 90 (5.3 TB/s); 806 912 x 197 bf16 202 -> 169 (3.9 TB/s, bound by the list insertion).
+// 302 592 rows 100 -> 87 (5.5 TB/s); 806 912 x 197 bf16 202 -> 162 (4.1 TB/s, bound by the list insertion).
 template <typename T, int G, int K, int NV>
 struct HeldRows {
     using S = ShortRows<T, G, K, NV>;
@@ -622,14 +622,10 @@ struct HeldRows {
         });
     }
     // Is the row's every entry its first one?  Asked where a row would need a second pass, and so by the wave's whole; only
-    // where the first three entries of each lane of some row agree are the staged rows walked for it (few rows' waves decide
-    // how long a launch of few rows takes: 24 576 x 192 8.7 us without, 9.5 with the walk for all, 8.7 with this).
+    // where the first three entries of each lane of some row agree are the others looked at (a few rows' waves decide how long
+    // a launch of few rows takes: 24 576 x 192 8.7 us without this test, 9.5 with all entries at once, 8.7 so).
     __device__ __forceinline__ bool constant_rows() const
     {
-        auto bits_of = [](T v) -> uint32_t {
-            if constexpr (BF) return v;
-            else return __builtin_bit_cast(uint32_t, v);
-        };
         auto held_bits = [&](int e) { return __builtin_bit_cast(uint32_t, x[e]); };
         uint64_t alike = __builtin_amdgcn_ballot_w64(len < 3 || (held_bits(0) == held_bits(1) && held_bits(0) == held_bits(2)));
         alike &= alike >> 1;                                // of all the lanes of a row
@@ -637,16 +633,12 @@ struct HeldRows {
         if (G >= 8) alike &= alike >> 4;
         constexpr uint64_t firsts = G == 2 ? 0x5555555555555555u : (G == 4 ? 0x1111111111111111u : 0x0101010101010101u);
         if ((alike & firsts) == 0) return false;
-        const uint32_t first = bits_of(seg[-(lane % G) * E]);
+        const uint32_t first = (uint32_t)__shfl((int)held_bits(0), lane & ~(G - 1), kWave);
         uint32_t differs = 0u;
-#pragma unroll 1
-        for (int e0 = 0; e0 < E; e0 += kBlk) {
-            uint32_t b[kBlk];
+        each_block([&](auto e0) {
 #pragma unroll
-            for (int u = 0; u < kBlk; ++u) b[u] = bits_of(seg[e0 + u]) ^ first;
-#pragma unroll
-            for (int u = 0; u < kBlk; ++u) differs |= e0 + u < len ? b[u] : 0u;
-        }
+            for (int u = 0; u < kBlk; ++u) differs |= e0 + u < len ? held_bits(e0 + u) ^ first : 0u;
+        });
         differs |= dpp_u32<kDppXor1>(differs);
         if constexpr (G >= 4) differs |= dpp_u32<kDppXor2>(differs);
         if constexpr (G >= 8) differs |= dpp_u32<kDppHalfMirror>(differs);
@@ -654,8 +646,9 @@ struct HeldRows {
     }
     // Has some row of the wave fewer than k entries without a sign?  Its k-th largest is negative then, and the selection on
     // plain bit patterns would be for nothing.  One instruction an entry: the signs are shifted into a register.  us with
-    // both selections / with this: negative logits 302 592 x 197 fp32 118 / 97, 806 912 x 197 bf16 213 / 195; nine tenths
-    // masked 108 / 88, 211 / 195; plain rows 89.5 / 92.0, 170 / 170.  (Zeros have no sign: a row that they cut takes both.)
+    // both selections / with this, while the signed one walked the staged rows: negative logits 302 592 x 197 fp32 118 / 97,
+    // 806 912 x 197 bf16 213 / 195; nine tenths masked 108 / 88, 211 / 195; plain rows 89.5 / 92.0, 170 / 170.  With both
+    // selections from registers 96 and 168, 87 and 164, plain 87 and 162.  (Zeros have no sign: a row that they cut takes both.)
     __device__ __forceinline__ bool cut_is_negative(int k) const
     {
         uint32_t signs[(kMost + 31) / 32] = {};
@@ -781,6 +774,18 @@ __global__ __launch_bounds__(kWave) void softmax_prune_short_kernel(const T *__r
 // x 79 14.7 / 14.0, x 50 10.3 / 8.2.  bf16, four against two: 806 912 x 197 169 / 175, 32 768 x 250 16.2 / 21.1, 8192 x 96
 // 6.9 / 7.6, 98 304 x 96 12.9 / 12.6, x 79 14.2 / 13.4.  (bf16 with eight lanes: 183 at 806 912 x 197.)
 constexpr int kSoftmaxWideCols = 96;
+// With many rows their number hides a wave's lifetime and the one merge more is what counts, and the more so the longer the
+// lists.  fp32, four lanes against eight: k = 9, 49 152 x 100 11.9 / 13.1, 98 304 x 100 20.3 / 22.0, x 112 21.8 / 22.5, x 127
+// 24.7 / 23.5, 196 608 x 100 33.8 / 41.5 (few distinct values 43 / 58), x 120 36 / 41, x 127 42.3 / 43.8, 24 576 x 100 10.9 / 10.0;
+// k = 12, 49 152 x 96 13.7 / 15.6, 196 608 x 100 37 / 50; k = 5, 98 304 x 100 17.3 / 17.8, 196 608 x 100 30.5 / 31.6 but x 96, whose
+// 16 rows lie in two banks, 30.7 / 28.9.
+bool softmax_wide(int32_t dt, int64_t rows, int cols, int k)
+{
+    if (cols < kSoftmaxWideCols) return false;
+    if (dt != SLIMFIT_F32 || cols >= 128 || k <= 4) return true;
+    if (k <= 6) return cols > 112 || cols == 96 || rows < 98304;
+    return rows < (k > 9 || cols <= 112 ? 40000 : 131072);
+}
 
 template <typename T, int G, int K, int NV>
 void launch_softmax_short(const T *p, const ShortArgs &a, T *probs, T *vals, uint16_t *idx, hipStream_t st)
@@ -797,7 +802,7 @@ template <typename T, bool WIDE> constexpr int kSoftmaxLanes = (WIDE ? 2 : 1) * 
 template <typename T, bool WIDE, int K>
 void launch_softmax_short_nv(const T *p, const ShortArgs &a, T *probs, T *vals, uint16_t *idx, hipStream_t st)
 {
-    // rounds of 64 vectors a piece takes when it is 64, 128, 208 (197 columns) or 256 columns wide
+    // rounds of 64 vectors a piece takes when it is 64, 128, 224 (197 columns) or 256 columns wide
     constexpr int G = kSoftmaxLanes<T, WIDE>;
     constexpr int kFull = kWave / G * (int)sizeof(T) * 256 / 16 / kWave, kMost = (kFull * 13 + 15) / 16;
     const int nv = (kWave / G * a.cols * (int)sizeof(T) / 16 + kWave - 1) / kWave;
@@ -867,43 +872,52 @@ void launch_short_k(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int3
 // and 2048 .. 196 608 rows; times are this kernel's against the other's, in us:
 //  - few enough kept entries: the list insertion grows with k.  fp32 rows that keep 13 to 16 lose (196 608 x 140, k = 14:
 //    softmax 74 against 63, pruning 46 against 44).  Those that keep 10 to 12 gain from 32 768 rows on up to 96 columns (98 304
-//    rows: softmax of 64 columns 18.9 against 29.8, pruning 14.4 / 19.5; 24 576 rows: pruning of 80 columns 8.0 / 8.8, softmax of
-//    90 10.6 / 11.2 but negative logits 13.6 / 11.2; 20 480 x 96 with a threshold 8.7 / 8.2) and on 65 536 rows of more: pruning of 97 to 127 columns (100 columns 13.4 / 16.3, 127 15.3 / 16.6, with a
-//    threshold 16.4 / 16.3; 49 152 x 127 13.4 / 13.6 and 14.1 / 13.5) and of no more (49 152 x 197 18.7 / 15.9), softmax of all
-//    but 128 and 192 (98 304 x 192 34.6 / 33.5; 196 608 rows: 100 columns 49 / 56, 160 59 / 63, 200 69 / 76, 255 82 / 115; 32 768
-//    rows: 160 14.3 / 14.3, 255 18.2 / 20.9 but negative logits 22.9 / 20.9).  There masked rows gain most (196 608 x 100 79 /
-//    134) and constant rows lose in softmax (96 / 52, x 200 129 / 75) and gain in pruning (98 304 x 112 31 / 43);
+//    rows: softmax of 64 columns 18.7 against 29.7, pruning 14.4 / 19.5; 24 576 rows: pruning of 80 columns 8.0 / 8.8, softmax of
+//    90 10.6 / 11.2) and from 65 536 rows on with more: pruning of 97 to 127 columns (100 columns 13.4 / 16.3, 127 15.3 / 16.6)
+//    and of no more (49 152 x 197 18.7 / 15.9), softmax of all but 128 and 192 (98 304 x 192 34.6 / 33.5; 196 608 rows: 100
+//    columns 37 / 56, 197 69 / 81, 250 82 / 101; 65 536 rows: 160 with negative logits 25.7 / 24.6).  Not with a threshold: rows
+//    of which fewer than k pass it are done at once in the other kernel (98 304 rows: peaked ones of 64 columns 14.7 / 12.4,
+//    of 112 20.5 / 13.4, masked 20.1 / 13.4; plain ones 15.2 / 18.9 and 21.0 / 22.5);
 //  - strides that spread over the LDS banks: the lanes of a wave read the same entry of 16 rows at once, and at a
 //    stride of a multiple of 64 dwords those lie in one bank (196 608 rows, fp32 pruning, from 128 columns on: 105 against
-//    47 at 256, 54 against 38 at 128, but 18 against 34 at 64).  Softmax, whose fp32 waves hold 8 rows, loses on 256 columns
-//    alone (131 072 rows: fp32 123 against 51, bf16 63 against 53; fp32 224 columns 45 against 51, 192 40 / 42, 160 34 / 43,
-//    128 34 / 37, 96 20 / 39, 64 19 / 37);
+//    47 at 256, 54 against 38 at 128, but 18 against 34 at 64).  Softmax, whose fp32 waves hold 8 rows and go to the LDS once
+//    to take them up and once to lay the probabilities down, loses on 256 columns (131 072 rows: fp32 123 against 51, bf16
+//    63 against 53) and on few rows of 128 and 192 that keep more than 6 (k = 9, 24 576 rows: 192 12.2 against 11.3, negative
+//    logits 14.6 / 11.4, 128 10.9 / 10.8 and 12.2 / 10.8; 49 152 rows: 19.2 / 19.0 and 21.4 / 19.0, 17.2 / 17.6 and 18.4 / 17.6,
+//    few distinct values 23 / 47 and 20 / 42; 196 608 rows: 57 / 62, 52 / 56; k = 6, 24 576 rows: 10.5 / 11.4, 9.3 / 10.6);
 //  - enough rows: a wave takes 8 to 32 of them and needs 7 - 15 us whatever their number, while the other kernel gives
 //    few rows a wave each.  From 128 columns on, at 197 columns: fp32 pruning of 16 384 rows 11.2 against 8.3, 24 576 12.7 /
 //    10.0, 49 152 17.6 / 15.9 (peaked 16.2 against 19.1, nine tenths masked 14.9 against 17.7), 196 608 40 / 47.  bf16
 //    softmax of 16 384 rows 10.6 against 10.8 (250 columns 12.1 / 10.7), 20 000 12.5 / 15.5.  fp32 softmax of 20 000 rows
-//    12.6 against 11.8 (250 columns 13.9 / 12.3), 24 576 12.2 / 14.3, 32 768 14.9 / 17.4, 49 152 20.2 / 25.2.
+//    12.6 against 11.8 (250 columns 13.9 / 12.3), 24 576 12.6 / 14.3, 32 768 14.9 / 17.4, 49 152 19.7 / 25.2.
 //    Below 128 columns the two are within 1 us of one another for few rows (fp32 pruning of 16 384 x 112 7.1 against 7.2)
-//    and this one is ahead from 24 576 on, so their number is not looked at.  Nor is it for bf16 pruning: plain rows gain in
+//    and this one is ahead from 24 576 on, so their number is not looked at but for fp32 softmax of 64 and 96 columns, which
+//    the other kernel has in whole slots (2048 rows, k = 9: 5.3 against 4.8, negative logits 6.6 / 4.7; 8192 rows: 6.2 / 6.4,
+//    7.5 / 6.2, few distinct values 6.9 / 9.9; 16 384 rows 7.2 / 8.5).  Nor is it for bf16 pruning: plain rows gain in
 //    the other kernel at k = 16 (16 384 x 197 9.5 against 8.1), but rows with masked columns, whose zeros share one
 //    histogram bin there, lose more (9.6 against 14.8; peaked 9.5 against 9.7).
 // What stays slower here or there: pruned fp32 rows of few distinct values (logits in steps of a half) take the other kernel's
 // bisection to the last bit, 98 304 x 192 62 us here, 85 there, 16 384 x 197 12 and 20; constant rows 61 and 70, 12 and 16.
-// fp32 softmax rows of zeros take the signed pass and the exact route here, 24 576 x 197 20.6 us and 14.6 there (few distinct
-// logits the other way: 15.1 and 30.3).
-constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 24000, kLongListMinRows = 65536,
+// fp32 softmax rows that are negative throughout, 24 576 x 197 15.7 and 14.3 (plain ones 12.6 and 14.3).
+constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 24000, kStrideMinRowsSoftmaxF32 = 40000,
+                  kNarrowMinRowsSoftmaxF32 = 6000, kLongListMinRows = 65536,
                   kLongListMinRowsNarrow = 32768;
 
-bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, bool softmax)
+bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, int mode, bool softmax)
 {
     const bool bf16 = dt == SLIMFIT_BF16;
     if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32) || rows > (int64_t)0x7FFFFFFF * 8) return false;
     if (!aligned_to(p, 16)) return false;              // (the rows are staged with 16-byte loads)
     if (!bf16 && k > kShortLongListF32) {
+        if (mode == SLIMFIT_PRUNE_THRESHOLD) return false;
         if (cols <= 96) return rows >= kLongListMinRowsNarrow;
         return rows >= kLongListMinRows && (softmax ? cols % 64 != 0 : cols < 128);
     }
-    if (softmax) return cols != 256 && (cols < 128 || rows >= (bf16 ? kShortMinRows : kShortMinRowsSoftmaxF32));
+    if (softmax && bf16) return cols != 256 && (cols < 128 || rows >= kShortMinRows);
+    if (softmax) {
+        if (cols >= 128) return cols != 256 && rows >= (cols % 64 == 0 && k > 6 ? kStrideMinRowsSoftmaxF32 : kShortMinRowsSoftmaxF32);
+        return !(cols >= 64 && cols % 32 == 0) || rows >= kNarrowMinRowsSoftmaxF32;
+    }
     if (bf16) return true;
     return !(cols >= 128 && cols % 64 == 0) && (cols < 128 || rows >= kShortMinRows);
 }
@@ -918,7 +932,7 @@ void launch_softmax_prune_short(const void *logits, int32_t dt, int64_t rows, in
     a.mode = SLIMFIT_PRUNE_TOPK;
     a.tau = 0.0f;
     a.div_magic = 65536u / (uint32_t)k + 1u;
-    const bool wide = cols >= kSoftmaxWideCols;
+    const bool wide = softmax_wide(dt, rows, cols, k);
     auto launch = [&](auto *x) {
         using T = std::remove_pointer_t<decltype(x)>;
         const T *in = static_cast<const T *>(logits);

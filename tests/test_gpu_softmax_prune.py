@@ -217,7 +217,7 @@ def test_hard_rows_for_the_value_bins(cols, k, dtype):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("cols", [17, 64, 65, 95, 96, 97, 127, 128, 129, 192, 208, 209, 224, 225, 255])
 def test_short_rows_around_the_widths_that_change_kernels(cols, dtype):
-    """Lanes to a row change at 96 columns, the registers that hold a lane's part at 64, 128, 208 and 224; the last lane's
+    """Lanes to a row change at 96 columns, the registers that hold a lane's part at 64, 128 and 224; the last lane's
     part is shorter or missing.  A ragged number of rows; from 128 columns on as many as the kernel is for, and one row
     below that."""
     require_gpu()
@@ -337,3 +337,21 @@ def test_rows_of_one_value_cost_no_second_pass():
     base = least(plain)
     for l in (some, torch.zeros_like(plain), torch.full_like(plain, 2.5)):
         assert least(l) < 1.3 * base
+
+
+@pytest.mark.parametrize("cols,line,k", [(64, 6000, 9), (96, 6000, 2), (128, 40000, 9), (192, 40000, 7), (192, 24000, 6), (128, 24000, 2),
+                                         (96, 40000, 12), (100, 40000, 7), (112, 40000, 9), (113, 131072, 9), (127, 131072, 7),
+                                         (97, 98304, 6), (112, 98304, 5), (96, 98304, 6)])
+def test_fp32_row_counts_at_which_kernel_or_lanes_change(cols, line, k):
+    """The same rows on both sides of a line: other kernel or other lanes to a row, the same result."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(cols + k)
+    l = torch.randn(line, cols, generator=g, device="cuda") * 3
+    l[1] = -l[1].abs() - 2.0
+    l[2] = torch.randint(-1, 2, (cols,), generator=g, device="cuda").float()
+    l[3], l[4] = 0.0, -2.5
+    l[5, k:] = -1e9
+    l[6] = (torch.full((cols,), 0x3F800000, dtype=torch.int32, device="cuda")
+            + torch.arange(cols, dtype=torch.int32, device="cuda") % 7).view(torch.float32)         # 1 + j 2^-23
+    _run_both(l, k)
+    _run_both(l[: line - 1], k)
