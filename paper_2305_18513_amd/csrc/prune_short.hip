@@ -40,6 +40,7 @@
 // meets a row whose k-th largest entry is not positive starts over with
 // sign * magnitude keys (-0 and +0 coincide, as float comparison has it).
 #include "common.hpp"
+#include "short_rows.hpp"
 
 #include <climits>
 #include <utility>
@@ -219,7 +220,7 @@ struct ShortRows {
             }
         }
         // the ragged end: entries some lanes do not have.  Such a lane reads a few entries past its segment
-        // (the next row's, or at most three entries past the staged rows: still inside the wave's LDS).
+        // (the next row's, or at most G - 1 entries past the staged rows, which the launch's LDS has room for).
         for (int e0 = n_blk * kBlk; e0 < E; e0 += kBlk) {
 #pragma unroll
             for (int u = 0; u < kBlk; ++u) {
@@ -509,7 +510,7 @@ __global__ __launch_bounds__(kWave) void prune_rows_short_kernel(const T *__rest
     const int lane = threadIdx.x;
     const int cols = a.cols, k = a.k;
     char *slab = reinterpret_cast<char *>(short_lds);
-    const int slab_bytes = (R * cols * (int)sizeof(T) + 15) & ~15;
+    const int slab_bytes = (int)short_rows_bytes(cols, G, (int)sizeof(T));
     uint32_t *oc = reinterpret_cast<uint32_t *>(slab + slab_bytes);        // R * k output slots
     u32x4 *dst_v = reinterpret_cast<u32x4 *>(slab);
 
@@ -573,7 +574,7 @@ struct HeldRows {
     using S = ShortRows<T, G, K, NV>;
     static constexpr bool BF = sizeof(T) == 2, HELD = true;
     static constexpr int PER16 = 16 / (int)sizeof(T);
-    static constexpr int kMost = NV * kWave * 16 / (int)sizeof(T) / kWave, kBlk = 4;    // entries a lane may have
+    static constexpr int kMost = NV * 16 / (int)sizeof(T), kBlk = kShortHeldBlock;      // entries a lane may have
     T *rows;                           // the staged rows (LDS)
     T *seg;                            // the lane's part
     T *out;                            // the wave's piece of the dense rows
@@ -588,7 +589,8 @@ struct HeldRows {
         e_all = max(cols - (G - 1) * E, 0);                // entries every lane has
         seg = rows + r * cols + q * E;
         each_block([&](auto e0) {
-            // (a lane without some of a block's entries reads the next row's, or at most four entries past the rows)
+            // (a lane without some of a block's entries reads the next row's, or at most G + 2 entries past the rows, which
+            // the launch's LDS has room for)
 #pragma unroll
             for (int u = 0; u < kBlk; ++u) x[e0 + u] = BF ? __builtin_bit_cast(float, (uint32_t)seg[e0 + u] << 16) : (float)seg[e0 + u];
         });
@@ -733,7 +735,7 @@ __global__ __launch_bounds__(kWave) void softmax_prune_short_kernel(const T *__r
     const int lane = threadIdx.x;
     const int cols = a.cols, k = a.k;
     char *slab = reinterpret_cast<char *>(short_lds);
-    const int slab_bytes = (R * cols * (int)sizeof(T) + 15) & ~15;
+    const int slab_bytes = (int)short_rows_bytes(cols, G, (int)sizeof(T));
     uint32_t *oc = reinterpret_cast<uint32_t *>(slab + slab_bytes);        // R * k output slots
     u32x4 *slab_v = reinterpret_cast<u32x4 *>(slab);
 
@@ -792,7 +794,7 @@ void launch_softmax_short(const T *p, const ShortArgs &a, T *probs, T *vals, uin
 {
     constexpr int R = kWave / G;
     const int64_t blocks = (a.rows + R - 1) / R;
-    const size_t lds = (size_t)((R * a.cols * (int)sizeof(T) + 15) & ~15) + (size_t)R * (size_t)a.k * 4u;
+    const size_t lds = short_lds_bytes(a.cols, a.k, G, (int)sizeof(T), kShortHeldBlock);
     softmax_prune_short_kernel<T, G, K, NV><<<(unsigned)blocks, kWave, lds, st>>>(p, a, probs, vals, idx);
 }
 
@@ -838,7 +840,7 @@ void launch_short(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int32_
 #ifndef SLIMFIT_SHORT_LDS_PAD
 #define SLIMFIT_SHORT_LDS_PAD 0        // timing experiments only: LDS a wave claims beyond what it uses
 #endif
-    const size_t lds = (size_t)((R * a.cols * (int)sizeof(T) + 15) & ~15) + (size_t)R * (size_t)a.k * 4u + SLIMFIT_SHORT_LDS_PAD;
+    const size_t lds = short_lds_bytes(a.cols, a.k, G, (int)sizeof(T), 1) + SLIMFIT_SHORT_LDS_PAD;
     prune_rows_short_kernel<T, G, K, NV><<<(unsigned)blocks, kWave, lds, st>>>(p, a, vals, idx, counts);
 }
 
