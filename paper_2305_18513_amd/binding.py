@@ -510,7 +510,8 @@ def prune_global(x: torch.Tensor, k: int, vals: torch.Tensor, idx: torch.Tensor,
 def restore_global(vals: torch.Tensor, idx: torch.Tensor, k: int, out: torch.Tensor,
                    tile_ptr: Optional[torch.Tensor] = None, stream=None) -> None:
     _require(out.is_contiguous() and vals.dtype == out.dtype and idx.dtype == torch.int32)
-    _require(tile_ptr is None or tile_ptr.dtype == torch.int32)
+    _require(vals.numel() >= k and idx.numel() >= k)
+    _require(tile_ptr is None or (tile_ptr.dtype == torch.int32 and tile_ptr.numel() >= global_tile_ptr_len(out.numel())))
     rc = lib().slimfit_restore_global(
         _dev(vals), _dev(idx), _dev(tile_ptr), C.c_int64(k), C.c_int32(_dt(out)), C.c_int64(out.numel()),
         _dev(out), _stream(stream))
@@ -665,7 +666,8 @@ def layernorm_backward_pruned(vals: torch.Tensor, idx: torch.Tensor, row_ptr: to
     _require(all(t.dtype == torch.float32 for t in (vals, rstd, gamma)) and dx.dtype == dy.dtype)
     _require(idx.dtype == torch.int32 and row_ptr.dtype == torch.int32)
     rows, H = dy.shape
-    _require(row_ptr.numel() >= rows + 1)
+    _require(row_ptr.numel() >= rows + 1 and vals.numel() >= k and idx.numel() >= k)
+    _require(rstd.numel() >= rows and gamma.numel() >= H)
     rc = lib().slimfit_layernorm_backward_pruned(
         _dev(vals), _dev(idx), _dev(row_ptr), C.c_int64(k), _dev(rstd), _dev(gamma), _dev(dy), C.c_int32(_dt(dy)),
         C.c_int64(rows), C.c_int64(H), _dev(dx), _stream(stream))

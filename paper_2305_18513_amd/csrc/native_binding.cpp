@@ -405,7 +405,8 @@ PyObject *layernorm_backward_pruned(PyObject *, PyObject *const *args, Py_ssize_
     int64_t rows = 0, H = 0;
     if (a.ok)
         a.need(rows_of(dy, rows, H) && activation(dy) && dx->sizes() == dy->sizes() && same_type(dx, dy) && f32(vals) && f32(rstd) &&
-               f32(gamma) && is(idx, at::kInt) && is(row_ptr, at::kInt) && row_ptr->numel() >= rows + 1);
+               f32(gamma) && is(idx, at::kInt) && is(row_ptr, at::kInt) && row_ptr->numel() >= rows + 1 && vals->numel() >= k &&
+               idx->numel() >= k && rstd->numel() >= rows && gamma->numel() >= H);
     if (!a.ok) return general();
     const float *vp = ptr<float>(vals), *rp = ptr<float>(rstd), *gp = ptr<float>(gamma);
     const int32_t *ip = ptr<int32_t>(idx), *row = ptr<int32_t>(row_ptr);

@@ -359,6 +359,24 @@ def test_binding_rejects_outputs_that_are_too_small():
         sf.softmax_backward_pruned(vals, idx, counts[:-1], p, torch.zeros_like(p))
 
 
+def test_binding_rejects_kept_pairs_and_parameters_that_are_too_small():
+    """What the frozen LayerNorm's backward pass and the restore read by a count of their own."""
+    import torch
+    rows, H, k = 8, 64, 40
+    dy = torch.zeros(rows, H)
+    good = dict(vals=torch.zeros(k), idx=torch.zeros(k, dtype=torch.int32), row_ptr=torch.zeros(rows + 1, dtype=torch.int32), k=k,
+                rstd=torch.zeros(rows), gamma=torch.zeros(H), dy=dy, dx=torch.empty_like(dy))
+    for name in ("vals", "idx", "row_ptr", "rstd", "gamma"):
+        with pytest.raises(ValueError):
+            sf.layernorm_backward_pruned(**dict(good, **{name: good[name][:-1]}))
+    n = 5000
+    good = dict(vals=torch.zeros(k), idx=torch.zeros(k, dtype=torch.int32), k=k, out=torch.zeros(n),
+                tile_ptr=torch.zeros(sf.global_tile_ptr_len(n), dtype=torch.int32))
+    for name in ("vals", "idx", "tile_ptr"):
+        with pytest.raises(ValueError):
+            sf.restore_global(**dict(good, **{name: good[name][:-1]}))
+
+
 def test_binding_rejects_layer_lists_of_mixed_dtype_or_size():
     import torch
     a = [torch.zeros(64), torch.zeros(32, dtype=torch.bfloat16)]          # an fp32 vector next to a bf16 matrix
