@@ -10,25 +10,36 @@ There is no fallback: if the library has not been built, loading it raises.
 
 The calls of a training step go through ``_native`` (``csrc/native_binding.cpp``), which reads plain CUDA tensors
 without ctypes; a call that it does not take (it returns NotImplemented) is judged and served by the ctypes code
-below, which all other functions use as well.
+below, which all other functions use as well.  ``_native`` is built against one torch: where it is missing, does not
+load or was built against another, ctypes serves every call, at 2.5 us more each, and loading the library says so.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import Optional, Sequence
 
 import numpy as np
 import torch
 
-try:
-    from . import _native
-except ImportError:                # not built: lib() says so
-    _native = None
-
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libslimfit.so")
-_NATIVE_PATH = os.path.join(_PKG, "_native.so")
+
+
+def _load_native():
+    """(module, None), or (None, why not).  It reads tensor objects by the layout that torch's headers gave them."""
+    try:
+        from . import _native as native
+    except ImportError as e:
+        return None, "it does not load (%s)" % e
+    built = getattr(native, "TORCH", None)
+    if built != torch.__version__:
+        return None, "it was built against torch %s, and this is %s" % (built, torch.__version__)
+    return native, None
+
+
+_native, _native_missing = _load_native()
 
 F32, BF16 = 0, 1
 Q_FIXED, Q_BLOCK = 0, 1
@@ -71,7 +82,7 @@ _lib = None
 
 
 def is_built() -> bool:
-    return os.path.exists(LIB_PATH) and os.path.exists(_NATIVE_PATH)
+    return os.path.exists(LIB_PATH)
 
 
 def lib():
@@ -80,7 +91,7 @@ def lib():
     if _lib is None:
         if not is_built():
             raise RuntimeError(
-                "libslimfit.so or its native binding is missing: build them with "
+                "libslimfit.so is missing: build it with "
                 "`python -m paper_2305_18513_amd.build` (there is no fallback path)")
         L = C.CDLL(LIB_PATH)
         L.slimfit_status_string.restype = C.c_char_p
@@ -94,8 +105,11 @@ def lib():
             fn = getattr(L, name)
             if fn.restype is C.c_int:          # ctypes default
                 fn.restype = C.c_int32
-        from . import _native as native            # (built since this module was loaded: the wrappers stay with ctypes)
-        native.bind(*[C.cast(getattr(L, name), C.c_void_p).value for name in native.CALLS])
+        if _native is not None:
+            _native.bind(*[C.cast(getattr(L, name), C.c_void_p).value for name in _native.CALLS])
+        else:
+            warnings.warn("the native binding is not used, every call goes through ctypes: %s; build it with "
+                          "`python -m paper_2305_18513_amd.build`" % _native_missing, RuntimeWarning)
         _lib = L
     return _lib
 
@@ -110,7 +124,7 @@ def _check(rc: int, where: str) -> None:
 
 
 def _fast(name: str):
-    """The native form of a call; one that takes nothing where it has not been built."""
+    """The native form of a call; one that takes nothing where the module is not used."""
     return getattr(_native, name) if _native is not None else lambda *args: NotImplemented
 
 

@@ -64,7 +64,8 @@ def build_native(verbose: bool = True) -> str:
     includes = [i for p in cpp_extension.include_paths("cuda") for i in ("-isystem", p)]
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE, *includes,
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           '-DSLIMFIT_TORCH="%s"' % torch.__version__, "-I", INCLUDE, *includes,
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "native_binding.cpp"), "-o", tmp,
            "-L", libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     subprocess.run(cmd, check=True)

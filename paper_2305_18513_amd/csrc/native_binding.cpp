@@ -618,7 +618,8 @@ PyMODINIT_FUNC PyInit__native(void)
     }
     SLIMFIT_CALLS(X)
 #undef X
-    if (!names || PyModule_AddObject(m, "CALLS", names) < 0) {
+    // the torch whose headers this was compiled with: binding.py does not use it with another
+    if (!names || PyModule_AddStringConstant(m, "TORCH", SLIMFIT_TORCH) < 0 || PyModule_AddObject(m, "CALLS", names) < 0) {
         Py_XDECREF(names);
         Py_DECREF(m);
         return nullptr;

@@ -400,6 +400,33 @@ def test_binding_wants_a_workspace_with_an_explicit_stream():
         sf.prune_global(x, 10, torch.zeros(10), torch.zeros(10, dtype=torch.int32), stream=12345)
 
 
+@pytest.mark.parametrize("stand_in", ["None", "types.SimpleNamespace(TORCH='0.0')"])
+def test_library_serves_without_its_native_binding(stand_in):
+    """A native binding that does not load, or that was built against another torch, is not used; ctypes serves the calls."""
+    import subprocess
+    import sys
+    code = """
+import sys, types, warnings
+import paper_2305_18513_amd
+sys.modules["paper_2305_18513_amd._native"] = paper_2305_18513_amd._native = %s
+from paper_2305_18513_amd import binding as sf
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    sf.lib()
+assert [w for w in seen if "ctypes" in str(w.message)], seen
+assert sf.is_built() and sf._native is None and sf.keep_count(128, 100000) == 12
+assert sf._native_quant_pack(1, 2) is NotImplemented
+import torch
+try:
+    sf.quant_pack(torch.zeros(64), sf.Q_BLOCK, 4, 64, 0, torch.zeros(8, dtype=torch.uint8), None)
+except ValueError:
+    print("served")
+""" % stand_in
+    out = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                         capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.strip() == "served", out.stderr
+
+
 def test_library_counts_reproduce_the_workloads_stated_figures():
     from paper_2305_18513_amd import synth
     for c in synth.CONFIGS:
