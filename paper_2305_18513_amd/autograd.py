@@ -234,7 +234,8 @@ class SoftmaxMatmulFunction(torch.autograd.Function):
             vals, idx, v = ctx.saved_tensors
         cols = shape[-1]
         rows = vals.shape[0]
-        grad_output = grad_output.contiguous()              # (both products would lay out a transposed one for themselves)
+        if grad_output.dim() > 3:                           # (three dimensions are multiplied as they lie)
+            grad_output = grad_output.contiguous()          # both products would lay out a transposed one for themselves
         dp = torch.matmul(grad_output, v.transpose(-1, -2)).contiguous().view(rows, cols)
         p_hat = torch.empty(rows, cols, dtype=vals.dtype, device=vals.device)
         sf.restore_scores(vals, idx, None, p_hat)
