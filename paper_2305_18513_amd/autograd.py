@@ -65,13 +65,19 @@ def _dequantise(codes, scales, bits: int, block: int, shape, dtype) -> torch.Ten
     return out
 
 
+def _right(t: torch.Tensor) -> torch.Tensor:
+    """The right operand of a batched product, laid out for bf16: torch's bf16 product has faulted the GPU where it was a
+    transposed view."""
+    return t.contiguous() if t.dtype == torch.bfloat16 else t
+
+
 class MatmulFunction(torch.autograd.Function):
     """out = a @ b with both operands cached in `bits` bits (the paper keeps MatMul's activations in 8 bits);
     backward multiplies the incoming gradient with the dequantised operands."""
 
     @staticmethod
     def forward(ctx, a: torch.Tensor, b: torch.Tensor, bits: int = 8, block: int = 64):
-        out = torch.matmul(a, b)
+        out = torch.matmul(a, _right(b))
         ca, sa = _quantise(a, bits, block)
         cb, sb = _quantise(b, bits, block)
         ctx.save_for_backward(ca, sa, cb, sb)
@@ -83,10 +89,10 @@ class MatmulFunction(torch.autograd.Function):
         ca, sa, cb, sb = ctx.saved_tensors
         bits, block, sha, shb, dtype = ctx.meta
         b_hat = _dequantise(cb, sb, bits, block, shb, dtype)
-        da = torch.matmul(grad_output, b_hat.transpose(-1, -2))
+        da = torch.matmul(grad_output, _right(b_hat.transpose(-1, -2)))
         del b_hat
         a_hat = _dequantise(ca, sa, bits, block, sha, dtype)
-        db = torch.matmul(a_hat.transpose(-1, -2), grad_output)
+        db = torch.matmul(a_hat.transpose(-1, -2), _right(grad_output))
         return da, db, None, None
 
 
@@ -215,7 +221,7 @@ class SoftmaxMatmulFunction(torch.autograd.Function):
         vals = torch.empty(rows, k, dtype=l2.dtype, device=l2.device)
         idx = torch.empty(rows, k, dtype=torch.uint16, device=l2.device)
         sf.softmax_prune(l2, k, probs, vals, idx)
-        out = torch.matmul(probs.view(logits.shape), v)
+        out = torch.matmul(probs.view(logits.shape), _right(v))
         if v_bits:
             cv, sv = _quantise(v, v_bits, block)
             ctx.save_for_backward(vals, idx, cv, sv)
@@ -236,10 +242,10 @@ class SoftmaxMatmulFunction(torch.autograd.Function):
         rows = vals.shape[0]
         if grad_output.dim() > 3:                           # (three dimensions are multiplied as they lie)
             grad_output = grad_output.contiguous()          # both products would lay out a transposed one for themselves
-        dp = torch.matmul(grad_output, v.transpose(-1, -2)).contiguous().view(rows, cols)
+        dp = torch.matmul(grad_output, _right(v.transpose(-1, -2))).contiguous().view(rows, cols)
         p_hat = torch.empty(rows, cols, dtype=vals.dtype, device=vals.device)
         sf.restore_scores(vals, idx, None, p_hat)
-        dv = torch.matmul(p_hat.view(shape).transpose(-1, -2), grad_output)
+        dv = torch.matmul(p_hat.view(shape).transpose(-1, -2), _right(grad_output))
         ds = torch.empty_like(dp)
         sf.softmax_backward_pruned(vals, idx, None, dp, ds)
         return ds.view(shape), dv, None, None, None

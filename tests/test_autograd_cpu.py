@@ -25,6 +25,21 @@ def _turned(*shape, dtype):
     return torch.zeros(*shape, dtype=dtype).transpose(-1, -2).contiguous().transpose(-1, -2).requires_grad_(True)
 
 
+@pytest.mark.parametrize("lead", [(3,), (2, 3)])
+def test_right_operands_of_bf16_products_are_laid_out(products, lead):
+    dt = torch.bfloat16
+    a, b = _turned(*lead, 8, 16, dtype=dt), _turned(*lead, 16, 8, dtype=dt)
+    out = ag.MatmulFunction.apply(a, b)
+    torch.autograd.grad(out, (a, b), _turned(*lead, 8, 8, dtype=dt).detach())
+    for v_bits in (0, 8):
+        s, v = _turned(*lead, 8, 16, dtype=dt), _turned(*lead, 16, 8, dtype=dt)
+        out = ag.SoftmaxMatmulFunction.apply(s, v, 100000, v_bits)
+        torch.autograd.grad(out, (s, v), _turned(*lead, 8, 8, dtype=dt).detach())
+    assert len(products) == 9
+    for _, right in products:
+        assert right.is_contiguous()
+
+
 def test_an_fp32_gradient_of_three_dimensions_is_multiplied_as_it_lies(products):
     s, v = torch.zeros(3, 8, 16, requires_grad=True), torch.zeros(3, 16, 8, requires_grad=True)
     grad = _turned(3, 8, 8, dtype=torch.float32).detach()
