@@ -77,22 +77,35 @@ def test_arguments():
             sf.merge_heads(q, bad[1], torch.empty_like(q), 1.0, bad[0])
 
 
-@pytest.mark.parametrize("heads", [2, 4])
-def test_encoder_block_is_what_it_was_with_reshapes(heads):
-    """Head sizes of 64 and 32: with the fused reordering (the factor on q, a power of two) and without it (divided products)."""
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("hidden,heads", [(128, 2), (128, 8), (128, 4), (96, 2), (240, 3), (128, 1), (40, 5)])
+def test_encoder_block_is_what_it_was_with_reshapes(monkeypatch, hidden, heads, dtype):
+    """Head sizes of 64 and 16 (the factor, a power of two, goes onto q), 32, 48, 80, 128 and 8 (the products are divided): with the
+    fused reordering and without it the products see the same operands."""
     require_gpu()
     g = torch.Generator(device="cuda").manual_seed(heads)
-    params = ag.encoder_block_params(128, "cuda", 3)
-    x = torch.randn(2, 48, 128, generator=g, device="cuda").requires_grad_(True)
-    dout = torch.randn(2, 48, 128, generator=g, device="cuda")
-    out = ag.frozen_encoder_block(x, params, heads, True)
-    (dx,) = torch.autograd.grad(out, x, dout)
-    kept, ag._halves = ag._halves, lambda dim: False
-    try:
-        want = ag.frozen_encoder_block(x, params, heads, True)
-        (want_dx,) = torch.autograd.grad(want, x, dout)
-    finally:
-        ag._halves = kept
-    # the products themselves are torch's and may add in another order where their operands lie differently
-    assert torch.allclose(out, want, rtol=1e-5, atol=1e-5)
-    assert float((dx - want_dx).norm() / want_dx.norm()) < 5e-4
+    params = ag.encoder_block_params(hidden, "cuda", 3, dtype)
+    x = torch.randn(2, 48, hidden, generator=g, device="cuda").to(dtype).requires_grad_(True)
+    dout = torch.randn(2, 48, hidden, generator=g, device="cuda").to(dtype)
+    calls = []
+    for name in ("split_heads", "merge_heads"):
+        kept = getattr(sf, name)
+        monkeypatch.setattr(ag.sf, name, lambda *args, name=name, kept=kept: (calls.append(name), kept(*args))[1])
+
+    def run():
+        out = ag.frozen_encoder_block(x, params, heads, True)
+        return out, torch.autograd.grad(out, x, dout)[0]
+
+    out, dx = run()
+    assert calls == ["split_heads", "merge_heads"]
+    monkeypatch.setattr(ag, "_rows_of_vectors", lambda dim, t: False)
+    want, want_dx = run()
+    assert len(calls) == 2                                             # the reshapes alone
+    assert torch.equal(out, want) and torch.equal(dx, want_dx)
+
+
+def test_heads_that_are_no_whole_vectors_keep_the_reshapes():
+    require_gpu()
+    params = ag.encoder_block_params(24, "cuda", 3, torch.bfloat16)
+    x = torch.randn(1, 16, 24, device="cuda").bfloat16()
+    assert torch.isfinite(ag.frozen_encoder_block(x, params, 2, True).float()).all()                 # 12 elements: 24 bytes
