@@ -50,7 +50,9 @@ extern "C" {
 typedef enum {
     SLIMFIT_OK = 0,
     SLIMFIT_ERR_INVALID_ARG = 1, /* NULL where data is required, negative size, k > cols ... */
-    SLIMFIT_ERR_UNSUPPORTED = 2, /* a value outside the supported set (bits, block, cols) */
+    SLIMFIT_ERR_UNSUPPORTED = 2, /* a value outside the supported set (bits, block, cols), or more work than one grid has
+                                    threads for where a call is one launch (LayerNorm: 2^26 rows and more; restore_scores and
+                                    softmax_backward_pruned: 2^36 entries and more) */
     SLIMFIT_ERR_ALIGNMENT = 3,   /* a device pointer is not aligned as required */
     SLIMFIT_ERR_WORKSPACE = 4,   /* workspace NULL or smaller than the size query says */
     SLIMFIT_ERR_HIP = 5,         /* the HIP runtime refused a launch or a query */

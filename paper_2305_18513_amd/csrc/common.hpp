@@ -24,6 +24,11 @@ private:
 };
 int32_t launch_status();                                    // hipGetLastError -> status
 
+// A grid's threads are counted in 32 bits: a launch of 2^32 or more starts what the low bits say and reports no error.
+// More work goes out in launches of kMaxGridThreads, or is refused.
+constexpr int64_t kMaxGridThreads = (int64_t)1 << 31;
+inline bool grid_fits(int64_t blocks, int threads) { return blocks <= 0xFFFFFFFFLL / threads; }
+
 // short rows that keep few entries have a kernel of their own (prune_short.hip)
 constexpr int kShortPruneMaxCols = 256;
 constexpr int kShortPruneMaxK = 16;                     // bf16 rows

@@ -61,20 +61,20 @@ struct Shape {
 // SPLIT: fused -> (q, kt, v); otherwise the other way round
 template <typename T, bool SPLIT>
 __global__ void __launch_bounds__(kThreads)
-heads_kernel(T *fused, T *q, T *kt, T *v, Shape s)
+heads_kernel(T *fused, T *q, T *kt, T *v, Shape s, unsigned first)
 {
     using V = Vec16<T>;
     constexpr int E = V::E, kCols = kSide / E, kRows = kThreads / kCols;        // vectors across a piece, rows a step
     __shared__ float piece[kSide * kPitch];
-    int at = blockIdx.x;
-    const int part = at % 3;
+    unsigned at = first + blockIdx.x;                       // of all launches' blocks (below 2^31)
+    const int part = (int)(at % 3);
     at /= 3;
-    const int d0 = at % s.dim_blocks * kSide;
-    at /= s.dim_blocks;
-    const int t0 = at % s.token_blocks * kSide;
-    at /= s.token_blocks;                                   // batch * heads + head
-    const int64_t head = at % s.heads, width = (int64_t)s.heads * s.dim;
-    T *const rows = fused + ((int64_t)(at / s.heads) * s.tokens * 3 + part) * width + head * s.dim;       // token 0's; 3 * width apart
+    const int d0 = (int)(at % (unsigned)s.dim_blocks) * kSide;
+    at /= (unsigned)s.dim_blocks;
+    const int t0 = (int)(at % (unsigned)s.token_blocks) * kSide;
+    at /= (unsigned)s.token_blocks;                                   // batch * heads + head
+    const int64_t head = at % (unsigned)s.heads, width = (int64_t)s.heads * s.dim;
+    T *const rows = fused + ((int64_t)(at / (unsigned)s.heads) * s.tokens * 3 + part) * width + head * s.dim;       // token 0's; 3 * width apart
     const int n_t = min(kSide, s.tokens - t0), n_d = min(kSide, s.dim - d0);
     const int c = threadIdx.x % kCols * E, r0 = threadIdx.x / kCols;
     if (part != 1) {
@@ -178,12 +178,18 @@ int32_t heads_entry(void *fused, int32_t dt, int64_t batch, int32_t tokens, int3
     if ((rc = check_device_range(kt, bytes)) != SLIMFIT_OK) return rc;
     if ((rc = check_device_range(v, bytes)) != SLIMFIT_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dt == SLIMFIT_F32)
-        heads_kernel<float, SPLIT><<<(unsigned)blocks, kThreads, 0, st>>>(static_cast<float *>(fused), static_cast<float *>(q),
-                                                                         static_cast<float *>(kt), static_cast<float *>(v), s);
-    else
-        heads_kernel<uint16_t, SPLIT><<<(unsigned)blocks, kThreads, 0, st>>>(static_cast<uint16_t *>(fused), static_cast<uint16_t *>(q),
-                                                                            static_cast<uint16_t *>(kt), static_cast<uint16_t *>(v), s);
+    constexpr int64_t kMost = kMaxGridThreads / kThreads;    // blocks of a launch
+    const int64_t all = (int64_t)blocks;
+    for (int64_t first = 0; first < all; first += kMost) {
+        const unsigned here = (unsigned)(all - first < kMost ? all - first : kMost);
+        if (dt == SLIMFIT_F32)
+            heads_kernel<float, SPLIT><<<here, kThreads, 0, st>>>(static_cast<float *>(fused), static_cast<float *>(q),
+                                                                  static_cast<float *>(kt), static_cast<float *>(v), s, (unsigned)first);
+        else
+            heads_kernel<uint16_t, SPLIT><<<here, kThreads, 0, st>>>(static_cast<uint16_t *>(fused), static_cast<uint16_t *>(q),
+                                                                     static_cast<uint16_t *>(kt), static_cast<uint16_t *>(v), s,
+                                                                     (unsigned)first);
+    }
     return launch_status();
 }
 

@@ -634,7 +634,7 @@ int32_t validate(int64_t rows, int64_t H, int32_t dt = SLIMFIT_F32)
     if (!dtype_ok(dt)) return SLIMFIT_ERR_INVALID_ARG;
     const int64_t epv = dt == SLIMFIT_F32 ? 4 : 8;             // elements per 16-byte vector
     if (rows < 0 || H < epv || H % epv != 0) return SLIMFIT_ERR_INVALID_ARG;
-    if (H > kMaxH || rows * H > 0x7FFFFFFFLL) return SLIMFIT_ERR_UNSUPPORTED;
+    if (H > kMaxH || rows * H > 0x7FFFFFFFLL || !grid_fits((rows + kWaves - 1) / kWaves, kThreads)) return SLIMFIT_ERR_UNSUPPORTED;
     return SLIMFIT_OK;
 }
 

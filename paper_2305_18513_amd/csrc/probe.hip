@@ -146,7 +146,7 @@ extern "C" int32_t slimfit_stream_probe(const void *src, void *dst, int64_t in_v
     const int64_t per_block = grow ? (int64_t)kGrowThreads * kGrowVecs : (int64_t)kThreads * kVecs;
     const int64_t work = grow ? in_vecs * (int64_t)(-ratio) : in_vecs;      // output vectors / source vectors
     const int64_t blocks = (work + per_block - 1) / per_block;
-    if (blocks > 0x7FFFFFFF) return SLIMFIT_ERR_UNSUPPORTED;
+    if (!grid_fits(blocks, grow ? kGrowThreads : kThreads)) return SLIMFIT_ERR_UNSUPPORTED;
     // bytes written: shrink 16 / ratio per vector; read-only one float per wavefront; grow whole workgroup tiles
     const size_t dst_bytes = shrink ? (size_t)in_vecs * (16 / (size_t)ratio)
                              : grow ? (size_t)in_vecs * (size_t)(-ratio) * 16

@@ -31,10 +31,7 @@ constexpr int kRowThreads = kRowWaves * kWave;
 #define SLIMFIT_PRUNE_WAVE_SLOTS 32
 #endif
 constexpr int kMaxRegSlots = SLIMFIT_PRUNE_WAVE_SLOTS;   // one-wave path: cols <= 64 * this (16, 32 or 64)
-#ifndef SLIMFIT_PRUNE_BLOCKS
-#define SLIMFIT_PRUNE_BLOCKS (1 << 30)
-#endif
-constexpr int64_t kMaxPruneBlocks = SLIMFIT_PRUNE_BLOCKS;
+constexpr int64_t kMaxPruneBlocks = kMaxGridThreads / kRowThreads;       // (waves go round for the rows beyond)
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {
@@ -1339,7 +1336,7 @@ extern "C" int32_t slimfit_restore_scores(const void *vals, const uint16_t *idx,
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t total = rows * (int64_t)cols;
     const int64_t tiles = (total + kTile - 1) / kTile;
-    if (tiles > 0x7FFFFFFF) return SLIMFIT_ERR_UNSUPPORTED;
+    if (!grid_fits(tiles, kThreads)) return SLIMFIT_ERR_UNSUPPORTED;
     if (dt == SLIMFIT_F32)
         restore_tile_kernel<float><<<(unsigned)tiles, kThreads, 0, st>>>(static_cast<const float *>(vals), idx, counts,
                                                                          rows, cols, k, static_cast<float *>(out));
@@ -1372,7 +1369,7 @@ extern "C" int32_t slimfit_softmax_backward_pruned(const void *vals, const uint1
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t total = rows * (int64_t)cols;
     const int64_t tiles = (total + kTile - 1) / kTile;
-    if (tiles > 0x7FFFFFFF) return SLIMFIT_ERR_UNSUPPORTED;
+    if (!grid_fits(tiles, kThreads)) return SLIMFIT_ERR_UNSUPPORTED;
     const bool small = k <= kSmallK && cols >= kSmallMinCols && k < SLIMFIT_SMB_SMALL_BELOW;
     if (dt == SLIMFIT_F32) {
         const float *v = static_cast<const float *>(vals), *g = static_cast<const float *>(dp);

@@ -789,13 +789,27 @@ bool softmax_wide(int32_t dt, int64_t rows, int cols, int k)
     return rows < (k > 9 || cols <= 112 ? 40000 : 131072);
 }
 
+// f(the call's arguments, its first row, its blocks) for pieces of rows that a grid has threads for
+template <int G, typename F>
+void in_pieces(const ShortArgs &a, F f)
+{
+    constexpr int R = kWave / G;
+    constexpr int64_t kMost = kMaxGridThreads / kWave * R;     // rows (a multiple of 64: pieces begin on 16 bytes)
+    for (int64_t row0 = 0; row0 < a.rows; row0 += kMost) {
+        ShortArgs piece = a;
+        piece.rows = a.rows - row0 < kMost ? a.rows - row0 : kMost;
+        f(piece, row0, (unsigned)((piece.rows + R - 1) / R));
+    }
+}
+
 template <typename T, int G, int K, int NV>
 void launch_softmax_short(const T *p, const ShortArgs &a, T *probs, T *vals, uint16_t *idx, hipStream_t st)
 {
-    constexpr int R = kWave / G;
-    const int64_t blocks = (a.rows + R - 1) / R;
     const size_t lds = short_lds_bytes(a.cols, a.k, G, (int)sizeof(T), kShortHeldBlock);
-    softmax_prune_short_kernel<T, G, K, NV><<<(unsigned)blocks, kWave, lds, st>>>(p, a, probs, vals, idx);
+    in_pieces<G>(a, [&](const ShortArgs &piece, int64_t row0, unsigned blocks) {
+        softmax_prune_short_kernel<T, G, K, NV><<<blocks, kWave, lds, st>>>(p + row0 * a.cols, piece, probs + row0 * a.cols, vals + row0 * a.k,
+                                                                            idx + row0 * a.k);
+    });
 }
 
 // WIDE: rows of at least kSoftmaxWideCols columns, and so many lanes to a row
@@ -835,13 +849,14 @@ constexpr int kShortLongListF32 = 9;       // fp32 rows that keep more have line
 template <typename T, int G, int K, int NV>
 void launch_short(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int32_t *counts, hipStream_t st)
 {
-    constexpr int R = kWave / G;
-    const int64_t blocks = (a.rows + R - 1) / R;
 #ifndef SLIMFIT_SHORT_LDS_PAD
 #define SLIMFIT_SHORT_LDS_PAD 0        // timing experiments only: LDS a wave claims beyond what it uses
 #endif
     const size_t lds = short_lds_bytes(a.cols, a.k, G, (int)sizeof(T), 1) + SLIMFIT_SHORT_LDS_PAD;
-    prune_rows_short_kernel<T, G, K, NV><<<(unsigned)blocks, kWave, lds, st>>>(p, a, vals, idx, counts);
+    in_pieces<G>(a, [&](const ShortArgs &piece, int64_t row0, unsigned blocks) {
+        prune_rows_short_kernel<T, G, K, NV><<<blocks, kWave, lds, st>>>(p + row0 * a.cols, piece, vals + row0 * a.k, idx + row0 * a.k,
+                                                                        counts ? counts + row0 : nullptr);
+    });
 }
 
 template <typename T, int G, int K>
@@ -908,7 +923,7 @@ constexpr int64_t kShortMinRows = 20000, kShortMinRowsSoftmaxF32 = 24000, kStrid
 bool prune_short_eligible(const void *p, int32_t dt, int64_t rows, int cols, int k, int mode, bool softmax)
 {
     const bool bf16 = dt == SLIMFIT_BF16;
-    if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32) || rows > (int64_t)0x7FFFFFFF * 8) return false;
+    if (cols > kShortPruneMaxCols || k > (bf16 ? kShortPruneMaxK : kShortPruneMaxKF32)) return false;
     if (!aligned_to(p, 16)) return false;              // (the rows are staged with 16-byte loads)
     if (!bf16 && k > kShortLongListF32) {
         if (mode == SLIMFIT_PRUNE_THRESHOLD) return false;

@@ -295,8 +295,12 @@ inline unsigned grid_for(int64_t n, int V, int unroll, int threads)
     return (unsigned)((n + per_block - 1) / per_block);
 }
 
+// Elements of one launch: whole tiles and blocks, and no more threads than a grid may have (8 elements a thread at least).
+constexpr int64_t kPiece = (int64_t)1 << 34;
+static_assert(kPiece / (4 * kUnrollQ) <= kMaxGridThreads && kPiece / (4 * kUnrollD) <= kMaxGridThreads, "a grid's threads");
+
 template <typename T, int BITS, bool GELU>
-void launch_quant(const void *x, int64_t n, int mode, int block, int frac_bits, uint8_t *codes, float *scales, void *y,
+void launch_quant_piece(const void *x, int64_t n, int mode, int block, int frac_bits, uint8_t *codes, float *scales, void *y,
                   hipStream_t st)
 {
     constexpr int V = Vec<T>::V;
@@ -318,7 +322,16 @@ void launch_quant(const void *x, int64_t n, int mode, int block, int frac_bits, 
 }
 
 template <typename T, int BITS, bool GELU>
-void launch_dequant(const uint8_t *codes, const float *scales, int64_t n, int mode, int block, int frac_bits, void *y,
+void launch_quant(const void *x, int64_t n, int mode, int block, int frac_bits, uint8_t *codes, float *scales, void *y, hipStream_t st)
+{
+    for (int64_t at = 0; at < n; at += kPiece)
+        launch_quant_piece<T, BITS, GELU>(static_cast<const T *>(x) + at, n - at < kPiece ? n - at : kPiece, mode, block, frac_bits,
+                                          codes + at * BITS / 8, mode == SLIMFIT_Q_BLOCK ? scales + at / block : nullptr,
+                                          GELU ? static_cast<T *>(y) + at : nullptr, st);
+}
+
+template <typename T, int BITS, bool GELU>
+void launch_dequant_piece(const uint8_t *codes, const float *scales, int64_t n, int mode, int block, int frac_bits, void *y,
                     const void *dy, hipStream_t st)
 {
     constexpr int V = Vec<T>::V;
@@ -333,6 +346,16 @@ void launch_dequant(const uint8_t *codes, const float *scales, int64_t n, int mo
                                                                         0.0f, yp, gp);
 }
 
+template <typename T, int BITS, bool GELU>
+void launch_dequant(const uint8_t *codes, const float *scales, int64_t n, int mode, int block, int frac_bits, void *y, const void *dy,
+                    hipStream_t st)
+{
+    for (int64_t at = 0; at < n; at += kPiece)
+        launch_dequant_piece<T, BITS, GELU>(codes + at * BITS / 8, mode == SLIMFIT_Q_BLOCK ? scales + at / block : nullptr,
+                                            n - at < kPiece ? n - at : kPiece, mode, block, frac_bits, static_cast<T *>(y) + at,
+                                            GELU ? static_cast<const T *>(dy) + at : nullptr, st);
+}
+
 int32_t validate(int32_t dt, int64_t n, int32_t mode, int32_t bits, int32_t block, int32_t frac_bits)
 {
     if (!dtype_ok(dt) || n < 0) return SLIMFIT_ERR_INVALID_ARG;
@@ -341,7 +364,6 @@ int32_t validate(int32_t dt, int64_t n, int32_t mode, int32_t bits, int32_t bloc
     if (mode == SLIMFIT_Q_FIXED && (frac_bits < -32 || frac_bits > 32)) return SLIMFIT_ERR_UNSUPPORTED;
     if (mode == SLIMFIT_Q_BLOCK && block != 32 && block != 64 && block != 128 && block != 256)
         return SLIMFIT_ERR_UNSUPPORTED;
-    // one workgroup per >= 1024 elements: the grid must fit a 31-bit launch dimension
     if (n > ((int64_t)1 << 40)) return SLIMFIT_ERR_UNSUPPORTED;
     return SLIMFIT_OK;
 }

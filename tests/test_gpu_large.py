@@ -179,3 +179,106 @@ def test_whole_tensor_pruning_at_the_int32_limit():
     sf.restore_global(vals, idx, k, out, ptr)
     torch.cuda.synchronize()
     assert int((out != 0).sum()) == int((vals != 0).sum()) and bool((out[il] == vals).all())
+
+
+# A grid's threads are counted in 32 bits, and a launch of more starts fewer without an error: calls of that size go out in
+# pieces.  Each is compared, around the pieces' ends and at its own, with the same call on that part alone.
+
+def _poisoned(shape, dtype, at):
+    t = torch.empty(shape, dtype=dtype, device="cuda")
+    for a, b in at:
+        t[a:b].view(torch.uint8).fill_(0x5A)
+    return t
+
+
+def test_quantiser_of_more_elements_than_a_grid_has_threads_for():
+    torch.cuda.empty_cache()
+    _need(160)
+    n, bits, block = (1 << 35) + 5000, 4, 256
+    at = [(0, 8192), ((1 << 34) - 4096, (1 << 34) + 4096), ((1 << 35) - 4096, n)]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.empty(n, device="cuda")
+    for a, b in at:
+        x[a:b] = torch.randn(b - a, generator=g, device="cuda")
+    kept = [x[a:b].clone() for a, b in at]
+    codes = _poisoned(sf.packed_bytes(n, bits), torch.uint8, [(a // 2, b // 2) for a, b in at])
+    scales = _poisoned(sf.num_blocks(n, block), torch.float32, [(a // block, -(-b // block)) for a, b in at])
+    sf.quant_pack(x, sf.Q_BLOCK, bits, block, 0, codes, scales)
+    torch.cuda.synchronize()
+    del x
+    torch.cuda.empty_cache()
+    y = _poisoned(n, torch.float32, at)
+    sf.dequant_unpack(codes, scales, sf.Q_BLOCK, bits, block, 0, y)
+    torch.cuda.synchronize()
+    for (a, b), part in zip(at, kept):
+        c, s = torch.empty(sf.packed_bytes(b - a, bits), dtype=torch.uint8, device="cuda"), torch.empty(sf.num_blocks(b - a, block), device="cuda")
+        sf.quant_pack(part, sf.Q_BLOCK, bits, block, 0, c, s)
+        assert torch.equal(codes[a // 2: a // 2 + c.numel()], c) and torch.equal(scales[a // block: a // block + s.numel()], s)
+        back = torch.empty_like(part)
+        sf.dequant_unpack(c, s, sf.Q_BLOCK, bits, block, 0, back)
+        assert torch.equal(y[a:b], back)
+    del y, codes, scales
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_heads_of_more_sequences_than_a_grid_has_threads_for(dtype):
+    torch.cuda.empty_cache()
+    _need(16)
+    batch, tokens, heads, dim = (1 << 21) + 3, 1, 3, 8                     # 3 * batch * heads blocks of 256 threads
+    qkv = torch.randint(-99, 99, (batch, tokens, 3 * heads * dim), device="cuda", dtype=torch.int8).to(dtype)
+    q, kt = torch.zeros(batch, heads, tokens, dim, dtype=dtype, device="cuda"), torch.zeros(batch, heads, dim, tokens, dtype=dtype, device="cuda")
+    v = torch.zeros_like(q)
+    sf.split_heads(qkv, 0.5, q, kt, v)
+    parts = qkv.view(batch, tokens, 3, heads, dim)
+    assert torch.equal(q, parts[:, :, 0].transpose(1, 2) * 0.5)
+    assert torch.equal(kt, parts[:, :, 1].permute(0, 2, 3, 1)) and torch.equal(v, parts[:, :, 2].transpose(1, 2))
+    back = torch.zeros_like(qkv)
+    sf.merge_heads(q, kt, v, 2.0, back)
+    assert torch.equal(back, qkv)
+
+
+def test_short_rows_of_more_rows_than_a_grid_has_threads_for():
+    torch.cuda.empty_cache()
+    _need(80)
+    rows, cols, k = (1 << 30) + 100, 2, 1
+    p = torch.empty(rows, cols, device="cuda")
+    p[:, 0], p[:, 1] = 0.25, 0.75
+    p[5::7, 0] = 0.875
+    for softmax in (False, True):
+        vals, idx = torch.zeros(rows, k, device="cuda"), torch.full((rows, k), 9, dtype=torch.int16, device="cuda").view(torch.uint16)
+        if softmax:
+            probs = torch.zeros_like(p)
+            sf.softmax_prune(p, k, probs, vals, idx)
+            assert bool((probs.sum(1) - 1).abs().max() < 1e-6)
+            del probs
+        else:
+            sf.prune_scores(p, k, sf.PRUNE_TOPK, 0.0, vals, idx, None)
+            assert torch.equal(vals[:, 0], p.amax(1))
+        assert torch.equal(idx.view(torch.int16)[:, 0], (p[:, 1] > p[:, 0]).to(torch.int16))
+        del vals, idx
+    del p
+    torch.cuda.empty_cache()
+
+
+def test_rows_of_a_wave_each_that_fill_a_grid_to_the_last_bit():
+    """2^26 waves are 2^32 threads: a grid whose low 32 bits are zero."""
+    torch.cuda.empty_cache()
+    _need(190)
+    rows, cols, k = 1 << 26, 320, 16
+    at = [(0, 64), ((1 << 25) - 64, (1 << 25) + 64), (rows - 64, rows)]
+    g = torch.Generator(device="cuda").manual_seed(6)
+    l = torch.empty(rows, cols, device="cuda")
+    for a, b in at:
+        l[a:b] = torch.randn(b - a, cols, generator=g, device="cuda")
+    probs, vals = _poisoned((rows, cols), torch.float32, at), _poisoned((rows, k), torch.float32, at)
+    idx = _poisoned((rows, k), torch.uint16, at)
+    sf.softmax_prune(l, k, probs, vals, idx)
+    torch.cuda.synchronize()
+    for a, b in at:
+        part = l[a:b].clone()
+        pr, v, i = torch.empty_like(part), torch.empty(b - a, k, device="cuda"), torch.empty(b - a, k, dtype=torch.uint16, device="cuda")
+        sf.softmax_prune(part, k, pr, v, i)
+        assert torch.equal(probs[a:b], pr) and torch.equal(vals[a:b], v) and torch.equal(idx[a:b].view(torch.int16), i.view(torch.int16))
+    del l, probs, vals, idx
+    torch.cuda.empty_cache()
