@@ -57,8 +57,11 @@ def test_captured_calls_replay_to_the_eager_results():
         "lq_scales": torch.empty(640 * H // 64, device="cuda"),
         "lq_dx": torch.empty(640, H, device="cuda"),
         "d_apply": torch.empty(3, device="cuda"),
+        "h_q": torch.empty(2, 3, 70, 64, device="cuda"), "h_kt": torch.empty(2, 3, 64, 70, device="cuda"),
+        "h_v": torch.empty(2, 3, 70, 64, device="cuda"), "h_back": torch.empty(2, 70, 3 * 3 * 64, device="cuda"),
         "w0": torch.empty_like(w_prev[0]), "w1": torch.empty_like(w_prev[1]), "w2": torch.empty_like(w_prev[2]),
     }
+    qkv = torch.randn(2, 70, 3 * 3 * 64, generator=g, device="cuda")
     w_apply = [out["w0"], out["w1"], out["w2"]]
     upd = [c - q for q, c in zip(w_prev, w_cur)]
     ws_delta = torch.empty(sf.layer_delta_workspace(numel), dtype=torch.uint8, device="cuda")
@@ -91,6 +94,8 @@ def test_captured_calls_replay_to_the_eager_results():
         sf.layernorm_forward_quant_pack(lnx, gamma, beta, 1e-5, 4, 64, o["lq_y"], o["mean"], o["rstd"], o["lq_codes"],
                                         o["lq_scales"])
         sf.layernorm_backward_dequant(o["lq_codes"], o["lq_scales"], 4, 64, o["mean"], o["rstd"], gamma, dy, o["lq_dx"])
+        sf.split_heads(qkv, 0.125, o["h_q"], o["h_kt"], o["h_v"])
+        sf.merge_heads(o["h_q"], o["h_kt"], o["h_v"], 0.125, o["h_back"])
         for dst, src in zip(w_apply, w_prev):                      # the update is applied to a fresh copy every time
             dst.copy_(src)
         sf.layer_delta_apply_run(numel, sf.F32, sf.F32, 0.0, o["d_apply"], ws_apply)
