@@ -568,7 +568,7 @@ __global__ __launch_bounds__(kWave) void prune_rows_short_kernel(const T *__rest
 // division a row) find it; the probabilities go back over the staged rows and leave for `probs` as one contiguous piece.
 // Bound by the waves' lifetime on few rows and by HBM on many: 87 468 x 197 fp32 37.2 us when selection, maximum,
 // exponentials and scaling each walked the staged rows, 34.2 from registers, 30.4 with eight lanes a row as well (4.7 TB/s);
-// 302 592 rows 100 -> 87 (5.5 TB/s); 806 912 x 197 bf16 202 -> 162 (4.1 TB/s, bound by the list insertion).
+// 302 592 rows 100 -> 90 (5.3 TB/s); 806 912 x 197 bf16 202 -> 162 (4.1 TB/s, bound by the list insertion).
 template <typename T, int G, int K, int NV>
 struct HeldRows {
     using S = ShortRows<T, G, K, NV>;
@@ -650,7 +650,7 @@ struct HeldRows {
     // plain bit patterns would be for nothing.  One instruction an entry: the signs are shifted into a register.  us with
     // both selections / with this, while the signed one walked the staged rows: negative logits 302 592 x 197 fp32 118 / 97,
     // 806 912 x 197 bf16 213 / 195; nine tenths masked 108 / 88, 211 / 195; plain rows 89.5 / 92.0, 170 / 170.  With both
-    // selections from registers 96 and 168, 87 and 164, plain 87 and 162.  (Zeros have no sign: a row that they cut takes both.)
+    // selections from registers 97 and 167, 87 and 164, plain 90 and 162.  (Zeros have no sign: a row that they cut takes both.)
     __device__ __forceinline__ bool cut_is_negative(int k) const
     {
         uint32_t signs[(kMost + 31) / 32] = {};
@@ -723,8 +723,14 @@ struct HeldRows {
     }
 };
 
+// Most waves a SIMD is to hold.  fp32 rows of 129 to 224 columns that keep 7 to 9 have registers for five, and are faster with
+// four, whose loads queue less, but at the ends: 197 columns, 60 000 rows 22.7 us with four, 22.1 with five, 80 000 27.5 / 28.0,
+// 98 304 32.2 / 32.9, 130 000 40.5 / 42.0, 160 000 48.8 / 50.8, 302 592 87.8 / 85.7.  Others lose with four (98 304 x 100, k = 5
+// 18.8 / 17.0) or have registers for no more.
+template <typename T, int G, int K, int NV> constexpr int kSoftmaxWaves = sizeof(T) == 4 && G == 8 && K == 9 && NV == 7 ? 4 : 8;
+
 template <typename T, int G, int K, int NV>
-__global__ __launch_bounds__(kWave) void softmax_prune_short_kernel(const T *__restrict__ p, ShortArgs a,
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, kSoftmaxWaves<T, G, K, NV>))) void softmax_prune_short_kernel(const T *__restrict__ p, ShortArgs a,
                                                                     T *__restrict__ probs, T *__restrict__ vals,
                                                                     uint16_t *__restrict__ idx)
 {
