@@ -173,7 +173,7 @@ __device__ __forceinline__ int code_field(uint32_t word, int i)
     return (int)(word << (32 - BITS - sh)) >> (32 - BITS);
 }
 
-// Whole-wave reductions of unsigned keys; the result is wave-uniform (SGPR).
+// The whole wave's largest unsigned key, wave-uniform (SGPR).
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
     v = max(v, dpp_u32<kDppXor1>(v));
@@ -183,16 +183,6 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
     uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
     return max(max(a, b), max(c, d));
-}
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
-{
-    v = min(v, dpp_u32<kDppXor1>(v));
-    v = min(v, dpp_u32<kDppXor2>(v));
-    v = min(v, dpp_u32<kDppHalfMirror>(v));
-    v = min(v, dpp_u32<kDppMirror>(v));
-    uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
-    uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
-    return min(min(a, b), min(c, d));
 }
 
 // number of set bits of `mask` strictly below this lane
