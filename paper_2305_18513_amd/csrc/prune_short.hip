@@ -15,8 +15,8 @@
 //   select   each lane keeps the largest CH keys of its segment in a sorted
 //            register list: inserting a key is one v_max plus CH-1 v_med3
 //            (new s[i] = median(s[i-1], s[i], key)), no branch, no cross-lane step.
-//            Where a lane has many, only the larger of two neighbours is inserted,
-//            and the partners of those that stayed afterwards.
+//            Where a lane has many (bf16), only the larger of two neighbours is
+//            inserted, and the partners of those that stayed afterwards.
 //            A key carries the entry's column below its value (bf16: the 16 value
 //            bits and the column; fp32: the upper 24 bits of the value's image and
 //            the column), so ties go to the lower column and the list itself names
@@ -177,12 +177,12 @@ struct ShortRows {
     static constexpr int LANE_BITS = G == 2 ? 1 : (G == 4 ? 2 : 3);
     static constexpr int TAG_BITS = 8 - LANE_BITS;             // entry's rank inside the lane's segment (at most 256 columns)
     static constexpr int N_OUT = (R * K + kWave - 1) / kWave;  // output pairs a lane stores
-    // Whether the larger of two neighbours stands for both in the selection's walk: where a lane has 65 (bf16) or 33 (fp32)
-    // entries or more (rows of more than 128 columns; NV is 4, 8, 13 or 16).  bf16 806 912 x 197, k = 9: 86.5 -> 78.0 us,
-    // 49 152 x 160, k = 16 12.5 -> 11.8, x 250, k = 12 14.1 -> 12.7; fp32 302 592 x 197 55.6 -> 54.2.  With fewer entries
-    // the partners cost as much or more: bf16 98 304 x 100 9.3 / 9.3, x 70 7.9 -> 8.1; fp32 x 50 8.0 -> 8.4, 196 608 x 33
-    // 9.7 -> 10.5.
-    static constexpr bool kPaired = NV >= 13;
+    // Whether the larger of two neighbours stands for both in the selection's walk: where a lane has 65 entries or more (bf16
+    // rows of more than 128 columns; NV is 4, 8, 13 or 16).  806 912 x 197, k = 9: 86.5 -> 78.0 us, 49 152 x 160, k = 16 12.5 -> 11.8,
+    // x 250, k = 12 14.1 -> 12.7; few rows of 130 columns lose (8192, k = 13 7.6 -> 8.0).  With fewer entries the partners cost
+    // as much or more: 98 304 x 100 9.3 / 9.3, x 70 7.9 -> 8.1, and so do fp32 rows of 33 to 64 entries a lane: 98 304 x 160
+    // 19.7 -> 20.5, nine tenths masked 18.9 -> 20.4, 49 152 x 224 17.7 -> 18.4, 302 592 x 197 55.6 -> 54.2.
+    static constexpr bool kPaired = BF && NV >= 13;
 
     // Visits the lane's entries e = 0 .. E-1 in column order: f(e, bits, ok) with the entry's bits (fp32: its
     // 32; bf16: its 16, zero-extended, or sign-extended when SEXT) and ok = "this lane has an entry e".  seg:
@@ -292,9 +292,7 @@ struct ShortRows {
             for (int j = 0; j < CHP - 1; ++j) {
                 const int other = (TAG_TOP - (m[j] & TAG_TOP)) ^ 1;
                 const bool has = m[j] != INT_MIN && other < len;
-                int bits;
-                if constexpr (BF) bits = NEG ? (int)(int16_t)seg[has ? other : 0] : (int)seg[has ? other : 0];
-                else bits = (int)__builtin_bit_cast(uint32_t, seg[has ? other : 0]);
+                const int bits = NEG ? (int)(int16_t)seg[has ? other : 0] : (int)seg[has ? other : 0];
                 partner[j] = has ? key_of(other, bits) : INT_MIN;
             }
             static_for(std::make_integer_sequence<int, CHP - 1>{}, [&](auto j) { chain_insert_below<CHP, j>(m, partner[j]); });

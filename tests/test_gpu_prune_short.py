@@ -137,7 +137,7 @@ def test_rows_enough_for_several_a_wave(dtype, cols, k, rows):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("cols", [129, 130, 131, 160, 161, 197, 199, 207, 208, 209, 250, 255])
 def test_rows_whose_neighbours_are_selected_together(cols, dtype):
-    """More than 128 columns: the walk takes entries in twos.  Odd and even parts, the largest entries side by side, apart,
+    """bf16 rows of more than 128 columns: the walk takes entries in twos; fp32 rows one by one.  Odd and even parts, the largest entries side by side, apart,
     at the ends of the lanes' parts, equal to one another, all of them of one sign or the other."""
     require_gpu()
     g = torch.Generator(device="cuda").manual_seed(cols)
