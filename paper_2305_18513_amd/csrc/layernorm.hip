@@ -16,16 +16,16 @@
 //                                     x^ = H g - sum g - x~ sum(g x~),
 //                                     g = gamma y^ / (H sqrt(Var + eps)), with
 //                                     x~ given as the (value, flat index) pairs
-//                                     Alg. 5 kept: the dense x~ is never rebuilt
-//                                     in memory.
+//                                     Alg. 5 kept: the dense x~ is rebuilt in LDS,
+//                                     never in memory.
 //
 // Both give a row of H elements to one wave: lane l holds the 16-byte vectors
 // l, l+64, ... of the row (NV of them), sums run over the lanes with DPP in a
-// fixed order, and nothing is read twice.  The backward kernel stages g and
-// then the output row in the wave's LDS region so that the kept pairs, which
-// arrive in index order and not in lane order, can be applied to it; the row's
-// pairs are found through row pointers (survivors ahead of every row), which
-// the pruner emits alongside the pairs.
+// fixed order, and nothing is read twice.  The pruned backward kernel scatters
+// the kept pairs, which arrive in index order and not in lane order, into the
+// wave's LDS region and reads them back as rows of x~; the row's pairs are found
+// through row pointers (survivors ahead of every row), which the pruner emits
+// alongside the pairs.
 #include "common.hpp"
 
 namespace slimfit {
@@ -215,108 +215,7 @@ layernorm_forward_kernel(const T *__restrict__ x, const float *__restrict__ gamm
     store_normalised<T, NV>(y + r * (int64_t)H, v, ga, be, nvec, lane, mu, rs);
 }
 
-template <typename T, int NV>
-__global__ void __launch_bounds__(kThreads)
-layernorm_backward_pruned_kernel(const float *__restrict__ vals, const int32_t *__restrict__ idx,
-                                 const int32_t *__restrict__ row_ptr, int64_t k, const float *__restrict__ rstd,
-                                 const float *__restrict__ gamma, const T *__restrict__ dy, int64_t rows, int H,
-                                 T *__restrict__ dx)
-{
-    constexpr int E = RowIO<T>::E;
-    extern __shared__ __align__(16) float lds[];             // kWaves rows of H floats
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t r = (int64_t)blockIdx.x * kWaves + wave;
-    if (r >= rows) return;
-    float *buf = lds + (size_t)wave * H;
-    const int nvec = H / E;
-    const int64_t e0 = r * (int64_t)H;
-
-    float g[NV][E], ga[NV][E];
-    load_row_t<T, NV>(dy + e0, nvec, lane, g);
-    load_params<E, NV>(gamma, nvec, lane, ga);
-
-    // the row's pairs: [row_ptr[r], row_ptr[r + 1]) of the index-ordered list
-    int64_t p0 = min(max((int64_t)row_ptr[r], (int64_t)0), k);
-    int64_t p1 = min(max((int64_t)row_ptr[r + 1], p0), min(k, p0 + H));
-
-    const float scale = rstd[r] / (float)H;
-    float part = 0.0f;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) g[i][e] = (ga[i][e] * g[i][e]) * scale;
-        part += sum_vec<E>(g[i]);
-        const int q = i * kWave + lane;
-        if (q < nvec) {
-#pragma unroll
-            for (int c = 0; c < E / 4; ++c)
-                reinterpret_cast<f32x4 *>(buf)[q * (E / 4) + c] = f32x4{g[i][4 * c], g[i][4 * c + 1], g[i][4 * c + 2], g[i][4 * c + 3]};
-        }
-    }
-    const float sum_g = wave_sum_f32(part);
-    __builtin_amdgcn_wave_barrier();                          // LDS serves a wave's accesses in order
-
-    // the row's pairs: the first kKeep * 64 stay in registers for both uses below
-    constexpr int kKeep = 4;
-    int kept_col[kKeep];
-    float kept_val[kKeep];
-#pragma unroll
-    for (int u = 0; u < kKeep; ++u) {
-        const int64_t s = p0 + u * kWave + lane;
-        kept_col[u] = -1;
-        kept_val[u] = 0.0f;
-        if (s < p1) {
-            const int64_t c = (int64_t)idx[s] - e0;
-            kept_col[u] = (c >= 0 && c < H) ? (int)c : -1;
-            kept_val[u] = vals[s];
-        }
-    }
-    part = 0.0f;
-#pragma unroll
-    for (int u = 0; u < kKeep; ++u)
-        if (kept_col[u] >= 0) part += buf[kept_col[u]] * kept_val[u];
-    for (int64_t s = p0 + kKeep * kWave + lane; s < p1; s += kWave) {
-        const int64_t c = (int64_t)idx[s] - e0;
-        if (c >= 0 && c < H) part += buf[c] * vals[s];
-    }
-    const float sum_gx = wave_sum_f32(part);
-    __builtin_amdgcn_wave_barrier();
-
-    const float fH = (float)H;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int q = i * kWave + lane;
-        if (q < nvec) {
-#pragma unroll
-            for (int c = 0; c < E / 4; ++c)
-                reinterpret_cast<f32x4 *>(buf)[q * (E / 4) + c] =
-                    f32x4{fH * g[i][4 * c] - sum_g, fH * g[i][4 * c + 1] - sum_g, fH * g[i][4 * c + 2] - sum_g,
-                          fH * g[i][4 * c + 3] - sum_g};
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    // distinct columns: no two lanes touch one slot
-#pragma unroll
-    for (int u = 0; u < kKeep; ++u)
-        if (kept_col[u] >= 0) buf[kept_col[u]] -= kept_val[u] * sum_gx;
-    for (int64_t s = p0 + kKeep * kWave + lane; s < p1; s += kWave) {
-        const int64_t c = (int64_t)idx[s] - e0;
-        if (c >= 0 && c < H) buf[c] -= vals[s] * sum_gx;
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int q = i * kWave + lane;
-        if (q < nvec) {
-            float o[E];
-            load_f32<E>(buf, q, o);
-            RowIO<T>::store(dx + e0, q, o);
-        }
-    }
-}
-
-// Shared back end of the two dense backward kernels: xt holds x~ (zeros in padding vectors), g holds y^.
+// Shared back end of the backward kernels: xt holds x~ (zeros in padding vectors), g holds y^.
 template <typename T, int NV>
 __device__ __forceinline__ void backward_from_xt(float (&xt)[NV][RowIO<T>::E], float (&g)[NV][RowIO<T>::E],
                                                  const float (&ga)[NV][RowIO<T>::E], int nvec, int lane, int H, float rs,
@@ -349,6 +248,75 @@ __device__ __forceinline__ void backward_from_xt(float (&xt)[NV][RowIO<T>::E], f
             RowIO<T>::store(dxrow, q, o);
         }
     }
+}
+
+// Bound by HBM (49152 x 1024 fp32, 10 % kept, 65.8 us, 6.7 TB/s of dy, pairs and dx; 50432 x 1024 bf16 41.8 us, 5.9).  The
+// row's x~ is rebuilt in the wave's LDS (zeros, then its pairs) and from there on the kernel is the dense one.  The pairs are
+// asked for with dy and not after its sum, and they pass through LDS once: with g staged, gathered by the pairs, the output
+// row staged and corrected by them, 67.5 and 45.6 us (half of the entries kept 126, now 111; 49152 x 256 bf16 21.5 and 19.0).
+template <typename T, int NV>
+__global__ void __launch_bounds__(kThreads)
+layernorm_backward_pruned_kernel(const float *__restrict__ vals, const int32_t *__restrict__ idx,
+                                 const int32_t *__restrict__ row_ptr, int64_t k, const float *__restrict__ rstd,
+                                 const float *__restrict__ gamma, const T *__restrict__ dy, int64_t rows, int H,
+                                 T *__restrict__ dx)
+{
+    constexpr int E = RowIO<T>::E;
+    extern __shared__ __align__(16) float lds[];             // kWaves rows of H floats
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = (int64_t)blockIdx.x * kWaves + wave;
+    if (r >= rows) return;
+    float *buf = lds + (size_t)wave * H;
+    const int nvec = H / E;
+    const int64_t e0 = r * (int64_t)H;
+
+    // the row's pairs: [row_ptr[r], row_ptr[r + 1]) of the index-ordered list
+    const int64_t p0 = min(max((int64_t)row_ptr[r], (int64_t)0), k);
+    const int64_t p1 = min(max((int64_t)row_ptr[r + 1], p0), min(k, p0 + H));
+    const int n_pairs = (int)(p1 - p0);
+    float xt[NV][E], g[NV][E], ga[NV][E];
+    load_row_t<T, NV>(dy + e0, nvec, lane, g);
+    load_params<E, NV>(gamma, nvec, lane, ga);
+
+    // The first 64 * kAhead pairs are asked for before anything is waited for; no branch around the loads.  (k > 0: where
+    // nothing is kept the host passes arrays of at least one entry.)
+    constexpr int kAhead = 2;
+    const int64_t last = max(p1, (int64_t)1) - 1;
+    int32_t at[kAhead];
+    float val[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        const int64_t s = min(p0 + u * kWave + lane, last);
+        at[u] = idx[s];
+        val[u] = vals[s];
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int q = i * kWave + lane;
+        if (q < nvec) {
+#pragma unroll
+            for (int c = 0; c < E / 4; ++c) reinterpret_cast<f32x4 *>(buf)[q * (E / 4) + c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    }
+    __builtin_amdgcn_wave_barrier();                          // LDS serves a wave's accesses in order
+    auto put = [&](int32_t where, float v) {                  // distinct columns: no two lanes touch one slot
+        const int64_t c = (int64_t)where - e0;
+        if (c >= 0 && c < H) buf[c] = v;
+    };
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+        if (u * kWave + lane < n_pairs) put(at[u], val[u]);
+    for (int s = kAhead * kWave + lane; s < n_pairs; s += kWave) put(idx[p0 + s], vals[p0 + s]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int q = i * kWave + lane;
+#pragma unroll
+        for (int e = 0; e < E; ++e) xt[i][e] = 0.0f;
+        if (q < nvec) load_f32<E>(buf, q, xt[i]);
+    }
+    backward_from_xt<T, NV>(xt, g, ga, nvec, lane, H, rstd[r], dx + e0);
 }
 
 template <typename T, int NV>
@@ -727,6 +695,10 @@ extern "C" int32_t slimfit_layernorm_backward_pruned(const float *vals, const in
     if (k > 0) {
         if ((rc = check_device_range(vals, (size_t)k * 4)) != SLIMFIT_OK) return rc;
         if ((rc = check_device_range(idx, (size_t)k * 4)) != SLIMFIT_OK) return rc;
+    }
+    if (k == 0) {                                                         // the kernel loads a pair ahead of looking at the count
+        vals = rstd;
+        idx = row_ptr;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     const unsigned grid = (unsigned)((rows + kWaves - 1) / kWaves);
