@@ -139,6 +139,19 @@ template <> __device__ __forceinline__ uint32_t make_key<uint16_t, false>(uint32
 template <> __device__ __forceinline__ uint32_t make_key<Bf16Row, true>(uint32_t b) { return make_key<float, true>(b); }
 template <> __device__ __forceinline__ uint32_t make_key<Bf16Row, false>(uint32_t b) { return make_key<float, false>(b); }
 
+// The element whose key is `key`, as a number, and whether an element's key reaches it: one comparison of numbers in
+// place of making the key.  (NaN: only which of them are kept could differ, and that is the caller's.)
+template <typename T, bool MAG> __device__ __forceinline__ float edge_of(uint32_t key)
+{
+    if (Elem<T>::KEYBITS == 16) key <<= 16;
+    return __builtin_bit_cast(float, MAG ? key >> 1 : (key & 0x80000000u) ? key ^ 0x80000000u : ~key);
+}
+template <typename T, bool MAG> __device__ __forceinline__ bool reaches(uint32_t bits, float edge)
+{
+    const float f = __builtin_bit_cast(float, Elem<T>::KEYBITS == 16 ? bits << 16 : bits);
+    return !((MAG ? __builtin_fabsf(f) : f) < edge);
+}
+
 __device__ __forceinline__ uint32_t raw_bits(const float *p) { return __builtin_bit_cast(uint32_t, *p); }
 __device__ __forceinline__ uint32_t raw_bits(const uint16_t *p) { return *p; }
 __device__ __forceinline__ uint32_t raw_bits(const Bf16Row *p) { return (uint32_t)p->h << 16; }
@@ -452,37 +465,67 @@ bracket_kernel(State *st, const u32x2 *__restrict__ sample, int wgs, uint32_t *f
 
 // ---- the sweep: records, key lists and totals --------------------------------------------
 // Bound by the read of the tensor and the records (0.7 bytes an element), with instruction issue close behind (bf16):
-// 50.3 M fp32 41.5 us, 5.7 TB/s; 51.6 M bf16 30 us, 4.6 TB/s.  A candidate's place comes from prefix sums over the
+// 50.3 M fp32 39 us, 6.1 TB/s; 51.6 M bf16 28 us, 5.2 TB/s.  A candidate's place comes from prefix sums over the
 // lanes' counts; a lane per element and two v_mbcnt each instead (4-byte loads, no counts) took 50 and 52 us.  The
 // records pass through LDS so that they leave in whole lines: 37 MB written here and read by the write below in
-// place of a second read of the tensor with one scattered store per survivor (42 us, bf16 44).
+// place of a second read of the tensor with one scattered store per survivor (42 us, bf16 44).  A candidate is compared,
+// counted and staged by its lane's bit of one mask; making and comparing its key for each, branching around each store and
+// leaving in 4-byte stores took 41.5 and 30 us.  Two tiles a workgroup: fp32 1.4 us slower, bf16 the same.
 // Leaves tile_cnt[tile] = (keys above the bracket | candidates << 16, keys filed).
+// byte address of a __shared__ object in the workgroup's LDS
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void *)p);
+}
+// Those lanes store two words at LDS byte address `at` and move 8 bytes on.  As an instruction sequence under the lane
+// mask: from `if` the compiler makes a branch around every store, which nearly always some lane of the 64 has to follow
+// there and back.
+__device__ __forceinline__ void stage_if(uint64_t lanes, uint32_t &at, uint32_t first, uint32_t second)
+{
+    uint64_t all;
+    asm volatile("s_and_saveexec_b64 %1, %2\n\t"
+                 "ds_write2_b32 %0, %3, %4 offset1:1\n\t"
+                 "v_add_u32_e32 %0, 8, %0\n\t"
+                 "s_mov_b64 exec, %1"
+                 : "+v"(at), "=&s"(all)
+                 : "s"(lanes), "v"(first), "v"(second)
+                 : "memory", "scc");
+}
 constexpr uint32_t kTooMany = 0x8000u;                      // in place of a tile's candidate count: it has no records
 // REC: make records; the tensor is not read again then, and its loads are non-temporal.
+template <bool REC>
+struct SweepLds {
+    alignas(16) u32x2 stage[REC ? kRecSlots : 2];           // (element bits, place in the tile)
+    uint32_t wave_cnt[kTileThreads / kWave];
+    uint32_t filed;
+};
 template <typename T, bool MAG, bool STD, bool INSIDE, bool REC>
 __device__ __forceinline__ void
 sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
-           uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, const Std &sd)
+           uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, const Std &sd,
+           SweepLds<REC> &lds)
 {
     constexpr int EPV = Elem<T>::EPV, G = kGroups<T>;
-    __shared__ u32x2 stage[REC ? kRecSlots : 1];                      // (element bits, place in the tile)
-    __shared__ uint32_t wave_cnt[kTileThreads / kWave];
-    __shared__ uint32_t filed;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t tile = blockIdx.x;
-    if (threadIdx.x == 0) filed = 0u;
+    if (threadIdx.x == 0) lds.filed = 0u;
     uint32_t bits[G][EPV];
     int valid[G];
     load_round<T, STD, INSIDE, REC>(x, n, tile, wave, lane, bits, valid, sd);
     const uint32_t lo = st->lo, last = st->last;
+    const float edge = edge_of<T, MAG>(lo);
 
     // candidates per group of 64 vectors: three 10-bit fields (at most 512 each) in one prefix sum
+    uint64_t cand[G][EPV];                                  // lane masks
     uint32_t packed[2] = {0u, 0u};
 #pragma unroll
     for (int j = 0; j < G; ++j) {
         uint32_t c = 0u;
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) c += ((INSIDE || e < valid[j]) && make_key<T, MAG>(bits[j][e]) >= lo) ? 1u : 0u;
+        for (int e = 0; e < EPV; ++e) {
+            cand[j][e] = __builtin_amdgcn_ballot_w64((INSIDE || e < valid[j]) && reaches<T, MAG>(bits[j][e], edge));
+            c += __builtin_amdgcn_inverse_ballot_w64(cand[j][e]) ? 1u : 0u;
+        }
         packed[j / 3] += c << (10 * (j % 3));
     }
     uint32_t incl[2], total[2];
@@ -494,45 +537,59 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
     uint32_t wave_total = 0u;
 #pragma unroll
     for (int j = 0; j < G; ++j) wave_total += (total[j / 3] >> (10 * (j % 3))) & 1023u;
-    if (lane == 0) wave_cnt[wave] = wave_total;
+    if (lane == 0) lds.wave_cnt[wave] = wave_total;
     __syncthreads();                                        // `filed` is zero as well
     uint32_t pos = 0u, n_cand = 0u;
 #pragma unroll
     for (int w = 0; w < kTileThreads / kWave; ++w) {
-        pos += (w < wave) ? wave_cnt[w] : 0u;
-        n_cand += wave_cnt[w];
+        const uint32_t c = lds.wave_cnt[w];
+        pos += (w < wave) ? c : 0u;
+        n_cand += c;
     }
+    n_cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_cand);
     uint32_t *keys = lists + tile * list_slots;
     const bool whole = REC && n_cand <= (uint32_t)kRecSlots;       // workgroup-uniform
     if (whole) {
 #pragma unroll
         for (int j = 0; j < G; ++j) {
-            uint32_t at = pos + (((incl[j / 3] - packed[j / 3]) >> (10 * (j % 3))) & 1023u);
+            uint32_t at = lds_address(lds.stage) + 8u * (pos + (((incl[j / 3] - packed[j / 3]) >> (10 * (j % 3))) & 1023u));
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) {
-                if ((INSIDE || e < valid[j]) && make_key<T, MAG>(bits[j][e]) >= lo)
-                    stage[at++] = u32x2{bits[j][e], (uint32_t)(((wave * G + j) * kWave + lane) * EPV + e)};
-            }
+            for (int e = 0; e < EPV; ++e)
+                stage_if(cand[j][e], at, bits[j][e], (uint32_t)(((wave * G + j) * kWave + lane) * EPV + e));
             pos += (total[j / 3] >> (10 * (j % 3))) & 1023u;
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the compiler does not count stage_if's writes
         __syncthreads();
+        // four records a lane
         uint32_t *rv = rec_val + tile * kRecSlots;
         uint16_t *rp = rec_pos + tile * kRecSlots;
-        for (uint32_t base = 0u; base < n_cand; base += kTileThreads) {
-            const uint32_t t = base + threadIdx.x;
-            const bool in = t < n_cand;
-            const u32x2 r = stage[min(t, n_cand - 1u)];
-            const uint32_t key = make_key<T, MAG>(r.x);
-            if (in) {
-                rv[t] = r.x;
-                rp[t] = (uint16_t)r.y;
+        static_assert(kRecSlots % 4 == 0 && kRecSlots <= 4 * kTileThreads, "one round");
+        const uint32_t t = 4u * threadIdx.x;
+        if ((uint32_t)(4 * kWave * wave) < n_cand) {        // wave-uniform
+            const u32x4 *r = reinterpret_cast<const u32x4 *>(lds.stage + min(t, (uint32_t)kRecSlots - 4u));
+            const u32x4 r0 = r[0], r1 = r[1];
+            const uint32_t v[4] = {r0.x, r0.z, r1.x, r1.z};
+            if (t < n_cand) {                               // (the slots up to the next vector take what is staged there)
+                *reinterpret_cast<u32x4 *>(rv + t) = u32x4{v[0], v[1], v[2], v[3]};
+                *reinterpret_cast<u32x2 *>(rp + t) = u32x2{r0.y | (r0.w << 16), r1.y | (r1.w << 16)};
             }
-            const uint64_t m = __builtin_amdgcn_ballot_w64(in && key <= last);
-            if (m != 0) {                                   // wave-uniform
+            uint64_t m[4];
+            uint32_t n_keys = 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                m[q] = __builtin_amdgcn_ballot_w64(t + q < n_cand && make_key<T, MAG>(v[q]) <= last);
+                n_keys += (uint32_t)__builtin_popcountll(m[q]);
+            }
+            if (n_keys != 0u) {                             // wave-uniform
                 uint32_t slot = 0u;
-                if (lane == 0) slot = atomicAdd(&filed, (uint32_t)__builtin_popcountll(m));
-                slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + lanes_below(m);
-                if (in && key <= last && slot < (uint32_t)list_slots) keys[slot] = key;
+                if (lane == 0) slot = atomicAdd(&lds.filed, n_keys);
+                slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t at = slot + lanes_below(m[q]);
+                    if (__builtin_amdgcn_inverse_ballot_w64(m[q]) && at < (uint32_t)list_slots) keys[at] = make_key<T, MAG>(v[q]);
+                    slot += (uint32_t)__builtin_popcountll(m[q]);
+                }
             }
         }
     } else {
@@ -548,7 +605,7 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
         const uint32_t upto = wave_scan_u32(in_bracket), all = wave_total_u32(upto);
         if (all) {                                          // wave-uniform
             uint32_t slot = 0u;
-            if (lane == 0) slot = atomicAdd(&filed, all);
+            if (lane == 0) slot = atomicAdd(&lds.filed, all);
             slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + upto - in_bracket;
 #pragma unroll
             for (int j = 0; j < G; ++j) {
@@ -565,7 +622,7 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t f = filed, gt = n_cand - f;
+        const uint32_t f = lds.filed, gt = n_cand - f;
         tile_cnt[tile] = u32x2{gt | ((whole ? n_cand : kTooMany) << 16), min(f, (uint32_t)list_slots)};
         if (f > (uint32_t)list_slots) st->overflow = 1u;
         atomicAdd(reinterpret_cast<unsigned long long *>(counters + (tile & (kCounters - 1)) * 8),
@@ -578,11 +635,12 @@ __global__ void __launch_bounds__(kTileThreads)
 sweep_kernel(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
              uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, Std sd)
 {
+    __shared__ SweepLds<REC> lds;
     if (st->plain) return;
     if (((int64_t)blockIdx.x + 1) * kTileElems <= n)        // workgroup-uniform: the whole tile lies below n
-        sweep_tile<T, MAG, STD, true, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd);
+        sweep_tile<T, MAG, STD, true, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd, lds);
     else
-        sweep_tile<T, MAG, STD, false, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd);
+        sweep_tile<T, MAG, STD, false, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd, lds);
 }
 
 // ---- one digit: LDS histogram of the matching keys, non-empty bins added to the global one ----
@@ -944,50 +1002,106 @@ __device__ __forceinline__ void write_tensor_tile(const T *__restrict__ x, int64
     }
 }
 
-// the survivors of a tile from its records (a wave; n_cand <= kRecSlots of them, 64 a register).  Bound by latency
-// (a wave's one round of loads, 1.7 waves a slot): 50.3 M fp32 entries, 5.03 M kept, 18 us for 80 MB.
-constexpr int kRecChunks = kRecSlots / kWave;
-constexpr int kFirstChunks = 8;            // loaded before the count is known
+// the survivors of a tile from its records (a wave; n_cand <= kRecSlots of them, four a lane and chunk): they pass through
+// the wave's LDS and leave as aligned 16-byte vectors, and a row's pointer is found among them by bisection.  Bound by
+// latency (a wave's one round of loads, 2.4 waves a slot): 50.3 M fp32 entries, 5.03 M kept, 19 us for 80 MB, 51.6 M bf16 16;
+// 22 and 19 with a record a lane, 4-byte stores and the pointers from each survivor's left neighbour.
+constexpr int kRecChunk = 4 * kWave;
+constexpr int kRecChunks = (kRecSlots + kRecChunk - 1) / kRecChunk;
+constexpr int kFirstChunks = 2;            // loaded before the count is known
+constexpr int kWriteSlots = kRecSlots + 4; // a wave's survivors in LDS, behind up to three unused slots
 template <typename T, bool MAG, bool STD>
-__device__ __forceinline__ void write_record_tile(const uint32_t (&v)[kRecChunks], const uint32_t (&p)[kRecChunks], uint32_t n_cand,
+__device__ __forceinline__ void write_record_tile(const u32x4 (&v)[kRecChunks], const u32x2 (&p)[kRecChunks], uint32_t n_cand,
                                                   int64_t n, int64_t tile, uint32_t Tk, uint32_t out_base, uint32_t budget,
-                                                  const Out<T> &out, const Std &sd)
+                                                  const Out<T> &out, const Std &sd, u32x2 *lds)
 {
+    using Val = typename Elem<T>::Out;
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t t0 = (uint32_t)(tile * kTileElems);
-    uint32_t kept = 0u, run_eq = 0u;
-    int row_run = -1;                                       // row of the last survivor (or the last row that began ahead of the tile)
-    const bool rows = STD && sd.row_ptr != nullptr;
-    if (rows && t0 > 0u) row_run = (int)row_of(t0 - 1u, sd);
+    // survivor s goes to lds[phase + s], so that where both outputs lie alike an aligned vector of theirs is one of lds
+    const uint32_t phase = ((uint32_t)(reinterpret_cast<uintptr_t>(out.idx) / 4) + out_base) & 3u;
+    uint32_t run_gt = 0u, run_eq = 0u;
 #pragma unroll
     for (int u = 0; u < kRecChunks; ++u) {
-        const uint32_t i = (uint32_t)(u * kWave + lane);
-        if ((uint32_t)(u * kWave) >= n_cand) break;         // wave-uniform
-        const uint32_t key = make_key<T, MAG>(v[u]);
-        const bool tie = i < n_cand && key == Tk;
-        const uint64_t ties = __builtin_amdgcn_ballot_w64(tie);
-        const bool keep = i < n_cand && (key > Tk || (tie && run_eq + lanes_below(ties) < budget));
-        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
-        const uint32_t pos = out_base + kept + lanes_below(m);
-        if (keep && pos < out.k) {                          // always below k for consistent counts; guards the stores
-            stream_raw(out.vals + pos, v[u]);
-            __builtin_nontemporal_store((int32_t)(t0 + p[u]), out.idx + pos);
+        if ((uint32_t)(u * kRecChunk) >= n_cand) break;     // wave-uniform
+        const uint32_t i = (uint32_t)(u * kRecChunk + 4 * lane);
+        const uint32_t r[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        const uint32_t at[4] = {p[u].x & 0xFFFFu, p[u].x >> 16, p[u].y & 0xFFFFu, p[u].y >> 16};
+        uint64_t above[4], tie[4];                          // lane masks
+        uint32_t c = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t key = make_key<T, MAG>(r[q]);
+            above[q] = __builtin_amdgcn_ballot_w64(i + q < n_cand && key > Tk);
+            tie[q] = __builtin_amdgcn_ballot_w64(i + q < n_cand && key == Tk);
+            c += __builtin_amdgcn_inverse_ballot_w64(above[q]) ? 1u : 0u;
         }
-        if (rows) {
-            // row_ptr[r] for the rows that begin between the previous survivor and this one
-            const int row = (int)row_of(t0 + p[u], sd);
-            const uint64_t below = m & (((uint64_t)1 << lane) - 1u);
-            const int prev = __shfl(row, below ? 63 - __builtin_clzll(below) : lane, kWave);
-            if (keep)
-                for (int r = (below ? prev : row_run) + 1; r <= row; ++r) sd.row_ptr[r] = (int32_t)pos;
-            if (m) row_run = __builtin_amdgcn_readlane(row, 63 - __builtin_clzll(m));
+        if ((tie[0] | tie[1] | tie[2] | tie[3]) != 0u) {    // wave-uniform
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c += __builtin_amdgcn_inverse_ballot_w64(tie[q]) ? 1u << 16 : 0u;
         }
-        kept += (uint32_t)__builtin_popcountll(m);
-        run_eq += (uint32_t)__builtin_popcountll(ties);
+        const uint32_t incl = wave_scan_u32(c), all = wave_total_u32(incl);
+        uint32_t my_eq = run_eq + ((incl - c) >> 16);
+        uint32_t to = lds_address(lds) + 8u * (phase + run_gt + ((incl - c) & 0xFFFFu) + min(my_eq, budget));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint64_t keep = above[q];
+            if (tie[q] != 0u) {                             // wave-uniform
+                const bool t = __builtin_amdgcn_inverse_ballot_w64(tie[q]);
+                keep |= __builtin_amdgcn_ballot_w64(t && my_eq < budget);
+                my_eq += t ? 1u : 0u;
+            }
+            stage_if(keep, to, r[q], t0 + at[q]);
+        }
+        run_gt += all & 0xFFFFu;
+        run_eq += all >> 16;
     }
-    if (rows) {
-        const int end = (int)row_of((uint32_t)(min((int64_t)t0 + kTileElems, n) - 1), sd);
-        for (int r = row_run + 1 + lane; r <= end; r += kWave) sd.row_ptr[r] = (int32_t)(out_base + kept);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the compiler does not count stage_if's writes
+    const uint32_t kept = run_gt + min(run_eq, budget);
+    const uint32_t first = min(out_base, out.k), end = phase + min(kept, out.k - first);     // (consistent counts never pass k)
+    const bool alike = sizeof(Val) == 4 && ((reinterpret_cast<uintptr_t>(out.vals) ^ reinterpret_cast<uintptr_t>(out.idx)) & 15u) == 0u;
+    if (alike) {
+        for (uint32_t b = 0u; b < end; b += kRecChunk) {
+            const uint32_t i = b + 4u * (uint32_t)lane;
+            const u32x4 *pair = reinterpret_cast<const u32x4 *>(lds + min(i, (uint32_t)kWriteSlots - 4u));
+            const u32x4 a = pair[0], c = pair[1];
+            const uint32_t val[4] = {a.x, a.z, c.x, c.z}, idx[4] = {a.y, a.w, c.y, c.w};
+            const int64_t o = (int64_t)first + i - phase;   // output slot of lds[i]
+            if (i >= phase && i + 4u <= end) {
+                __builtin_nontemporal_store(u32x4{val[0], val[1], val[2], val[3]}, reinterpret_cast<u32x4 *>(out.vals + o));
+                __builtin_nontemporal_store(u32x4{idx[0], idx[1], idx[2], idx[3]}, reinterpret_cast<u32x4 *>(out.idx + o));
+            } else {                                        // the vectors shared with the tiles before and after
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (i + q >= phase && i + q < end) {
+                        stream_raw(out.vals + o + q, val[q]);
+                        __builtin_nontemporal_store((int32_t)idx[q], out.idx + o + q);
+                    }
+                }
+            }
+        }
+    } else {
+        for (uint32_t i = phase + (uint32_t)lane; i < end; i += kWave) {
+            const u32x2 r = lds[i];
+            stream_raw(out.vals + (first + i - phase), r.x);
+            __builtin_nontemporal_store((int32_t)r.y, out.idx + (first + i - phase));
+        }
+    }
+    if constexpr (STD) {
+        if (sd.row_ptr) {
+            // the rows that begin in the tile: how many survivors lie ahead of their first element
+            const int r0 = t0 > 0u ? (int)row_of(t0 - 1u, sd) + 1 : 0, r1 = (int)row_of((uint32_t)(min((int64_t)t0 + kTileElems, n) - 1), sd);
+            for (int r = r0 + lane; r <= r1; r += kWave) {
+                const uint32_t e = (uint32_t)r * sd.H;
+                uint32_t before = 0u;
+#pragma unroll
+                for (uint32_t step = 512u; step > 0u; step >>= 1) {
+                    const uint32_t to = before + step;
+                    if (to <= kept && lds[phase + min(to, (uint32_t)kRecSlots) - 1u].y < e) before = to;
+                }
+                sd.row_ptr[r] = (int32_t)(out_base + before);
+            }
+        }
     }
 }
 
@@ -1106,21 +1220,25 @@ write_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *__restr
     // the records travel while the sums ahead are added up; no branch around any load
     const int64_t here = min(tile, ntiles - 1);
     const uint32_t n_cand = tile_cnt[here].x >> 16;
-    const uint32_t *rv = rec_val + here * kRecSlots;
-    const uint16_t *rp = rec_pos + here * kRecSlots;
-    uint32_t v[kRecChunks], p[kRecChunks];
+    const u32x4 *rv = reinterpret_cast<const u32x4 *>(rec_val + here * kRecSlots);
+    const u32x2 *rp = reinterpret_cast<const u32x2 *>(rec_pos + here * kRecSlots);
+    static_assert(kRecSlots % 4 == 0 && kFirstChunks * kRecChunk <= kRecSlots, "whole vectors");
+    u32x4 v[kRecChunks];
+    u32x2 p[kRecChunks];
 #pragma unroll
     for (int u = 0; u < kFirstChunks; ++u) {                // (a list's unused slots hold anything)
         v[u] = rv[u * kWave + lane];
         p[u] = rp[u * kWave + lane];
     }
-    const bool more = n_cand > (uint32_t)(kFirstChunks * kWave) && n_cand != kTooMany;
+    const bool more = n_cand > (uint32_t)(kFirstChunks * kRecChunk) && n_cand != kTooMany;
 #pragma unroll
     for (int u = kFirstChunks; u < kRecChunks; ++u) {
-        v[u] = p[u] = 0u;
+        v[u] = u32x4{0u, 0u, 0u, 0u};
+        p[u] = u32x2{0u, 0u};
         if (more) {
-            v[u] = rv[u * kWave + lane];
-            p[u] = rp[u * kWave + lane];
+            const int i = min(u * kWave + lane, kRecSlots / 4 - 1);
+            v[u] = rv[i];
+            p[u] = rp[i];
         }
     }
     const u32x2 ahead = sums_ahead(tile_sum, group_sum, here, group_tiles);
@@ -1129,11 +1247,12 @@ write_kernel(const T *__restrict__ x, int64_t n, State *st, const u32x2 *__restr
     // written from the tensor by the whole workgroup, whose waves read a quarter each.  By its own wave alone, a quarter
     // after another, the launch waited for it: such rows 50432 x 1024 bf16 100.8 us in all against 96.6, 49152 x 1024 fp32
     // 113.6 against 111.3.
+    __shared__ alignas(16) u32x2 kept[4][kWriteSlots];
     __shared__ u32x2 left[4];                               // such tiles: first output slot, ties to keep
     if (lane == 0) left[wave] = tile < ntiles && n_cand == kTooMany ? u32x2{out_base, budget} : u32x2{~0u, 0u};
     if (tile < ntiles) {
         write_pointers<T>(out, tile, ntiles, out_base, sd, STD);
-        if (n_cand != kTooMany) write_record_tile<T, MAG, STD>(v, p, n_cand, n, tile, Tk, out_base, budget, out, sd);
+        if (n_cand != kTooMany) write_record_tile<T, MAG, STD>(v, p, n_cand, n, tile, Tk, out_base, budget, out, sd, kept[wave]);
     }
     __syncthreads();
     for (int w = 0; w < 4; ++w) {
@@ -1432,11 +1551,11 @@ void launch_select(const T *x, int64_t n, uint32_t k, typename Elem<T>::Out *val
                                                         w.list_slots);
     }
     if (records)
-        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, w.rec_val,
-                                                                                 w.rec_pos, sd);
+        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
+                                                                                 w.rec_val, w.rec_pos, sd);
     else
-        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, nullptr,
-                                                                                  nullptr, sd);
+        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
+                                                                                  nullptr, nullptr, sd);
     digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, w.hist2,
                                                               ntiles, k, sd);
     if constexpr (Elem<T>::KEYBITS == 32)
