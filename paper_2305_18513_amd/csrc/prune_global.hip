@@ -12,12 +12,11 @@
 //             fold with -0 mapped onto +0 (by value); 32 bits for fp32, 16 for
 //             bf16.  A key's top 12 bits name its bin (1/16 of a binade by
 //             magnitude, 1/8 by value).
-//   sample    16 workgroups histogram the bins of up to 16384 vectors drawn one
-//             from each equal stretch of the tensor; one workgroup adds the
-//             histograms and fixes the bracket, the bins that hold the sample's
-//             k-th largest entry give or take six standard deviations of its
-//             rank.  Nothing depends on the sample being right: the counts of the
-//             next pass show whether T lies inside the bracket.
+//   sample    16 workgroups histogram the bins of up to 1024 vectors each, drawn one
+//             from each equal stretch of the tensor in turn, and each fixes a bracket
+//             of its own, the bin of its sample's entry of T's rank; the sweep joins
+//             the 16.  Nothing depends on the sample being right: the sweep's counts
+//             show whether T lies inside the joint bracket.
 //   sweep     one pass over the tensor, a workgroup per tile of 4096 elements:
 //             the candidates (keys not below the bracket) are collected in index
 //             order in LDS and leave as a contiguous run of (value, position)
@@ -80,10 +79,9 @@ constexpr int kMaxGroupTiles = 2048;       // 2^31 elements are 2^19 tiles
 constexpr int64_t kApartTiles = 4096;      // 1024 workgroups of the write
 
 struct State {                             // first 128 bytes of the workspace
-    uint32_t plain;                        // set ahead of the sweep: the lists will not be used
+    uint32_t plain;                        // the sweep made no lists
     uint32_t overflow;                     // set by the sweep: a tile's key list ran out of slots
-    uint32_t lo;                           // the bracket: keys lo .. lo + 2^range_bits - 1, as far as they exist
-    uint32_t last;                         // its largest key
+    uint32_t lo, last;                     // the bracket's smallest and largest key
     uint32_t digit2, shift2;               // bits of the first digit over the lists, and where it starts
     uint32_t use_plain;                    // set after the sweep: what every later launch goes by
     uint32_t prefix;                       // plain route: the top digit
@@ -373,15 +371,47 @@ __global__ void __launch_bounds__(kWideThreads) clear_kernel(u32x4 *zero, int n1
 }
 
 // ---- the sample ------------------------------------------------------------------------
+// A workgroup's own bracket: the bins of its sample's entries of the ranks rank_hi <= rank_lo, counted from the largest,
+// and how many of its entries lie between.  The sweep's bracket runs from the lowest to the highest of the workgroups'.
+struct alignas(8) Edges {
+    uint16_t hi, lo;
+    uint32_t within;
+};
+// hist: kTopBins counts; the threads of a workgroup of kWideThreads call it, thread 0 gets the answer
+__device__ __forceinline__ Edges find_edges(const uint32_t *hist, uint32_t rank_hi, uint32_t rank_lo)
+{
+    __shared__ uint32_t wave_sums[kWideWaves];
+    __shared__ uint32_t edge[4];                           // highest bin, entries above it, lowest bin, entries down to it
+    constexpr int PER = kTopBins / kWideThreads;           // 4
+    const int slot = kWideThreads - 1 - (int)threadIdx.x;  // bins 4 * slot .. 4 * slot + 3, highest first
+    const u32x4 f = reinterpret_cast<const u32x4 *>(hist)[slot];
+    const uint32_t h[PER] = {f.w, f.z, f.y, f.x};
+    if (threadIdx.x < 4) edge[threadIdx.x] = 0u;           // ranks outside the sample leave a bracket at the bottom: T is missed
+    uint32_t above = block_exclusive_scan<kWideThreads>(h[0] + h[1] + h[2] + h[3], wave_sums);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t bin = (uint32_t)(4 * slot + PER - 1 - j);
+        if (above < rank_hi && rank_hi <= above + h[j]) { edge[0] = bin; edge[1] = above; }
+        if (above < rank_lo && rank_lo <= above + h[j]) { edge[2] = bin; edge[3] = above + h[j]; }
+        above += h[j];
+    }
+    __syncthreads();
+    return Edges{(uint16_t)edge[0], (uint16_t)edge[2], edge[3] - edge[1]};
+}
+
 // One vector of each of `total` equal stretches of the tensor (all vectors when there are no more than that), for
-// stretch i at a place in it that depends on i only.  step: length of a stretch times 2^16.
+// stretch i at a place in it that depends on i only.  step: length of a stretch times 2^16.  The workgroups take the
+// stretches in turn, so that each of them sees the whole tensor.  Bound by latency (16 workgroups; one vector, its row's
+// statistics, the histogram, the scan): a launch of one workgroup that added up the histograms and chose one bracket took
+// 5 us after it.
 template <typename T, bool MAG, bool STD>
 __global__ void __launch_bounds__(kWideThreads)
-sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, u32x2 *__restrict__ sample, u32x4 *zero, int n16, Std sd)
+sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, uint32_t rank_hi, uint32_t rank_lo, Edges *__restrict__ edges,
+              State *st, u32x4 *zero, int n16, Std sd)
 {
     constexpr int EPV = Elem<T>::EPV;
-    __shared__ uint32_t bins[kTopBins];
-    const uint32_t mine = blockIdx.x * kWideThreads + threadIdx.x, i = min(mine, total - 1u);
+    __shared__ alignas(16) uint32_t bins[kTopBins];
+    const uint32_t mine = threadIdx.x * gridDim.x + blockIdx.x, i = min(mine, total - 1u);
     const uint64_t v0 = (i * step) >> 16, v1 = ((i + 1) * step) >> 16;
     uint32_t h = i * 0x9E3779B1u;
     h ^= h >> 15;
@@ -399,68 +429,57 @@ sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, u32x2 *__r
         for (int e = 0; e < EPV; ++e) atomicAdd(&bins[make_key<T, MAG>(bits[e]) >> (Elem<T>::KEYBITS - kTop)], 1u);
     }
     __syncthreads();
-    // 16-bit counts (a workgroup holds at most 16384 entries), four bins a thread
-    const uint32_t *b = bins + 4 * threadIdx.x;
-    sample[blockIdx.x * kWideThreads + threadIdx.x] = u32x2{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
+    const Edges e = find_edges(bins, rank_hi, rank_lo);
+    if (threadIdx.x < kSampleWgs / gridDim.x) edges[blockIdx.x + threadIdx.x] = e;      // (gridDim.x is kSampleWgs or 1)
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->overflow = 0u;
 }
 
-// One workgroup: the bracket from the sample's histograms (FULL: from the tensor's own, which is cleared again).
-// rank_hi <= rank_lo: the ranks, counted from the largest, whose bins bound it; size: entries counted.
-template <bool FULL>
-__global__ void __launch_bounds__(kWideThreads)
-bracket_kernel(State *st, const u32x2 *__restrict__ sample, int wgs, uint32_t *full, int key_bits, uint32_t rank_hi, uint32_t rank_lo,
-               uint32_t size, int list_slots)
+// The same from the tensor's own top digit, where T's rank is too close to an end for a sample.
+// (The histogram is cleared again.)
+__global__ void __launch_bounds__(kWideThreads) edges_kernel(uint32_t *hist, uint32_t k, Edges *__restrict__ edges, State *st)
 {
-    __shared__ uint32_t wave_sums[kWideWaves];
-    __shared__ uint32_t edge[4];                           // highest bin, entries above it, lowest bin, entries down to it
-    constexpr int PER = kTopBins / kWideThreads;           // 4
-    const int slot = kWideThreads - 1 - (int)threadIdx.x;  // bins 4 * slot .. 4 * slot + 3, highest first
-    uint32_t h[PER] = {0u, 0u, 0u, 0u};
-    if (FULL) {
-        const u32x4 f = reinterpret_cast<const u32x4 *>(full)[slot];
-        h[0] = f.w; h[1] = f.z; h[2] = f.y; h[3] = f.x;
-        reinterpret_cast<u32x4 *>(full)[slot] = u32x4{0u, 0u, 0u, 0u};
-    } else {
-        u32x2 s[kSampleWgs];
-#pragma unroll
-        for (int w = 0; w < kSampleWgs; ++w) s[w] = sample[min(w, wgs - 1) * kWideThreads + slot];
-#pragma unroll
-        for (int w = 0; w < kSampleWgs; ++w) {
-            if (w < wgs) {
-                h[0] += s[w].y >> 16; h[1] += s[w].y & 0xFFFFu;
-                h[2] += s[w].x >> 16; h[3] += s[w].x & 0xFFFFu;
-            }
-        }
-    }
-    if (threadIdx.x < 4) edge[threadIdx.x] = 0u;           // ranks outside the sample leave a bracket at the bottom: T is missed
-    uint32_t above = block_exclusive_scan<kWideThreads>(h[0] + h[1] + h[2] + h[3], wave_sums);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const uint32_t bin = (uint32_t)(4 * slot + PER - 1 - j);
-        if (above < rank_hi && rank_hi <= above + h[j]) { edge[0] = bin; edge[1] = above; }
-        if (above < rank_lo && rank_lo <= above + h[j]) { edge[2] = bin; edge[3] = above + h[j]; }
-        above += h[j];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int shift = key_bits - kTop;
-        const uint32_t nb = edge[0] - edge[2] + 1u;
-        int log_nb = 0;
-        while ((1u << log_nb) < nb && log_nb < 12) ++log_nb;
-        // too wide for the digits, or too much for the lists (on average 1/14 of the tensor where they hold 1/10.7 of a tile)
-        const bool plain = nb > (uint32_t)kMaxBracketBins ||
-                           (uint64_t)(edge[3] - edge[1]) * (14 * kListSlots) > (uint64_t)size * (uint32_t)list_slots;
-        const int range_bits = log_nb + shift;
-        // the rest is at most 14 bits, 12 for the usual brackets of up to 16 bins: every workgroup of the count reads that
-        // histogram whole (2^14 bins: 4096 x 768 in all 44.3 us, 2^12 40.9); more in this digit is more global atomics
-        const int digit2 = min(range_bits, min(kTop, max(9, log_nb + 8)));
-        st->plain = plain ? 1u : 0u;
-        st->overflow = 0u;
-        st->lo = edge[2] << shift;
-        st->last = (edge[2] << shift) + ((nb << shift) - 1u);
-        st->digit2 = (uint32_t)digit2;
-        st->shift2 = (uint32_t)(range_bits - digit2);
-    }
+    const Edges e = find_edges(hist, k, k);
+    reinterpret_cast<u32x4 *>(hist)[threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
+    if (threadIdx.x < kSampleWgs) edges[threadIdx.x] = e;
+    if (threadIdx.x == 0) st->overflow = 0u;
+}
+
+// The sweep's bracket; every workgroup works it out for itself.  size: entries that the sixteen edges were found among.
+struct Bracket {
+    uint32_t lo, last;                     // its smallest and largest key
+    int range_bits, digit2;
+    bool plain;                            // too wide for the digits or too much for the lists
+};
+__device__ __forceinline__ bool too_much(uint32_t bins, uint32_t within, uint64_t size, int list_slots)
+{
+    // the lists: on average 1/14 of the tensor where they hold 1/10.7 of a tile
+    return bins > (uint32_t)kMaxBracketBins || (uint64_t)within * (14 * kListSlots) > size * (uint32_t)list_slots;
+}
+__device__ __forceinline__ Bracket join_edges(u32x2 mine, int key_bits, uint64_t size, int list_slots)
+{
+    // a lane of each sixteen per pair of edges; by scalar loads and instructions, which a compute unit starts one at a time,
+    // the sweep of 49152 x 1024 took 4 us longer
+    static_assert(kSampleWgs == 16, "a DPP row");
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)group_max_u32(mine.x & 0xFFFFu, 16));
+    const uint32_t lo = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)group_max_u32(~(mine.x >> 16), 16));
+    uint32_t sum = mine.y;
+    sum += dpp_u32<kDppXor1>(sum);
+    sum += dpp_u32<kDppXor2>(sum);
+    sum += dpp_u32<kDppHalfMirror>(sum);
+    sum += dpp_u32<kDppMirror>(sum);
+    const uint32_t within = (uint32_t)__builtin_amdgcn_readfirstlane((int)sum);
+    const int shift = key_bits - kTop;
+    const uint32_t nb = hi - lo + 1u;
+    const int log_nb = nb > 1u ? 32 - __builtin_clz(nb - 1u) : 0;
+    Bracket b;
+    b.lo = lo << shift;
+    b.last = b.lo + ((nb << shift) - 1u);
+    b.range_bits = min(log_nb, 12) + shift;
+    // the rest is at most 14 bits, 12 for the usual brackets of up to 16 bins: every workgroup of the count reads that
+    // histogram whole (2^14 bins: 4096 x 768 in all 44.3 us, 2^12 40.9); more in this digit is more global atomics
+    b.digit2 = min(b.range_bits, min(kTop, max(9, log_nb + 8)));
+    b.plain = too_much(nb, within, size, list_slots);
+    return b;
 }
 
 // ---- the sweep: records, key lists and totals --------------------------------------------
@@ -501,7 +520,7 @@ struct SweepLds {
 };
 template <typename T, bool MAG, bool STD, bool INSIDE, bool REC>
 __device__ __forceinline__ void
-sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
+sweep_tile(const T *__restrict__ x, int64_t n, u32x2 edges, uint64_t size, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
            uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, const Std &sd,
            SweepLds<REC> &lds)
 {
@@ -512,7 +531,16 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
     uint32_t bits[G][EPV];
     int valid[G];
     load_round<T, STD, INSIDE, REC>(x, n, tile, wave, lane, bits, valid, sd);
-    const uint32_t lo = st->lo, last = st->last;
+    const Bracket br = join_edges(edges, Elem<T>::KEYBITS, size, list_slots);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {             // for the launches that follow
+        st->plain = br.plain ? 1u : 0u;
+        st->lo = br.lo;
+        st->last = br.last;
+        st->digit2 = (uint32_t)br.digit2;
+        st->shift2 = (uint32_t)(br.range_bits - br.digit2);
+    }
+    if (br.plain) return;
+    const uint32_t lo = br.lo, last = br.last;
     const float edge = edge_of<T, MAG>(lo);
 
     // candidates per group of 64 vectors: three 10-bit fields (at most 512 each) in one prefix sum
@@ -632,15 +660,20 @@ sweep_tile(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__
 
 template <typename T, bool MAG, bool STD, bool REC>
 __global__ void __launch_bounds__(kTileThreads)
-sweep_kernel(const T *__restrict__ x, int64_t n, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
+sweep_kernel(const T *__restrict__ x, int64_t n, const Edges *__restrict__ edges, uint64_t size, State *st, uint64_t *__restrict__ counters, u32x2 *__restrict__ tile_cnt,
              uint32_t *__restrict__ lists, int list_slots, uint32_t *__restrict__ rec_val, uint16_t *__restrict__ rec_pos, Std sd)
 {
     __shared__ SweepLds<REC> lds;
-    if (st->plain) return;
+    const u32x2 mine = reinterpret_cast<const u32x2 *>(edges)[threadIdx.x & (kSampleWgs - 1)];
+    // The tile is asked for before the edges have arrived, unless one pair of them says that it may not be needed.
+    const u32x2 one = reinterpret_cast<const u32x2 *>(edges)[blockIdx.x & (kSampleWgs - 1)];
+    if (too_much((one.x & 0xFFFFu) - (one.x >> 16) + 1u, one.y * kSampleWgs, size, list_slots) && blockIdx.x != 0 &&
+        join_edges(mine, Elem<T>::KEYBITS, size, list_slots).plain)
+        return;
     if (((int64_t)blockIdx.x + 1) * kTileElems <= n)        // workgroup-uniform: the whole tile lies below n
-        sweep_tile<T, MAG, STD, true, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd, lds);
+        sweep_tile<T, MAG, STD, true, REC>(x, n, mine, size, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd, lds);
     else
-        sweep_tile<T, MAG, STD, false, REC>(x, n, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd, lds);
+        sweep_tile<T, MAG, STD, false, REC>(x, n, mine, size, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd, lds);
 }
 
 // ---- one digit: LDS histogram of the matching keys, non-empty bins added to the global one ----
@@ -1363,13 +1396,12 @@ restore_tiles_kernel(const T *__restrict__ vals, const int32_t *__restrict__ idx
     for (int e = full * PER16 + tid; e < m; e += kTileThreads) out[t0 + e] = tile[e];
 }
 
-// Workspace: state | counters | group sums | three histograms | sample | tile counts | tile sums | key lists | records.
+// Workspace: state | counters | group sums | three histograms | the sample's edges | tile counts | tile sums | key lists | records.
 // From the counters to the histograms everything has to be zero at the start.
 //
 // That is 1.3 bytes an element.  Before the records there was a quarter of a byte, and a caller may hold a workspace of
 // that size: it is still served, in one of two smaller layouts.
-//   lists   no records (the survivors are written from the tensor), the sample where the lists will be, and as many list
-//           slots as there is room for;
+//   lists   no records (the survivors are written from the tensor), and as many list slots as there is room for;
 //   plain   where not even 192 slots fit beside the histograms (below 4 - 6 M elements): no sample and no sweep, the
 //           plain route's launches alone, with the state, two histograms and the sums.
 struct Workspace {
@@ -1377,7 +1409,7 @@ struct Workspace {
     uint64_t *counters;
     u32x2 *group_sum;
     uint32_t *hist2, *hist3, *hist4;
-    u32x2 *sample;
+    Edges *edges;
     u32x2 *tile_cnt, *tile_sum;
     uint32_t *lists, *rec_val;
     uint16_t *rec_pos;
@@ -1399,7 +1431,6 @@ struct Carver {
 };
 size_t tiles_of(int64_t n) { return (size_t)((n + kPtrTile - 1) / kPtrTile); }
 int group_tiles_for(int64_t ntiles) { return (int)(((ntiles + kMaxGroups - 1) / kMaxGroups + 3) / 4 * 4); }
-constexpr size_t kSampleBytes = (size_t)kSampleWgs * kTopBins * 2;
 Workspace carve(void *base, int64_t n, int list_slots, bool records)
 {
     Workspace w = {};
@@ -1415,16 +1446,13 @@ Workspace carve(void *base, int64_t n, int list_slots, bool records)
     w.hist4 = c.take<uint32_t>((size_t)kTopBins * 4);
     w.zero = reinterpret_cast<u32x4 *>(w.counters);
     w.zero16 = (int)((c.off - sizeof(State)) / 16);
-    if (records) w.sample = c.take<u32x2>(kSampleBytes);
+    w.edges = c.take<Edges>(kSampleWgs * sizeof(Edges));
     w.tile_cnt = c.take<u32x2>(tiles * 8);
     w.tile_sum = c.take<u32x2>(tiles * 8);
-    const size_t list_bytes = tiles * (size_t)list_slots * 4;
-    w.lists = c.take<uint32_t>(records || list_bytes > kSampleBytes ? list_bytes : kSampleBytes);
+    w.lists = c.take<uint32_t>(tiles * (size_t)list_slots * 4);
     if (records) {
         w.rec_val = c.take<uint32_t>(tiles * kRecSlots * 4);
         w.rec_pos = c.take<uint16_t>(tiles * kRecSlots * 2);
-    } else {
-        w.sample = reinterpret_cast<u32x2 *>(w.lists);      // (read before the sweep files the first key)
     }
     w.bytes = c.off;
     return w;
@@ -1461,8 +1489,8 @@ size_t least_workspace_for(int64_t n)
 Workspace carve_room(void *base, int64_t n, size_t room)            // room >= least_workspace_for(n)
 {
     if (room >= workspace_bytes_for(n)) return carve(base, n, kListSlots, true);
-    const size_t bare = carve(origin, n, 0, false).bytes - kSampleBytes, tiles = tiles_of(n);
-    if (room >= bare + kSampleBytes) {
+    const size_t bare = carve(origin, n, 0, false).bytes, tiles = tiles_of(n);
+    if (room >= bare) {
         const size_t fit = (room - bare) / (tiles * 4);             // (whole lines: a multiple of 32)
         const int slots = (int)(fit < (size_t)kListSlots ? fit / 32 * 32 : (size_t)kListSlots);
         if (slots >= kMinListSlots) return carve(base, n, slots, false);
@@ -1470,33 +1498,42 @@ Workspace carve_room(void *base, int64_t n, size_t room)            // room >= l
     return carve_plain(base, n);
 }
 
-// Which ranks of the sample bound the bracket.  The rank of T in a sample of `size` unlike entries has a standard
-// deviation of at most sqrt(size f (1 - f)), f = k / n: six of them either way, 0.7 % of the tensor at f = 0.1.  (All
-// of a vector's four entries alike: three.)
+// Which ranks of a workgroup's sample bound its bracket: those next to T's own, f = k / n of the sample.  The 16 samples are
+// as good as independent of one another, and T is as likely above a workgroup's bracket as below it: it is missed on one
+// side of all 16 once in 2^15 tensors, whatever their distribution (and hardly ever where the workgroups see every vector:
+// 16 counts cannot all lie on one side of their mean).  The joint bracket spans 3.5 standard deviations sqrt(size f (1 - f)) of
+// a workgroup's rank, 1.7 % of the tensor at f = 0.1, and the rest of its outer bins.  (One bracket of six deviations either
+// way from the sum of the 16 histograms, 1.4 %, took a launch of one workgroup more: 4096 x 768 37.3 us in all and 33.7
+// now, 8192 x 1024 bf16 41.8 and 38.3, 49152 x 1024 87.7 and 88.2.)
 struct SamplePlan {
     bool use;                              // false: T's rank is too close to an end, the tensor's own histogram is taken
+    int wgs;
     uint32_t total, hi, lo, size;
     uint64_t step;
 };
 SamplePlan plan_sample(int64_t n, int64_t k, int epv)
 {
-    SamplePlan p = {false, 0u, 0u, 0u, 0u, 0u};
+    SamplePlan p = {false, 0, 0u, 0u, 0u, 0u, 0u};
     const int64_t vectors = n / epv, most = (int64_t)kSampleWgs * kWideThreads;
     if (vectors == 0) return p;
-    const int64_t total = vectors < most ? vectors : most, size = total * epv, rest = n - vectors * epv;
+    const int64_t total = vectors < most ? vectors : most, rest = n - vectors * epv;
     p.total = (uint32_t)total;
-    p.size = (uint32_t)size;
+    p.size = (uint32_t)(total * epv);
     p.step = ((uint64_t)vectors << 16) / (uint64_t)total;
-    int64_t hi, lo;
-    if (total == vectors) {                // every vector: only the last few entries were not seen
+    int64_t hi, lo, size;
+    if (vectors <= kWideThreads) {         // one workgroup sees every vector: only the last few entries were not seen
+        p.wgs = 1;
+        size = total * epv;
         hi = k - rest;
         lo = k;
     } else {
         const double f = (double)k / (double)n;
-        const int64_t r = (int64_t)(f * (double)size), margin = (int64_t)(6.0 * std::sqrt((double)size * f * (1.0 - f))) + rest + 1;
-        if (r < 256 || size - r < 256) return p;
-        hi = r - margin;
-        lo = r + margin;
+        if (vectors > most && (f * p.size < 256 || (1.0 - f) * p.size < 256)) return p;
+        p.wgs = kSampleWgs;
+        size = total / kSampleWgs * epv;   // (some have a vector more)
+        const double r = f * (double)size;
+        hi = (int64_t)r;
+        lo = (int64_t)r + 1;
     }
     p.use = true;
     p.hi = (uint32_t)(hi < 1 ? 1 : hi);
@@ -1540,21 +1577,19 @@ void launch_select(const T *x, int64_t n, uint32_t k, typename Elem<T>::Out *val
     const SamplePlan plan = plan_sample(n, (int64_t)k, Elem<T>::EPV);
 
     if (plan.use) {
-        const int wgs = (int)((plan.total + kWideThreads - 1) / kWideThreads);
-        sample_kernel<T, MAG, STD><<<wgs, kWideThreads, 0, s>>>(x, plan.total, plan.step, w.sample, w.zero, w.zero16, sd);
-        bracket_kernel<false><<<1, kWideThreads, 0, s>>>(w.st, w.sample, wgs, nullptr, Elem<T>::KEYBITS, plan.hi, plan.lo,
-                                                         plan.size, w.list_slots);
+        sample_kernel<T, MAG, STD><<<plan.wgs, kWideThreads, 0, s>>>(x, plan.total, plan.step, plan.hi, plan.lo, w.edges, w.st, w.zero,
+                                                                     w.zero16, sd);
     } else {
         clear_kernel<<<1, kWideThreads, 0, s>>>(w.zero, w.zero16, nullptr);
         top_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.hist4, sd);
-        bracket_kernel<true><<<1, kWideThreads, 0, s>>>(w.st, nullptr, 0, w.hist4, Elem<T>::KEYBITS, k, k, (uint32_t)n,
-                                                        w.list_slots);
+        edges_kernel<<<1, kWideThreads, 0, s>>>(w.hist4, k, w.edges, w.st);
     }
+    const uint64_t size = plan.use && plan.wgs == kSampleWgs ? plan.size : (plan.use ? (uint64_t)plan.size : (uint64_t)n) * kSampleWgs;
     if (records)
-        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
+        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.edges, size, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
                                                                                  w.rec_val, w.rec_pos, sd);
     else
-        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
+        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.edges, size, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
                                                                                   nullptr, nullptr, sd);
     digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, w.hist2,
                                                               ntiles, k, sd);
