@@ -525,6 +525,20 @@ int32_t slimfit_merge_heads(const void *q, const void *kt, const void *v, int32_
                             int32_t heads, int32_t head_dim, float q_scale, void *qkv, void *stream);
 
 /* ------------------------------------------------------------------------
+ * Product of fp32 matrices (the dense products of the linear layers):
+ *        out[i][j] = sum over k of a[i][k] * b[j][k]     (b_deep != 0: b is N x K)
+ *        out[i][j] = sum over k of a[i][k] * b[k][j]     (b_deep == 0: b is K x N)
+ *  a, b, out : DEVICE fp32, row-major and contiguous; a, b 16-byte aligned, out 4-byte; out overlaps neither.
+ *  K has to be a multiple of 32: ERR_UNSUPPORTED.
+ *  Each operand is split exactly into three bf16 numbers and six of the nine partial products are added up in fp32
+ *  (the other three are below 2^-26 of theirs): no further from the exact product than fp32 additions in any order,
+ *      |out - exact| <= K * 2^-24 * sum |a||b|,
+ *  for entries of magnitude above 2^-100.  Infinities and NaN come out as in plain fp32 arithmetic.  Deterministic.
+ * ---------------------------------------------------------------------- */
+int32_t slimfit_product(const float *a, const float *b, int32_t b_deep, int64_t M, int64_t N, int64_t K, float *out,
+                        void *stream);
+
+/* ------------------------------------------------------------------------
  * (d) Inter-layer scheduling on the host -- Alg. 1 and Sec. 3.2 / Fig. 4:
  *        idx = argsort(d)[: int(L*F)]   -> these layers are frozen;
  *     afterwards only the layers that were active take their new distance,

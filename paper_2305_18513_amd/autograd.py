@@ -3,7 +3,8 @@
 Each Function runs its forward through the library, keeps only the compressed
 form of the activation its backward needs, and skips the weight gradient of a
 frozen layer.  Nothing here computes on its own what a kernel of the library
-computes; the dense matrix products of the linear layer are torch's.
+computes; the dense matrix products of the linear layers are the library's for
+large fp32 operands and torch's otherwise.
 
   GeluFunction       y = GELU(x); caches x in `bits` bits (per-block scales);
                      backward multiplies by GELU'(x^) straight from the cache.
@@ -274,6 +275,33 @@ class SplitHeadsFunction(torch.autograd.Function):
         return dqkv, None, None
 
 
+def _plain(t: torch.Tensor) -> bool:
+    """Whether a kernel may be handed the tensor's memory as it is."""
+    return type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and t.data_ptr() % 16 == 0
+
+
+def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
+    """x @ weight.T or x @ weight over x's last dimension by the library's fp32 product, or None where that is torch's.
+
+    It is the faster one where the product has at least 192 tiles of 128 x 64, three for four compute units (rows x columns x
+    depth, torch's and this in us: 4096 x 768 x 3072 140 and 95, 2048 x 768 x 3072 76 and 65, 192 tiles; 2048 x 512 x 2048 34
+    and 44, 1024 x 1024 x 4096 63 and 85, 128 tiles each, which torch splits along their depth)."""
+    if torch.is_grad_enabled() or torch.is_autocast_enabled() or torch.compiler.is_compiling():
+        return None                                        # products to be differentiated, cast or traced are torch's
+    if not (_plain(x) and _plain(weight) and x.dim() >= 2 and weight.dim() == 2):
+        return None
+    K = x.shape[-1]
+    N, depth = weight.shape if transposed else weight.shape[::-1]
+    if depth != K or K == 0 or K % 32 != 0:
+        return None
+    M = x.numel() // K
+    if -(-M // 128) * -(-N // 64) < 192:
+        return None
+    y = torch.empty(*x.shape[:-1], N, dtype=x.dtype, device=x.device)
+    sf.product(x.view(M, K), weight, transposed, y.view(M, N))
+    return y
+
+
 class LinearFunction(torch.autograd.Function):
     """y = x W^T (+ b) under the freezing rule of Alg. 4.  Whether the layer is frozen is read off the weight itself
     (``weight.requires_grad``, which is what an inter-layer scheduler flips between iterations): a frozen layer
@@ -282,7 +310,9 @@ class LinearFunction(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x: torch.Tensor, weight: torch.Tensor, bias, bits: int = 8, block: int = 64):
-        y = torch.nn.functional.linear(x, weight, bias)
+        y = _dense(x, weight, True) if bias is None else None
+        if y is None:
+            y = torch.nn.functional.linear(x, weight, bias)
         ctx.cache = None                                   # descriptor of what is kept of x: nothing, or (bits, block, shape, dtype)
         ctx.bias_active = bias is not None and bias.requires_grad
         if weight.requires_grad:
@@ -296,7 +326,11 @@ class LinearFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dy: torch.Tensor):
         weight = ctx.saved_tensors[0]
-        dx = dy.matmul(weight) if ctx.needs_input_grad[0] else None
+        dx = None
+        if ctx.needs_input_grad[0]:
+            dx = _dense(dy, weight, False)
+            if dx is None:
+                dx = dy.matmul(weight)
         dy2 = dy.reshape(-1, dy.shape[-1])
         dw = None
         if ctx.cache is not None:

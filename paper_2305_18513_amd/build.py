@@ -29,7 +29,7 @@ LIB = os.path.join(PKG, "libslimfit.so")
 NATIVE = os.path.join(PKG, "_native.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
-SOURCES = ("api.hip", "quant.hip", "layer_delta.hip", "prune.hip", "prune_short.hip", "prune_global.hip", "layernorm.hip", "heads.hip", "probe.hip")
+SOURCES = ("api.hip", "quant.hip", "layer_delta.hip", "prune.hip", "prune_short.hip", "prune_global.hip", "layernorm.hip", "heads.hip", "product.hip", "probe.hip")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
