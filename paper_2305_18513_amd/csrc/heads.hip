@@ -183,10 +183,10 @@ int32_t heads_entry(void *fused, int32_t dt, int64_t batch, int32_t tokens, int3
     for (int64_t first = 0; first < all; first += kMost) {
         const unsigned here = (unsigned)(all - first < kMost ? all - first : kMost);
         if (dt == SLIMFIT_F32)
-            heads_kernel<float, SPLIT><<<here, kThreads, 0, st>>>(static_cast<float *>(fused), static_cast<float *>(q),
+            launch(heads_kernel<float, SPLIT>, here, kThreads, 0, st, static_cast<float *>(fused), static_cast<float *>(q),
                                                                   static_cast<float *>(kt), static_cast<float *>(v), s, (unsigned)first);
         else
-            heads_kernel<uint16_t, SPLIT><<<here, kThreads, 0, st>>>(static_cast<uint16_t *>(fused), static_cast<uint16_t *>(q),
+            launch(heads_kernel<uint16_t, SPLIT>, here, kThreads, 0, st, static_cast<uint16_t *>(fused), static_cast<uint16_t *>(q),
                                                                      static_cast<uint16_t *>(kt), static_cast<uint16_t *>(v), s,
                                                                      (unsigned)first);
     }

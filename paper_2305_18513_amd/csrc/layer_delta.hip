@@ -297,11 +297,11 @@ void launch_partials(bool is_delta, bool apply, unsigned grid, hipStream_t st, c
                      float eps, double *partials)
 {
     if (apply)
-        layer_delta_partials_kernel<TP, TC, true, true><<<grid, kApplyThreads, 0, st>>>(ws, L, chunks, eps, partials);
+        launch(layer_delta_partials_kernel<TP, TC, true, true>, grid, kApplyThreads, 0, st, ws, L, chunks, eps, partials);
     else if (is_delta)
-        layer_delta_partials_kernel<TP, TC, true><<<grid, kThreads, 0, st>>>(ws, L, chunks, eps, partials);
+        launch(layer_delta_partials_kernel<TP, TC, true>, grid, kThreads, 0, st, ws, L, chunks, eps, partials);
     else
-        layer_delta_partials_kernel<TP, TC, false><<<grid, kThreads, 0, st>>>(ws, L, chunks, eps, partials);
+        launch(layer_delta_partials_kernel<TP, TC, false>, grid, kThreads, 0, st, ws, L, chunks, eps, partials);
 }
 
 }  // namespace
@@ -359,7 +359,7 @@ static int32_t plan_entry(const void *const *w_prev, int32_t prev_dt, const void
             batch.e[t].first_chunk = next_chunk;
             next_chunk += (numel[i] + kChunk - 1) / kChunk;
         }
-        plan_write_kernel<<<1, kWave, 0, st>>>(static_cast<char *>(workspace), h, first, count, batch);
+        launch(plan_write_kernel, 1, kWave, 0, st, static_cast<char *>(workspace), h, first, count, batch);
     }
     return launch_status();
 }
@@ -401,7 +401,7 @@ static int32_t run_entry(const int64_t *numel, int32_t L, int32_t prev_dt, int32
         else
             launch_partials<uint16_t, uint16_t>(is_delta, apply, grid, st, ws, L, lay.total_chunks, eps, partials);
     }
-    layer_delta_finish_kernel<<<(unsigned)L, kWave, 0, st>>>(ws, L, lay.total_chunks, prev_dt, cur_dt, partials, d_out);
+    launch(layer_delta_finish_kernel, (unsigned)L, kWave, 0, st, ws, L, lay.total_chunks, prev_dt, cur_dt, partials, d_out);
     return launch_status();
 }
 

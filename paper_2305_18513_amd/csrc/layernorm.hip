@@ -665,7 +665,7 @@ extern "C" int32_t slimfit_layernorm_forward(const void *x, int32_t dt, const fl
     if ((rc = check_device_range(rstd, (size_t)rows * 4)) != SLIMFIT_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const unsigned grid = (unsigned)((rows + kWaves - 1) / kWaves);
-    SLIMFIT_LN_DISPATCH_T(dt, H, (layernorm_forward_kernel<TT, NV><<<grid, kThreads, 0, s>>>(
+    SLIMFIT_LN_DISPATCH_T(dt, H, (launch(layernorm_forward_kernel<TT, NV>, grid, kThreads, 0, s, 
                                      static_cast<const TT *>(x), gamma, beta, rows, (int)H, eps, static_cast<TT *>(y), mean,
                                      rstd)));
     return launch_status();
@@ -703,7 +703,7 @@ extern "C" int32_t slimfit_layernorm_backward_pruned(const float *vals, const in
     hipStream_t s = static_cast<hipStream_t>(stream);
     const unsigned grid = (unsigned)((rows + kWaves - 1) / kWaves);
     const size_t lds_bytes = (size_t)kWaves * (size_t)H * 4;              // at most 64 KB
-    SLIMFIT_LN_DISPATCH_T(dt, H, (layernorm_backward_pruned_kernel<TT, NV><<<grid, kThreads, lds_bytes, s>>>(
+    SLIMFIT_LN_DISPATCH_T(dt, H, (launch(layernorm_backward_pruned_kernel<TT, NV>, grid, kThreads, lds_bytes, s, 
                                      vals, idx, row_ptr, k, rstd, gamma, static_cast<const TT *>(dy), rows, (int)H,
                                      static_cast<TT *>(dx))));
     return launch_status();
@@ -754,16 +754,16 @@ extern "C" int32_t slimfit_layernorm_param_grads(const void *x, int32_t dt, cons
     const int groups = (int)((H / epv + kGroupVecs - 1) / kGroupVecs);
     if (slabs > 0) {
         if (dt == SLIMFIT_F32)
-            param_grad_partials_kernel<float><<<(unsigned)(slabs * groups), kThreads, 0, s>>>(
+            launch(param_grad_partials_kernel<float>, (unsigned)(slabs * groups), kThreads, 0, s, 
                 static_cast<const float *>(x), mean, rstd, static_cast<const float *>(dy), rows, (int)H, groups, slab_rows,
                 partials);
         else
-            param_grad_partials_kernel<uint16_t><<<(unsigned)(slabs * groups), kThreads, 0, s>>>(
+            launch(param_grad_partials_kernel<uint16_t>, (unsigned)(slabs * groups), kThreads, 0, s, 
                 static_cast<const uint16_t *>(x), mean, rstd, static_cast<const uint16_t *>(dy), rows, (int)H, groups,
                 slab_rows, partials);
     }
     const unsigned fgrid = (unsigned)((2 * H + kFinishCols - 1) / kFinishCols);
-    param_grad_finish_kernel<<<fgrid, kFinishThreads, 0, s>>>(partials, slabs, (int)H, dgamma, dbeta);
+    launch(param_grad_finish_kernel, fgrid, kFinishThreads, 0, s, partials, slabs, (int)H, dgamma, dbeta);
     return launch_status();
 }
 
@@ -788,7 +788,7 @@ extern "C" int32_t slimfit_layernorm_backward(const void *x, int32_t dt, const f
     if ((rc = check_device_range(rstd, (size_t)rows * 4)) != SLIMFIT_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const unsigned grid = (unsigned)((rows + kWaves - 1) / kWaves);
-    SLIMFIT_LN_DISPATCH_T(dt, H, (layernorm_backward_kernel<TT, NV><<<grid, kThreads, 0, s>>>(
+    SLIMFIT_LN_DISPATCH_T(dt, H, (launch(layernorm_backward_kernel<TT, NV>, grid, kThreads, 0, s, 
                                      static_cast<const TT *>(x), mean, rstd, gamma, static_cast<const TT *>(dy), rows, (int)H,
                                      static_cast<TT *>(dx))));
     return launch_status();
@@ -823,11 +823,11 @@ extern "C" int32_t slimfit_layernorm_forward_quant_pack(const void *x, int32_t d
     const unsigned grid = (unsigned)((rows + kWaves - 1) / kWaves);
     const int G = block / (dt == SLIMFIT_F32 ? 4 : 8), shift = __builtin_ctz((unsigned)block);
     if (bits == 4)
-        SLIMFIT_LN_DISPATCH_T(dt, H, (layernorm_forward_quant_kernel<TT, NV, 4><<<grid, kThreads, 0, s>>>(
+        SLIMFIT_LN_DISPATCH_T(dt, H, (launch(layernorm_forward_quant_kernel<TT, NV, 4>, grid, kThreads, 0, s, 
                                          static_cast<const TT *>(x), gamma, beta, rows, (int)H, eps, G, shift,
                                          static_cast<TT *>(y), mean, rstd, codes, scales)));
     else
-        SLIMFIT_LN_DISPATCH_T(dt, H, (layernorm_forward_quant_kernel<TT, NV, 8><<<grid, kThreads, 0, s>>>(
+        SLIMFIT_LN_DISPATCH_T(dt, H, (launch(layernorm_forward_quant_kernel<TT, NV, 8>, grid, kThreads, 0, s, 
                                          static_cast<const TT *>(x), gamma, beta, rows, (int)H, eps, G, shift,
                                          static_cast<TT *>(y), mean, rstd, codes, scales)));
     return launch_status();
@@ -860,11 +860,11 @@ extern "C" int32_t slimfit_layernorm_backward_dequant(const uint8_t *codes, cons
     const unsigned grid = (unsigned)((rows + kWaves - 1) / kWaves);
     const int shift = __builtin_ctz((unsigned)block);
     if (bits == 4)
-        SLIMFIT_LN_DISPATCH_T(dt, H, (layernorm_backward_dequant_kernel<TT, NV, 4><<<grid, kThreads, 0, s>>>(
+        SLIMFIT_LN_DISPATCH_T(dt, H, (launch(layernorm_backward_dequant_kernel<TT, NV, 4>, grid, kThreads, 0, s, 
                                          codes, scales, shift, mean, rstd, gamma, static_cast<const TT *>(dy), rows, (int)H,
                                          static_cast<TT *>(dx))));
     else
-        SLIMFIT_LN_DISPATCH_T(dt, H, (layernorm_backward_dequant_kernel<TT, NV, 8><<<grid, kThreads, 0, s>>>(
+        SLIMFIT_LN_DISPATCH_T(dt, H, (launch(layernorm_backward_dequant_kernel<TT, NV, 8>, grid, kThreads, 0, s, 
                                          codes, scales, shift, mean, rstd, gamma, static_cast<const TT *>(dy), rows, (int)H,
                                          static_cast<TT *>(dx))));
     return launch_status();

@@ -158,13 +158,13 @@ extern "C" int32_t slimfit_stream_probe(const void *src, void *dst, int64_t in_v
     const f32x4 *s = static_cast<const f32x4 *>(src);
     const unsigned grid = (unsigned)blocks;
     switch (ratio) {
-    case 0: stream_probe_read_kernel<<<grid, kThreads, 0, st>>>(s, static_cast<float *>(dst), in_vecs); break;
-    case -2: stream_probe_write_kernel<2><<<grid, kGrowThreads, 0, st>>>(static_cast<const u32x2 *>(src), static_cast<f32x4 *>(dst), work); break;
-    case -4: stream_probe_write_kernel<4><<<grid, kGrowThreads, 0, st>>>(static_cast<const uint32_t *>(src), static_cast<f32x4 *>(dst), work); break;
-    case -8: stream_probe_write_kernel<8><<<grid, kGrowThreads, 0, st>>>(static_cast<const uint16_t *>(src), static_cast<f32x4 *>(dst), work); break;
+    case 0: launch(stream_probe_read_kernel, grid, kThreads, 0, st, s, static_cast<float *>(dst), in_vecs); break;
+    case -2: launch(stream_probe_write_kernel<2>, grid, kGrowThreads, 0, st, static_cast<const u32x2 *>(src), static_cast<f32x4 *>(dst), work); break;
+    case -4: launch(stream_probe_write_kernel<4>, grid, kGrowThreads, 0, st, static_cast<const uint32_t *>(src), static_cast<f32x4 *>(dst), work); break;
+    case -8: launch(stream_probe_write_kernel<8>, grid, kGrowThreads, 0, st, static_cast<const uint16_t *>(src), static_cast<f32x4 *>(dst), work); break;
 #define SLIMFIT_PROBE_CASE(R)                                                                                    \
     case R:                                                                                                      \
-        stream_probe_kernel<R><<<grid, kThreads, 0, st>>>(s, static_cast<Out<R>::type *>(dst), in_vecs);         \
+        launch(stream_probe_kernel<R>, grid, kThreads, 0, st, s, static_cast<Out<R>::type *>(dst), in_vecs);         \
         break;
         SLIMFIT_PROBE_CASE(1) SLIMFIT_PROBE_CASE(2) SLIMFIT_PROBE_CASE(4) SLIMFIT_PROBE_CASE(8) SLIMFIT_PROBE_CASE(16)
 #undef SLIMFIT_PROBE_CASE

@@ -251,11 +251,11 @@ product_kernel(const float *__restrict__ a, const float *__restrict__ b, int64_t
 int64_t tiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
 
 template <int TN, int GROUPS>
-void launch(const float *a, const float *b, bool b_deep, int64_t M, int64_t N, int64_t K, float *out, hipStream_t s)
+void launch_tiles(const float *a, const float *b, bool b_deep, int64_t M, int64_t N, int64_t K, float *out, hipStream_t s)
 {
     const int tm = (int)tiles_of(M, kTileM), tn = (int)tiles_of(N, TN);
-    if (b_deep) product_kernel<TN, true, GROUPS><<<(unsigned)(tm * tn), GROUPS * kGroup, 0, s>>>(a, b, M, N, K, out, tm, tn);
-    else product_kernel<TN, false, GROUPS><<<(unsigned)(tm * tn), GROUPS * kGroup, 0, s>>>(a, b, M, N, K, out, tm, tn);
+    if (b_deep) launch(product_kernel<TN, true, GROUPS>, (unsigned)(tm * tn), GROUPS * kGroup, 0, s, a, b, M, N, K, out, tm, tn);
+    else launch(product_kernel<TN, false, GROUPS>, (unsigned)(tm * tn), GROUPS * kGroup, 0, s, a, b, M, N, K, out, tm, tn);
 }
 
 }  // namespace
@@ -284,9 +284,9 @@ extern "C" int32_t slimfit_product(const float *a, const float *b, int32_t b_dee
     // 4096 x 2304 x 768 93 us, of 96 80; of 128 they need more registers than three workgroups have).
     constexpr int64_t kUnits = 256;
     const int64_t tm = tiles_of(M, kTileM);
-    if (tm * tiles_of(N, 64) <= kUnits) launch<64, 2>(a, b, b_deep != 0, M, N, K, out, s);
-    else if (tm * tiles_of(N, 96) <= kUnits) launch<96, 2>(a, b, b_deep != 0, M, N, K, out, s);
-    else if (tm * tiles_of(N, 128) <= kUnits) launch<128, 2>(a, b, b_deep != 0, M, N, K, out, s);
-    else launch<96, 1>(a, b, b_deep != 0, M, N, K, out, s);
+    if (tm * tiles_of(N, 64) <= kUnits) launch_tiles<64, 2>(a, b, b_deep != 0, M, N, K, out, s);
+    else if (tm * tiles_of(N, 96) <= kUnits) launch_tiles<96, 2>(a, b, b_deep != 0, M, N, K, out, s);
+    else if (tm * tiles_of(N, 128) <= kUnits) launch_tiles<128, 2>(a, b, b_deep != 0, M, N, K, out, s);
+    else launch_tiles<96, 1>(a, b, b_deep != 0, M, N, K, out, s);
     return launch_status();
 }

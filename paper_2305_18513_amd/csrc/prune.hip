@@ -1203,13 +1203,13 @@ void launch_prune(const void *p, int64_t rows, int cols, int k, int mode, float 
     if (slots > kMaxRegSlots) {                       // never with SOFTMAX: the entry point rejects such rows
         const int bslots = (cols + kThreads - 1) / kThreads;              // slots per thread of a whole workgroup
         const unsigned bgrid = (unsigned)(rows < (1 << 20) ? rows : (1 << 20));
-        if (bslots <= 8) prune_rows_block_kernel<T, 8><<<bgrid, kThreads, 0, st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts);
-        else if (bslots <= 16) prune_rows_block_kernel<T, 16><<<bgrid, kThreads, 0, st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts);
-        else if (bslots <= 32) prune_rows_block_kernel<T, 32><<<bgrid, kThreads, 0, st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts);
-        else if (bslots <= 64) prune_rows_block_kernel<T, 64><<<bgrid, kThreads, 0, st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts);
+        if (bslots <= 8) launch(prune_rows_block_kernel<T, 8>, bgrid, kThreads, 0, st, pp, rows, cols, k, mode, tau, vv, idx, counts);
+        else if (bslots <= 16) launch(prune_rows_block_kernel<T, 16>, bgrid, kThreads, 0, st, pp, rows, cols, k, mode, tau, vv, idx, counts);
+        else if (bslots <= 32) launch(prune_rows_block_kernel<T, 32>, bgrid, kThreads, 0, st, pp, rows, cols, k, mode, tau, vv, idx, counts);
+        else if (bslots <= 64) launch(prune_rows_block_kernel<T, 64>, bgrid, kThreads, 0, st, pp, rows, cols, k, mode, tau, vv, idx, counts);
         else {
             const unsigned grid = (unsigned)(rows < 16384 ? rows : 16384);
-            prune_rows_wide_kernel<T><<<grid, kThreads, 0, st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts);
+            launch(prune_rows_wide_kernel<T>, grid, kThreads, 0, st, pp, rows, cols, k, mode, tau, vv, idx, counts);
         }
         return;
     }
@@ -1218,7 +1218,7 @@ void launch_prune(const void *p, int64_t rows, int cols, int k, int mode, float 
     const int64_t blocks_needed = (n_units + kRowWaves - 1) / kRowWaves;
     const unsigned grid = (unsigned)(blocks_needed < kMaxPruneBlocks ? blocks_needed : kMaxPruneBlocks);
 #define SLIMFIT_PRUNE_LAUNCH(MM, FF, SS)                                                                       \
-    prune_rows_kernel<T, MM, FF, SS, SOFTMAX><<<grid, kRowThreads, kRowWaves * row_lds_bytes(SOFTMAX || sizeof(T) == 4, SS, unit_rows, k), st>>>(pp, rows, cols, k, mode, tau, vv, idx, counts, pr, unit_rows, n_units)
+    launch(prune_rows_kernel<T, MM, FF, SS, SOFTMAX>, grid, kRowThreads, kRowWaves * row_lds_bytes(SOFTMAX || sizeof(T) == 4, SS, unit_rows, k), st, pp, rows, cols, k, mode, tau, vv, idx, counts, pr, unit_rows, n_units)
 #define SLIMFIT_PRUNE_CASE(MM)                                                                                  \
     do {                                                                                                        \
         const bool full = cols == MM * kWave, staged = k <= kStage;                                             \
@@ -1338,10 +1338,10 @@ extern "C" int32_t slimfit_restore_scores(const void *vals, const uint16_t *idx,
     const int64_t tiles = (total + kTile - 1) / kTile;
     if (!grid_fits(tiles, kThreads)) return SLIMFIT_ERR_UNSUPPORTED;
     if (dt == SLIMFIT_F32)
-        restore_tile_kernel<float><<<(unsigned)tiles, kThreads, 0, st>>>(static_cast<const float *>(vals), idx, counts,
+        launch(restore_tile_kernel<float>, (unsigned)tiles, kThreads, 0, st, static_cast<const float *>(vals), idx, counts,
                                                                          rows, cols, k, static_cast<float *>(out));
     else
-        restore_tile_kernel<uint16_t><<<(unsigned)tiles, kThreads, 0, st>>>(static_cast<const uint16_t *>(vals), idx,
+        launch(restore_tile_kernel<uint16_t>, (unsigned)tiles, kThreads, 0, st, static_cast<const uint16_t *>(vals), idx,
                                                                             counts, rows, cols, k,
                                                                             static_cast<uint16_t *>(out));
     return launch_status();
@@ -1374,13 +1374,13 @@ extern "C" int32_t slimfit_softmax_backward_pruned(const void *vals, const uint1
     if (dt == SLIMFIT_F32) {
         const float *v = static_cast<const float *>(vals), *g = static_cast<const float *>(dp);
         float *o = static_cast<float *>(ds);
-        if (small) softmax_backward_small_kernel<float><<<(unsigned)tiles, kThreads, 0, st>>>(v, idx, counts, g, rows, cols, k, o);
-        else softmax_backward_tile_kernel<float><<<(unsigned)tiles, kThreads, 0, st>>>(v, idx, counts, g, rows, cols, k, o);
+        if (small) launch(softmax_backward_small_kernel<float>, (unsigned)tiles, kThreads, 0, st, v, idx, counts, g, rows, cols, k, o);
+        else launch(softmax_backward_tile_kernel<float>, (unsigned)tiles, kThreads, 0, st, v, idx, counts, g, rows, cols, k, o);
     } else {
         const uint16_t *v = static_cast<const uint16_t *>(vals), *g = static_cast<const uint16_t *>(dp);
         uint16_t *o = static_cast<uint16_t *>(ds);
-        if (small) softmax_backward_small_kernel<uint16_t><<<(unsigned)tiles, kThreads, 0, st>>>(v, idx, counts, g, rows, cols, k, o);
-        else softmax_backward_tile_kernel<uint16_t><<<(unsigned)tiles, kThreads, 0, st>>>(v, idx, counts, g, rows, cols, k, o);
+        if (small) launch(softmax_backward_small_kernel<uint16_t>, (unsigned)tiles, kThreads, 0, st, v, idx, counts, g, rows, cols, k, o);
+        else launch(softmax_backward_tile_kernel<uint16_t>, (unsigned)tiles, kThreads, 0, st, v, idx, counts, g, rows, cols, k, o);
     }
     return launch_status();
 }

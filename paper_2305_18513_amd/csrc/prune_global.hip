@@ -1556,20 +1556,20 @@ void launch_select(const T *x, int64_t n, uint32_t k, typename Elem<T>::Out *val
         // The plain layout.  The digit launches look at a list's head before they know the route: they are told of one
         // tile and given the histogram to look at.  The first digit's histogram serves again as the last one's.
         const u32x2 *no_cnt = reinterpret_cast<const u32x2 *>(w.hist2);
-        clear_kernel<<<1, kWideThreads, 0, s>>>(w.zero, w.zero16, w.st);
-        digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, reinterpret_cast<const uint64_t *>(w.hist2), no_cnt, w.hist2,
+        launch(clear_kernel, 1, kWideThreads, 0, s, w.zero, w.zero16, w.st);
+        launch(digit_kernel<T, MAG, STD>, groups, kWideThreads, 0, s, x, n, w.st, reinterpret_cast<const uint64_t *>(w.hist2), no_cnt, w.hist2,
                                                                   0, w.hist2, 1, k, sd);
         uint32_t *last = w.hist3;
         if constexpr (Elem<T>::KEYBITS == 32) {
-            second_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, no_cnt, w.hist2, 0, w.hist2, w.hist3, 1, sd);
+            launch(second_digit_kernel<T, MAG, STD>, groups, kWideThreads, 0, s, x, n, w.st, no_cnt, w.hist2, 0, w.hist2, w.hist3, 1, sd);
             last = w.hist2;
-            clear_kernel<<<1, kWideThreads, 0, s>>>(reinterpret_cast<u32x4 *>(last), kTopBins / 4, nullptr);
+            launch(clear_kernel, 1, kWideThreads, 0, s, reinterpret_cast<u32x4 *>(last), kTopBins / 4, nullptr);
         }
-        count_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, no_cnt, w.hist2, 0, w.hist2, w.hist3, last, w.tile_sum,
+        launch(count_kernel<T, MAG, STD>, groups, kWideThreads, 0, s, x, n, w.st, no_cnt, w.hist2, 0, w.hist2, w.hist3, last, w.tile_sum,
                                                                   w.group_sum, 1, group_tiles, sd);
-        dense_write_kernel<T, MAG, STD><<<plain_grid, kTileThreads, 0, s>>>(x, n, w.st, last, w.tile_sum, w.group_sum, ntiles, group_tiles,
+        launch(dense_write_kernel<T, MAG, STD>, plain_grid, kTileThreads, 0, s, x, n, w.st, last, w.tile_sum, w.group_sum, ntiles, group_tiles,
                                                                             out, sd);
-        plain_write_kernel<T, MAG, STD><<<plain_grid, kTileThreads, 0, s>>>(x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out,
+        launch(plain_write_kernel<T, MAG, STD>, plain_grid, kTileThreads, 0, s, x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out,
                                                                             sd);
         return;
     }
@@ -1577,34 +1577,34 @@ void launch_select(const T *x, int64_t n, uint32_t k, typename Elem<T>::Out *val
     const SamplePlan plan = plan_sample(n, (int64_t)k, Elem<T>::EPV);
 
     if (plan.use) {
-        sample_kernel<T, MAG, STD><<<plan.wgs, kWideThreads, 0, s>>>(x, plan.total, plan.step, plan.hi, plan.lo, w.edges, w.st, w.zero,
+        launch(sample_kernel<T, MAG, STD>, plan.wgs, kWideThreads, 0, s, x, plan.total, plan.step, plan.hi, plan.lo, w.edges, w.st, w.zero,
                                                                      w.zero16, sd);
     } else {
-        clear_kernel<<<1, kWideThreads, 0, s>>>(w.zero, w.zero16, nullptr);
-        top_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.hist4, sd);
-        edges_kernel<<<1, kWideThreads, 0, s>>>(w.hist4, k, w.edges, w.st);
+        launch(clear_kernel, 1, kWideThreads, 0, s, w.zero, w.zero16, nullptr);
+        launch(top_digit_kernel<T, MAG, STD>, groups, kWideThreads, 0, s, x, n, w.hist4, sd);
+        launch(edges_kernel, 1, kWideThreads, 0, s, w.hist4, k, w.edges, w.st);
     }
     const uint64_t size = plan.use && plan.wgs == kSampleWgs ? plan.size : (plan.use ? (uint64_t)plan.size : (uint64_t)n) * kSampleWgs;
     if (records)
-        sweep_kernel<T, MAG, STD, true><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.edges, size, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
+        launch(sweep_kernel<T, MAG, STD, true>, (unsigned)ntiles, kTileThreads, 0, s, x, n, w.edges, size, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
                                                                                  w.rec_val, w.rec_pos, sd);
     else
-        sweep_kernel<T, MAG, STD, false><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.edges, size, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
+        launch(sweep_kernel<T, MAG, STD, false>, (unsigned)ntiles, kTileThreads, 0, s, x, n, w.edges, size, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots,
                                                                                   nullptr, nullptr, sd);
-    digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, w.hist2,
+    launch(digit_kernel<T, MAG, STD>, groups, kWideThreads, 0, s, x, n, w.st, w.counters, w.tile_cnt, w.lists, w.list_slots, w.hist2,
                                                               ntiles, k, sd);
     if constexpr (Elem<T>::KEYBITS == 32)
-        second_digit_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.list_slots, w.hist2, w.hist3,
+        launch(second_digit_kernel<T, MAG, STD>, groups, kWideThreads, 0, s, x, n, w.st, w.tile_cnt, w.lists, w.list_slots, w.hist2, w.hist3,
                                                                          ntiles, sd);
-    count_kernel<T, MAG, STD><<<groups, kWideThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.lists, w.list_slots, w.hist2, w.hist3, w.hist4, w.tile_sum,
+    launch(count_kernel<T, MAG, STD>, groups, kWideThreads, 0, s, x, n, w.st, w.tile_cnt, w.lists, w.list_slots, w.hist2, w.hist3, w.hist4, w.tile_sum,
                                                               w.group_sum, ntiles, group_tiles, sd);
     if (records)
-        write_kernel<T, MAG, STD><<<(unsigned)((ntiles + 3) / 4), kTileThreads, 0, s>>>(x, n, w.st, w.tile_cnt, w.rec_val, w.rec_pos, w.hist4,
+        launch(write_kernel<T, MAG, STD>, (unsigned)((ntiles + 3) / 4), kTileThreads, 0, s, x, n, w.st, w.tile_cnt, w.rec_val, w.rec_pos, w.hist4,
                                                                                        w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
     else
-        dense_write_kernel<T, MAG, STD><<<(unsigned)ntiles, kTileThreads, 0, s>>>(x, n, w.st, w.hist4, w.tile_sum, w.group_sum, ntiles,
+        launch(dense_write_kernel<T, MAG, STD>, (unsigned)ntiles, kTileThreads, 0, s, x, n, w.st, w.hist4, w.tile_sum, w.group_sum, ntiles,
                                                                                  group_tiles, out, sd);
-    plain_write_kernel<T, MAG, STD><<<plain_grid, kTileThreads, 0, s>>>(x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
+    launch(plain_write_kernel<T, MAG, STD>, plain_grid, kTileThreads, 0, s, x, n, w.st, w.tile_sum, w.group_sum, ntiles, group_tiles, out, sd);
 }
 
 }  // namespace
@@ -1746,10 +1746,10 @@ extern "C" int32_t slimfit_restore_global(const void *vals, const int32_t *idx, 
         const int64_t tiles = (n + kPtrTile - 1) / kPtrTile;
         if ((rc = check_device_range(tile_ptr, (size_t)(tiles + 1) * 4)) != SLIMFIT_OK) return rc;
         if (dt == SLIMFIT_F32)
-            restore_tiles_kernel<float><<<(unsigned)tiles, kTileThreads, 0, s>>>(
+            launch(restore_tiles_kernel<float>, (unsigned)tiles, kTileThreads, 0, s, 
                 static_cast<const float *>(vals), idx, tile_ptr, k, n, static_cast<float *>(out));
         else
-            restore_tiles_kernel<uint16_t><<<(unsigned)tiles, kTileThreads, 0, s>>>(
+            launch(restore_tiles_kernel<uint16_t>, (unsigned)tiles, kTileThreads, 0, s, 
                 static_cast<const uint16_t *>(vals), idx, tile_ptr, k, n, static_cast<uint16_t *>(out));
         return launch_status();
     }
@@ -1759,15 +1759,15 @@ extern "C" int32_t slimfit_restore_global(const void *vals, const int32_t *idx, 
     const int64_t per_block = (int64_t)kTileThreads * kVecPerThread;
     int64_t zblocks = (nvec16 + per_block - 1) / per_block;
     if (zblocks < 1) zblocks = 1;
-    zero_kernel<<<(unsigned)zblocks, kTileThreads, 0, s>>>(static_cast<u32x4 *>(out), nvec16,
+    launch(zero_kernel, (unsigned)zblocks, kTileThreads, 0, s, static_cast<u32x4 *>(out), nvec16,
                                                           static_cast<uint8_t *>(out) + (size_t)nvec16 * 16, tail_bytes);
     if (k > 0) {
         const unsigned sblocks = (unsigned)((k + kTileThreads - 1) / kTileThreads);
         if (dt == SLIMFIT_F32)
-            scatter_kernel<float><<<sblocks, kTileThreads, 0, s>>>(static_cast<const float *>(vals), idx, k, n,
+            launch(scatter_kernel<float>, sblocks, kTileThreads, 0, s, static_cast<const float *>(vals), idx, k, n,
                                                                    static_cast<float *>(out));
         else
-            scatter_kernel<uint16_t><<<sblocks, kTileThreads, 0, s>>>(static_cast<const uint16_t *>(vals), idx, k, n,
+            launch(scatter_kernel<uint16_t>, sblocks, kTileThreads, 0, s, static_cast<const uint16_t *>(vals), idx, k, n,
                                                                       static_cast<uint16_t *>(out));
     }
     return launch_status();

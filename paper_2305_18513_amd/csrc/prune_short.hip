@@ -811,7 +811,7 @@ void launch_softmax_short(const T *p, const ShortArgs &a, T *probs, T *vals, uin
 {
     const size_t lds = short_lds_bytes(a.cols, a.k, G, (int)sizeof(T), kShortHeldBlock);
     in_pieces<G>(a, [&](const ShortArgs &piece, int64_t row0, unsigned blocks) {
-        softmax_prune_short_kernel<T, G, K, NV><<<blocks, kWave, lds, st>>>(p + row0 * a.cols, piece, probs + row0 * a.cols, vals + row0 * a.k,
+        launch(softmax_prune_short_kernel<T, G, K, NV>, blocks, kWave, lds, st, p + row0 * a.cols, piece, probs + row0 * a.cols, vals + row0 * a.k,
                                                                             idx + row0 * a.k);
     });
 }
@@ -858,7 +858,7 @@ void launch_short(const T *p, const ShortArgs &a, T *vals, uint16_t *idx, int32_
 #endif
     const size_t lds = short_lds_bytes(a.cols, a.k, G, (int)sizeof(T), 1) + SLIMFIT_SHORT_LDS_PAD;
     in_pieces<G>(a, [&](const ShortArgs &piece, int64_t row0, unsigned blocks) {
-        prune_rows_short_kernel<T, G, K, NV><<<blocks, kWave, lds, st>>>(p + row0 * a.cols, piece, vals + row0 * a.k, idx + row0 * a.k,
+        launch(prune_rows_short_kernel<T, G, K, NV>, blocks, kWave, lds, st, p + row0 * a.cols, piece, vals + row0 * a.k, idx + row0 * a.k,
                                                                         counts ? counts + row0 : nullptr);
     });
 }

@@ -308,16 +308,16 @@ void launch_quant_piece(const void *x, int64_t n, int mode, int block, int frac_
     const T *xp = static_cast<const T *>(x);
     T *yp = static_cast<T *>(y);
     if (mode == SLIMFIT_Q_FIXED) {
-        quant_pack_kernel<T, BITS, false, 4, GELU><<<grid, tb, 0, st>>>(xp, n, __builtin_ldexpf(1.0f, frac_bits), codes,
+        launch(quant_pack_kernel<T, BITS, false, 4, GELU>, grid, tb, 0, st, xp, n, __builtin_ldexpf(1.0f, frac_bits), codes,
                                                                         nullptr, yp);
         return;
     }
     switch (block / V) {
-    case 4: quant_pack_kernel<T, BITS, true, 4, GELU><<<grid, tb, 0, st>>>(xp, n, 0.0f, codes, scales, yp); break;
-    case 8: quant_pack_kernel<T, BITS, true, 8, GELU><<<grid, tb, 0, st>>>(xp, n, 0.0f, codes, scales, yp); break;
-    case 16: quant_pack_kernel<T, BITS, true, 16, GELU><<<grid, tb, 0, st>>>(xp, n, 0.0f, codes, scales, yp); break;
-    case 32: quant_pack_kernel<T, BITS, true, 32, GELU><<<grid, tb, 0, st>>>(xp, n, 0.0f, codes, scales, yp); break;
-    default: quant_pack_kernel<T, BITS, true, 64, GELU><<<grid, tb, 0, st>>>(xp, n, 0.0f, codes, scales, yp); break;
+    case 4: launch(quant_pack_kernel<T, BITS, true, 4, GELU>, grid, tb, 0, st, xp, n, 0.0f, codes, scales, yp); break;
+    case 8: launch(quant_pack_kernel<T, BITS, true, 8, GELU>, grid, tb, 0, st, xp, n, 0.0f, codes, scales, yp); break;
+    case 16: launch(quant_pack_kernel<T, BITS, true, 16, GELU>, grid, tb, 0, st, xp, n, 0.0f, codes, scales, yp); break;
+    case 32: launch(quant_pack_kernel<T, BITS, true, 32, GELU>, grid, tb, 0, st, xp, n, 0.0f, codes, scales, yp); break;
+    default: launch(quant_pack_kernel<T, BITS, true, 64, GELU>, grid, tb, 0, st, xp, n, 0.0f, codes, scales, yp); break;
     }
 }
 
@@ -339,10 +339,10 @@ void launch_dequant_piece(const uint8_t *codes, const float *scales, int64_t n, 
     T *yp = static_cast<T *>(y);
     const T *gp = static_cast<const T *>(dy);
     if (mode == SLIMFIT_Q_FIXED)
-        dequant_unpack_kernel<T, BITS, false, GELU><<<grid, tb, 0, st>>>(codes, nullptr, n, 0,
+        launch(dequant_unpack_kernel<T, BITS, false, GELU>, grid, tb, 0, st, codes, nullptr, n, 0,
                                                                          __builtin_ldexpf(1.0f, -frac_bits), yp, gp);
     else
-        dequant_unpack_kernel<T, BITS, true, GELU><<<grid, tb, 0, st>>>(codes, scales, n, __builtin_ctz((unsigned)block),
+        launch(dequant_unpack_kernel<T, BITS, true, GELU>, grid, tb, 0, st, codes, scales, n, __builtin_ctz((unsigned)block),
                                                                         0.0f, yp, gp);
 }
 
