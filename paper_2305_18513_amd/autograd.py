@@ -42,6 +42,7 @@ kept standardised values fp32); the kernels run on torch's current stream.
 from __future__ import annotations
 
 import torch
+from torch.autograd import forward_ad
 
 from . import binding as sf
 
@@ -277,7 +278,14 @@ class SplitHeadsFunction(torch.autograd.Function):
 
 def _plain(t: torch.Tensor) -> bool:
     """Whether a kernel may be handed the tensor's memory as it is."""
-    return type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and t.data_ptr() % 16 == 0
+    return (type(t) in (torch.Tensor, torch.nn.Parameter) and not torch._C._functorch.is_functorch_wrapped_tensor(t) and t.is_cuda
+            and t.is_contiguous() and not t.is_neg() and t.data_ptr() % 16 == 0)
+
+
+def _watched() -> bool:
+    """Whether more than the value is asked for: a product to be differentiated (either way), cast, traced or intercepted."""
+    return (torch.is_grad_enabled() or torch.is_autocast_enabled() or torch.compiler.is_compiling() or torch.jit.is_tracing()
+            or forward_ad._current_level >= 0 or torch._C._len_torch_dispatch_stack() > 0 or torch._C._len_torch_function_stack() > 0)
 
 
 def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
@@ -286,17 +294,17 @@ def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
     It is the faster one where the product has at least 192 tiles of 128 x 64, three for four compute units (rows x columns x
     depth, torch's and this in us: 4096 x 768 x 3072 140 and 95, 2048 x 768 x 3072 76 and 65, 192 tiles; 2048 x 512 x 2048 34
     and 44, 1024 x 1024 x 4096 63 and 85, 128 tiles each, which torch splits along their depth)."""
-    if torch.is_grad_enabled() or torch.is_autocast_enabled() or torch.compiler.is_compiling():
-        return None                                        # products to be differentiated, cast or traced are torch's
-    if not (_plain(x) and _plain(weight) and x.dim() >= 2 and weight.dim() == 2):
+    if x.dtype != torch.float32 or weight.dtype != torch.float32 or x.dim() < 2 or weight.dim() != 2:
         return None
     K = x.shape[-1]
     N, depth = weight.shape if transposed else weight.shape[::-1]
     if depth != K or K == 0 or K % 32 != 0:
         return None
     M = x.numel() // K
-    if -(-M // 128) * -(-N // 64) < 192:
+    if -(-M // 128) * -(-N // 64) < 192 or _watched() or not (_plain(x) and _plain(weight)):
         return None
+    if not (x.get_device() == weight.get_device() == torch.cuda.current_device()):
+        return None                                        # the library launches on the current device
     y = torch.empty(*x.shape[:-1], N, dtype=x.dtype, device=x.device)
     sf.product(x.view(M, K), weight, transposed, y.view(M, N))
     return y

@@ -150,6 +150,32 @@ def test_linear_layers(monkeypatch):
 
 
 @pytest.mark.gpu
+def test_products_that_are_watched_are_torchs(monkeypatch):
+    """Batched gradients, forward-mode tangents of a gradient, dispatch modes and negated views reach torch's product."""
+    from torch.autograd import forward_ad as fw
+    from torch.utils.flop_counter import FlopCounterMode
+    require_gpu()
+    seen = _calls(monkeypatch)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    w = torch.randn(768, 512, generator=g, device="cuda")
+    x = torch.randn(4096, 512, generator=g, device="cuda", requires_grad=True)
+    dy, tangent = (torch.randn(4096, 768, generator=g, device="cuda") for _ in range(2))
+    y = ag.LinearFunction.apply(x, w, None)
+    assert seen == [True]
+    (both,) = torch.autograd.grad(y, x, torch.stack([dy, tangent]), is_grads_batched=True, retain_graph=True)
+    torch.testing.assert_close(both, torch.stack([dy @ w, tangent @ w]))
+    with fw.dual_level():
+        (dx,) = torch.autograd.grad(y, x, fw.make_dual(dy, tangent), retain_graph=True)
+        torch.testing.assert_close(fw.unpack_dual(dx).tangent, tangent @ w)
+    with FlopCounterMode(display=False) as counter:
+        torch.autograd.grad(y, x, dy, retain_graph=True)
+    assert counter.get_total_flops() == 2 * 4096 * 768 * 512
+    (dx,) = torch.autograd.grad(y, x, torch._neg_view(dy))
+    torch.testing.assert_close(dx, -(dy @ w))
+    assert seen == [True]
+
+
+@pytest.mark.gpu
 def test_captured_and_replayed():
     require_gpu()
     a, b = _operands(4100, 1000, 160, True, 5)
