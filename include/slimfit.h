@@ -530,13 +530,18 @@ int32_t slimfit_merge_heads(const void *q, const void *kt, const void *v, int32_
  *        out[i][j] = sum over k of a[i][k] * b[k][j]     (b_deep == 0: b is K x N)
  *  a, b, out : DEVICE fp32, row-major and contiguous; a, b 16-byte aligned, out 4-byte; out overlaps neither.
  *  K has to be a multiple of 32: ERR_UNSUPPORTED.
- *  Each operand is split exactly into three bf16 numbers and six of the nine partial products are added up in fp32
- *  (the other three are below 2^-26 of theirs): no further from the exact product than fp32 additions in any order,
- *      |out - exact| <= K * 2^-24 * sum |a||b|,
- *  for entries of magnitude above 2^-100.  Infinities and NaN come out as in plain fp32 arithmetic.  Deterministic.
+ *  workspace : DEVICE, 16-byte aligned, of slimfit_product_workspace(M, N, K) bytes (those of a and b and a few); contents
+ *  overwritten; overlaps nothing else.
+ *  Each row of a and each row (b_deep) or column of b is scaled by a power of two and split into two fp16 numbers; three of
+ *  the four partial products are added up in fp32:
+ *      |out - exact| <= (K + 10) * 2^-24 * sum |a||b| + 2^-50 * K * max |a[i]| * max |b[j]|,
+ *  no further from the exact product than fp32 additions in any order but for entries below 2^-28 of their row's largest.
+ *  Infinities and NaN come out as in plain fp32 arithmetic.  Deterministic.
  * ---------------------------------------------------------------------- */
+int32_t slimfit_product_workspace(int64_t M, int64_t N, int64_t K, size_t *bytes);
+
 int32_t slimfit_product(const float *a, const float *b, int32_t b_deep, int64_t M, int64_t N, int64_t K, float *out,
-                        void *stream);
+                        void *workspace, size_t workspace_bytes, void *stream);
 
 /* ------------------------------------------------------------------------
  * (d) Inter-layer scheduling on the host -- Alg. 1 and Sec. 3.2 / Fig. 4:

@@ -57,7 +57,7 @@ EXPORTS = (
     "slimfit_restore_scores", "slimfit_softmax_prune", "slimfit_softmax_backward_pruned", "slimfit_prune_global_workspace", "slimfit_global_tile_ptr_len", "slimfit_prune_global",
     "slimfit_restore_global", "slimfit_layernorm_forward", "slimfit_prune_global_standardized",
     "slimfit_layernorm_backward_pruned", "slimfit_layernorm_forward_quant_pack", "slimfit_layernorm_backward_dequant", "slimfit_layernorm_backward", "slimfit_layernorm_param_grads_workspace", "slimfit_layernorm_param_grads",
-    "slimfit_split_heads", "slimfit_merge_heads", "slimfit_product",
+    "slimfit_split_heads", "slimfit_merge_heads", "slimfit_product_workspace", "slimfit_product",
     "slimfit_freeze_count", "slimfit_ils_select", "slimfit_ils_select_blocks",
     "slimfit_ils_update", "slimfit_schedule_random", "slimfit_schedule_progressive",
 )
@@ -729,14 +729,22 @@ def merge_heads(q: torch.Tensor, kt: torch.Tensor, v: torch.Tensor, q_scale: flo
     _check(rc, "merge_heads")
 
 
-def product(a: torch.Tensor, b: torch.Tensor, b_deep: bool, out: torch.Tensor, stream=None) -> None:
+def product_workspace(M: int, N: int, K: int) -> int:
+    out = C.c_size_t(0)
+    _check(lib().slimfit_product_workspace(C.c_int64(M), C.c_int64(N), C.c_int64(K), C.byref(out)), "product_workspace")
+    return int(out.value)
+
+
+def product(a: torch.Tensor, b: torch.Tensor, b_deep: bool, out: torch.Tensor, workspace: Optional[torch.Tensor] = None,
+            stream=None) -> None:
     """out = a @ b.T (``b_deep``: b is N x K) or a @ b (b is K x N); fp32, K a multiple of 32."""
     _require(a.dim() == 2 and b.dim() == 2 and out.dim() == 2 and a.dtype == b.dtype == out.dtype == torch.float32)
     M, K = a.shape
     N = b.shape[0] if b_deep else b.shape[1]
     _require(b.shape[1 if b_deep else 0] == K and out.shape == (M, N))
+    workspace = _own_workspace(workspace, product_workspace(M, N, K), a.device, stream)
     rc = lib().slimfit_product(_dev(a), _dev(b), C.c_int32(int(bool(b_deep))), C.c_int64(M), C.c_int64(N), C.c_int64(K), _dev(out),
-                               _stream(stream))
+                               _dev(workspace), C.c_size_t(workspace.numel()), _stream(stream))
     _check(rc, "product")
 
 

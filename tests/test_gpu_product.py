@@ -1,8 +1,9 @@
 """slimfit_product and the linear layers that use it, against 64-bit products of the same operands.
 
-Bound: fp32 additions in any order are at most K 2^-24 sum |a||b| off; what the kernel leaves out of a product is below
-2^-26 of it (one 2^-24 more covers both).  The error's 2-norm grows with the square root of K where signs are mixed: half of
-sqrt(K) 2^-24 of the result's norm (an fp32 product measures 0.3 sqrt(K) 2^-24 at K = 768)."""
+Bound: fp32 additions in any order are at most K 2^-24 sum |a||b| off; the two fp16 parts of an operand leave at most 2^-23 of an
+entry out (2^-51 of its row's largest for the smallest entries) and the product of the lower parts is below 2^-22, 10 x 2^-24
+in all.  The error's 2-norm grows with the square root of K where signs are mixed: half of sqrt(K) 2^-24 of the result's norm (an
+fp32 product measures 0.3 sqrt(K) 2^-24 at K = 768)."""
 import numpy as np
 import pytest
 import torch
@@ -32,28 +33,50 @@ def _check(a, b, deep):
     want = a.double() @ bt
     off = (_product(a, b, deep).double() - want).abs()
     K = a.shape[1]
-    assert bool((off <= (K + 1) * 2.0 ** -24 * (a.double().abs() @ bt.abs()) + 1e-300).all())
+    largest = a.double().abs().amax(1, keepdim=True) * bt.abs().amax(0, keepdim=True)
+    assert bool((off <= (K + 10) * 2.0 ** -24 * (a.double().abs() @ bt.abs()) + K * 2.0 ** -50 * largest + 1e-300).all())
     assert float(off.norm()) <= 0.5 * K ** 0.5 * 2.0 ** -24 * float(want.norm()) + 1e-300
 
 
-# tiles of 64 columns and two groups (up to 256 tiles), edges of rows, columns and depth (an odd number of steps, one step)
+# the smallest tile; edges of rows, columns and depth (an odd number of steps, one step, 16 waves' worth held in registers and
+# rows that are read twice)
 @pytest.mark.gpu
 @pytest.mark.parametrize("deep", [True, False])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 32), (3, 64, 64), (127, 63, 96), (128, 65, 128), (129, 128, 160), (257, 200, 32),
-                                   (640, 333, 224), (1000, 960, 256)])
+                                   (640, 333, 224), (1000, 960, 256), (100, 70, 1536), (50, 90, 1568), (33, 17, 3072), (70, 40, 3136)])
 def test_small(M, N, K, deep):
     require_gpu()
     _check(*_operands(M, N, K, deep, M + N + K), deep)
 
 
-# 96 and 128 columns with two groups, 96 with one: sizes on either side of each change, ragged rows and columns
+# every other tile (128 x 64, 96, 128, 144, 256 x 96, 144, 192), whole ones and ragged rows and columns
 @pytest.mark.gpu
 @pytest.mark.parametrize("deep", [True, False])
 @pytest.mark.parametrize("M,N,K", [(4096, 512, 96), (4096, 520, 96), (4000, 768, 160), (4096, 769, 64), (4090, 1021, 96),
-                                   (4096, 1025, 64), (4100, 1000, 160), (9000, 1500, 32)])
+                                   (4096, 1025, 64), (4100, 1000, 160), (4001, 1500, 96), (2040, 3001, 32), (4000, 2200, 96), (9000, 1500, 32),
+                                   (4096, 3072, 64), (4090, 3000, 96)])
 def test_large(M, N, K, deep):
     require_gpu()
     _check(*_operands(M, N, K, deep, M + N + K), deep)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("deep", [True, False])
+def test_rows_of_unlike_size(deep):
+    """Rows and columns of any scale, and entries of a row spread over many binades or beside one that meets zeros."""
+    require_gpu()
+    a, b = _operands(300, 200, 256, deep, 5)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    rows = torch.exp(torch.randn(300, 1, generator=g, device="cuda") * 10)
+    a, rows = a * rows, (b if deep else b.t())
+    rows *= torch.exp(torch.randn(200, 1, generator=g, device="cuda") * 8)
+    want = a.double() @ rows.double().t()
+    off = (_product(a, b, deep).double() - want).abs()
+    assert bool((off <= 266 * 2.0 ** -24 * (a.double().abs() @ rows.double().abs().t()) + 256 * 2.0 ** -149).all())
+    wide = a * torch.exp(torch.randn(300, 256, generator=g, device="cuda") * 2)
+    _check(wide, b, deep)
+    a[:, 5], rows[:, 5] = 1e8 * a.abs().amax(1), 0.0
+    _check(a, b, deep)
 
 
 @pytest.mark.gpu
@@ -198,13 +221,16 @@ def test_captured_and_replayed():
 def test_arguments():
     import ctypes as C
     lib = sf.lib()
-    call = lambda a, b, M, N, K, out: lib.slimfit_product(                                     # noqa: E731
-        C.c_void_p(a), C.c_void_p(b), C.c_int32(1), C.c_int64(M), C.c_int64(N), C.c_int64(K), C.c_void_p(out), None)
+    call = lambda a, b, M, N, K, out, work=16, size=1 << 40: lib.slimfit_product(              # noqa: E731
+        C.c_void_p(a), C.c_void_p(b), C.c_int32(1), C.c_int64(M), C.c_int64(N), C.c_int64(K), C.c_void_p(out), C.c_void_p(work),
+        C.c_size_t(size), None)
     assert call(16, 16, -1, 4, 32, 16) == call(16, 16, 4, 4, -32, 16) == sf.ERR_INVALID_ARG
     assert call(None, None, 0, 4, 32, None) == call(None, None, 4, 0, 32, None) == sf.OK
     assert call(16, 16, 4, 4, 33, 16) == call(16, 16, 4, 4, 0, 16) == sf.ERR_UNSUPPORTED
     assert call(None, 16, 4, 4, 32, 16) == call(16, None, 4, 4, 32, 16) == call(16, 16, 4, 4, 32, None) == sf.ERR_INVALID_ARG
     assert call(4, 16, 4, 4, 32, 16) == call(16, 8, 4, 4, 32, 16) == call(16, 16, 4, 4, 32, 2) == sf.ERR_ALIGNMENT
+    assert call(16, 16, 4, 4, 32, 16, None) == sf.ERR_INVALID_ARG and call(16, 16, 4, 4, 32, 16, 8) == sf.ERR_ALIGNMENT
+    assert call(16, 16, 4, 4, 32, 16, 16, sf.product_workspace(4, 4, 32) - 1) == sf.ERR_WORKSPACE
     assert call(16, 16, 1 << 40, 1 << 40, 1 << 20, 16) == call(16, 16, 1 << 30, 1 << 20, 32, 16) == sf.ERR_UNSUPPORTED
 
 
