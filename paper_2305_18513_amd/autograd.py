@@ -294,7 +294,9 @@ def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
     It is the faster one where the product has at least 192 tiles of 128 x 64, three for four compute units (rows x columns x
     depth, torch's and this in us: 4096 x 768 x 3072 138 and 80, 2048 x 768 x 3072 76 and 56, 4096 x 384 x 384 18.4 and 18.1,
     192 tiles the last two; 2048 x 512 x 2048 34 and 42, 1024 x 1024 x 4096 62 and 70, 128 tiles each, which torch splits along
-    their depth)."""
+    their depth).  Smaller ones are shorter than the host takes to ask for them, 18 us torch's and 8 this: up to a depth of
+    768 this one is through in that time (256 x 256 x 256 11 us on the GPU, 1024 x 768 x 768 23, torch's 6 and 14), deeper ones
+    are not (1024 x 768 x 3072 57 and 42), and a graph that is captured has no host to wait for."""
     if x.dtype != torch.float32 or weight.dtype != torch.float32 or x.dim() < 2 or weight.dim() != 2:
         return None
     K = x.shape[-1]
@@ -302,7 +304,10 @@ def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
     if depth != K or K == 0 or K % 32 != 0:
         return None
     M = x.numel() // K
-    if -(-M // 128) * -(-N // 64) < 192 or _watched() or not (_plain(x) and _plain(weight)):
+    few = -(-M // 128) * -(-N // 64) < 192
+    if (few and K > 768) or _watched() or not (_plain(x) and _plain(weight)):
+        return None
+    if few and torch.cuda.is_current_stream_capturing():
         return None
     if not (x.get_device() == weight.get_device() == torch.cuda.current_device()):
         return None                                        # the library launches on the current device

@@ -735,9 +735,15 @@ def product_workspace(M: int, N: int, K: int) -> int:
     return int(out.value)
 
 
+_native_product = _fast("product")
+
+
 def product(a: torch.Tensor, b: torch.Tensor, b_deep: bool, out: torch.Tensor, workspace: Optional[torch.Tensor] = None,
             stream=None) -> None:
     """out = a @ b.T (``b_deep``: b is N x K) or a @ b (b is K x N); fp32, K a multiple of 32."""
+    rc = _native_product(a, b, b_deep, out, workspace, stream)
+    if rc is not NotImplemented:
+        return None if rc is None else _check(rc, "product")
     _require(a.dim() == 2 and b.dim() == 2 and out.dim() == 2 and a.dtype == b.dtype == out.dtype == torch.float32)
     M, K = a.shape
     N = b.shape[0] if b_deep else b.shape[1]

@@ -29,7 +29,7 @@ namespace {
     X(softmax_prune) X(softmax_backward_pruned) X(prune_global_standardized) X(prune_global_workspace)                 \
     X(layernorm_forward) X(layernorm_backward) X(layernorm_backward_pruned) X(layernorm_forward_quant_pack)            \
     X(layernorm_backward_dequant) X(layernorm_param_grads) X(layernorm_param_grads_workspace) X(layer_delta_run)         \
-    X(split_heads) X(merge_heads)
+    X(split_heads) X(merge_heads) X(product) X(product_workspace)
 #define X(name) decltype(&slimfit_##name) name##_fn = nullptr;
 SLIMFIT_CALLS(X)
 #undef X
@@ -555,6 +555,29 @@ PyObject *merge_heads(PyObject *, PyObject *const *args, Py_ssize_t n_args)
     SLIMFIT_RUN(merge_heads_fn(qp, kp, vp, dt, batch, tokens, heads, dim, scale, fp, st));
 }
 
+PyObject *product(PyObject *, PyObject *const *args, Py_ssize_t n_args)
+{
+    Args a(args, n_args, 6);
+    const at::Tensor *x = a.tensor(), *y = a.tensor();
+    const int32_t y_deep = a.truth();
+    const at::Tensor *out = a.tensor(), *workspace = a.tensor_or_none();
+    void *st = a.stream();
+    int64_t M = 0, N = 0, K = 0;
+    size_t need = 0;
+    if (a.ok) {
+        a.need(x->dim() == 2 && y->dim() == 2 && out->dim() == 2 && f32(x) && f32(y) && f32(out));
+        if (a.ok) {
+            M = x->size(0), K = x->size(1), N = y->size(y_deep ? 0 : 1);
+            a.need(y->size(y_deep ? 1 : 0) == K && out->size(0) == M && out->size(1) == N && product_workspace_fn(M, N, K, &need) == SLIMFIT_OK);
+        }
+    }
+    Scratch w;
+    if (!a.ok || !w.take(workspace, a.own_stream, need, x)) return general();
+    const float *xp = ptr<float>(x), *yp = ptr<float>(y);
+    float *op = ptr<float>(out);
+    SLIMFIT_RUN(product_fn(xp, yp, y_deep, M, N, K, op, w.at, w.bytes, st));
+}
+
 // a C++ exception must not cross into the interpreter (torch's allocator raises one when memory runs out: the general
 // path, which asks again, raises torch's own)
 template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
@@ -598,6 +621,7 @@ PyMethodDef methods[] = {
     METHOD(restore_scores), METHOD(softmax_prune), METHOD(softmax_backward_pruned), METHOD(prune_global_standardized),
     METHOD(layernorm_forward), METHOD(layernorm_backward), METHOD(layernorm_backward_pruned), METHOD(layernorm_forward_quant_pack),
     METHOD(layernorm_backward_dequant), METHOD(layernorm_param_grads), METHOD(layer_delta_run), METHOD(split_heads), METHOD(merge_heads),
+    METHOD(product),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -86,6 +86,8 @@ def _calls(dt):
         "layernorm_backward_dequant": (sf.layernorm_backward_dequant, [codes, scales, 4, 64, mean, rstd, gamma, dy, dx], (8,)),
         "split_heads": (sf.split_heads, [randn(3, 5, 48), 0.25, randn(3, 2, 5, 8), randn(3, 2, 8, 5), randn(3, 2, 5, 8)], (2, 3, 4)),
         "merge_heads": (sf.merge_heads, [randn(3, 2, 5, 8), randn(3, 2, 8, 5), randn(3, 2, 5, 8), 0.25, randn(3, 5, 48)], (4,)),
+        "product": (sf.product, [f32(40, 64), f32(50, 64), True, f32(40, 50), empty(sf.product_workspace(40, 50, 64), dtype=torch.uint8)], (3,)),
+        "product_own": (sf.product, [f32(40, 64), f32(64, 50), False, f32(40, 50)], (3,)),
         "layernorm_param_grads": (sf.layernorm_param_grads, [x, mean, rstd, dy, new(gamma), new(gamma)], (4, 5)),
         "layer_delta_run": (sf.layer_delta_run, [numel, sf.F32, sf.F32, False, 0.0, d, plan], (5,)),
     }
@@ -95,7 +97,7 @@ NAMES = ["quant_pack", "quant_pack_fixed", "dequant_unpack", "gelu_quant_pack", 
          "prune_scores_threshold", "restore_scores", "softmax_prune", "softmax_backward_pruned", "prune_global_standardized",
          "prune_global_standardized_own", "layernorm_forward", "layernorm_backward", "layernorm_backward_pruned",
          "layernorm_forward_quant_pack", "layernorm_backward_dequant", "layernorm_param_grads", "layer_delta_run",
-         "split_heads", "merge_heads"]
+         "split_heads", "merge_heads", "product", "product_own"]
 
 
 class _Subclass(torch.Tensor):

@@ -155,14 +155,15 @@ def test_linear_layers(monkeypatch):
     assert seen == [True, False]
     for got, want in ((y, x.double() @ w.double().t()), (dx, dy.double() @ w.double())):
         assert bool((got.double() - want).norm() <= 0.5 * 768 ** 0.5 * 2.0 ** -24 * want.norm())
-    # a gradient that is to be differentiated again, strides, other types, other devices, few rows, a bias
+    # a gradient that is to be differentiated again, strides, other types, other devices, few and deep rows, a bias
     seen.clear()
     y = ag.LinearFunction.apply(x, w, None)
     (dx,) = torch.autograd.grad(y, x, dy.requires_grad_(True), create_graph=True)
     assert dx.requires_grad and seen == [True]
     seen.clear()
     with torch.no_grad():
-        for xx, ww, bias in ((x.transpose(0, 1), w, None), (x.bfloat16(), w.bfloat16(), None), (x[:1, :64], w, None),
+        for xx, ww, bias in ((x.transpose(0, 1), w, None), (x.bfloat16(), w.bfloat16(), None),
+                             (x.view(1024, 2048), w.view(192, 2048), None),
                              (x, w, torch.zeros(768, device="cuda")), (x[..., :511], w[:, :511], None), (x, w.t().contiguous().t(), None),
                              (torch.randn(4096, 512), torch.randn(768, 512), None)):
             want = torch.nn.functional.linear(xx, ww, bias)
@@ -170,6 +171,32 @@ def test_linear_layers(monkeypatch):
         with torch.autocast("cuda", dtype=torch.bfloat16):
             assert ag.LinearFunction.apply(x, w, None).dtype == torch.bfloat16
     assert seen == []
+
+
+@pytest.mark.gpu
+def test_small_products_are_the_librarys_where_the_host_waits(monkeypatch):
+    """Up to a depth of 768 outside a capture; the captured ones are torch's."""
+    require_gpu()
+    seen = _calls(monkeypatch)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x, w = (torch.randn(n, 768, generator=g, device="cuda") for n in (70, 50))
+    with torch.no_grad():
+        y = ag.LinearFunction.apply(x, w, None)
+        want = x.double() @ w.double().t()
+        assert seen == [True] and bool((y.double() - want).norm() <= 0.5 * 768 ** 0.5 * 2.0 ** -24 * want.norm())
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            torch.nn.functional.linear(x, w)                           # torch's own first call is not captured
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            y = ag.LinearFunction.apply(x, w, None)
+        assert seen == [True]
+        for _ in range(3):
+            y.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert bool((y.double() - want).norm() <= 1e-5 * want.norm())
 
 
 @pytest.mark.gpu
