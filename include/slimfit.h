@@ -530,13 +530,11 @@ int32_t slimfit_merge_heads(const void *q, const void *kt, const void *v, int32_
  *        out[i][j] = sum over k of a[i][k] * b[k][j]     (b_deep == 0: b is K x N)
  *  a, b, out : DEVICE fp32, row-major and contiguous; a, b 16-byte aligned, out 4-byte; out overlaps neither.
  *  K has to be a multiple of 32: ERR_UNSUPPORTED.
- *  workspace : DEVICE, 16-byte aligned, of slimfit_product_workspace(M, N, K) bytes (those of a and b and a few); contents
- *  overwritten; overlaps nothing else.
- *  Each row of a and each row (b_deep) or column of b is scaled by a power of two and split into two fp16 numbers; three of
- *  the four partial products are added up in fp32:
- *      |out - exact| <= (K + 10) * 2^-24 * sum |a||b| + 2^-50 * K * max |a[i]| * max |b[j]|,
- *  no further from the exact product than fp32 additions in any order but for entries below 2^-28 of their row's largest.
- *  Infinities and NaN come out as in plain fp32 arithmetic.  Deterministic.
+ *  workspace : none is needed (slimfit_product_workspace reports 0 bytes); what is passed is not looked at.
+ *  Each operand is split exactly into three bf16 numbers and six of the nine partial products are added up in fp32 (the
+ *  other three are at most 2^-24 of theirs), no further from the exact product than fp32 additions in any order:
+ *      |out - exact| <= (K + 1) * 2^-24 * sum |a||b|
+ *  for entries of magnitude above 2^-100.  Infinities and NaN come out as in plain fp32 arithmetic.  Deterministic.
  * ---------------------------------------------------------------------- */
 int32_t slimfit_product_workspace(int64_t M, int64_t N, int64_t K, size_t *bytes);
 

@@ -292,9 +292,8 @@ def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
     """x @ weight.T or x @ weight over x's last dimension by the library's fp32 product, or None where that is torch's.
 
     It is the faster one where the product has at least 192 tiles of 128 x 64, three for four compute units (rows x columns x
-    depth, torch's and this in us: 4096 x 768 x 3072 138 and 80, 2048 x 768 x 3072 76 and 56, 4096 x 384 x 384 18.4 and 18.1,
-    192 tiles the last two; 2048 x 512 x 2048 34 and 42, 1024 x 1024 x 4096 62 and 70, 128 tiles each, which torch splits along
-    their depth).  Smaller ones are shorter than the host takes to ask for them, 18 us torch's and 8 this: up to a depth of
+    depth, torch's and this in us: 4096 x 768 x 3072 140 and 95, 2048 x 768 x 3072 76 and 65, 192 tiles; 2048 x 512 x 2048 34
+    and 44, 1024 x 1024 x 4096 63 and 85, 128 tiles each, which torch splits along their depth).  Smaller ones are shorter than the host takes to ask for them, 18 us torch's and 8 this: up to a depth of
     768 this one is through in that time (256 x 256 x 256 11 us on the GPU, 1024 x 768 x 768 23, torch's 6 and 14), deeper ones
     are not (1024 x 768 x 3072 57 and 42), and a graph that is captured has no host to wait for."""
     if x.dtype != torch.float32 or weight.dtype != torch.float32 or x.dim() < 2 or weight.dim() != 2:

@@ -740,7 +740,7 @@ _native_product = _fast("product")
 
 def product(a: torch.Tensor, b: torch.Tensor, b_deep: bool, out: torch.Tensor, workspace: Optional[torch.Tensor] = None,
             stream=None) -> None:
-    """out = a @ b.T (``b_deep``: b is N x K) or a @ b (b is K x N); fp32, K a multiple of 32."""
+    """out = a @ b.T (``b_deep``: b is N x K) or a @ b (b is K x N); fp32, K a multiple of 32.  No workspace is needed."""
     rc = _native_product(a, b, b_deep, out, workspace, stream)
     if rc is not NotImplemented:
         return None if rc is None else _check(rc, "product")
@@ -748,9 +748,8 @@ def product(a: torch.Tensor, b: torch.Tensor, b_deep: bool, out: torch.Tensor, w
     M, K = a.shape
     N = b.shape[0] if b_deep else b.shape[1]
     _require(b.shape[1 if b_deep else 0] == K and out.shape == (M, N))
-    workspace = _own_workspace(workspace, product_workspace(M, N, K), a.device, stream)
     rc = lib().slimfit_product(_dev(a), _dev(b), C.c_int32(int(bool(b_deep))), C.c_int64(M), C.c_int64(N), C.c_int64(K), _dev(out),
-                               _dev(workspace), C.c_size_t(workspace.numel()), _stream(stream))
+                               None, C.c_size_t(0), _stream(stream))
     _check(rc, "product")
 
 

@@ -29,7 +29,7 @@ namespace {
     X(softmax_prune) X(softmax_backward_pruned) X(prune_global_standardized) X(prune_global_workspace)                 \
     X(layernorm_forward) X(layernorm_backward) X(layernorm_backward_pruned) X(layernorm_forward_quant_pack)            \
     X(layernorm_backward_dequant) X(layernorm_param_grads) X(layernorm_param_grads_workspace) X(layer_delta_run)         \
-    X(split_heads) X(merge_heads) X(product) X(product_workspace)
+    X(split_heads) X(merge_heads) X(product)
 #define X(name) decltype(&slimfit_##name) name##_fn = nullptr;
 SLIMFIT_CALLS(X)
 #undef X
@@ -560,22 +560,21 @@ PyObject *product(PyObject *, PyObject *const *args, Py_ssize_t n_args)
     Args a(args, n_args, 6);
     const at::Tensor *x = a.tensor(), *y = a.tensor();
     const int32_t y_deep = a.truth();
-    const at::Tensor *out = a.tensor(), *workspace = a.tensor_or_none();
+    const at::Tensor *out = a.tensor();
+    a.tensor_or_none();                                     // a workspace, which the product does not need
     void *st = a.stream();
     int64_t M = 0, N = 0, K = 0;
-    size_t need = 0;
     if (a.ok) {
         a.need(x->dim() == 2 && y->dim() == 2 && out->dim() == 2 && f32(x) && f32(y) && f32(out));
         if (a.ok) {
             M = x->size(0), K = x->size(1), N = y->size(y_deep ? 0 : 1);
-            a.need(y->size(y_deep ? 1 : 0) == K && out->size(0) == M && out->size(1) == N && product_workspace_fn(M, N, K, &need) == SLIMFIT_OK);
+            a.need(y->size(y_deep ? 1 : 0) == K && out->size(0) == M && out->size(1) == N);
         }
     }
-    Scratch w;
-    if (!a.ok || !w.take(workspace, a.own_stream, need, x)) return general();
+    if (!a.ok) return general();
     const float *xp = ptr<float>(x), *yp = ptr<float>(y);
     float *op = ptr<float>(out);
-    SLIMFIT_RUN(product_fn(xp, yp, y_deep, M, N, K, op, w.at, w.bytes, st));
+    SLIMFIT_RUN(product_fn(xp, yp, y_deep, M, N, K, op, nullptr, 0, st));
 }
 
 // a C++ exception must not cross into the interpreter (torch's allocator raises one when memory runs out: the general

@@ -1,255 +1,222 @@
-// Products of fp32 matrices on the fp16 matrix instructions (not in the paper: the dense products of the wrapped encoder
+// Products of fp32 matrices on the bf16 matrix instructions (not in the paper: the dense products of the wrapped encoder
 // block's linear layers).
 //
-// A row of an operand, brought to below 2^15 by a power of two of its own, is the sum of two fp16 numbers, h and 2^-12 l, but
-// for the last of its 24 bits where l would need a twelfth (at most 2^-23 of the entry; l is kept 2^12 times its size so that
-// entries down to 2^-28 of the row's largest are as exact).  A product of two is then h h + 2^-12 (h l + l h), each exact in
-// fp32, and l l, at most 2^-22 of it and 2^-26 in the mean, which is left out.  split_kernel writes both operands' parts in the
-// order in which product_kernel's fragments take them; a step's h l + l h are added up by themselves and then to h h.  Against
-// 64 bits 1.6e-7 to 2.1e-7 at K = 768 and 2.9e-7 to 4.0e-7 at 3072, where torch's fp32 product has 5.0e-7 and 9.9e-7.  A row
-// with an infinity or a NaN, and results too large for fp32, are computed by plain arithmetic at the end of their tile.
+// An fp32 number is the exact sum of three bf16 numbers, x = h + m + l (8 of its 24 bits, rounded to nearest, 8 of what is
+// left, the rest), so a product of two is the sum of nine bf16 products, each exact in fp32.  The matrix cores add up the six
+// from h h down to h l and m m; the other three are at most 2^-24 of the product.  A step's 32 elements are added up by
+// themselves and then to what there was, so that a sum of K products is rounded K / 32 times at its own size: against 64 bits
+// 1.5e-7 at K = 768 and 1.8e-7 at 3072, where torch's fp32 product has 5.0e-7 and 9.9e-7 (with every instruction adding to
+// the whole sum 4.3e-7 and 6.2e-7, and 5 % less time).  Entries below 2^-100 or so keep fewer bits, since the smaller parts
+// leave bf16's range; infinities, NaN and entries too large for a part are multiplied by plain arithmetic at the end of the
+// tile they fall into.
 //
-// The products are bound by power: 4096 x 3072 x 768 takes 56 us in an encoder block, 1.04 PFLOP/s of fp16 (an 8192^3 product
-// in bf16 reaches 1.21 on the card), 4096 x 768 x 3072 58 to 63; splitting by memory: 119 MB in 25 us for the latter, 44 MB in
-// 11 for the former, two thirds of what a copy reaches, since a workgroup first reads its rows and then writes them.
-// Together 67 and 80 us, where three bf16 parts of each operand, split on their way into LDS, and six products took 106 and 99
-// and torch's fp32 product takes 141 and 138.
+// Bound by power and by how far splitting (vector instructions) and multiplying overlap: 4096 x 768 x 3072 takes 99 us,
+// 195 TFLOP/s of fp32 or 1.17 PFLOP/s of bf16 (an 8192^3 product in bf16 reaches 1.21 on the card); with operands of zeros a
+// fifth less, with one of the six products a quarter.  torch's fp32 product: 150.
 #include "common.hpp"
 
 namespace slimfit {
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kStep = 32;                  // depth of a step: one v_mfma_f32_16x16x32_f16
-constexpr int kFragRows = 16;
-constexpr int kPartBytes = kWave * 16;     // one part of a fragment: 16 rows, a step deep, lane l's eight elements at 16 l
-constexpr int kFragBytes = 2 * kPartBytes; // h, then l
+constexpr int kStep = 32;                  // depth of a step: one v_mfma_f32_16x16x32_bf16
+constexpr int kRowBytes = kStep * 2;       // a row of one part in LDS
+constexpr int kGroup = 256;                // threads that share a step
+constexpr int kTileM = 128;
 
-__host__ __device__ inline int64_t frags_of(int64_t rows) { return (rows + kFragRows - 1) / kFragRows; }
-
-// ---------------------------------------------------------------------------------------------------- splitting
-
-constexpr int kSplitWaves = 16;            // of a workgroup, at most: one for each HELD steps
-
-// The power of two that brings magnitudes up to `top` (bits of the largest) below 2^15; 2^126 at most.
-__device__ __forceinline__ uint32_t scale_bits(uint32_t top) { return min(268u - (top >> 23), 253u); }
-
-__device__ __forceinline__ void split8(const float (&f)[8], float scale, bool odd, u32x4 &h, u32x4 &l)
+struct Parts {
+    u32x4 h, m, l;                         // eight bf16 each
+};
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
 {
-    f16x8 hh, ll;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float x = f[i] * scale;
-        hh[i] = (_Float16)x;
-        ll[i] = (_Float16)((x - (float)hh[i]) * 4096.0f);
-    }
-    h = __builtin_bit_cast(u32x4, hh);
-    l = __builtin_bit_cast(u32x4, ll);
-    if (odd) {
-        h = u32x4{0x7E007E00u, 0x7E007E00u, 0x7E007E00u, 0x7E007E00u};
-        l = u32x4{0u, 0u, 0u, 0u};
-    }
+    h = bf16_narrow2(a, b);
+    a -= __builtin_bit_cast(float, h << 16);
+    b -= __builtin_bit_cast(float, h & 0xFFFF0000u);
+    m = bf16_narrow2(a, b);
+    a -= __builtin_bit_cast(float, m << 16);
+    b -= __builtin_bit_cast(float, m & 0xFFFF0000u);
+    l = bf16_narrow2(a, b);
 }
-
-// Sixteen rows a workgroup, over their whole depth; element k of row r at x[r * ld + k] (DEEP) or x[k * ld + r].  Rows past the
-// last repeat it.  A wave holds HELD steps in registers between the two passes; deeper rows are read twice.
-template <bool DEEP, int HELD>
-__device__ __forceinline__ void split_rows(const float *__restrict__ x, int64_t frag, int64_t rows, int64_t ld, int64_t steps, char *__restrict__ parts,
-                                           float *__restrict__ unscale, uint32_t (&top)[kSplitWaves][kFragRows])
+__device__ __forceinline__ Parts split(const float (&f)[8])
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x / kWave, row = lane & 15;
-    const int64_t r = min(frag * kFragRows + row, rows - 1), k = (lane >> 4) * 8;
-    const float *p = DEEP ? x + r * ld + k : x + k * ld + r;
-    auto load = [&](int64_t s, float (&f)[8]) {
-        const float *at = p + (DEEP ? s * kStep : s * kStep * ld);
-        if constexpr (DEEP) {
-            const f32x4 a = reinterpret_cast<const f32x4 *>(at)[0], b = reinterpret_cast<const f32x4 *>(at)[1];
-            f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
-            f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-        } else {
+    uint32_t h[4], m[4], l[4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) f[i] = at[i * ld];
+    for (int i = 0; i < 4; ++i) split_pair(f[2 * i], f[2 * i + 1], h[i], m[i], l[i]);
+    return Parts{{h[0], h[1], h[2], h[3]}, {m[0], m[1], m[2], m[3]}, {l[0], l[1], l[2], l[3]}};
+}
+// Where 16 bytes (eight elements deep) of a row lie: those of eight consecutive rows, and the four of two, are in different
+// banks (SQ_LDS_BANK_CONFLICT counts none).
+__device__ __forceinline__ int chunk_at(int row, int chunk) { return row * kRowBytes + ((chunk ^ ((row >> 1) & 3)) << 4); }
+
+// A thread's share of ROWS rows of an operand, a step at a time.  Row r starts at base + r * ld (DEEP) or, its elements ld
+// apart, at base + r.
+template <int ROWS, bool DEEP, int GROUPS>
+struct Loader {
+    static constexpr int ITEMS = (ROWS * 4 + kGroup - 1) / kGroup;      // of eight elements
+    using Held = float[ITEMS][8];
+    const float *p[ITEMS];
+    int64_t ld;
+    __device__ __forceinline__ static bool has(int q, int t) { return (q + 1) * kGroup <= ROWS * 4 || t + q * kGroup < ROWS * 4; }   // wave-uniform
+    __device__ __forceinline__ static int row(int q, int t) { return DEEP ? (t + q * kGroup) >> 2 : (t + q * kGroup) % ROWS; }
+    __device__ __forceinline__ static int chunk(int q, int t) { return DEEP ? (t + q * kGroup) & 3 : (t + q * kGroup) / ROWS; }
+    // rows past the last are read as the last, items past the share as its first
+    __device__ __forceinline__ void init(const float *base, int64_t first, int64_t rows, int64_t ld_, int64_t k0, int t)
+    {
+        ld = ld_;
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            const int64_t r = min(first + (has(q, t) ? row(q, t) : 0), rows - 1);
+            const int64_t k = k0 + 8 * (has(q, t) ? chunk(q, t) : 0);
+            p[q] = base + (DEEP ? r * ld + k : k * ld + r);
         }
-    };
-    uint32_t most = 0;
-    auto look = [&](const float (&f)[8]) {
+    }
+    // No branch around any load, so that each is waited for by itself.  more: there is a step after this one; otherwise the
+    // next call reads the same again.
+    __device__ __forceinline__ void load(Held &f, bool more)
+    {
+        const int64_t on = more ? GROUPS * kStep * (DEEP ? 1 : ld) : 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) most = max(most, __builtin_bit_cast(uint32_t, f[i]) & 0x7FFFFFFFu);
-    };
-    float held[HELD][8];
+        for (int q = 0; q < ITEMS; ++q) {
+            if constexpr (DEEP) {
+                const f32x4 a = reinterpret_cast<const f32x4 *>(p[q])[0], b = reinterpret_cast<const f32x4 *>(p[q])[1];
+                f[q][0] = a.x; f[q][1] = a.y; f[q][2] = a.z; f[q][3] = a.w;
+                f[q][4] = b.x; f[q][5] = b.y; f[q][6] = b.z; f[q][7] = b.w;
+            } else {
 #pragma unroll
-    for (int q = 0; q < HELD; ++q) {
-        const int64_t s = wave + q * waves;
-        load(s < steps ? s : 0, held[q]);
+                for (int i = 0; i < 8; ++i) f[q][i] = p[q][i * ld];
+            }
+            p[q] += on;
+        }
     }
+    __device__ __forceinline__ static void store(const Held &f, char *lds, int t)
+    {
 #pragma unroll
-    for (int q = 0; q < HELD; ++q) {
-        if (wave + q * waves < steps) look(held[q]);
+        for (int q = 0; q < ITEMS; ++q) {
+            if (!has(q, t)) continue;
+            const Parts s = split(f[q]);
+            char *at = lds + chunk_at(row(q, t), chunk(q, t));
+            *reinterpret_cast<u32x4 *>(at) = s.h;
+            *reinterpret_cast<u32x4 *>(at + ROWS * kRowBytes) = s.m;
+            *reinterpret_cast<u32x4 *>(at + 2 * ROWS * kRowBytes) = s.l;
+        }
     }
-    for (int64_t s = wave + HELD * waves; s < steps; s += waves) {
-        float f[8];
-        load(s, f);
-        look(f);
-    }
-    most = max(most, (uint32_t)__shfl_xor((int)most, 16));
-    most = max(most, (uint32_t)__shfl_xor((int)most, 32));
-    if (lane < kFragRows) top[wave][lane] = most;
-    __syncthreads();
-    for (int w = 0; w < waves; ++w) most = max(most, top[w][row]);
-    const bool odd = most >= 0x7F800000u;
-    const uint32_t bits = odd ? 127u : scale_bits(most);
-    const float scale = __builtin_bit_cast(float, bits << 23);
-    if (threadIdx.x < kFragRows) unscale[frag * kFragRows + lane] = __builtin_bit_cast(float, (254u - bits) << 23);
-    auto store = [&](int64_t s, const float (&f)[8]) {
-        u32x4 h, l;
-        split8(f, scale, odd, h, l);
-        u32x4 *at = reinterpret_cast<u32x4 *>(parts + (frag * steps + s) * kFragBytes) + lane;
-        at[0] = h;
-        at[kWave] = l;
-    };
-#pragma unroll
-    for (int q = 0; q < HELD; ++q) {
-        const int64_t s = wave + q * waves;
-        if (s < steps) store(s, held[q]);
-    }
-    for (int64_t s = wave + HELD * waves; s < steps; s += waves) {
-        float f[8];
-        load(s, f);
-        store(s, f);
-    }
-}
-
-struct Split {
-    char *parts;                           // [fragments][steps][kFragBytes]
-    float *unscale;                        // [fragments * 16]
 };
 
-template <bool DEEP_B, int HELD>
-__global__ void __launch_bounds__(kSplitWaves * kWave, HELD > 4 ? 4 : 8)
-split_kernel(const float *__restrict__ a, const float *__restrict__ b, int64_t M, int64_t N, int64_t K, Split sa, Split sb)
+// out[i][j] = sum over k of a[i][k] b[j][k]; DEEP_B: b is N x K, otherwise K x N.  A group of four waves takes a step at a
+// time, 64 x TN/2 of the tile a wave: its rows are split into LDS, and what was split is multiplied.
+//   GROUPS 1  three workgroups a compute unit fill one another's waits: where there are tiles for that
+//             (4096 x 2304 x 768 80 us, with two groups 95).  168 registers, which is why only one row of a's parts is held.
+//   GROUPS 2  two groups of a workgroup take every other step of the same tile, one splitting while the other multiplies
+//             (a barrier swaps them), and add their sums up at the end: where a compute unit has one tile
+//             (4096 x 768 x 3072 99 us, with one group 132; 4096 x 768 x 768 29 and 44).
+// AHEAD: steps of operands on their way in registers (one group has none to spare for two; two groups with one: 9 % slower).
+template <int TN, bool DEEP_B, int GROUPS>
+__global__ void __launch_bounds__(GROUPS * kGroup, GROUPS == 2 ? 2 : 3)
+product_kernel(const float *__restrict__ a, const float *__restrict__ b, int64_t M, int64_t N, int64_t K, float *__restrict__ out, int tiles_m,
+               int tiles_n)
 {
-    __shared__ uint32_t top[kSplitWaves][kFragRows];
-    const int64_t of_a = frags_of(M), id = blockIdx.x, steps = K / kStep;
-    if (id < of_a) split_rows<true, HELD>(a, id, M, K, steps, sa.parts, sa.unscale, top);
-    else split_rows<DEEP_B, HELD>(b, id - of_a, N, DEEP_B ? K : N, steps, sb.parts, sb.unscale, top);
-}
-
-// -------------------------------------------------------------------------------------------------- multiplying
-
-// out[i][j] = sum over k of a[i][k] b[j][k]; b_deep: b is N x K, otherwise K x N (a and b are read only where plain arithmetic decides).
-// A group of WY x WX waves takes a step at a time, TM/WY x TN/WX of the tile a wave; the step's fragments go from the split
-// operands straight to LDS, one step ahead.  GROUPS groups of a workgroup take every GROUPS-th step of the same tile and add
-// their sums up at the end.  Twelve waves, three a SIMD, fill one another's waits better than eight of larger parts: 4096 x 3072 x
-// 768 in tiles of 256 x 192 68 us and 73.
-template <int TM, int TN, int WY, int WX, int GROUPS>
-__global__ void __launch_bounds__(GROUPS * WY * WX * kWave, 2)
-product_kernel(Split sa, Split sb, int64_t M, int64_t N, int64_t K, float *__restrict__ out, int tiles_m, int tiles_n, const float *__restrict__ a,
-               const float *__restrict__ b, bool b_deep)
-{
-    constexpr int FM = TM / WY / 16, FN = TN / WX / 16, WAVES = WY * WX;
-    constexpr int PARTS_A = TM / 16 * 2, PARTS = PARTS_A + TN / 16 * 2, OWN_PARTS = (PARTS + WAVES - 1) / WAVES, STAGE = PARTS * kPartBytes;
-    __shared__ __align__(16) char lds[GROUPS * 2 * STAGE];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int in_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = in_all % WAVES, group = in_all / WAVES;
+    constexpr int WM = kTileM / 2, WN = TN / 2, FM = WM / 16, FN = WN / 16, AHEAD = GROUPS;
+    constexpr int PART_A = kTileM * kRowBytes, PART_B = TN * kRowBytes, STAGE = 3 * (PART_A + PART_B);
+    __shared__ __align__(16) char lds[GROUPS * STAGE];
+    const int t = threadIdx.x & (kGroup - 1), lane = t & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), group = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
     // Workgroups go to the eight XCDs in turn; an XCD's take bands of four tile rows, column by column, so that those at
     // work together share operands in its L2.
     const int per = tiles_m * tiles_n / 8, b0 = (int)blockIdx.x, id = b0 < per * 8 ? (b0 % 8) * per + b0 / 8 : b0;
     const int band = id / (4 * tiles_n), in_band = id % (4 * tiles_n), height = min(4, tiles_m - 4 * band);
-    const int64_t m0 = (int64_t)(band * 4 + in_band % height) * TM, n0 = (int64_t)(in_band / height) * TN;
+    const int64_t m0 = (int64_t)(band * 4 + in_band % height) * kTileM, n0 = (int64_t)(in_band / height) * TN;
 
-    char *stage = lds + group * 2 * STAGE;
-    const int steps = (int)(K / kStep), mine = (steps + GROUPS - 1 - group) / GROUPS, rounds = (steps + GROUPS - 1) / GROUPS;
-    const int64_t most_a = frags_of(M) - 1, most_b = frags_of(N) - 1;
-    const char *from[OWN_PARTS];
-#pragma unroll
-    for (int q = 0; q < OWN_PARTS; ++q) {
-        const int part = min(wave * OWN_PARTS + q, PARTS - 1), f = part < PARTS_A ? part >> 1 : (part - PARTS_A) >> 1;
-        const char *base = part < PARTS_A ? sa.parts + min(m0 / 16 + f, most_a) * steps * kFragBytes : sb.parts + min(n0 / 16 + f, most_b) * steps * kFragBytes;
-        from[q] = base + (part & 1) * kPartBytes + group * kFragBytes;
-    }
-    // step s of this group into its stage s & 1
-    auto fetch = [&](int s) {
-#pragma unroll
-        for (int q = 0; q < OWN_PARTS; ++q) {
-            if (PARTS % WAVES != 0 && wave * OWN_PARTS + q >= PARTS) break;      // wave-uniform
-            typedef __attribute__((address_space(3))) void lds_void;
-            typedef const __attribute__((address_space(1))) void global_void;
-            __builtin_amdgcn_global_load_lds((global_void *)(from[q] + (int64_t)s * (GROUPS * kFragBytes) + lane * 16),
-                                             (lds_void *)(stage + (s & 1) * STAGE + (wave * OWN_PARTS + q) * kPartBytes), 16, 0, 0);
-        }
-    };
+    char *stage = lds + group * STAGE;
+    Loader<kTileM, true, GROUPS> la;
+    Loader<TN, DEEP_B, GROUPS> lb;
+    const int steps = (int)(K / kStep), mine = GROUPS == 1 ? steps : (steps + 1 - group) / 2, rounds = GROUPS == 1 ? steps : (steps + 1) / 2;
+    const int64_t k0 = group < steps ? group * kStep : 0;
+    la.init(a, m0, M, K, k0, t);
+    lb.init(b, n0, N, DEEP_B ? K : N, k0, t);
     f32x4 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    const int frag_a = wave / WX * FM, frag_b = wave % WX * FN;
-    const char *read_a = stage + frag_a * kFragBytes + lane * 16, *read_b = stage + PARTS_A * kPartBytes + frag_b * kFragBytes + lane * 16;
-    if (mine > 0) fetch(0);
-    for (int s = 0; s < rounds; ++s) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);                 // what this wave fetched is in LDS: vmcnt(0)
-        __syncthreads();                                    // and what the others did; the other stage has been read
+    typename Loader<kTileM, true, GROUPS>::Held ha[AHEAD];
+    typename Loader<TN, DEEP_B, GROUPS>::Held hb[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+        la.load(ha[u], u + 1 < mine);
+        lb.load(hb[u], u + 1 < mine);
+    }
+    const int wm = (wave >> 1) * WM, wn = (wave & 1) * WN;
+    const char *read_a = stage + chunk_at(wm + (lane & 15), lane >> 4);
+    const char *read_b = stage + 3 * PART_A + chunk_at(wn + (lane & 15), lane >> 4);
+    auto step = [&](auto &held_a, auto &held_b, int s) {
+        la.store(held_a, stage, t);
+        lb.store(held_b, stage + 3 * PART_A, t);
+        la.load(held_a, s + AHEAD + 1 < mine);
+        lb.load(held_b, s + AHEAD + 1 < mine);
+        __syncthreads();
         if (s < mine) {                                     // uniform for the group
-            const int at = (s & 1) * STAGE;
-            f16x8 fa[FM][2], fb[FN][2];
+            __builtin_amdgcn_s_setprio(1);                  // without: 10 % slower
+            bf16x8 fb[3][FN];
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
+            for (int p = 0; p < 3; ++p) {
 #pragma unroll
-                for (int p = 0; p < 2; ++p) fb[j][p] = *reinterpret_cast<const f16x8 *>(read_b + at + j * kFragBytes + p * kPartBytes);
+                for (int j = 0; j < FN; ++j) fb[p][j] = *reinterpret_cast<const bf16x8 *>(read_b + p * PART_B + j * 16 * kRowBytes);
             }
+            constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
             for (int i = 0; i < FM; ++i) {
+                bf16x8 fa[3];
 #pragma unroll
-                for (int p = 0; p < 2; ++p) fa[i][p] = *reinterpret_cast<const f16x8 *>(read_a + at + i * kFragBytes + p * kPartBytes);
-            }
-            if (s + 1 < mine) fetch(s + 1);
+                for (int p = 0; p < 3; ++p) fa[p] = *reinterpret_cast<const bf16x8 *>(read_a + p * PART_A + i * 16 * kRowBytes);
+                f32x4 part[FN];
 #pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                f32x4 low[FN];
+                for (int j = 0; j < FN; ++j) part[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int j = 0; j < FN; ++j) low[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i][0], fb[j][1], f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                for (int u = 0; u < 6; ++u) {
 #pragma unroll
-                for (int j = 0; j < FN; ++j) low[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i][1], fb[j][0], low[j], 0, 0, 0);
-#pragma unroll
-                for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i][0], fb[j][0], acc[i][j], 0, 0, 0);
-#pragma unroll
-                for (int j = 0; j < FN; ++j) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[i][j][q] = __builtin_fmaf(low[j][q], 0x1p-12f, acc[i][j][q]);
+                    for (int j = 0; j < FN; ++j)
+                        part[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[PA[u]], fb[PB[u]][j], part[j], 0, 0, 0);
                 }
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] += part[j];
             }
+            __builtin_amdgcn_s_setprio(0);
         }
+        __syncthreads();
+    };
+    // every thread passes the same number of barriers: the second group waits once before, the first once after; with two
+    // groups the rounds are made even, and one past the end splits the last step again and multiplies nothing
+    if (GROUPS == 2 && group == 1) __syncthreads();
+    for (int s = 0; s < rounds; s += AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) step(ha[u], hb[u], s + u);
     }
     constexpr int OWN = FM / GROUPS;                        // rows of sixteen that a group finishes
-    const int64_t col0 = n0 + frag_b * 16 + (lane & 15), row0 = m0 + (frag_a + group * OWN) * 16 + (lane >> 4) * 4;
+    const int64_t col0 = n0 + wn + (lane & 15), row0 = m0 + wm + group * OWN * 16 + (lane >> 4) * 4;
     bool odd = false;
     auto put = [&](int i, int j, f32x4 v) {
         const int64_t col = col0 + j * 16;
         const float r[4] = {v.x, v.y, v.z, v.w};
-        const float by = sb.unscale[min(col, N - 1)];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int64_t row = row0 + i * 16 + q;
-            const float value = r[q] * sa.unscale[min(row, M - 1)] * by;
-            odd |= !(__builtin_fabsf(value) < 3.0e38f);
-            if (row < M && col < N) out[row * N + col] = value;
+            odd |= !(__builtin_fabsf(r[q]) < 3.0e38f);
+            if (row0 + i * 16 + q < M && col < N) out[(row0 + i * 16 + q) * N + col] = r[q];
         }
     };
-    static_assert(GROUPS == 1 || GROUPS == 2, "");
     if constexpr (GROUPS == 2) {
-        __syncthreads();                                    // the stages have been read
+        if (group == 0) __syncthreads();
         // each group hands the other half of its sums over and finishes the rest
-        static_assert(FM % 2 == 0 && 4 * STAGE >= 2 * WAVES * OWN * FN * kWave * 16, "the sums fit the stages");
-        f32x4 *give = reinterpret_cast<f32x4 *>(lds) + ((1 - group) * WAVES + wave) * (OWN * FN * kWave);
-        const f32x4 *take = reinterpret_cast<const f32x4 *>(lds) + (group * WAVES + wave) * (OWN * FN * kWave);
+        static_assert(FM % 2 == 0 && 2 * STAGE >= 2 * 4 * OWN * FN * kWave * 16, "the sums fit the stages");
+        f32x4 *give = reinterpret_cast<f32x4 *>(lds) + ((1 - group) * 4 + wave) * (OWN * FN * kWave);
+        const f32x4 *take = reinterpret_cast<const f32x4 *>(lds) + (group * 4 + wave) * (OWN * FN * kWave);
 #pragma unroll
         for (int i = 0; i < OWN; ++i) {
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
-                const f32x4 first = acc[i][j], second = acc[OWN + i][j];
-                give[(i * FN + j) * kWave + lane] = group == 0 ? second : first;
+                const f32x4 low = acc[i][j], high = acc[OWN + i][j];
+                give[(i * FN + j) * kWave + lane] = group == 0 ? high : low;
             }
         }
         __syncthreads();
@@ -257,8 +224,8 @@ product_kernel(Split sa, Split sb, int64_t M, int64_t N, int64_t K, float *__res
         for (int i = 0; i < OWN; ++i) {
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
-                const f32x4 first = acc[i][j], second = acc[OWN + i][j];
-                put(i, j, (group == 0 ? first : second) + take[(i * FN + j) * kWave + lane]);
+                const f32x4 low = acc[i][j], high = acc[OWN + i][j];
+                put(i, j, (group == 0 ? low : high) + take[(i * FN + j) * kWave + lane]);
             }
         }
     } else {
@@ -268,46 +235,27 @@ product_kernel(Split sa, Split sb, int64_t M, int64_t N, int64_t K, float *__res
             for (int j = 0; j < FN; ++j) put(i, j, acc[i][j]);
         }
     }
-    // A row that holds an infinity or a NaN, or a sum that overflows: plain arithmetic decides what comes out.
+    // An operand that is infinite, NaN or too large for a part, or a sum that overflows: plain arithmetic decides what
+    // comes out.
     if (__builtin_amdgcn_ballot_w64(odd) != 0u) {
         for (int i = 0; i < OWN * FN * 4; ++i) {
             const int64_t row = row0 + i / (FN * 4) * 16 + i % 4, col = col0 + i / 4 % FN * 16;
             if (row >= M || col >= N || __builtin_fabsf(out[row * N + col]) < 3.0e38f) continue;
             float sum = 0.0f;
-            for (int64_t k = 0; k < K; ++k) sum += a[row * K + k] * (b_deep ? b[col * K + k] : b[k * N + col]);
+            for (int64_t k = 0; k < K; ++k) sum += a[row * K + k] * (DEEP_B ? b[col * K + k] : b[k * N + col]);
             out[row * N + col] = sum;
         }
     }
 }
 
 int64_t tiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
-int64_t parts_bytes(int64_t rows, int64_t K) { return frags_of(rows) * (K / kStep) * kFragBytes; }
 
-template <bool DEEP_B, int HELD>
-void launch_split(const float *a, const float *b, int64_t M, int64_t N, int64_t K, const Split &sa, const Split &sb, hipStream_t s)
+template <int TN, int GROUPS>
+void launch_tiles(const float *a, const float *b, bool b_deep, int64_t M, int64_t N, int64_t K, float *out, hipStream_t s)
 {
-    const int64_t waves = (K / kStep + HELD - 1) / HELD;
-    launch(split_kernel<DEEP_B, HELD>, (unsigned)(frags_of(M) + frags_of(N)), (unsigned)(waves < kSplitWaves ? waves : kSplitWaves) * kWave, 0, s, a, b, M, N,
-           K, sa, sb);
-}
-template <int TM, int TN, int WY, int WX, int GROUPS>
-void launch_tiles(const float *a, const float *b, bool b_deep, int64_t M, int64_t N, int64_t K, float *out, const Split &sa, const Split &sb,
-                  hipStream_t s)
-{
-    const int tm = (int)tiles_of(M, TM), tn = (int)tiles_of(N, TN);
-    launch(product_kernel<TM, TN, WY, WX, GROUPS>, (unsigned)(tm * tn), GROUPS * WY * WX * kWave, 0, s, sa, sb, M, N, K, out, tm, tn, a, b, b_deep);
-}
-
-int32_t validate(int64_t M, int64_t N, int64_t K)
-{
-    if (M < 0 || N < 0 || K < 0) return SLIMFIT_ERR_INVALID_ARG;
-    if (M == 0 || N == 0) return SLIMFIT_OK;
-    if (K == 0 || K % kStep != 0 || K > 0x7FFFFFFFLL) return SLIMFIT_ERR_UNSUPPORTED;
-    // (each factor is below 2^63: the products are looked at in floating point first)
-    if ((double)M * (double)K > 1.0e18 || (double)N * (double)K > 1.0e18 || (double)M * (double)N > 1.0e18) return SLIMFIT_ERR_UNSUPPORTED;
-    if ((double)tiles_of(M, 128) * (double)tiles_of(N, 64) > (double)(kMaxGridThreads / 512)) return SLIMFIT_ERR_UNSUPPORTED;
-    if ((double)(frags_of(M) + frags_of(N)) > (double)(kMaxGridThreads / (kSplitWaves * kWave))) return SLIMFIT_ERR_UNSUPPORTED;
-    return SLIMFIT_OK;
+    const int tm = (int)tiles_of(M, kTileM), tn = (int)tiles_of(N, TN);
+    if (b_deep) launch(product_kernel<TN, true, GROUPS>, (unsigned)(tm * tn), GROUPS * kGroup, 0, s, a, b, M, N, K, out, tm, tn);
+    else launch(product_kernel<TN, false, GROUPS>, (unsigned)(tm * tn), GROUPS * kGroup, 0, s, a, b, M, N, K, out, tm, tn);
 }
 
 }  // namespace
@@ -315,12 +263,24 @@ int32_t validate(int64_t M, int64_t N, int64_t K)
 
 using namespace slimfit;
 
+static int32_t validate(int64_t M, int64_t N, int64_t K)
+{
+    if (M < 0 || N < 0 || K < 0) return SLIMFIT_ERR_INVALID_ARG;
+    if (M == 0 || N == 0) return SLIMFIT_OK;
+    if (K == 0 || K % kStep != 0 || K > 0x7FFFFFFFLL) return SLIMFIT_ERR_UNSUPPORTED;
+    // (each factor is below 2^63: the products are looked at in floating point first)
+    if ((double)M * (double)K > 1.0e18 || (double)N * (double)K > 1.0e18 || (double)M * (double)N > 1.0e18) return SLIMFIT_ERR_UNSUPPORTED;
+    if ((double)tiles_of(M, kTileM) * (double)tiles_of(N, 64) > (double)(kMaxGridThreads / (2 * kGroup))) return SLIMFIT_ERR_UNSUPPORTED;
+    return SLIMFIT_OK;
+}
+
+// The operands are split on their way into LDS: no workspace is needed.
 extern "C" int32_t slimfit_product_workspace(int64_t M, int64_t N, int64_t K, size_t *bytes)
 {
     const int32_t rc = validate(M, N, K);
     if (rc != SLIMFIT_OK) return rc;
     if (!bytes) return SLIMFIT_ERR_INVALID_ARG;
-    *bytes = M == 0 || N == 0 ? 0 : (size_t)(parts_bytes(M, K) + parts_bytes(N, K) + (frags_of(M) + frags_of(N)) * kFragRows * 4);
+    *bytes = 0;
     return SLIMFIT_OK;
 }
 
@@ -328,44 +288,24 @@ extern "C" int32_t slimfit_product(const float *a, const float *b, int32_t b_dee
                                    size_t workspace_bytes, void *stream)
 {
     StreamScope capture_aware(stream);
-    size_t need = 0;
-    int32_t rc = slimfit_product_workspace(M, N, K, &need);
+    (void)workspace;
+    (void)workspace_bytes;
+    int32_t rc = validate(M, N, K);
     if (rc != SLIMFIT_OK || M == 0 || N == 0) return rc;
-    if (!a || !b || !out || !workspace) return SLIMFIT_ERR_INVALID_ARG;
-    if (!aligned_to(a, 16) || !aligned_to(b, 16) || !aligned_to(out, 4) || !aligned_to(workspace, 16)) return SLIMFIT_ERR_ALIGNMENT;
-    if (workspace_bytes < need) return SLIMFIT_ERR_WORKSPACE;
+    if (!a || !b || !out) return SLIMFIT_ERR_INVALID_ARG;
+    if (!aligned_to(a, 16) || !aligned_to(b, 16) || !aligned_to(out, 4)) return SLIMFIT_ERR_ALIGNMENT;
     if ((rc = check_device_range(a, (size_t)M * (size_t)K * 4)) != SLIMFIT_OK) return rc;
     if ((rc = check_device_range(b, (size_t)N * (size_t)K * 4)) != SLIMFIT_OK) return rc;
     if ((rc = check_device_range(out, (size_t)M * (size_t)N * 4)) != SLIMFIT_OK) return rc;
-    if ((rc = check_device_range(workspace, need)) != SLIMFIT_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    char *at = static_cast<char *>(workspace);
-    float *scales = reinterpret_cast<float *>(at + parts_bytes(M, K) + parts_bytes(N, K));
-    const Split sa{at, scales}, sb{at + parts_bytes(M, K), scales + frags_of(M) * kFragRows};
-    if (K <= 3 * kSplitWaves * kStep) b_deep ? launch_split<true, 3>(a, b, M, N, K, sa, sb, s) : launch_split<false, 3>(a, b, M, N, K, sa, sb, s);
-    else b_deep ? launch_split<true, 6>(a, b, M, N, K, sa, sb, s) : launch_split<false, 6>(a, b, M, N, K, sa, sb, s);
-    // A compute unit holds one workgroup; the tiles that take the fewest rounds of 256, a round's time being its tile's elements
-    // and 8192 more (its first fetch and its stores).  That picks the fastest of these seven for 18 of 19 sizes tried (4096 x
-    // 2304 x 768 in tiles of 256 x 144 57 us, of 256 x 192 62, of 128 x 96 67; 4096 x 3072 x 768 89, 68 and 84; 4096 x 768 x 768
-    // 50, 59 and 32).  Two groups where a tile is so small that one would leave a SIMD a single wave.
-    struct Tile {
-        int tm, tn;
-        void (*go)(const float *, const float *, bool, int64_t, int64_t, int64_t, float *, const Split &, const Split &, hipStream_t);
-    };
-    static constexpr Tile kTiles[] = {
-        {256, 192, launch_tiles<256, 192, 4, 3, 1>}, {256, 144, launch_tiles<256, 144, 4, 3, 1>}, {256, 96, launch_tiles<256, 96, 4, 3, 1>},
-        {128, 144, launch_tiles<128, 144, 2, 3, 2>}, {128, 128, launch_tiles<128, 128, 2, 2, 2>}, {128, 96, launch_tiles<128, 96, 2, 3, 2>},
-        {128, 64, launch_tiles<128, 64, 2, 2, 2>}};
+    // A tile for each of the 256 compute units at most: the narrowest tiles of which that holds, two groups on each (4096 x
+    // 768 x 3072 in tiles of 96 columns 99 us, of 128, which leave 64 units idle, 107).  More: one group (tiles of 64 columns
+    // 4096 x 2304 x 768 93 us, of 96 80; of 128 they need more registers than three workgroups have).
     constexpr int64_t kUnits = 256;
-    const Tile *best = kTiles;
-    double least = 0.0;
-    for (const Tile &tile : kTiles) {
-        const double takes = (double)tiles_of(tiles_of(M, tile.tm) * tiles_of(N, tile.tn), kUnits) * (tile.tm * tile.tn + 8192);
-        if (&tile == kTiles || takes < least) {
-            best = &tile;
-            least = takes;
-        }
-    }
-    best->go(a, b, b_deep != 0, M, N, K, out, sa, sb, s);
+    const int64_t tm = tiles_of(M, kTileM);
+    if (tm * tiles_of(N, 64) <= kUnits) launch_tiles<64, 2>(a, b, b_deep != 0, M, N, K, out, s);
+    else if (tm * tiles_of(N, 96) <= kUnits) launch_tiles<96, 2>(a, b, b_deep != 0, M, N, K, out, s);
+    else if (tm * tiles_of(N, 128) <= kUnits) launch_tiles<128, 2>(a, b, b_deep != 0, M, N, K, out, s);
+    else launch_tiles<96, 1>(a, b, b_deep != 0, M, N, K, out, s);
     return launch_status();
 }
