@@ -7,8 +7,8 @@
 // themselves and then to what there was, so that a sum of K products is rounded K / 32 times at its own size: against 64 bits
 // 1.5e-7 at K = 768 and 1.8e-7 at 3072, where torch's fp32 product has 5.0e-7 and 9.9e-7 (with every instruction adding to
 // the whole sum 4.3e-7 and 6.2e-7, and 5 % less time).  Entries below 2^-100 or so keep fewer bits, since the smaller parts
-// leave bf16's range; infinities, NaN and entries too large for a part are multiplied by plain arithmetic at the end of the
-// tile they fall into.
+// leave bf16's range; infinities, NaN and entries too large for a part are multiplied by the fp32 matrix instructions at
+// the end of the tile they fall into.
 //
 // Bound by power and by how far splitting (vector instructions) and multiplying overlap: 4096 x 768 x 3072 takes 99 us,
 // 195 TFLOP/s of fp32 or 1.17 PFLOP/s of bf16 (an 8192^3 product in bf16 reaches 1.21 on the card); with operands of zeros a
@@ -194,17 +194,7 @@ product_kernel(const float *__restrict__ a, const float *__restrict__ b, int64_t
         for (int u = 0; u < AHEAD; ++u) step(ha[u], hb[u], s + u);
     }
     constexpr int OWN = FM / GROUPS;                        // rows of sixteen that a group finishes
-    const int64_t col0 = n0 + wn + (lane & 15), row0 = m0 + wm + group * OWN * 16 + (lane >> 4) * 4;
-    bool odd = false;
-    auto put = [&](int i, int j, f32x4 v) {
-        const int64_t col = col0 + j * 16;
-        const float r[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            odd |= !(__builtin_fabsf(r[q]) < 3.0e38f);
-            if (row0 + i * 16 + q < M && col < N) out[(row0 + i * 16 + q) * N + col] = r[q];
-        }
-    };
+    f32x4 sum[OWN][FN];
     if constexpr (GROUPS == 2) {
         if (group == 0) __syncthreads();
         // each group hands the other half of its sums over and finishes the rest
@@ -225,25 +215,83 @@ product_kernel(const float *__restrict__ a, const float *__restrict__ b, int64_t
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
                 const f32x4 low = acc[i][j], high = acc[OWN + i][j];
-                put(i, j, (group == 0 ? low : high) + take[(i * FN + j) * kWave + lane]);
+                sum[i][j] = (group == 0 ? low : high) + take[(i * FN + j) * kWave + lane];
             }
         }
     } else {
 #pragma unroll
         for (int i = 0; i < OWN; ++i) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j) put(i, j, acc[i][j]);
+            for (int j = 0; j < FN; ++j) sum[i][j] = acc[i][j];
         }
     }
-    // An operand that is infinite, NaN or too large for a part, or a sum that overflows: plain arithmetic decides what
-    // comes out.
+    const int64_t first_row = m0 + wm + group * OWN * 16, first_col = n0 + wn;
+    // An operand that is infinite, NaN or too large for a part, or a sum that overflows: what comes out there is what the fp32
+    // matrix instructions make of the operands, for which the wave computes its share of the tile again (4096 x 3072 x 768 with
+    // all entries of a NaN 290 us in all; by a loop over the depth for each output, one after the other, 17000).
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) odd |= !(__builtin_fabsf(sum[i][j][q]) < __builtin_inff());
+        }
+    }
     if (__builtin_amdgcn_ballot_w64(odd) != 0u) {
-        for (int i = 0; i < OWN * FN * 4; ++i) {
-            const int64_t row = row0 + i / (FN * 4) * 16 + i % 4, col = col0 + i / 4 % FN * 16;
-            if (row >= M || col >= N || __builtin_fabsf(out[row * N + col]) < 3.0e38f) continue;
-            float sum = 0.0f;
-            for (int64_t k = 0; k < K; ++k) sum += a[row * K + k] * (DEEP_B ? b[col * K + k] : b[k * N + col]);
-            out[row * N + col] = sum;
+        const int64_t deep = (lane >> 4) * 4;               // lane l holds depths k + 4 (l / 16) + q of both in the q-th of four instructions
+        const float *pa[OWN], *pb[FN];
+        f32x4 plain[OWN][FN];
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) pa[i] = a + min(first_row + i * 16 + (lane & 15), M - 1) * K + deep;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const int64_t col = min(first_col + j * 16 + (lane & 15), N - 1);
+            pb[j] = DEEP_B ? b + col * K + deep : b + deep * N + col;
+#pragma unroll
+            for (int i = 0; i < OWN; ++i) plain[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        for (int64_t k = 0; k < K; k += 16) {
+            f32x4 fa[OWN], fb[FN];
+#pragma unroll
+            for (int i = 0; i < OWN; ++i) fa[i] = *reinterpret_cast<const f32x4 *>(pa[i] + k);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if constexpr (DEEP_B) {
+                    fb[j] = *reinterpret_cast<const f32x4 *>(pb[j] + k);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) fb[j][q] = pb[j][(k + q) * N];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int i = 0; i < OWN; ++i) {
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) plain[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], plain[i][j], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sum[i][j][q] = __builtin_fabsf(sum[i][j][q]) < __builtin_inff() ? sum[i][j][q] : plain[i][j][q];
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const int64_t col = first_col + j * 16 + (lane & 15);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t row = first_row + i * 16 + (lane >> 4) * 4 + q;
+                if (row < M && col < N) out[row * N + col] = sum[i][j][q];
+            }
         }
     }
 }

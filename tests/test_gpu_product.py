@@ -118,6 +118,40 @@ def test_not_finite(M, N, K, deep):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("deep", [True, False])
+@pytest.mark.parametrize("M,N,K", [(150, 100, 96), (4100, 1000, 64), (2100, 3000, 32)])
+def test_nothing_finite(M, N, K, deep):
+    """Whole operands of NaN, and of infinities and finite numbers in turn, come out element by element as fp32 sums do."""
+    require_gpu()
+    a, b = _operands(M, N, K, deep, 11)
+    assert bool(torch.isnan(_product(torch.full_like(a, float("nan")), b, deep)).all())
+    a[::2] = float("inf")
+    got, ref = _product(a, b.abs() + 0.5, deep).cpu(), a.cpu() @ (b.cpu().t() if deep else b.cpu()).abs().add(0.5)
+    assert bool((got[::2] == float("inf")).all()) and bool(torch.isfinite(got[1::2]).all())
+    assert float((got[1::2] - ref[1::2]).abs().max()) <= 2 * (K + 1) * 2.0 ** -24 * 36 * K
+
+
+@pytest.mark.gpu
+def test_what_is_not_finite_takes_little_longer():
+    """A step that has diverged (every entry NaN) takes two to three times an ordinary one's time, not the 130 of an output at a time."""
+    require_gpu()
+    a, b = _operands(4096, 768, 768, True, 12)
+    out = torch.empty(4096, 768, device="cuda")
+
+    def took(x):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        sf.product(x, b, True, out)
+        start.record()
+        for _ in range(10):
+            sf.product(x, b, True, out)
+        end.record()
+        torch.cuda.synchronize()
+        return start.elapsed_time(end)
+
+    assert took(torch.full_like(a, float("nan"))) < 20 * took(a)
+
+
+@pytest.mark.gpu
 def test_refused_and_empty():
     require_gpu()
     t = lambda *s: torch.zeros(*s, device="cuda")                      # noqa: E731
