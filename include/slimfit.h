@@ -533,8 +533,8 @@ int32_t slimfit_merge_heads(const void *q, const void *kt, const void *v, int32_
  *  workspace : none is needed (slimfit_product_workspace reports 0 bytes); what is passed is not looked at.
  *  Each operand is split exactly into three bf16 numbers and six of the nine partial products are added up in fp32 (the
  *  other three are at most 2^-24 of theirs), no further from the exact product than fp32 additions in any order:
- *      |out - exact| <= (K + 1) * 2^-24 * sum |a||b|
- *  for entries of magnitude above 2^-100.  Infinities and NaN come out as in plain fp32 arithmetic.  Deterministic.
+ *      |out - exact| <= (K + 1) * 2^-24 * sum |a||b| + 2^-149,
+ *  whatever the sizes of the entries.  Infinities and NaN come out as in plain fp32 arithmetic.  Deterministic.
  * ---------------------------------------------------------------------- */
 int32_t slimfit_product_workspace(int64_t M, int64_t N, int64_t K, size_t *bytes);
 

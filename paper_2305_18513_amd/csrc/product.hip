@@ -6,9 +6,10 @@
 // from h h down to h l and m m; the other three are at most 2^-24 of the product.  A step's 32 elements are added up by
 // themselves and then to what there was, so that a sum of K products is rounded K / 32 times at its own size: against 64 bits
 // 1.5e-7 at K = 768 and 1.8e-7 at 3072, where torch's fp32 product has 5.0e-7 and 9.9e-7 (with every instruction adding to
-// the whole sum 4.3e-7 and 6.2e-7, and 5 % less time).  Entries below 2^-100 or so keep fewer bits, since the smaller parts
-// leave bf16's range; infinities, NaN and entries too large for a part are multiplied by the fp32 matrix instructions at
-// the end of the tile they fall into.
+// the whole sum 4.3e-7 and 6.2e-7, and 5 % less time).  Entries are split at 2^24 times their size, where
+// the last bit of the smallest subnormal still has a normal bf16 number to go to (2 % of the time, in two multiplications more a
+// pair).  Infinities, NaN, and entries and results too large for that (2^104, 2^80), are left to the fp32 matrix instructions
+// at the end of the tile they fall into.
 //
 // Bound by power and by how far splitting (vector instructions) and multiplying overlap: 4096 x 768 x 3072 takes 99 us,
 // 195 TFLOP/s of fp32 or 1.17 PFLOP/s of bf16 (an 8192^3 product in bf16 reaches 1.21 on the card); with operands of zeros a
@@ -28,8 +29,11 @@ constexpr int kTileM = 128;
 struct Parts {
     u32x4 h, m, l;                         // eight bf16 each
 };
+constexpr float kUp = 0x1p24f, kBack = 0x1p-48f;            // of an operand and of a product of two
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
 {
+    a *= kUp;
+    b *= kUp;
     h = bf16_narrow2(a, b);
     a -= __builtin_bit_cast(float, h << 16);
     b -= __builtin_bit_cast(float, h & 0xFFFF0000u);
@@ -215,14 +219,14 @@ product_kernel(const float *__restrict__ a, const float *__restrict__ b, int64_t
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
                 const f32x4 low = acc[i][j], high = acc[OWN + i][j];
-                sum[i][j] = (group == 0 ? low : high) + take[(i * FN + j) * kWave + lane];
+                sum[i][j] = ((group == 0 ? low : high) + take[(i * FN + j) * kWave + lane]) * kBack;
             }
         }
     } else {
 #pragma unroll
         for (int i = 0; i < OWN; ++i) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j) sum[i][j] = acc[i][j];
+            for (int j = 0; j < FN; ++j) sum[i][j] = acc[i][j] * kBack;
         }
     }
     const int64_t first_row = m0 + wm + group * OWN * 16, first_col = n0 + wn;

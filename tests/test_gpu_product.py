@@ -78,6 +78,22 @@ def test_rows_of_unlike_size(deep):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("deep", [True, False])
+def test_the_whole_range_of_fp32(deep):
+    """Subnormal rows against columns near the largest numbers, the reverse, and both small: no bits are lost on the way."""
+    require_gpu()
+    a, b = _operands(200, 100, 96, deep, 7)
+    rows = b if deep else b.t()
+    for up, down in ((2.0 ** -142, 2.0 ** 124), (2.0 ** -110, 2.0 ** 60), (2.0 ** -120, 1.0), (2.0 ** -60, 2.0 ** -70), (2.0 ** 110, 2.0 ** -100),
+                     (2.0 ** 60, 2.0 ** 40)):
+        x, y = (a.double() * up).float(), (rows.double() * down).float()
+        y = y.contiguous() if deep else y.t().contiguous()
+        yt = (y.t() if deep else y).double()
+        off = (_product(x, y, deep).double() - x.double() @ yt).abs()
+        assert bool((off <= 97 * 2.0 ** -24 * (x.double().abs() @ yt.abs()) + 2.0 ** -149).all()), (up, down)
+
+
+@pytest.mark.gpu
 def test_scales_and_zeros():
     require_gpu()
     for scale in (1e-12, 1e-6, 1e10, 1e25):
