@@ -288,6 +288,9 @@ def _watched() -> bool:
             or forward_ad._current_level >= 0 or torch._C._len_torch_dispatch_stack() > 0 or torch._C._len_torch_function_stack() > 0)
 
 
+_MOST_TILES = (1 << 31) // 512                             # of 128 x 64 that a launch of the library's product can have
+
+
 def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
     """x @ weight.T or x @ weight over x's last dimension by the library's fp32 product, or None where that is torch's.
 
@@ -303,8 +306,9 @@ def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
     if depth != K or K == 0 or K % 32 != 0:
         return None
     M = x.numel() // K
-    few = -(-M // 128) * -(-N // 64) < 192
-    if (few and K > 768) or _watched() or not (_plain(x) and _plain(weight)):
+    tiles = -(-M // 128) * -(-N // 64)
+    few = tiles < 192
+    if (few and K > 768) or tiles > _MOST_TILES or _watched() or not (_plain(x) and _plain(weight)):
         return None
     if few and torch.cuda.is_current_stream_capturing():
         return None

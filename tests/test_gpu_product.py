@@ -328,6 +328,24 @@ def test_arguments():
     assert call(16, 16, 1 << 40, 1 << 40, 1 << 20, 16) == call(16, 16, 1 << 30, 1 << 20, 32, 16) == sf.ERR_UNSUPPORTED
 
 
+def test_rows_that_the_library_refuses_are_torchs(monkeypatch):
+    """A linear layer's rows are as many as torch takes: past the library's limit they never reach it."""
+    asked = []
+    monkeypatch.setattr(sf, "product", lambda a, b, deep, out: asked.append((a.shape[0], b.shape[0 if deep else 1])))
+    monkeypatch.setattr(ag, "_plain", lambda t: True)
+    monkeypatch.setattr(torch.Tensor, "get_device", lambda t: 0)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+    with torch.no_grad():
+        for rows, columns in ((1 << 20, 64), (34_000_000, 32), (1 << 29, 64), ((1 << 29) + 1, 64), (1 << 29, 65), (1 << 33, 64)):
+            x, w = torch.empty(rows, 32, device="meta"), torch.empty(columns, 32, device="meta")
+            ag._dense(x, w, True)
+            ag._dense(x, w.t(), False)
+    assert asked == [(1 << 20, 64)] * 2 + [(34_000_000, 32)] * 2 + [(1 << 29, 64)] * 2
+    for M, N in asked:
+        assert sf.product_workspace(M, N, 32) == 0                     # it takes them
+
+
 def test_linear_layers_on_the_cpu_are_torchs():
     x, w = torch.randn(4096, 96, requires_grad=True), torch.randn(800, 96)
     y = ag.LinearFunction.apply(x, w, None)
