@@ -291,14 +291,23 @@ def _watched() -> bool:
 _MOST_TILES = (1 << 31) // 512                             # of 128 x 64 that a launch of the library's product can have
 
 
-def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
-    """x @ weight.T or x @ weight over x's last dimension by the library's fp32 product, or None where that is torch's.
+def _quicker(M: int, N: int, K: int, transposed: bool) -> bool:
+    """Whether the library's product takes the shorter time on the GPU (rows x columns x depth, torch's and this in us).
 
-    It is the faster one where the product has at least 192 tiles of 128 x 64, three for four compute units (rows x columns x
-    depth, torch's and this in us: 4096 x 768 x 3072 140 and 95, 2048 x 768 x 3072 76 and 65, 192 tiles; 2048 x 512 x 2048 34
-    and 44, 1024 x 1024 x 4096 63 and 85, 128 tiles each, which torch splits along their depth).  Smaller ones are shorter than the host takes to ask for them, 18 us torch's and 8 this: up to a depth of
-    768 this one is through in that time (256 x 256 x 256 11 us on the GPU, 1024 x 768 x 768 23, torch's 6 and 14), deeper ones
-    are not (1024 x 768 x 3072 57 and 42), and a graph that is captured has no host to wait for."""
+    It does from about 170 tiles of 128 x 64 on, two for three compute units (1792 x 768 x 768 25.2 and 22.0, 3600 x 384 x 384 19.5 and
+    13.4, 4096 x 768 x 3072 140 and 102); fewer torch splits along their depth (2048 x 512 x 2048 35 and 50, 1024 x 768 x 768 14 and
+    22, 257 x 256 x 256 5.5 and 9.5).  Weights that lie K x N and are deep need 208 (1500 x 960 x 3072 78 and 81, 3300 x 512 x 2048
+    57.1 and 56.0), and a quarter of the tiles at most may be padding (260 x 6144 x 1024 32 and 35, 400 x 6000 x 1024 55 and 42).
+    And where torch does not split: up to 256 x 256 and a depth below 1024, but for the very smallest (256 x 256 x 256 63 and 9.5,
+    128 x 128 x 768 88 and 21, 64 x 192 x 64 7.1 and 5.9, 64 x 128 x 64 5.5 and 5.9; of depth 1024 8 and 26)."""
+    outputs, tiles = M * N, -(-M // 128) * -(-N // 64)
+    if M <= 256 and N <= 256 and 64 <= K < 1024:
+        return outputs >= 64 * 192
+    return outputs >= (168 if transposed or K <= 1536 else 208) * 128 * 64 and 4 * outputs >= 3 * 128 * 64 * tiles and tiles <= _MOST_TILES
+
+
+def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
+    """x @ weight.T or x @ weight over x's last dimension by the library's fp32 product, or None where that is torch's."""
     if x.dtype != torch.float32 or weight.dtype != torch.float32 or x.dim() < 2 or weight.dim() != 2:
         return None
     K = x.shape[-1]
@@ -306,11 +315,7 @@ def _dense(x: torch.Tensor, weight: torch.Tensor, transposed: bool):
     if depth != K or K == 0 or K % 32 != 0:
         return None
     M = x.numel() // K
-    tiles = -(-M // 128) * -(-N // 64)
-    few = tiles < 192
-    if (few and K > 768) or tiles > _MOST_TILES or _watched() or not (_plain(x) and _plain(weight)):
-        return None
-    if few and torch.cuda.is_current_stream_capturing():
+    if not _quicker(M, N, K, transposed) or _watched() or not (_plain(x) and _plain(weight)):
         return None
     if not (x.get_device() == weight.get_device() == torch.cuda.current_device()):
         return None                                        # the library launches on the current device

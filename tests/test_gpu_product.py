@@ -203,7 +203,7 @@ def test_linear_layers(monkeypatch):
     assert seen == [True, False]
     for got, want in ((y, x.double() @ w.double().t()), (dx, dy.double() @ w.double())):
         assert bool((got.double() - want).norm() <= 0.5 * 768 ** 0.5 * 2.0 ** -24 * want.norm())
-    # a gradient that is to be differentiated again, strides, other types, other devices, few and deep rows, a bias
+    # a gradient that is to be differentiated again, strides, other types, other devices, few rows, a bias
     seen.clear()
     y = ag.LinearFunction.apply(x, w, None)
     (dx,) = torch.autograd.grad(y, x, dy.requires_grad_(True), create_graph=True)
@@ -222,29 +222,31 @@ def test_linear_layers(monkeypatch):
 
 
 @pytest.mark.gpu
-def test_small_products_are_the_librarys_where_the_host_waits(monkeypatch):
-    """Up to a depth of 768 outside a capture; the captured ones are torch's."""
+def test_captured_linear_layers_are_the_eager_ones(monkeypatch):
+    """Which product a layer takes goes by its sizes alone: a captured step has the bits of an eager one, small or large."""
     require_gpu()
     seen = _calls(monkeypatch)
     g = torch.Generator(device="cuda").manual_seed(1)
-    x, w = (torch.randn(n, 768, generator=g, device="cuda") for n in (70, 50))
-    with torch.no_grad():
-        y = ag.LinearFunction.apply(x, w, None)
-        want = x.double() @ w.double().t()
-        assert seen == [True] and bool((y.double() - want).norm() <= 0.5 * 768 ** 0.5 * 2.0 ** -24 * want.norm())
-        s = torch.cuda.Stream()
-        with torch.cuda.stream(s):
-            torch.nn.functional.linear(x, w)                           # torch's own first call is not captured
-        torch.cuda.synchronize()
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
-            y = ag.LinearFunction.apply(x, w, None)
-        assert seen == [True]
-        for _ in range(3):
-            y.zero_()
-            graph.replay()
+    for rows, columns, library in ((70, 50, False), (200, 130, True), (1024, 768, False), (1800, 768, True)):
+        x, w = (torch.randn(n, 768, generator=g, device="cuda") for n in (rows, columns))
+        seen.clear()
+        with torch.no_grad():
+            want = ag.LinearFunction.apply(x, w, None)
+            off = (want.double() - x.double() @ w.double().t()).norm() / want.double().norm()
+            assert seen == [True] * library and float(off) <= 0.5 * 768 ** 0.5 * 2.0 ** -24
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                ag.LinearFunction.apply(x, w, None)                    # torch's own first call is not captured
             torch.cuda.synchronize()
-            assert bool((y.double() - want).norm() <= 1e-5 * want.norm())
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                y = ag.LinearFunction.apply(x, w, None)
+            assert seen == [True] * 3 * library
+            for _ in range(3):
+                y.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(y, want)
 
 
 @pytest.mark.gpu
@@ -328,6 +330,17 @@ def test_arguments():
     assert call(16, 16, 1 << 40, 1 << 40, 1 << 20, 16) == call(16, 16, 1 << 30, 1 << 20, 32, 16) == sf.ERR_UNSUPPORTED
 
 
+def test_which_products_are_the_librarys():
+    """By sizes alone: few tiles, padding, and depths of weights that lie K x N."""
+    for M, N, K, transposed, want in ((1792, 768, 768, True, True), (1791, 768, 768, True, False),
+                                      (1024, 768, 768, True, False), (1792, 768, 1536, False, True), (1792, 768, 1568, False, False),
+                                      (1792, 768, 1568, True, True), (2219, 768, 3072, False, True), (260, 6144, 1024, True, False),
+                                      (400, 6000, 1024, True, True), (130, 12288, 768, False, False), (4096, 768, 3072, False, True),
+                                      (256, 256, 256, True, True), (257, 256, 256, True, False), (256, 256, 1024, True, False),
+                                      (192, 64, 64, False, True), (191, 64, 64, False, False), (192, 64, 32, False, False)):
+        assert ag._quicker(M, N, K, transposed) == want, (M, N, K, transposed)
+
+
 def test_rows_that_the_library_refuses_are_torchs(monkeypatch):
     """A linear layer's rows are as many as torch takes: past the library's limit they never reach it."""
     asked = []
@@ -337,11 +350,11 @@ def test_rows_that_the_library_refuses_are_torchs(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
     with torch.no_grad():
-        for rows, columns in ((1 << 20, 64), (34_000_000, 32), (1 << 29, 64), ((1 << 29) + 1, 64), (1 << 29, 65), (1 << 33, 64)):
+        for rows, columns in ((1 << 20, 64), (34_000_000, 64), (1 << 29, 64), ((1 << 29) + 1, 64), (1 << 29, 128), (1 << 33, 64)):
             x, w = torch.empty(rows, 32, device="meta"), torch.empty(columns, 32, device="meta")
             ag._dense(x, w, True)
             ag._dense(x, w.t(), False)
-    assert asked == [(1 << 20, 64)] * 2 + [(34_000_000, 32)] * 2 + [(1 << 29, 64)] * 2
+    assert asked == [(1 << 20, 64)] * 2 + [(34_000_000, 64)] * 2 + [(1 << 29, 64)] * 2
     for M, N in asked:
         assert sf.product_workspace(M, N, 32) == 0                     # it takes them
 
