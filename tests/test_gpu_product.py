@@ -330,6 +330,20 @@ def test_arguments():
     assert call(16, 16, 1 << 40, 1 << 40, 1 << 20, 16) == call(16, 16, 1 << 30, 1 << 20, 32, 16) == sf.ERR_UNSUPPORTED
 
 
+def test_a_precision_that_the_program_chose_is_torchs():
+    """set_float32_matmul_precision and its kin say what becomes of these layers' products, as of any other."""
+    assert torch.get_float32_matmul_precision() == "highest"
+    with torch.no_grad():
+        assert not ag._watched()
+        try:
+            for precision in ("high", "medium"):
+                torch.set_float32_matmul_precision(precision)
+                assert ag._watched()
+        finally:
+            torch.set_float32_matmul_precision("highest")
+        assert not ag._watched()
+
+
 def test_which_products_are_the_librarys():
     """By sizes alone: few tiles, padding, and depths of weights that lie K x N."""
     for M, N, K, transposed, want in ((1792, 768, 768, True, True), (1791, 768, 768, True, False),
