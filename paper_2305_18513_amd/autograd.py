@@ -279,7 +279,7 @@ class SplitHeadsFunction(torch.autograd.Function):
 def _plain(t: torch.Tensor) -> bool:
     """Whether a kernel may be handed the tensor's memory as it is."""
     return (type(t) in (torch.Tensor, torch.nn.Parameter) and torch._C._has_storage(t) and t.is_cuda
-            and t.is_contiguous() and not t.is_neg() and t.data_ptr() % 16 == 0)
+            and t.is_contiguous() and not t.is_neg() and not t._is_zerotensor() and t.data_ptr() % 16 == 0)
 
 
 def _watched() -> bool:

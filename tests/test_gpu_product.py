@@ -270,8 +270,11 @@ def test_products_that_are_watched_are_torchs(monkeypatch):
     with FlopCounterMode(display=False) as counter:
         torch.autograd.grad(y, x, dy, retain_graph=True)
     assert counter.get_total_flops() == 2 * 4096 * 768 * 512
-    (dx,) = torch.autograd.grad(y, x, torch._neg_view(dy))
+    (dx,) = torch.autograd.grad(y, x, torch._neg_view(dy), retain_graph=True)
     torch.testing.assert_close(dx, -(dy @ w))
+    # a gradient of zeros that autograd holds without memory
+    (dx,) = torch.autograd.grad(y, x, torch._efficientzerotensor(4096, 768, device="cuda"))
+    assert dx.shape == x.shape and not dx.any()
     assert seen == [True]
 
 
