@@ -13,9 +13,10 @@
 //             bf16.  A key's top 12 bits name its bin (1/16 of a binade by
 //             magnitude, 1/8 by value).
 //   sample    16 workgroups histogram the bins of up to 1024 vectors each, drawn one
-//             from each equal stretch of the tensor in turn, and each fixes a bracket
-//             of its own, the bin of its sample's entry of T's rank; the sweep joins
-//             the 16.  Nothing depends on the sample being right: the sweep's counts
+//             from each equal stretch of the tensor; of 16 neighbouring stretches each
+//             workgroup takes one, in an order that is shuffled from sixteen to sixteen.
+//             Each fixes a bracket of its own, the bin of its sample's entry of T's
+//             rank; the sweep joins the 16.  Nothing depends on the sample being right: the sweep's counts
 //             show whether T lies inside the joint bracket.
 //   sweep     one pass over the tensor, a workgroup per tile of 4096 elements:
 //             the candidates (keys not below the bracket) are collected in index
@@ -399,11 +400,21 @@ __device__ __forceinline__ Edges find_edges(const uint32_t *hist, uint32_t rank_
     return Edges{(uint16_t)edge[0], (uint16_t)edge[2], edge[3] - edge[1]};
 }
 
+__device__ __forceinline__ uint32_t mix(uint32_t i)
+{
+    uint32_t h = i * 0x9E3779B1u;
+    h ^= h >> 15;
+    h *= 0x85EBCA77u;
+    return h ^ (h >> 13);
+}
+
 // One vector of each of `total` equal stretches of the tensor (all vectors when there are no more than that), for
-// stretch i at a place in it that depends on i only.  step: length of a stretch times 2^16.  The workgroups take the
-// stretches in turn, so that each of them sees the whole tensor.  Bound by latency (16 workgroups; one vector, its row's
-// statistics, the histogram, the scan): a launch of one workgroup that added up the histograms and chose one bracket took
-// 5 us after it.
+// stretch i at a place in it that depends on i only.  step: length of a stretch times 2^16.  Of each 16 stretches a
+// workgroup takes one, which one being as good as random, so that columns of unlike scale come to all workgroups alike.
+// Taken in turn, a workgroup saw the same columns of every row where a row is a multiple of 16 stretches, and the brackets
+// lay apart: 512 x 128 with scales over a factor of e either way had 18 % of the tensor in the joint one, now 3 (without such columns 3
+// either way).  Bound by latency (16 workgroups; one vector, its row's statistics, the histogram, the scan): a launch of one
+// workgroup that added up the histograms and chose one bracket took 5 us after it.
 template <typename T, bool MAG, bool STD>
 __global__ void __launch_bounds__(kWideThreads)
 sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, uint32_t rank_hi, uint32_t rank_lo, Edges *__restrict__ edges,
@@ -411,13 +422,10 @@ sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, uint32_t r
 {
     constexpr int EPV = Elem<T>::EPV;
     __shared__ alignas(16) uint32_t bins[kTopBins];
-    const uint32_t mine = threadIdx.x * gridDim.x + blockIdx.x, i = min(mine, total - 1u);
+    static_assert((kSampleWgs & (kSampleWgs - 1)) == 0, "gridDim.x, kSampleWgs or 1, is a power of two");
+    const uint32_t mine = threadIdx.x * gridDim.x + ((blockIdx.x + (mix(threadIdx.x) >> 28)) & (gridDim.x - 1u)), i = min(mine, total - 1u);
     const uint64_t v0 = (i * step) >> 16, v1 = ((i + 1) * step) >> 16;
-    uint32_t h = i * 0x9E3779B1u;
-    h ^= h >> 15;
-    h *= 0x85EBCA77u;
-    h ^= h >> 13;
-    const int64_t at = (int64_t)v0 + __umulhi(h, (uint32_t)(v1 - v0));
+    const int64_t at = (int64_t)v0 + __umulhi(mix(i), (uint32_t)(v1 - v0));
     uint32_t bits[EPV];
     load_tile_vec<T, true>(x, 0, 0, at, bits);
     for (int b = threadIdx.x; b < kTopBins; b += kWideThreads) bins[b] = 0u;
@@ -1500,7 +1508,7 @@ Workspace carve_room(void *base, int64_t n, size_t room)            // room >= l
 
 // Which ranks of a workgroup's sample bound its bracket: those next to T's own, f = k / n of the sample.  The 16 samples are
 // as good as independent of one another, and T is as likely above a workgroup's bracket as below it: it is missed on one
-// side of all 16 once in 2^15 tensors, whatever their distribution (and hardly ever where the workgroups see every vector:
+// side of all 16 once in 2^15 tensors, as long as neighbouring stretches are as good as exchangeable (and hardly ever where the workgroups see every vector:
 // 16 counts cannot all lie on one side of their mean).  The joint bracket spans 3.5 standard deviations sqrt(size f (1 - f)) of
 // a workgroup's rank, 1.7 % of the tensor at f = 0.1, and the rest of its outer bins.  (One bracket of six deviations either
 // way from the sum of the 16 histograms, 1.4 %, took a launch of one workgroup more: 4096 x 768 37.3 us in all and 33.7

@@ -273,6 +273,20 @@ def test_sample_that_misses_the_cut(dtype, scale):
             assert int(ws.t[24:28].view(torch.int32)) == 1, (k, by_mag)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("spread", [0.3, 1.0])
+@pytest.mark.parametrize("rows,H", [(256, 128), (512, 128), (512, 256), (1024, 512), (2048, 256), (128, 1024), (4096, 768)])
+def test_columns_of_unlike_scale(rows, H, spread, dtype):
+    """Rows that are whole multiples of 16, or 2 to 8, of the sample's stretches, with columns of log-normal scales: the
+    workgroups' brackets lie together, and no list overflows (word 6 of the workspace: the plain route)."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(rows + H)
+    x = torch.randn(rows, H, generator=g, device="cuda") * torch.exp(spread * torch.randn(H, generator=g, device="cuda"))
+    ws = Guarded(sf.prune_global_workspace(x.numel()), torch.uint8)
+    _run_both(x.view(-1).to(dtype), x.numel() // 10, True, restore=False, workspace=ws)
+    assert int(ws.t[24:28].view(torch.int32)) == 0
+
+
 def _least_workspace(n):
     tiles = (n + sf.GLOBAL_TILE - 1) // sf.GLOBAL_TILE
     return 16512 + 2 * ((8 * tiles + 127) // 128 * 128) + 1024 * (tiles + 1)
