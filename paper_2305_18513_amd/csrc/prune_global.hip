@@ -446,7 +446,10 @@ sample_kernel(const T *__restrict__ x, uint32_t total, uint64_t step, uint32_t r
 // (The histogram is cleared again.)
 __global__ void __launch_bounds__(kWideThreads) edges_kernel(uint32_t *hist, uint32_t k, Edges *__restrict__ edges, State *st)
 {
-    const Edges e = find_edges(hist, k, k);
+    Edges e = find_edges(hist, k, k);
+    // sixteen times this has to fit 32 bits below; a fourteenth of the largest tensor, from which on it is too much, is less
+    e.within = min(e.within, 0xFFFFFFFFu / kSampleWgs);
+    static_assert(0xFFFFFFFFu / kSampleWgs > 0x7FFFFFFFu / 14, "still too much");
     reinterpret_cast<u32x4 *>(hist)[threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
     if (threadIdx.x < kSampleWgs) edges[threadIdx.x] = e;
     if (threadIdx.x == 0) st->overflow = 0u;

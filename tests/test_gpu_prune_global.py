@@ -287,6 +287,19 @@ def test_columns_of_unlike_scale(rows, H, spread, dtype):
     assert int(ws.t[24:28].view(torch.int32)) == 0
 
 
+def test_a_bin_of_more_entries_than_a_sixteenth_of_32_bits():
+    """All of 2^28 entries share T's bin and the rank is too close to the top for a sample: the bracket is seen to be too much for
+    the lists (word 0 of the workspace), not only once they overflow (word 1)."""
+    require_gpu()
+    n, k = 1 << 28, 1000
+    x = torch.full((n,), 1.5, dtype=torch.bfloat16, device="cuda")
+    vals, idx = torch.empty(k, dtype=torch.bfloat16, device="cuda"), torch.empty(k, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(sf.prune_global_workspace(n), dtype=torch.uint8, device="cuda")
+    sf.prune_global(x, k, vals, idx, by_magnitude=True, workspace=ws)
+    assert ws[:8].view(torch.int32).tolist() == [1, 0]
+    assert torch.equal(idx, torch.arange(k, dtype=torch.int32, device="cuda")) and bool((vals == 1.5).all())
+
+
 def _least_workspace(n):
     tiles = (n + sf.GLOBAL_TILE - 1) // sf.GLOBAL_TILE
     return 16512 + 2 * ((8 * tiles + 127) // 128 * 128) + 1024 * (tiles + 1)
