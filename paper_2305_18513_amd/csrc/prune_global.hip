@@ -47,6 +47,7 @@
 // and made the sweeps 2-25x slower when it was tried), but a step that one
 // workgroup could do is done by every workgroup of the next launch for itself.
 #include "common.hpp"
+#include "key_order.hpp"
 
 #include <cmath>
 #include <type_traits>
@@ -122,34 +123,7 @@ template <> struct Elem<Bf16Row> {
 };
 
 // raw element bits -> key (larger key <=> earlier in the descending order)
-template <typename T, bool MAG> __device__ __forceinline__ uint32_t make_key(uint32_t bits);
-template <> __device__ __forceinline__ uint32_t make_key<float, true>(uint32_t b) { return b << 1; }
-template <> __device__ __forceinline__ uint32_t make_key<float, false>(uint32_t b)
-{
-    b = (b == 0x80000000u) ? 0u : b;                      // -0 orders as +0
-    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
-}
-template <> __device__ __forceinline__ uint32_t make_key<uint16_t, true>(uint32_t h) { return (h << 1) & 0xFFFFu; }
-template <> __device__ __forceinline__ uint32_t make_key<uint16_t, false>(uint32_t h)
-{
-    h = (h == 0x8000u) ? 0u : h;
-    return h ^ ((h & 0x8000u) ? 0xFFFFu : 0x8000u);
-}
-template <> __device__ __forceinline__ uint32_t make_key<Bf16Row, true>(uint32_t b) { return make_key<float, true>(b); }
-template <> __device__ __forceinline__ uint32_t make_key<Bf16Row, false>(uint32_t b) { return make_key<float, false>(b); }
-
-// The element whose key is `key`, as a number, and whether an element's key reaches it: one comparison of numbers in
-// place of making the key.  (NaN: only which of them are kept could differ, and that is the caller's.)
-template <typename T, bool MAG> __device__ __forceinline__ float edge_of(uint32_t key)
-{
-    if (Elem<T>::KEYBITS == 16) key <<= 16;
-    return __builtin_bit_cast(float, MAG ? key >> 1 : (key & 0x80000000u) ? key ^ 0x80000000u : ~key);
-}
-template <typename T, bool MAG> __device__ __forceinline__ bool reaches(uint32_t bits, float edge)
-{
-    const float f = __builtin_bit_cast(float, Elem<T>::KEYBITS == 16 ? bits << 16 : bits);
-    return !((MAG ? __builtin_fabsf(f) : f) < edge);
-}
+template <typename T, bool MAG> __device__ __forceinline__ uint32_t make_key(uint32_t bits) { return key_of<Elem<T>::KEYBITS, MAG>(bits); }
 
 __device__ __forceinline__ uint32_t raw_bits(const float *p) { return __builtin_bit_cast(uint32_t, *p); }
 __device__ __forceinline__ uint32_t raw_bits(const uint16_t *p) { return *p; }
@@ -459,14 +433,15 @@ __global__ void __launch_bounds__(kWideThreads) edges_kernel(uint32_t *hist, uin
 struct Bracket {
     uint32_t lo, last;                     // its smallest and largest key
     int range_bits, digit2;
-    bool plain;                            // too wide for the digits or too much for the lists
+    bool plain;                            // too wide for the digits, too much for the lists or among the NaN
 };
 __device__ __forceinline__ bool too_much(uint32_t bins, uint32_t within, uint64_t size, int list_slots)
 {
     // the lists: on average 1/14 of the tensor where they hold 1/10.7 of a tile
     return bins > (uint32_t)kMaxBracketBins || (uint64_t)within * (14 * kListSlots) > size * (uint32_t)list_slots;
 }
-__device__ __forceinline__ Bracket join_edges(u32x2 mine, int key_bits, uint64_t size, int list_slots)
+template <int KEYBITS, bool MAG>
+__device__ __forceinline__ Bracket join_edges(u32x2 mine, uint64_t size, int list_slots)
 {
     // a lane of each sixteen per pair of edges; by scalar loads and instructions, which a compute unit starts one at a time,
     // the sweep of 49152 x 1024 took 4 us longer
@@ -479,7 +454,7 @@ __device__ __forceinline__ Bracket join_edges(u32x2 mine, int key_bits, uint64_t
     sum += dpp_u32<kDppHalfMirror>(sum);
     sum += dpp_u32<kDppMirror>(sum);
     const uint32_t within = (uint32_t)__builtin_amdgcn_readfirstlane((int)sum);
-    const int shift = key_bits - kTop;
+    constexpr int shift = KEYBITS - kTop;
     const uint32_t nb = hi - lo + 1u;
     const int log_nb = nb > 1u ? 32 - __builtin_clz(nb - 1u) : 0;
     Bracket b;
@@ -489,7 +464,7 @@ __device__ __forceinline__ Bracket join_edges(u32x2 mine, int key_bits, uint64_t
     // the rest is at most 14 bits, 12 for the usual brackets of up to 16 bins: every workgroup of the count reads that
     // histogram whole (2^14 bins: 4096 x 768 in all 44.3 us, 2^12 40.9); more in this digit is more global atomics
     b.digit2 = min(b.range_bits, min(kTop, max(9, log_nb + 8)));
-    b.plain = too_much(nb, within, size, list_slots);
+    b.plain = too_much(nb, within, size, list_slots) || !reach_exists<KEYBITS, MAG>(b.lo);
     return b;
 }
 
@@ -542,7 +517,7 @@ sweep_tile(const T *__restrict__ x, int64_t n, u32x2 edges, uint64_t size, State
     uint32_t bits[G][EPV];
     int valid[G];
     load_round<T, STD, INSIDE, REC>(x, n, tile, wave, lane, bits, valid, sd);
-    const Bracket br = join_edges(edges, Elem<T>::KEYBITS, size, list_slots);
+    const Bracket br = join_edges<Elem<T>::KEYBITS, MAG>(edges, size, list_slots);
     if (blockIdx.x == 0 && threadIdx.x == 0) {             // for the launches that follow
         st->plain = br.plain ? 1u : 0u;
         st->lo = br.lo;
@@ -552,19 +527,29 @@ sweep_tile(const T *__restrict__ x, int64_t n, u32x2 edges, uint64_t size, State
     }
     if (br.plain) return;
     const uint32_t lo = br.lo, last = br.last;
-    const float edge = edge_of<T, MAG>(lo);
 
+    uint64_t cand[G][EPV];                                  // lane masks of the candidates
+    auto mark = [&](auto reach) {
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) cand[j][e] = __builtin_amdgcn_ballot_w64((INSIDE || e < valid[j]) && reach(bits[j][e]));
+        }
+    };
+    constexpr int BITS = Elem<T>::KEYBITS;
+    if (!MAG && reach_is_positive<BITS>(lo)) {              // uniform
+        mark([&](uint32_t b) { return reaches_positive<BITS>(b, lo); });
+    } else {
+        const Reach edge = reach_of<BITS, MAG>(lo);
+        mark([&](uint32_t b) { return reaches<BITS, MAG>(b, edge); });
+    }
     // candidates per group of 64 vectors: three 10-bit fields (at most 512 each) in one prefix sum
-    uint64_t cand[G][EPV];                                  // lane masks
     uint32_t packed[2] = {0u, 0u};
 #pragma unroll
     for (int j = 0; j < G; ++j) {
         uint32_t c = 0u;
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            cand[j][e] = __builtin_amdgcn_ballot_w64((INSIDE || e < valid[j]) && reaches<T, MAG>(bits[j][e], edge));
-            c += __builtin_amdgcn_inverse_ballot_w64(cand[j][e]) ? 1u : 0u;
-        }
+        for (int e = 0; e < EPV; ++e) c += __builtin_amdgcn_inverse_ballot_w64(cand[j][e]) ? 1u : 0u;
         packed[j / 3] += c << (10 * (j % 3));
     }
     uint32_t incl[2], total[2];
@@ -679,7 +664,7 @@ sweep_kernel(const T *__restrict__ x, int64_t n, const Edges *__restrict__ edges
     // The tile is asked for before the edges have arrived, unless one pair of them says that it may not be needed.
     const u32x2 one = reinterpret_cast<const u32x2 *>(edges)[blockIdx.x & (kSampleWgs - 1)];
     if (too_much((one.x & 0xFFFFu) - (one.x >> 16) + 1u, one.y * kSampleWgs, size, list_slots) && blockIdx.x != 0 &&
-        join_edges(mine, Elem<T>::KEYBITS, size, list_slots).plain)
+        join_edges<Elem<T>::KEYBITS, MAG>(mine, size, list_slots).plain)
         return;
     if (((int64_t)blockIdx.x + 1) * kTileElems <= n)        // workgroup-uniform: the whole tile lies below n
         sweep_tile<T, MAG, STD, true, REC>(x, n, mine, size, st, counters, tile_cnt, lists, list_slots, rec_val, rec_pos, sd, lds);

@@ -287,6 +287,42 @@ def test_columns_of_unlike_scale(rows, H, spread, dtype):
     assert int(ws.t[24:28].view(torch.int32)) == 0
 
 
+def _keys(x: torch.Tensor, by_magnitude):
+    """Larger key, earlier in the order; NaN above the infinities by magnitude, beyond the one of their sign by value."""
+    b = to_np(x.float()).view(np.uint32).astype(np.int64)
+    if by_magnitude:
+        return b & 0x7FFFFFFF
+    return np.where(b >> 31 == 1, -(b & 0x7FFFFFFF), b)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("by_mag", [True, False])
+@pytest.mark.parametrize("n,positive,negative", [(200003, 0.0, 0.02), (200003, 0.02, 0.02), (200003, 0.0, 0.3), (200003, 0.2, 0.2),
+                                                 (40 * 4096 + 77, 0.01, 0.005), (3000, 0.02, 0.1)])
+def test_nan_have_their_place(n, positive, negative, by_mag, dtype):
+    """NaN of either sign, fewer and more of them than are kept: every slot is written, by the order of the keys."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n, generator=g, device="cuda").to(dtype)
+    u = torch.rand(n, generator=g, device="cuda")
+    bits = x.view(torch.int32 if dtype == torch.float32 else torch.int16)
+    some = torch.randint(1, 100, (n,), generator=g, device="cuda").to(bits.dtype)
+    base, sign = (0x7FC00000, -(1 << 31)) if dtype == torch.float32 else (0x7FC0, -(1 << 15))
+    some = torch.where(some < 60, some, torch.zeros_like(some)) if dtype == torch.float32 else some % 60
+    bits[u < positive] = (some + base)[u < positive]
+    low = u > 1.0 - negative
+    bits[low] = ((some + base) | sign)[low]
+    k = n // 10
+    vals, idx = Guarded(k, dtype), Guarded(k, torch.int32)
+    sf.prune_global(x, k, vals.t, idx.t, by_magnitude=by_mag)
+    torch.cuda.synchronize()
+    vals.check(); idx.check()
+    want = np.sort(np.argsort(-_keys(x, by_mag), kind="stable")[:k])
+    np.testing.assert_array_equal(to_np(idx.t), want)
+    got, ref_bits = vals.t.view(bits.dtype).cpu().numpy(), bits.cpu().numpy()[want]
+    np.testing.assert_array_equal(got, ref_bits)
+
+
 def test_a_bin_of_more_entries_than_a_sixteenth_of_32_bits():
     """All of 2^28 entries share T's bin and the rank is too close to the top for a sample: the bracket is seen to be too much for
     the lists (word 0 of the workspace), not only once they overflow (word 1)."""
