@@ -200,6 +200,40 @@ def test_backward_with_nothing_kept_and_inconsistent_pointers():
         assert bool(torch.isfinite(dx.t).all())
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,H", [(6, 64), (6, 768), (6, 1024)])
+def test_infinities_in_the_gradient_reach_what_they_reach(rows, H, dtype):
+    """A dropped entry takes part in neither sum nor correction: an infinity in dy leaves infinities, and NaN only where two of them
+    meet (fp32 arithmetic over the kept entries alone)."""
+    require_gpu()
+    x, gamma, beta, dy = _inputs(rows + H, rows, H)
+    x, dy = x.to(dtype), dy.to(dtype)
+    mean, rstd = _forward_both(x, gamma, beta)
+    k = rows * H // 10
+    vals, idx, ptr = _prune_both(x, mean, rstd, k)
+    xt = np.zeros(rows * H, np.float32)
+    kept = np.zeros(rows * H, bool)
+    xt[to_np(idx)], kept[to_np(idx)] = to_np(vals), True
+    xt, kept = xt.reshape(rows, H), kept.reshape(rows, H)
+    assert kept[:4].any(1).all()
+    dy[0, int(np.argmin(kept[0]))] = float("inf")                      # a dropped column
+    dy[1, int(np.argmax(kept[1]))] = -float("inf")                     # a kept one
+    dy[2, int(np.argmin(kept[2]))] = float("nan")
+    dy[3, int(np.argmin(kept[3]))], dy[3, int(np.argmax(kept[3]))] = float("inf"), float("inf")
+    dx = Guarded(rows * H, dtype)
+    sf.layernorm_backward_pruned(vals, idx, ptr, k, rstd, gamma, dy, dx.t.view(rows, H))
+    torch.cuda.synchronize()
+    dx.check()
+    got = _f32(dx.t).reshape(rows, H)
+    with np.errstate(invalid="ignore"):
+        g = to_np(gamma) * _f32(dy).reshape(rows, H) * (to_np(rstd)[:, None] / np.float32(H))
+        everywhere = np.float32(H) * g - g.sum(1, keepdims=True)
+        want = np.where(kept, everywhere - xt * np.where(kept, g * xt, np.float32(0)).sum(1, keepdims=True), everywhere)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_array_equal(np.where(np.isinf(got), np.sign(got), 0), np.where(np.isinf(want), np.sign(want), 0))
+    assert np.isinf(got[0]).sum() == H - 1 and np.isfinite(got[4:]).all()
+
+
 def test_argument_errors():
     require_gpu()
     x = torch.randn(8, 64, device="cuda")
