@@ -180,6 +180,21 @@ def test_prune_with_arbitrary_statistics_and_ties():
         _prune_both(x, mean, rstd, k)
 
 
+@pytest.mark.parametrize("rows,H,dtype", [(30000, 4, torch.float32), (11000, 12, torch.float32), (5000, 20, torch.float32), (30000, 8, torch.bfloat16),
+                                          (6000, 24, torch.bfloat16)])
+def test_rows_shorter_than_a_tile_s_records(rows, H, dtype):
+    """Row pointers found among a tile's survivors: rows with none, one and several of them, and whole stretches of rows without."""
+    require_gpu()
+    x, gamma, beta, dy = _inputs(rows, rows, H)
+    x, dy = x.to(dtype), dy.to(dtype)
+    mean, rstd = _forward_both(x, gamma, beta)
+    rstd[rows // 3:rows // 2] *= 1e-3                                  # rows that keep nothing, over several tiles
+    k = rows * H // 10
+    vals, idx, ptr = _prune_both(x, mean, rstd, k)
+    assert int((ptr[1:] - ptr[:-1]).max()) >= (2 if H > 4 else 1) and bool((ptr[rows // 3:rows // 2] == ptr[rows // 3]).all())
+    _backward_both(vals, idx, ptr, k, rstd, gamma, dy)
+
+
 def test_backward_with_nothing_kept_and_inconsistent_pointers():
     require_gpu()
     rows, H = 17, 256

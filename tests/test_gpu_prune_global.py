@@ -287,6 +287,27 @@ def test_columns_of_unlike_scale(rows, H, spread, dtype):
     assert int(ws.t[24:28].view(torch.int32)) == 0
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("at_vals,at_idx", [(0, 0), (1, 1), (2, 2), (3, 3), (0, 1), (3, 2), (2, 0), (1, 3)])
+def test_outputs_at_any_place_in_a_vector(at_vals, at_idx, dtype):
+    """Survivors leave as 16-byte vectors where both outputs lie alike: values and indices that begin at every element of one, the
+    same and another, with nothing written before or behind them."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(61)
+    for n, k in ((200003, 20000), (300001, 30001), (70 * 4096, 28001)):
+        x = torch.randn(n, generator=g, device="cuda").to(dtype)
+        want_vals, want_idx = torch.empty(k, dtype=dtype, device="cuda"), torch.empty(k, dtype=torch.int32, device="cuda")
+        sf.prune_global(x, k, want_vals, want_idx)
+        oi = ref.prune_global(to_np(x), k, by_magnitude=True)[1]
+        np.testing.assert_array_equal(to_np(want_idx), oi)
+        vals, idx = Guarded(at_vals + k, dtype), Guarded(at_idx + k, torch.int32)
+        sf.prune_global(x, k, vals.t[at_vals:], idx.t[at_idx:])
+        torch.cuda.synchronize()
+        vals.check(); idx.check()
+        assert bool((vals.raw[: at_vals * dtype.itemsize] == 0xAB).all()) and bool((idx.raw[: at_idx * 4] == 0xAB).all())
+        assert torch.equal(idx.t[at_idx:], want_idx) and torch.equal(vals.t[at_vals:], want_vals)
+
+
 def _keys(x: torch.Tensor, by_magnitude):
     """Larger key, earlier in the order; NaN above the infinities by magnitude, beyond the one of their sign by value."""
     b = to_np(x.float()).view(np.uint32).astype(np.int64)
