@@ -299,11 +299,15 @@ def _quicker(M: int, N: int, K: int, transposed: bool) -> bool:
     13.4, 4096 x 768 x 3072 140 and 102); fewer torch splits along their depth (2048 x 512 x 2048 35 and 50, 1024 x 768 x 768 14 and
     22, 257 x 256 x 256 5.5 and 9.5).  Weights that lie K x N and are deep need 208 (1500 x 960 x 3072 78 and 81, 3300 x 512 x 2048
     57.1 and 56.0), and a quarter of the tiles at most may be padding (260 x 6144 x 1024 32 and 35, 400 x 6000 x 1024 55 and 42).
+    Nor do tall ones of few columns and some depth, which go in tiles of 96 columns (40000 x 64 x 1024 54 and 69, 34000 x 128 x 1536 118 and
+    139; 22000 x 128 x 1024, whose tiles have 64, 70 and 45), or one step of depth (17000 x 128 x 32 6.7 and 8.7).
     And where torch does not split: up to 256 x 256 and a depth below 1024, but for the very smallest (256 x 256 x 256 63 and 9.5,
     128 x 128 x 768 88 and 21, 64 x 192 x 64 7.1 and 5.9, 64 x 128 x 64 5.5 and 5.9; of depth 1024 8 and 26)."""
     outputs, tiles = M * N, -(-M // 128) * -(-N // 64)
     if M <= 256 and N <= 256 and 64 <= K < 1024:
         return outputs >= 64 * 192
+    if K < 64 or (M > 256 * 128 and N <= 128 and K >= 512):
+        return False
     return outputs >= (168 if transposed or K <= 1536 else 208) * 128 * 64 and 4 * outputs >= 3 * 128 * 64 * tiles and tiles <= _MOST_TILES
 
 

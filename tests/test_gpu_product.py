@@ -348,13 +348,16 @@ def test_a_precision_that_the_program_chose_is_torchs():
 
 
 def test_which_products_are_the_librarys():
-    """By sizes alone: few tiles, padding, and depths of weights that lie K x N."""
+    """By sizes alone: few tiles, padding, depths of weights that lie K x N, tall products of few columns, single steps of depth."""
     for M, N, K, transposed, want in ((1792, 768, 768, True, True), (1791, 768, 768, True, False),
                                       (1024, 768, 768, True, False), (1792, 768, 1536, False, True), (1792, 768, 1568, False, False),
                                       (1792, 768, 1568, True, True), (2219, 768, 3072, False, True), (260, 6144, 1024, True, False),
                                       (400, 6000, 1024, True, True), (130, 12288, 768, False, False), (4096, 768, 3072, False, True),
                                       (256, 256, 256, True, True), (257, 256, 256, True, False), (256, 256, 1024, True, False),
-                                      (192, 64, 64, False, True), (191, 64, 64, False, False), (192, 64, 32, False, False)):
+                                      (192, 64, 64, False, True), (191, 64, 64, False, False), (192, 64, 32, False, False),
+                                      (32768, 128, 512, True, True), (32769, 128, 512, True, False), (40000, 64, 2048, False, False),
+                                      (32769, 128, 480, False, True), (32769, 129, 512, True, False), (32769, 192, 512, True, True),
+                                      (17000, 128, 32, True, False), (17000, 128, 64, True, True)):
         assert ag._quicker(M, N, K, transposed) == want, (M, N, K, transposed)
 
 
@@ -368,12 +371,12 @@ def test_rows_that_the_library_refuses_are_torchs(monkeypatch):
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
     with torch.no_grad():
         for rows, columns in ((1 << 20, 64), (34_000_000, 64), (1 << 29, 64), ((1 << 29) + 1, 64), (1 << 29, 128), (1 << 33, 64)):
-            x, w = torch.empty(rows, 32, device="meta"), torch.empty(columns, 32, device="meta")
+            x, w = torch.empty(rows, 64, device="meta"), torch.empty(columns, 64, device="meta")
             ag._dense(x, w, True)
             ag._dense(x, w.t(), False)
     assert asked == [(1 << 20, 64)] * 2 + [(34_000_000, 64)] * 2 + [(1 << 29, 64)] * 2
     for M, N in asked:
-        assert sf.product_workspace(M, N, 32) == 0                     # it takes them
+        assert sf.product_workspace(M, N, 64) == 0                     # it takes them
 
 
 def test_linear_layers_on_the_cpu_are_torchs():
