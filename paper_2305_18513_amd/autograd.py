@@ -285,8 +285,10 @@ def _plain(t: torch.Tensor) -> bool:
 def _watched() -> bool:
     """Whether more than the value is asked for, or less: a product to be differentiated (either way), cast, traced or
     intercepted, or one for which the program allows torch fewer than 32 bits."""
-    return (torch.backends.cuda.matmul.fp32_precision not in ("none", "ieee") or torch.is_grad_enabled() or torch.is_autocast_enabled() or torch.compiler.is_compiling() or torch.jit.is_tracing()
-            or forward_ad._current_level >= 0 or torch._C._len_torch_dispatch_stack() > 0 or torch._C._len_torch_function_stack() > 0)
+    return (torch.is_grad_enabled() or torch.is_autocast_enabled() or torch.compiler.is_compiling() or torch.jit.is_tracing()
+            or forward_ad._current_level >= 0 or torch._C._len_torch_dispatch_stack() > 0 or torch._C._len_torch_function_stack() > 0
+            # torch.backends.cuda.matmul.fp32_precision, which takes 2.1 us to read, this 0.6
+            or torch._C._get_fp32_precision_getter("cuda", "matmul") not in ("none", "ieee"))
 
 
 _MOST_TILES = (1 << 31) // 512                             # of 128 x 64 that a launch of the library's product can have
