@@ -4,7 +4,7 @@ Each Function runs its forward through the library, keeps only the compressed
 form of the activation its backward needs, and skips the weight gradient of a
 frozen layer.  Nothing here computes on its own what a kernel of the library
 computes; the dense matrix products of the linear layers are the library's for
-large fp32 operands and torch's otherwise.
+fp32 operands of sizes at which it is the quicker one, and torch's otherwise.
 
   GeluFunction       y = GELU(x); caches x in `bits` bits (per-block scales);
                      backward multiplies by GELU'(x^) straight from the cache.
@@ -335,7 +335,9 @@ class LinearFunction(torch.autograd.Function):
     """y = x W^T (+ b) under the freezing rule of Alg. 4.  Whether the layer is frozen is read off the weight itself
     (``weight.requires_grad``, which is what an inter-layer scheduler flips between iterations): a frozen layer
     keeps nothing of x and produces no weight gradient; an active one keeps x as ``bits``-bit block-scaled codes
-    and forms its weight gradient from the dequantised x^."""
+    and forms its weight gradient from the dequantised x^.  The library's fp32 product (sizes: ``_quicker``) holds all bits of
+    its operands and is no further from the exact one than fp32 additions in any order; where the program allows torch fewer
+    bits (``torch.set_float32_matmul_precision``) the products are torch's."""
 
     @staticmethod
     def forward(ctx, x: torch.Tensor, weight: torch.Tensor, bias, bits: int = 8, block: int = 64):

@@ -8,9 +8,9 @@ hipcc cross-compiles without a GPU.  The flags keep fp32 arithmetic IEEE
 gfx9) and switch packed-fp32 instruction selection off.  The first 16 dwords of a
 kernel's arguments arrive in scalar registers with the launch instead of being
 fetched by every wavefront: 0.1 to 0.5 us of each dependent launch
-(layernorm_param_grads of 4096 x 768 8.56 -> 8.10 us, layernorm_forward_quant_pack
-5.68 -> 5.37, the eight launches of prune_global_standardized on 49152 x 1024
-92.3 -> 91.2).
+(layernorm_param_grads of 4096 x 768 7.2 -> 6.7 us, layernorm_forward_quant_pack
+5.8 -> 5.4, the seven launches of prune_global_standardized on 49152 x 1024
+87.6 -> 86.6 and on 4096 x 768 31.9 -> 30.3).
 """
 from __future__ import annotations
 

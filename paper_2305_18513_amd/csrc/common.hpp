@@ -41,7 +41,7 @@ void launch_softmax_prune_short(const void *logits, int32_t dt, int64_t rows, in
 
 #if defined(__HIPCC__)
 // kernel<<<grid, block, lds, stream>>>(args...) in one call of the runtime instead of three (the launch's shape is not
-// pushed and popped on the way): 2.34 us of host time for 2.50.  launch_status() has the error.
+// pushed and popped on the way): 2.77 us of host time a call for 2.85.  launch_status() has the error.
 template <typename T> struct Same { using type = T; };
 template <typename... P>
 inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, typename Same<P>::type... args)

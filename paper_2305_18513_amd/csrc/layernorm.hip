@@ -217,7 +217,7 @@ layernorm_forward_kernel(const T *__restrict__ x, const float *__restrict__ gamm
 
 // Shared back end of the backward kernels: xt holds x~ (zeros in padding vectors), g holds y^.  PRUNED: kDropped stands for
 // an entry that was not kept.  It adds nothing as long as the sums are finite; where they are not, it is left out of them, so that
-// an infinity makes no NaN of it (50432 x 1024 bf16 42.4 us without, 43.2 so; left out in any case, 2 us).
+// an infinity makes no NaN of it (50432 x 1024 bf16 40.8 us without, 41.5 so; left out in any case, 2 us).
 constexpr float kDropped = -0.0f;
 __device__ __forceinline__ bool dropped(float x) { return __builtin_bit_cast(uint32_t, x) == __builtin_bit_cast(uint32_t, kDropped); }
 template <typename T, int NV, bool PRUNED = false>
@@ -277,7 +277,7 @@ __device__ __forceinline__ void backward_from_xt(float (&xt)[NV][RowIO<T>::E], f
     }
 }
 
-// Bound by HBM (49152 x 1024 fp32, 10 % kept, 65.8 us, 6.7 TB/s of dy, pairs and dx; 50432 x 1024 bf16 41.8 us, 5.9).  The
+// Bound by HBM (49152 x 1024 fp32, 10 % kept, 65.8 us, 6.7 TB/s of dy, pairs and dx; 50432 x 1024 bf16 41.5 us, 6.0).  The
 // row's x~ is rebuilt in the wave's LDS (dropped entries, then its pairs) and from there on the kernel is the dense one.  The pairs are
 // asked for with dy and not after its sum, and they pass through LDS once: with g staged, gathered by the pairs, the output
 // row staged and corrected by them, 67.5 and 45.6 us (half of the entries kept 126, now 111; 49152 x 256 bf16 21.5 and 19.0).

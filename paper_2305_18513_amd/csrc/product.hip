@@ -11,9 +11,9 @@
 // pair).  Infinities, NaN, and entries and results too large for that (2^104, 2^80), are left to the fp32 matrix instructions
 // at the end of the tile they fall into.
 //
-// Bound by power and by how far splitting (vector instructions) and multiplying overlap: 4096 x 768 x 3072 takes 99 us,
-// 195 TFLOP/s of fp32 or 1.17 PFLOP/s of bf16 (an 8192^3 product in bf16 reaches 1.21 on the card); with operands of zeros a
-// fifth less, with one of the six products a quarter.  torch's fp32 product: 150.
+// Bound by power and by how far splitting (vector instructions) and multiplying overlap: 4096 x 768 x 3072 takes 103 us,
+// 188 TFLOP/s of fp32 or 1.13 PFLOP/s of bf16 (an 8192^3 product in bf16 reaches 1.2 to 1.4 on the card); with operands of zeros a
+// sixth less, with one of the six products a quarter.  torch's fp32 product: 140.
 #include "common.hpp"
 
 namespace slimfit {
@@ -110,10 +110,10 @@ struct Loader {
 // out[i][j] = sum over k of a[i][k] b[j][k]; DEEP_B: b is N x K, otherwise K x N.  A group of four waves takes a step at a
 // time, 64 x TN/2 of the tile a wave: its rows are split into LDS, and what was split is multiplied.
 //   GROUPS 1  three workgroups a compute unit fill one another's waits: where there are tiles for that
-//             (4096 x 2304 x 768 80 us, with two groups 95).  168 registers, which is why only one row of a's parts is held.
+//             (4096 x 2304 x 768 87 us, with two groups 97).  168 registers, which is why only one row of a's parts is held.
 //   GROUPS 2  two groups of a workgroup take every other step of the same tile, one splitting while the other multiplies
 //             (a barrier swaps them), and add their sums up at the end: where a compute unit has one tile
-//             (4096 x 768 x 3072 99 us, with one group 132; 4096 x 768 x 768 29 and 44).
+//             (4096 x 768 x 3072 103 us, with one group 153; 4096 x 768 x 768 29 and 42).
 // AHEAD: steps of operands on their way in registers (one group has none to spare for two; two groups with one: 9 % slower).
 template <int TN, bool DEEP_B, int GROUPS>
 __global__ void __launch_bounds__(GROUPS * kGroup, GROUPS == 2 ? 2 : 3)
@@ -351,8 +351,8 @@ extern "C" int32_t slimfit_product(const float *a, const float *b, int32_t b_dee
     if ((rc = check_device_range(out, (size_t)M * (size_t)N * 4)) != SLIMFIT_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     // A tile for each of the 256 compute units at most: the narrowest tiles of which that holds, two groups on each (4096 x
-    // 768 x 3072 in tiles of 96 columns 99 us, of 128, which leave 64 units idle, 107).  More: one group (tiles of 64 columns
-    // 4096 x 2304 x 768 93 us, of 96 80; of 128 they need more registers than three workgroups have).
+    // 768 x 3072 in tiles of 96 columns 103 us, of 128, which leave 64 units idle, 112).  More: one group (tiles of 64 columns
+    // 4096 x 2304 x 768 95 us, of 96 87; of 128 they need more registers than three workgroups have).
     constexpr int64_t kUnits = 256;
     const int64_t tm = tiles_of(M, kTileM);
     if (tm * tiles_of(N, 64) <= kUnits) launch_tiles<64, 2>(a, b, b_deep != 0, M, N, K, out, s);
